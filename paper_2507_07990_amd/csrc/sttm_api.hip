@@ -20,7 +20,7 @@ inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
   size_t part, partu, nsum, nrm2, sim, m, sel_key_s, sel_w_s, sel_key_t, tau_s, tau_t, target_s, target_t, sel_s, sel_t, lvl,
       titems, tcount, pd_part, sig, e, parent, ptr_a, ptr_b;
-  size_t rank, key_a, val_a, key_b, val_b, order, orow, hist, tot, gsum, tile_roots, tile_live, seg, kdev,
+  size_t rank, key_a, val_a, key_b, val_b, order, orow, hist, tot, gsum, tile_roots, seg, kdev,
       bigpart, bigw, biglist, zpos, possum, poscnt;
   size_t total;
 };
@@ -69,7 +69,6 @@ size_t layout_reduce(const Geo& g, size_t off, Layout* lp) {
   l.tot = take(2048 * sizeof(int32_t));
   l.gsum = take(reduce_gsum_entries() * sizeof(int32_t));
   l.tile_roots = take(reduce_tiles(g.N) * sizeof(int32_t));
-  l.tile_live = take(reduce_tiles(g.N) * sizeof(int32_t));
   l.seg = take((N + 1) * sizeof(int32_t));
   l.kdev = take(4 * sizeof(int32_t));
   l.bigpart = take(reduce_bigpart_floats(g) * sizeof(float));
@@ -191,7 +190,6 @@ ReduceBuffers reduce_buffers(char* base, const Layout& l) {
   rb.tot = i32(l.tot);
   rb.gsum = i32(l.gsum);
   rb.tile_roots = i32(l.tile_roots);
-  rb.tile_live = i32(l.tile_live);
   rb.seg = i32(l.seg);
   rb.kdev = i32(l.kdev);
   rb.bigpart = reinterpret_cast<float*>(base + l.bigpart);

@@ -484,7 +484,6 @@ struct ReduceBuffers {
   int32_t* tot;         // [digits] column totals (very large inputs)
   int32_t* gsum;        // [groups of tiles][digits] partial column sums (medium inputs)
   int32_t* tile_roots;  // [tiles]
-  int32_t* tile_live;   // [tiles]
   int32_t* seg;         // [N+1] first list position of every output row
   int32_t* kdev;        // [4] number of clusters, length of the live list, length of the big-cluster list
   int32_t* zpos;        // [N] output row of every cluster rank under the Z-shaped scan

@@ -9,9 +9,15 @@
 
 namespace sttm {
 
-constexpr int kSortThreads = 256;
-constexpr int kSortPer = 8;
-constexpr int kSortTile = kSortThreads * kSortPer;  // 2048 elements per workgroup
+constexpr int kSortTile = 2048;  // elements per workgroup of the sort kernels
+// The sort kernels run a few microseconds on a handful of workgroups each, and what a workgroup spends there is mostly
+// the first fetch of its instructions (about 40 ns per 64 bytes of straight-line code: a one-workgroup scatter pass of
+// 16 KB took 11 us). So a tile is spread over many wavefronts with few elements each instead of being unrolled eight
+// deep in four of them, and nothing is inlined more than once.
+constexpr int kPrepThreads = 1024;
+constexpr int kPrepPer = kSortTile / kPrepThreads;
+constexpr int kSortThreads = 512;
+constexpr int kSortPer = kSortTile / kSortThreads;
 constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kMaxDigitBits = 11;
 constexpr int kItem = 16;  // list positions per gather item
@@ -47,9 +53,10 @@ size_t reduce_tiles(int N) { return (size_t)(N + kSortTile - 1) / kSortTile; }
 size_t reduce_gsum_entries() { return (size_t)kMaxGroups * kMaxDigits; }
 size_t reduce_hist_entries(int N) { return (size_t)kMaxDigits * reduce_tiles(N); }
 
-// Exclusive prefix of v over the 256 threads of the workgroup; *total = sum over all threads.
+// Exclusive prefix of v over the threads of a workgroup of WAVES wavefronts; *total = sum over all threads.
+template <int WAVES>
 __device__ inline int block_exclusive_scan(int v, int* total) {
-  __shared__ int wsum[kSortWaves];
+  __shared__ int wsum[WAVES];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int inc = v;
 #pragma unroll
@@ -61,20 +68,13 @@ __device__ inline int block_exclusive_scan(int v, int* total) {
   __syncthreads();
   int base = 0, tot = 0;
 #pragma unroll
-  for (int w = 0; w < kSortWaves; ++w) {
+  for (int w = 0; w < WAVES; ++w) {
     if (w < wave) base += wsum[w];
     tot += wsum[w];
   }
   __syncthreads();
   *total = tot;
   return base + inc - v;
-}
-
-// Sum of v over the workgroup, returned to every thread.
-__device__ inline int block_sum(int v) {
-  int total;
-  (void)block_exclusive_scan(v, &total);
-  return total;
 }
 
 __device__ inline int node_cells(const Geo& g, int cell_in_frame, int lvl) {
@@ -89,69 +89,66 @@ __device__ inline int node_second_cell(const Geo& g, int c) { return (c % g.W) +
 // ------------------------------------------------------------------------------------------------
 // k_reduce_prep: one workgroup per tile of 2048 cells. Sort keys (cluster id, or -1 for a cell covered by a
 // stored node sum), tile-local exclusive ranks of the roots (cells that are their own cluster id), the
-// tile's totals, and the tile's digit histogram of the first sort pass.
+// tile's number of roots, and the tile's digit histogram of the first sort pass.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kSortThreads) void k_reduce_prep(Geo g, const int32_t* __restrict__ cluster_ids,
+__global__ __launch_bounds__(kPrepThreads) void k_reduce_prep(Geo g, const int32_t* __restrict__ cluster_ids,
                                                               const int32_t* __restrict__ node_map,
                                                               const uint8_t* __restrict__ node_level, int dbits,
                                                               int32_t* __restrict__ keys, int32_t* __restrict__ rank,
                                                               int32_t* __restrict__ tile_roots,
-                                                              int32_t* __restrict__ tile_live,
                                                               int32_t* __restrict__ hist,
                                                               int32_t* __restrict__ bigcount) {
+  constexpr int kWaves = kPrepThreads / kWave;
   __shared__ int cnt[kMaxDigits];
-  const int DIG = 1 << dbits, b = blockIdx.x, tid = threadIdx.x;
-  for (int d = tid; d < DIG; d += kSortThreads) cnt[d] = 0;
+  __shared__ int wroots[kWaves];
+  const int DIG = 1 << dbits, b = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int e0 = b * kSortTile + wave * (kPrepPer * kWave) + lane;  // a wavefront takes consecutive cells
+  int cid[kPrepPer], rep[kPrepPer], lv[kPrepPer];
+#pragma unroll
+  for (int r = 0; r < kPrepPer; ++r) {  // all loads first: they do not depend on one another
+    const int i = min(e0 + r * kWave, g.N - 1);
+    cid[r] = cluster_ids[i];
+    rep[r] = lv[r] = 0;
+    if (node_map) {
+      rep[r] = node_map[i];
+      lv[r] = node_level[i];
+    }
+  }
+  for (int d = tid; d < DIG; d += kPrepThreads) cnt[d] = 0;
   if (b == 0 && tid == 0) *bigcount = 0;  // the list of big clusters starts empty
   __syncthreads();
-  const int i0 = b * kSortTile + tid * kSortPer;
-  int root[kSortPer], nroot = 0, nlive = 0;
-  int cidv[kSortPer], repv[kSortPer], lvv[kSortPer];
+  int before[kPrepPer], nroot = 0;  // roots of the wavefront before this cell
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {  // all loads first: they do not depend on one another
-    const int i = i0 + j;
-    cidv[j] = repv[j] = lvv[j] = 0;
-    if (i < g.N) {
-      cidv[j] = cluster_ids[i];
-      if (node_map) {
-        repv[j] = node_map[i];
-        lvv[j] = node_level[i];
-      }
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
-    const int i = i0 + j;
-    root[j] = 0;
-    if (i < g.N) {
-      const int cid = cidv[j];
+  for (int r = 0; r < kPrepPer; ++r) {
+    const int i = e0 + r * kWave;
+    const bool in = i < g.N;
+    const unsigned long long roots = __ballot(in && cid[r] == i);
+    before[r] = nroot + __popcll(roots & ((1ull << lane) - 1ull));
+    nroot += __popcll(roots);
+    if (in) {
       bool live = true;
-      if (lvv[j] >= 3) {  // a node with a stored sum: only the cells standing for it stay
-        const int rep = repv[j], c = rep % g.HW;
-        if (node_is_summed(g, c, lvv[j]))
-          live = i == rep || (g.vec == 8 && i == rep - c + node_second_cell(g, c));
+      if (lv[r] >= 3) {  // a node with a stored sum: only the cells standing for it stay
+        const int c = rep[r] % g.HW;
+        if (node_is_summed(g, c, lv[r]))
+          live = i == rep[r] || (g.vec == 8 && i == rep[r] - c + node_second_cell(g, c));
       }
-      keys[i] = live ? cid : -1;
-      root[j] = cid == i;
-      nroot += root[j];
-      nlive += live;
-      if (live) atomicAdd(&cnt[cid & (DIG - 1)], 1);
+      keys[i] = live ? cid[r] : -1;
+      if (live) atomicAdd(&cnt[cid[r] & (DIG - 1)], 1);
     }
   }
-  int total;
-  int ex = block_exclusive_scan(nroot, &total);
-#pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
-    if (i0 + j < g.N) rank[i0 + j] = ex;
-    ex += root[j];
-  }
-  const int live_total = block_sum(nlive);
-  if (tid == 0) {
-    tile_roots[b] = total;
-    tile_live[b] = live_total;
-  }
+  if (lane == 0) wroots[wave] = nroot;
   __syncthreads();
-  for (int d = tid; d < DIG; d += kSortThreads) hist[(size_t)b * DIG + d] = cnt[d];
+  int base = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    if (w < wave) base += wroots[w];
+    total += wroots[w];
+  }
+#pragma unroll
+  for (int r = 0; r < kPrepPer; ++r)
+    if (e0 + r * kWave < g.N) rank[e0 + r * kWave] = base + before[r];
+  if (tid == 0) tile_roots[b] = total;
+  for (int d = tid; d < DIG; d += kPrepThreads) hist[(size_t)b * DIG + d] = cnt[d];
 }
 
 // Digit histogram per tile of the (compacted) keys of a later pass; tiles beyond the list write zeros.
@@ -214,31 +211,28 @@ __global__ __launch_bounds__(256) void k_sort_groupsum(int nb, int DIG, const in
 }
 
 // Adds rows [r0, r1) of a table of 2^dbits-int rows to at[] (if to_total) and, for the rows below `limit`, to
-// am[]. The table is read as 16-byte pieces, consecutive threads next to each other, sixteen loads in flight per
-// thread; the four digits a thread sees do not change from load to load (two sets when a row has more pieces
-// than the workgroup has threads).
+// am[]. The table is read as 16-byte pieces, consecutive threads next to each other, eight loads in flight per
+// thread; the four digits a thread sees do not change from load to load (a row has at most as many pieces as the
+// workgroup has threads).
 __device__ inline void sort_add_rows(const int32_t* __restrict__ table, int r0, int r1, int dbits, int limit,
-                                     bool to_total, int (&at)[2][4], int (&am)[2][4]) {
+                                     bool to_total, int (&at)[4], int (&am)[4]) {
+  constexpr int kBatch = 8;
+  static_assert(kMaxDigits / 4 <= kSortThreads, "one digit piece per thread");
   const int vshift = dbits - 2;  // log2 of the 16-byte pieces per row
   const int first = r0 << vshift, last = r1 << vshift;
   const int4* h4 = reinterpret_cast<const int4*>(table);
-  for (int q0 = first + (int)threadIdx.x; q0 < last; q0 += 16 * kSortThreads) {
-    int4 v[16];
+  const int take_total = to_total ? -1 : 0;
+#pragma unroll 1
+  for (int q0 = first + (int)threadIdx.x; q0 < last; q0 += kBatch * kSortThreads) {
+    int4 v[kBatch];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
+    for (int u = 0; u < kBatch; ++u) v[u] = h4[min(q0 + u * kSortThreads, last - 1)];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
       const int q = q0 + u * kSortThreads;
-      v[u] = q < last ? h4[q] : make_int4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int q = q0 + u * kSortThreads;
-      const bool before = (q >> vshift) < limit;
-      const int e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (to_total) at[u & 1][i] += e[i];
-        if (before) am[u & 1][i] += e[i];
-      }
+      const int in = q < last ? -1 : 0, mb = (q >> vshift) < limit ? in : 0, mt = in & take_total;
+      at[0] += v[u].x & mt; at[1] += v[u].y & mt; at[2] += v[u].z & mt; at[3] += v[u].w & mt;
+      am[0] += v[u].x & mb; am[1] += v[u].y & mb; am[2] += v[u].z & mb; am[3] += v[u].w & mb;
     }
   }
 }
@@ -246,13 +240,14 @@ __device__ inline void sort_add_rows(const int32_t* __restrict__ table, int r0, 
 // ------------------------------------------------------------------------------------------------
 // k_sort_pass: one stable scatter pass, one workgroup per tile of 2048 elements. The workgroup first turns
 // the histogram into its own start offset for every digit (summing the columns over the tiles before it
-// unless k_sort_colscan did so), then every wavefront ranks its 512 consecutive elements 64 at a time in
+// unless k_sort_colscan did so), then every wavefront ranks its 256 consecutive elements 64 at a time in
 // index order (ballot matching), so the order of equal keys is kept.
 //   FIRST: elements are the cells themselves (value = index), dropped cells (key < 0) stay behind, so the
 //          output is compact. Also makes the root ranks global, and writes out_ids, the per-video offsets
 //          and the totals (K, list length).
 //   LAST:  writes the sorted element list, the output row of every list position and the first list
 //          position of every row (the root is the smallest index of its cluster, hence first in its list).
+// A wavefront's cursors are counts inside the tile (at most 2048) and are kept as 16-bit halves, two digits to a word.
 // ------------------------------------------------------------------------------------------------
 struct SortArgs {
   int n, shift, dbits, nb, mode;  // mode: how the start offsets are found (see kDirectTiles)
@@ -267,7 +262,6 @@ struct SortArgs {
   const int32_t* cluster_ids;
   int32_t* rank;
   const int32_t* tile_roots;
-  const int32_t* tile_live;
   int32_t* kdev;  // [0] = K, [1] = list length
   int32_t* out_ids;
   int64_t* offsets;
@@ -280,73 +274,74 @@ struct SortArgs {
 
 template <bool FIRST, bool LAST>
 __global__ __launch_bounds__(kSortThreads) void k_sort_pass(SortArgs a) {
-  __shared__ int s_base[kMaxDigits];
-  __shared__ int cur[kSortWaves][kMaxDigits];
+  __shared__ int s_base[kMaxDigits];                  // first list position of every digit for this tile
+  __shared__ unsigned cur[kSortWaves * kMaxDigits / 2];  // [wavefront][two digits to a word]
+  __shared__ int s_roots[2];                          // roots in the tiles before this one, and in all
   const int DIG = 1 << a.dbits, b = blockIdx.x, tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = FIRST ? a.n : a.kdev[1];
 
   // ---- everything this tile reads per element is requested first, so that it arrives while the offsets
-  //      are worked out
+  //      are worked out (a position beyond the list reads something stale that is not used)
   const int e0 = b * kSortTile + wave * (kSortTile / kSortWaves);
   int key[kSortPer], val[kSortPer], aux[kSortPer];
   int rk0[kSortPer], cid[kSortPer];
-  bool ok[kSortPer];
 #pragma unroll
   for (int r = 0; r < kSortPer; ++r) {
-    const int i = e0 + r * 64 + lane;
-    key[r] = -1;
-    val[r] = rk0[r] = cid[r] = 0;
-    if (i < n) {
-      key[r] = a.keys[i];
-      val[r] = FIRST ? i : a.vals[i];
-      if (FIRST) {
-        rk0[r] = a.rank[i];
-        cid[r] = a.cluster_ids[i];
-      }
-    }
-    ok[r] = key[r] >= 0;
+    const int i = e0 + r * 64 + lane, j = min(i, a.n - 1);
+    key[r] = a.keys[j];
+    val[r] = FIRST ? i : a.vals[j];
+    rk0[r] = FIRST ? a.rank[j] : 0;
+    cid[r] = FIRST ? a.cluster_ids[j] : 0;
   }
-  int roots_before = 0, roots_all = 0, live_all = 0;
+  int roots_before = 0, roots_all = 0;
   if (FIRST) {
     for (int t = tid; t < a.nb; t += kSortThreads) {
       const int v = a.tile_roots[t];
       roots_all += v;
       if (t < b) roots_before += v;
-      if (b == 0) live_all += a.tile_live[t];
     }
   }
 
   // ---- start offset of every digit for this tile
-  int* tot = cur[0];   // column totals and the part of them that lies in the tiles before this one
-  int* mine = cur[1];  // (the cursors are not in use yet)
-  if (a.mode != 2) {
-    for (int d = tid; d < DIG; d += kSortThreads) tot[d] = mine[d] = 0;
-    __syncthreads();
-    int at[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}}, am[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
-    if (a.mode == 0) {
-      sort_add_rows(a.hist, 0, a.nb, a.dbits, b, true, at, am);
-    } else {  // the sums of all groups, then the rows of this tile's own group up to the tile
-      const int grp = b / kGroupTiles, ngrp = (a.nb + kGroupTiles - 1) / kGroupTiles;
-      sort_add_rows(a.gsum, 0, ngrp, a.dbits, grp, true, at, am);
-      sort_add_rows(a.hist, grp * kGroupTiles, min(a.nb, (grp + 1) * kGroupTiles), a.dbits, b, false, at, am);
-    }
-    const int VC = 1 << (a.dbits - 2);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int vc = (tid + k * kSortThreads) & (VC - 1);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (at[k][i]) atomicAdd(&tot[vc * 4 + i], at[k][i]);
-        if (am[k][i]) atomicAdd(&mine[vc * 4 + i], am[k][i]);
-      }
-    }
-    __syncthreads();
+  int* tot = reinterpret_cast<int*>(cur);  // column totals and the part of them that lies in the tiles before this one
+  int* mine = tot + kMaxDigits;            // (the cursors are not in use yet)
+  static_assert(kSortWaves >= 4, "the two column tables fit the cursors' place");
+  if (tid < 2) s_roots[tid] = 0;
+  for (int d = tid; d < DIG; d += kSortThreads) tot[d] = mine[d] = 0;
+  __syncthreads();
+  if (FIRST) {
+    if (roots_before) atomicAdd(&s_roots[0], roots_before);
+    if (roots_all) atomicAdd(&s_roots[1], roots_all);
   }
+  if (a.mode != 2) {
+    int at[4] = {0, 0, 0, 0}, am[4] = {0, 0, 0, 0};
+    const int grp = b / kGroupTiles, ngrp = (a.nb + kGroupTiles - 1) / kGroupTiles;
+#pragma unroll 1
+    for (int part = 0; part <= a.mode; ++part) {
+      // mode 0: all rows of all tiles; mode 1: the sums of all groups, then the rows of this tile's own group
+      const bool sums = a.mode == 1 && part == 0, own = part == 1;
+      sort_add_rows(sums ? a.gsum : a.hist, own ? grp * kGroupTiles : 0,
+                    sums ? ngrp : (own ? min(a.nb, (grp + 1) * kGroupTiles) : a.nb), a.dbits, sums ? grp : b, !own, at, am);
+    }
+    const int vc = tid & ((1 << (a.dbits - 2)) - 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (at[i]) atomicAdd(&tot[vc * 4 + i], at[i]);
+      if (am[i]) atomicAdd(&mine[vc * 4 + i], am[i]);
+    }
+  } else {
+    for (int d = tid; d < DIG; d += kSortThreads) {
+      tot[d] = a.tot[d];
+      mine[d] = a.hist[(size_t)b * DIG + d];
+    }
+  }
+  __syncthreads();
 #pragma unroll
   for (int r = 0; r < kSortPer; ++r) {
+    if (e0 + r * 64 + lane >= n) key[r] = -1;
     aux[r] = 0;
-    if (LAST && ok[r]) aux[r] = a.rank[key[r]];  // output row of the element's cluster (arrives during the scan)
+    if (LAST && key[r] >= 0) aux[r] = a.rank[key[r]];  // output row of the element's cluster (arrives during the scan)
   }
   {
     constexpr int kDpt = kMaxDigits / kSortThreads;
@@ -355,64 +350,66 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(SortArgs a) {
 #pragma unroll
     for (int j = 0; j < kDpt; ++j) {
       const int d = tid * dpt + j;
-      tv[j] = cv[j] = 0;
-      if (j < dpt && d < DIG) {
-        tv[j] = a.mode == 2 ? a.tot[d] : tot[d];
-        cv[j] = a.mode == 2 ? a.hist[(size_t)b * DIG + d] : mine[d];
-      }
+      const bool in = j < dpt && d < DIG;
+      tv[j] = in ? tot[d] : 0;
+      cv[j] = in ? mine[d] : 0;
       s += tv[j];
     }
-    int total;
-    int ex = block_exclusive_scan(s, &total);  // (its barriers also fence the reads above from the clearing below)
+    int live;  // all elements of the list
+    int ex = block_exclusive_scan<kSortWaves>(s, &live);  // (its barriers also fence the reads above from the clearing below)
 #pragma unroll
     for (int j = 0; j < kDpt; ++j) {
       const int d = tid * dpt + j;
       if (j < dpt && d < DIG) s_base[d] = ex + cv[j];
       ex += tv[j];
     }
-  }
-  int root_prefix = 0;
-  if (FIRST) {
-    root_prefix = block_sum(roots_before);
-    if (b == 0) {
-      const int all = block_sum(roots_all), live = block_sum(live_all);
-      if (tid == 0) {
+    if (b == 0 && tid == 0) {
+      if (FIRST) {
+        const int all = s_roots[1];
         a.kdev[0] = all;
         a.kdev[1] = live;
         a.offsets[a.B] = all;
         if (LAST) a.seg[all] = live;
+      } else if (LAST) {
+        a.seg[a.kdev[0]] = n;
       }
     }
   }
-  if (LAST && !FIRST && b == 0 && tid == 0) a.seg[a.kdev[0]] = n;
-  for (int d = tid; d < DIG; d += kSortThreads)
-#pragma unroll
-    for (int w = 0; w < kSortWaves; ++w) cur[w][d] = 0;
+  const int hd = DIG >> 1;
+  for (int d = tid; d < kSortWaves * hd; d += kSortThreads) cur[d] = 0;
   __syncthreads();
 
-  // ---- per-wavefront digit counts of its 512 elements
+  // ---- per-wavefront digit counts of its 256 elements
+  unsigned* mycur = cur + wave * hd;
 #pragma unroll
-  for (int r = 0; r < kSortPer; ++r)
-    if (ok[r]) atomicAdd(&cur[wave][(key[r] >> a.shift) & (DIG - 1)], 1);
+  for (int r = 0; r < kSortPer; ++r) {
+    const int digit = (key[r] >> a.shift) & (DIG - 1);
+    if (key[r] >= 0) atomicAdd(&mycur[digit >> 1], 1u << ((digit & 1) * 16));
+  }
   if (FIRST) {
-    // bookkeeping outputs of the cells themselves
+    // bookkeeping outputs of the cells themselves; the wavefront's first video start at or after its first cell
+    const int root_prefix = s_roots[0];
+    int video = (e0 + a.per_video - 1) / a.per_video;
+    long long start = (long long)video * a.per_video;
 #pragma unroll
     for (int r = 0; r < kSortPer; ++r) {
       const int i = e0 + r * 64 + lane;
-      if (i >= n) continue;
       const int rk = rk0[r] + root_prefix;
-      if (b != 0) a.rank[i] = rk;
-      if (cid[r] == i && a.out_ids && rk < a.capacity) a.out_ids[rk] = i;
-      if (i % a.per_video == 0) a.offsets[i / a.per_video] = rk;
+      if (i < n) {
+        if (b != 0) a.rank[i] = rk;
+        if (cid[r] == i && a.out_ids && rk < a.capacity) a.out_ids[rk] = i;
+      }
+      for (; start < e0 + (r + 1) * 64 && start < n; start += a.per_video, ++video)
+        if (i == start) a.offsets[video] = rk;
     }
   }
   __syncthreads();
-  for (int d = tid; d < DIG; d += kSortThreads) {
-    int run = s_base[d];
+  for (int d = tid; d < hd; d += kSortThreads) {
+    unsigned run = 0;
 #pragma unroll
     for (int w = 0; w < kSortWaves; ++w) {
-      const int c = cur[w][d];
-      cur[w][d] = run;
+      const unsigned c = cur[w * hd + d];
+      cur[w * hd + d] = run;
       run += c;
     }
   }
@@ -421,34 +418,34 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(SortArgs a) {
   // ---- ranked scatter, 64 elements at a time in index order: first which lanes hold the same digit (no
   //      memory involved), then the cursors
   const unsigned long long below = (1ull << lane) - 1ull;
-  int* mycur = cur[wave];
   unsigned long long same[kSortPer];
 #pragma unroll
-  for (int r = 0; r < kSortPer; ++r) {
-    const int digit = (key[r] >> a.shift) & (DIG - 1);
-    same[r] = __ballot(ok[r]);
-    for (int bit = 0; bit < a.dbits; ++bit) {
-      const unsigned long long m = __ballot((digit >> bit) & 1);
-      same[r] &= ((digit >> bit) & 1) ? m : ~m;
+  for (int r = 0; r < kSortPer; ++r) same[r] = __ballot(key[r] >= 0);
+#pragma unroll 1
+  for (int bit = 0; bit < a.dbits; ++bit) {
+#pragma unroll
+    for (int r = 0; r < kSortPer; ++r) {
+      const bool one = (key[r] >> (a.shift + bit)) & 1;
+      const unsigned long long m = __ballot(one);
+      same[r] &= one ? m : ~m;
     }
   }
 #pragma unroll
   for (int r = 0; r < kSortPer; ++r) {  // the stores of one round travel while the next round's cursors are read
-    const int digit = (key[r] >> a.shift) & (DIG - 1);
-    if (ok[r]) {
-      const int dst = mycur[digit] + __popcll(same[r] & below);
+    const int digit = (key[r] >> a.shift) & (DIG - 1), half = (digit & 1) * 16;
+    if (key[r] >= 0) {
+      const int dst = s_base[digit] + (int)((mycur[digit >> 1] >> half) & 0xffffu) + __popcll(same[r] & below);
+      a.vals_out[dst] = val[r];
       if (LAST) {
-        a.vals_out[dst] = val[r];
         a.orow[dst] = aux[r];
         if (key[r] == val[r]) a.seg[aux[r]] = dst;
       } else {
         a.keys_out[dst] = key[r];
-        a.vals_out[dst] = val[r];
       }
     }
     wave_lds_fence();
-    if (ok[r] && ((same[r] >> lane) >> 1) == 0)  // highest lane of its digit group advances the cursor
-      mycur[digit] += __popcll(same[r]);
+    if (r + 1 < kSortPer && key[r] >= 0 && ((same[r] >> lane) >> 1) == 0)  // highest lane of its digit group advances the cursor
+      atomicAdd(&mycur[digit >> 1], (unsigned)__popcll(same[r]) << half);
     wave_lds_fence();
   }
 }
@@ -809,7 +806,7 @@ __global__ __launch_bounds__(256) void k_zorder(Geo g, const int32_t* __restrict
     sum += v[j];
   }
   int total;
-  int ex = block_exclusive_scan(sum, &total);
+  int ex = block_exclusive_scan<256 / kWave>(sum, &total);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     if (tid * 4 + j < PP) flag[tid * 4 + j] = ex;
@@ -921,8 +918,8 @@ void launch_reduce_prepare(const Geo& g, const int32_t* cluster_ids, const int32
   const SortPlan pl = sort_plan(N);
   const int DIG = 1 << pl.dbits;
   const dim3 grid(pl.nb), block(kSortThreads);
-  hipLaunchKernelGGL(k_reduce_prep, grid, block, 0, s, g, cluster_ids, node_map, node_level, pl.dbits, rb.key_a,
-                     rb.rank, rb.tile_roots, rb.tile_live, rb.hist, rb.kdev + 2);
+  hipLaunchKernelGGL(k_reduce_prep, grid, dim3(kPrepThreads), 0, s, g, cluster_ids, node_map, node_level, pl.dbits,
+                     rb.key_a, rb.rank, rb.tile_roots, rb.hist, rb.kdev + 2);
   const int32_t* kin = rb.key_a;
   const int32_t* vin = nullptr;
   int32_t* kout = rb.key_b;
@@ -940,7 +937,7 @@ void launch_reduce_prepare(const Geo& g, const int32_t* cluster_ids, const int32
     a.n = N; a.shift = pass * pl.dbits; a.dbits = pl.dbits; a.nb = pl.nb; a.mode = pl.mode; a.gsum = rb.gsum;
     a.keys = kin; a.vals = vin; a.keys_out = kout; a.vals_out = last ? rb.order : vout;
     a.hist = rb.hist; a.tot = rb.tot;
-    a.cluster_ids = cluster_ids; a.rank = rb.rank; a.tile_roots = rb.tile_roots; a.tile_live = rb.tile_live;
+    a.cluster_ids = cluster_ids; a.rank = rb.rank; a.tile_roots = rb.tile_roots;
     a.kdev = rb.kdev; a.out_ids = zscan ? nullptr : out_ids; a.offsets = offsets; a.capacity = capacity;
     a.per_video = g.T * g.HW; a.B = g.B;
     a.orow = rb.orow; a.seg = rb.seg;
