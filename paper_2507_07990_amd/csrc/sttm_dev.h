@@ -414,8 +414,8 @@ __device__ inline float sel_last_digit(const SelState* __restrict__ st) {
 // 2 = and S_n(t) . S_n(t+1) of every 2x2 and 4x4 block n.
 void launch_pyramid_stats(const Geo& g, const void* feats, int cell_dots, float* part, float* nsum, SelState* sel,
                           hipStream_t s);
-// Also works out the levels above an 8x8 unit from the stored unit sums (extends `part` and `nsum`).
-void launch_spatial_finalize(const Geo& g, const float* part, float* partu, float* nsum, float* nrm2, float* sim, float* m,
+// Also works out the levels above an 8x8 unit from the stored unit sums (extends `nsum`).
+void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float* nrm2, float* sim, float* m,
                              uint32_t* sel_key, uint8_t* sel_w, SelState* sel, hipStream_t s);
 // `pending` (may be NULL): the search states of a budget search whose last digit has not been resolved yet; the
 // kernel then works the threshold out itself (and leaves it in `tau` for later readers) instead of reading `tau`.

@@ -404,53 +404,6 @@ __global__ __launch_bounds__(64, 2) void k_pyramid_stats(Geo g, const void* __re
         reinterpret_cast<const float4*>(st)[lane];
 }
 
-// ------------------------------------------------------------------------------------------------
-// pyramid_upper_node: one node of a level >= 4 of one frame from the stored sums of its children, for one
-// chunk, by one wavefront; a lane owns four channels (the chunk is covered in VEC/4 sweeps). Stores the node's
-// sum next to the level-3 sums and the partial dot product of every child with it in the same per-chunk
-// tables as above. Runs at the head of the finalize kernel, level by level.
-// ------------------------------------------------------------------------------------------------
-__device__ inline void pyramid_upper_node(const Geo& g, float* partu, float* nsum, int chunk, int f, int lane, int lvl,
-                                          int nd) {
-  const int NB = g.NN - g.lvl_base[3];
-  float* pd = partu + (size_t)(f * g.nC + chunk) * NB;  // indexed by node - first level-3 node
-  float* rows = nsum + (size_t)f * NB * g.D;
-  const int G = g.P >> lvl;
-  const int by = nd / G, bx = nd - by * G;
-  if (!node_exists(g, lvl, by, bx)) return;  // wave-uniform
-  float tot[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int c = lane * 4; c < g.cch; c += 256) {
-    const int ch = chunk * g.cch + c;
-    if (ch >= g.D) continue;
-    float4 a[4];
-    float4 S = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int cy = 2 * by + (k >> 1), cx = 2 * bx + (k & 1);
-      a[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (node_exists(g, lvl - 1, cy, cx))
-        a[k] = *reinterpret_cast<const float4*>(rows + (size_t)(node_index(g, lvl - 1, cy, cx) - g.lvl_base[3]) * g.D + ch);
-    }
-    S.x = (a[0].x + a[1].x) + (a[2].x + a[3].x);
-    S.y = (a[0].y + a[1].y) + (a[2].y + a[3].y);
-    S.z = (a[0].z + a[1].z) + (a[2].z + a[3].z);
-    S.w = (a[0].w + a[1].w) + (a[2].w + a[3].w);
-    *reinterpret_cast<float4*>(rows + (size_t)(node_index(g, lvl, by, bx) - g.lvl_base[3]) * g.D + ch) = S;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      tot[k] = fmaf(a[k].x, S.x, fmaf(a[k].y, S.y, fmaf(a[k].z, S.z, fmaf(a[k].w, S.w, tot[k]))));
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) tot[j] = wave_sum(tot[j]);
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int cy = 2 * by + (k >> 1), cx = 2 * bx + (k & 1);
-      if (node_exists(g, lvl - 1, cy, cx)) pd[node_index(g, lvl - 1, cy, cx) - g.lvl_base[3]] = tot[k];
-    }
-  }
-}
-
 template <int CC>
 static void launch_pyramid_cc(const Geo& g, const void* feats, float* part, float* nsum, SelState* sel, hipStream_t s) {
   const int NU = unit_cols(g) * unit_rows(g);
@@ -481,111 +434,181 @@ void launch_pyramid_stats(const Geo& g, const void* feats, int cell_dots, float*
 }
 
 // ------------------------------------------------------------------------------------------------
-// k_spatial_finalize: one workgroup per frame. First the levels above the 8x8 units (see pyramid_upper_node),
-// then it sums the per-chunk partials in chunk order, turns
+// k_spatial_finalize: one workgroup per frame. First the levels above the 8x8 units (UP = 1: a 16x16 grid, one node of
+// level 4; UP = 2: a 32x32 grid, four of level 4 and, if the root is one node, the one of level 5): a thread owns four
+// channels, loads them from all level-3 sums of the frame at once, adds the levels up in registers, stores the sums
+// next to the level-3 ones and keeps its share of the dot products child . parent, which are added up over the
+// workgroup at the end. (One wavefront per node and chunk, level by level, paid the memory latency once per node, chunk
+// and level: 44 us of 180 frames of 18x24 tokens at D = 8192, 50 us of 1024 frames of 27x27 at D = 1152.)
+// Then it sums the per-chunk partials of the lower levels in chunk order, 16 bytes per thread into LDS, turns
 // them into sigma(parent, child) (Sec. 3.2: cosine between a level's nodes and their children),
 // m_n = min over existing children, and the split score s_n = max of m along the path from the root.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(512) void k_spatial_finalize(Geo g, const float* __restrict__ part, float* partu,
-                                                          float* __restrict__ nsum,
-                                                          float* __restrict__ nrm2, float* __restrict__ sim,
-                                                          float* __restrict__ m, uint32_t* __restrict__ sel_key,
-                                                          uint8_t* __restrict__ sel_w,
-                                                          SelState* __restrict__ sel) {
+constexpr int kUnitStats = 4 * kTileRows + 4;  // the scalars of a unit's block that this kernel reads
+static_assert(kUnitStats % 4 == 0, "whole 16-byte pieces");
+constexpr int kUpRows = 24;                    // dot products with a parent at level 4 (16) or 5 (4), whole batches of 8
+constexpr int kFinThreads = 512;
+
+__device__ inline float dot4(const float4& a, const float4& b, float c) {
+  return fmaf(a.x, b.x, fmaf(a.y, b.y, fmaf(a.z, b.z, fmaf(a.w, b.w, c))));
+}
+__device__ inline float4 add4(const float4& a, const float4& b) {
+  return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+
+// The upper levels of frame f by a workgroup of kFinThreads threads; leaves the dot product of level-3 node
+// (2 py + ky, 2 px + kx) with its parent p = (py, px) in up[4 p + 2 ky + kx], that of level-4 node p with its parent in
+// up[16 + p] (call a barrier before reading them). `red` is kUpRows * 64 floats of LDS.
+template <int UP>
+__device__ inline void upper_levels(const Geo& g, float* nsum, int f, float* red, float* up) {
+  constexpr int S4 = UP == 1 ? 1 : 2, N4 = S4 * S4;
+  const int NB = g.NN - g.lvl_base[3], D4 = g.D >> 2, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float4* rows = reinterpret_cast<float4*>(nsum + (size_t)f * NB * g.D);
+  const int base4 = 4 * N4;  // nodes of level 3 come first, then level 4, then level 5
+  float tot[kUpRows];
+#pragma unroll
+  for (int i = 0; i < kUpRows; ++i) tot[i] = 0.f;
+#pragma unroll 1
+  for (int c = threadIdx.x; c < D4; c += kFinThreads) {
+    float4 a[4 * N4], s4[N4];
+#pragma unroll
+    for (int i = 0; i < 4 * N4; ++i) {  // i = 4 p + k
+      const int p = i >> 2, k = i & 3, y = 2 * (p / S4) + (k >> 1), x = 2 * (p % S4) + (k & 1);
+      a[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (node_exists(g, 3, y, x)) a[i] = rows[(size_t)(y * 2 * S4 + x) * D4 + c];
+    }
+#pragma unroll
+    for (int p = 0; p < N4; ++p) {
+      s4[p] = add4(add4(a[4 * p], a[4 * p + 1]), add4(a[4 * p + 2], a[4 * p + 3]));
+      if (node_exists(g, 4, p / S4, p % S4)) rows[(size_t)(base4 + p) * D4 + c] = s4[p];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) tot[4 * p + k] = dot4(a[4 * p + k], s4[p], tot[4 * p + k]);
+    }
+    if (UP == 2 && g.L >= 5) {
+      const float4 s5 = add4(add4(s4[0], s4[1 % N4]), add4(s4[2 % N4], s4[3 % N4]));
+      rows[(size_t)(base4 + N4) * D4 + c] = s5;
+#pragma unroll
+      for (int p = 0; p < N4; ++p) tot[16 + p] = dot4(s4[p], s5, tot[16 + p]);
+    }
+  }
+  constexpr int kBatches = UP == 1 ? 1 : kUpRows / 8;
+#pragma unroll
+  for (int i = 0; i < kBatches; ++i) {
+    const float v[8] = {tot[8 * i], tot[8 * i + 1], tot[8 * i + 2], tot[8 * i + 3],
+                        tot[8 * i + 4], tot[8 * i + 5], tot[8 * i + 6], tot[8 * i + 7]};
+    red[(8 * i + (lane & 7)) * 64 + wave * 8 + (lane >> 3)] = group_sums8(v, lane);
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < 8 * kBatches) {
+    const float4* r = reinterpret_cast<const float4*>(red + threadIdx.x * 64);
+    float4 s = r[0];
+#pragma unroll
+    for (int j = 1; j < 16; ++j) s = add4(s, r[j]);
+    up[threadIdx.x] = (s.x + s.y) + (s.z + s.w);
+  }
+}
+
+template <int UP>
+__global__ __launch_bounds__(kFinThreads) void k_spatial_finalize(Geo g, const float* __restrict__ part,
+                                                                  float* __restrict__ nsum, float* __restrict__ nrm2,
+                                                                  float* __restrict__ sim, float* __restrict__ m,
+                                                                  uint32_t* __restrict__ sel_key,
+                                                                  uint8_t* __restrict__ sel_w,
+                                                                  SelState* __restrict__ sel) {
   STTM_DYNAMIC_LDS(float, sm);
   __shared__ unsigned h0[kSelBins];
-  for (int j = threadIdx.x; j < kSelBins; j += blockDim.x) h0[j] = 0;
-  float* s_n = sm;
-  float* s_sim = sm + g.NN;
-  float* s_m = sm + 2 * g.NN;
+  __shared__ __attribute__((aligned(16))) float red[UP ? kUpRows * 64 : 1];
+  __shared__ float up[kUpRows];
+  // dynamic: the units' scalars, then per node squared norm, similarity to the parent, m, and (level, row, column)
+  const int NU = unit_cols(g) * unit_rows(g), UC = unit_cols(g), tid = threadIdx.x, nthr = blockDim.x;
+  float* s_part = sm;
+  float* s_n = sm + NU * kUnitStats;
+  float* s_sim = s_n + g.NN;
+  float* s_m = s_sim + g.NN;
+  int* s_pos = reinterpret_cast<int*>(s_m + g.NN);
   const int f = blockIdx.x;
   const size_t fo = (size_t)f * g.NN;
-  for (int lvl = 4; lvl <= g.L; ++lvl) {  // the levels above the 8x8 units: one wavefront per (node, chunk)
-    const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6, side = g.P >> lvl;
-    for (int w = wave; w < side * side * g.nC; w += nwaves)
-      pyramid_upper_node(g, partu, nsum, w % g.nC, f, threadIdx.x & 63, lvl, w / g.nC);
-    __syncthreads();  // sums and dot products written above are read by other wavefronts of this workgroup
+  {
+    constexpr int kPieces = kUnitStats / 4;
+    const float4* p4 = reinterpret_cast<const float4*>(part) + (size_t)f * g.nC * NU * (kUnitScalars / 4);
+    const size_t cstride = (size_t)NU * (kUnitScalars / 4);  // from one chunk's block to the next
+#pragma unroll 1
+    for (int j = tid; j < NU * kPieces; j += nthr) {
+      const int u = j / kPieces;
+      const float4* p = p4 + u * (kUnitScalars / 4) + (j - u * kPieces);
+      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+      for (int c0 = 0; c0 < g.nC; c0 += 8) {  // eight chunks' partials in flight, added in chunk order
+        float4 v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = p[(size_t)min(c0 + i, g.nC - 1) * cstride];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (c0 + i < g.nC) s = add4(s, v[i]);
+      }
+      reinterpret_cast<float4*>(s_part)[j] = s;
+    }
   }
-  for (int idx = threadIdx.x; idx < g.NN; idx += blockDim.x) {
+  if (UP) upper_levels<UP>(g, nsum, f, red, up);
+  for (int j = tid; j < kSelBins; j += nthr) h0[j] = 0;
+  for (int idx = tid; idx < g.NN; idx += nthr) {
     int lvl, by, bx;
     node_decode(g, idx, lvl, by, bx);
+    s_pos[idx] = node_exists(g, lvl, by, bx) ? (lvl << 16) | (by << 8) | bx : -1;
+  }
+  __syncthreads();
+  // dot product of every node's sum with its parent's; the squared norm of a cell
+  for (int idx = tid; idx < g.NN; idx += nthr) {
+    const int pos = s_pos[idx], lvl = pos >> 16, by = (pos >> 8) & 255, bx = pos & 255;
     float n = 0.f, d = 0.f;
-    if (node_exists(g, lvl, by, bx)) {
-      // where the first pass (levels 0..2) or the step above (levels >= 3) left this node's partials
-      const float* p;
-      size_t cstride;  // from one chunk's value to the next
-      int dn = 0;      // offset of the squared norm relative to the dot product (cells only)
+    if (pos >= 0) {
       if (lvl <= 2) {
         const int y = by << lvl, x = bx << lvl;
-        const int NU = unit_cols(g) * unit_rows(g);
         const int q2 = ((y >> 2) & 1) * 2 + ((x >> 2) & 1), q1 = ((y >> 1) & 1) * 2 + ((x >> 1) & 1);
         const int slot = lvl == 2 ? 4 * kTileRows + q2
                                   : q2 * kTileRows + (lvl == 1 ? 32 + q1 : 16 + q1 * 4 + (y & 1) * 2 + (x & 1));
-        p = part + ((size_t)f * g.nC * NU + (y >> 3) * unit_cols(g) + (x >> 3)) * kUnitScalars + slot;
-        cstride = (size_t)NU * kUnitScalars;
-        dn = -16;
-      } else {
-        const int NB = g.NN - g.lvl_base[3];
-        p = partu + (size_t)f * g.nC * NB + (idx - g.lvl_base[3]);
-        cstride = NB;
-      }
-      const bool want_n = lvl == 0, want_d = lvl < g.L;
-      for (int c0 = 0; c0 < g.nC; c0 += 8) {  // eight chunks' partials in flight, added in chunk order
-        float pn[8], pd[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const bool in = c0 + u < g.nC;
-          pn[u] = in && want_n ? p[(size_t)(c0 + u) * cstride + dn] : 0.f;
-          pd[u] = in && want_d ? p[(size_t)(c0 + u) * cstride] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          n += pn[u];
-          d += pd[u];
-        }
+        const float* q = s_part + ((y >> 3) * UC + (x >> 3)) * kUnitStats + slot;
+        if (lvl < g.L) d = q[0];
+        if (lvl == 0) n = q[-16];
+      } else if (UP && lvl < g.L) {
+        d = lvl == 3 ? up[((by >> 1) * UP + (bx >> 1)) * 4 + (by & 1) * 2 + (bx & 1)] : up[16 + by * 2 + bx];
       }
     }
     s_n[idx] = n;
-    s_sim[idx] = d;  // dot for now
+    s_sim[idx] = d;
   }
   __syncthreads();
   // squared norm of a node above the cells = sum over its children of (child sum) . (node sum)
-  for (int idx = threadIdx.x; idx < g.NN; idx += blockDim.x) {
-    int lvl, by, bx;
-    node_decode(g, idx, lvl, by, bx);
+  for (int idx = tid; idx < g.NN; idx += nthr) {
+    const int pos = s_pos[idx], lvl = pos >> 16, by = (pos >> 8) & 255, bx = pos & 255;
     float n = s_n[idx];
-    if (lvl >= 1) {
-      n = 0.f;
-      if (node_exists(g, lvl, by, bx))
-        for (int k = 0; k < 4; ++k) {
-          const int cy = 2 * by + (k >> 1), cx = 2 * bx + (k & 1);
-          if (node_exists(g, lvl - 1, cy, cx)) n += s_sim[node_index(g, lvl - 1, cy, cx)];
-        }
+    if (pos >= 0 && lvl >= 1) {
+      const int c = node_index(g, lvl - 1, 2 * by, 2 * bx), side = g.P >> (lvl - 1);
+      n = ((s_sim[c] + s_sim[c + 1]) + s_sim[c + side]) + s_sim[c + side + 1];  // (zero where there is no child)
       s_n[idx] = n;
     }
     nrm2[fo + idx] = n;
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < g.NN; idx += blockDim.x) {
-    int lvl, by, bx;
-    node_decode(g, idx, lvl, by, bx);
+  for (int idx = tid; idx < g.NN; idx += nthr) {
+    const int pos = s_pos[idx], lvl = pos >> 16, by = (pos >> 8) & 255, bx = pos & 255;
     float v = 0.f;
-    if (lvl < g.L && node_exists(g, lvl, by, bx))
-      v = cosine_from(s_sim[idx], s_n[idx], s_n[node_index(g, lvl + 1, by >> 1, bx >> 1)]);
+    if (pos >= 0 && lvl < g.L) v = cosine_from(s_sim[idx], s_n[idx], s_n[node_index(g, lvl + 1, by >> 1, bx >> 1)]);
     sim[fo + idx] = v;
-    s_m[idx] = v;  // reuse as sim storage until the next phase reads it
+    s_m[idx] = v;  // the similarities, until the next step has read them
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < g.NN; idx += blockDim.x) {
-    int lvl, by, bx;
-    node_decode(g, idx, lvl, by, bx);
+  for (int idx = tid; idx < g.NN; idx += nthr) {
+    const int pos = s_pos[idx], lvl = pos >> 16, by = (pos >> 8) & 255, bx = pos & 255;
     float mv = 2.f;
-    if (lvl >= 1 && node_exists(g, lvl, by, bx)) {
+    if (pos >= 0 && lvl >= 1) {
+      const int c = node_index(g, lvl - 1, 2 * by, 2 * bx), side = g.P >> (lvl - 1);
       bool nan = false;
+#pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const int cy = 2 * by + (k >> 1), cx = 2 * bx + (k & 1);
-        if (!node_exists(g, lvl - 1, cy, cx)) continue;
-        const float v = s_m[node_index(g, lvl - 1, cy, cx)];
+        const int ci = c + (k >> 1) * side + (k & 1);
+        if (s_pos[ci] < 0) continue;
+        const float v = s_m[ci];
         if (v != v) nan = true;
         mv = fminf(mv, v);
       }
@@ -595,33 +618,27 @@ __global__ __launch_bounds__(512) void k_spatial_finalize(Geo g, const float* __
     m[fo + idx] = mv;
   }
   __syncthreads();
-  for (int i0 = 0; i0 < g.NN; i0 += blockDim.x) {  // uniform trip count: the histogram update is wave-wide
-    const int idx = i0 + threadIdx.x;
+#pragma unroll 1
+  for (int i0 = g.lvl_base[1]; i0 < g.NN; i0 += nthr) {  // uniform trip count: the histogram update is wave-wide
+    const int idx = i0 + tid;
     uint32_t key = 0;
     unsigned wgt = 0;
     if (idx < g.NN) {
-      int lvl, by, bx;
-      node_decode(g, idx, lvl, by, bx);
-      float s = -2.f;
-      if (lvl >= 1 && node_exists(g, lvl, by, bx)) {
-        int l = lvl, y = by, x = bx;
-        while (true) {
+      const int pos = s_pos[idx], lvl = pos >> 16, by = (pos >> 8) & 255, bx = pos & 255;
+      // compact (value, weight) element of the budget search: upper-level nodes with >= 2 children
+      if (pos >= 0) {
+        float s = -2.f;
+        for (int l = lvl, y = by, x = bx; l <= g.L; ++l, y >>= 1, x >>= 1) {
           const float v = s_sim[node_index(g, l, y, x)];
           s = fmaxf(s, (v != v) ? -2.f : v);  // NaN always splits
-          if (l == g.L) break;
-          ++l; y >>= 1; x >>= 1;
         }
+        const int h = ((2 * by + 1) << (lvl - 1)) < g.H, w = ((2 * bx + 1) << (lvl - 1)) < g.W;
+        wgt = (unsigned)((1 + h) * (1 + w) - 1);  // children beyond the first
+        if (wgt) key = float_key(s);
       }
-      // compact (value, weight) element of the budget search: upper-level nodes with >= 2 children
-      if (lvl >= 1) {
-        int kids = 0;
-        if (node_exists(g, lvl, by, bx))
-          for (int k = 0; k < 4; ++k) kids += node_exists(g, lvl - 1, 2 * by + (k >> 1), 2 * bx + (k & 1));
-        const size_t o = (size_t)f * (g.NN - g.lvl_base[1]) + (idx - g.lvl_base[1]);
-        if (kids >= 2) { key = float_key(s); wgt = (unsigned)(kids - 1); }
-        sel_key[o] = key;
-        sel_w[o] = (uint8_t)wgt;
-      }
+      const size_t o = (size_t)f * (g.NN - g.lvl_base[1]) + (idx - g.lvl_base[1]);
+      sel_key[o] = key;
+      sel_w[o] = (uint8_t)wgt;
     }
     wave_hist_add(h0, wgt != 0, key >> 21, wgt);
   }
@@ -629,12 +646,17 @@ __global__ __launch_bounds__(512) void k_spatial_finalize(Geo g, const float* __
   sel_flush_level0(sel + f / g.T, h0);
 }
 
-void launch_spatial_finalize(const Geo& g, const float* part, float* partu, float* nsum, float* nrm2, float* sim,
-                             float* m, uint32_t* sel_key, uint8_t* sel_w, SelState* sel, hipStream_t s) {
-  const int threads = g.NN <= 256 ? 256 : 512;  // one node per thread where it fits; more workgroups per CU beyond
-  hipLaunchKernelGGL(k_spatial_finalize, dim3(g.F), dim3(threads), 3 * g.NN * sizeof(float), s, g, part, partu, nsum, nrm2,
-                     sim,
-                     m, sel_key, sel_w, sel);
+void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float* nrm2, float* sim, float* m,
+                             uint32_t* sel_key, uint8_t* sel_w, SelState* sel, hipStream_t s) {
+  const int up = g.L < 4 ? 0 : (g.P == 16 ? 1 : 2);
+  const int threads = g.NN <= 256 && !up ? 256 : kFinThreads;  // one node per thread where it fits
+  const size_t lds = ((size_t)unit_cols(g) * unit_rows(g) * kUnitStats + 4 * (size_t)g.NN) * sizeof(float);
+  if (up == 0)
+    hipLaunchKernelGGL(k_spatial_finalize<0>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel);
+  else if (up == 1)
+    hipLaunchKernelGGL(k_spatial_finalize<1>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel);
+  else
+    hipLaunchKernelGGL(k_spatial_finalize<2>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel);
 }
 
 // ------------------------------------------------------------------------------------------------

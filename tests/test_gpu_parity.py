@@ -682,3 +682,14 @@ def test_randomized_shapes_and_settings(lib):
                       ctx=shared if case % 2 == 0 else None, **kw)
         info = P.check_parity(lib, feats, r, root_grid=R, mode=mode, order=order, **kw)
         assert info["K"] >= 1
+
+
+@pytest.mark.parametrize("seed,B,T,H,W,D,dtype,R", [
+    (60, 1, 3, 32, 32, 8, "f32", 2),       # four roots at level 4: nothing above them
+    (61, 1, 2, 17, 9, 2056, "f32", 1),     # level-4 and level-5 nodes partly beyond the edge, more columns than threads
+    (62, 2, 2, 16, 16, 1032, "bf16", 1),   # one node of level 4 over four full units
+    (63, 1, 2, 9, 9, 4104, "f16", 1),      # units of one row / column, nine chunks
+])
+def test_levels_above_the_units(lib, seed, B, T, H, W, D, dtype, R):
+    _run_and_check(lib, _variant(seed, B, T, H, W, D, dtype), tau_s=0.85, tau_t=0.8, root_grid=R)
+    _run_and_check(lib, _variant(seed, B, T, H, W, D, dtype, sigma=0.02), keep=0.2, root_grid=R)
