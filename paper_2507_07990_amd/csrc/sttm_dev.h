@@ -279,7 +279,7 @@ struct SelFound {
 // in kSelCopies copies, one per accelerator die (workgroups go to the dies round-robin by their index), so that
 // the hot counters stay in one die's L2 instead of travelling between the dies with every atomic.
 constexpr int kSelCopies = 8;
-struct SelState {
+struct alignas(16) SelState {
   unsigned hist0[kSelCopies][kSelBins];  // weight per leading digit over all elements; the copies add up
   unsigned hist[2][kSelBins];            // second and third digit under the found prefix
   unsigned lo_out;             // largest key whose leading 22 bits are below the found prefix (0 = none)
@@ -300,6 +300,7 @@ __device__ inline void sel_clear(SelState* st) {
 // LDS atomics.
 __device__ inline void wave_hist_add(unsigned* hist, bool valid, unsigned digit, unsigned w) {
   unsigned long long todo = __ballot(valid);
+#pragma unroll 1
   for (int it = 0; it < 2 && todo; ++it) {
     const int leader = __ffsll((long long)todo) - 1;
     const unsigned d = __shfl(digit, leader, 64);
@@ -321,20 +322,21 @@ __device__ inline void sel_flush_level0(SelState* st, const unsigned* lds_hist) 
 
 constexpr int kSelThreads = 256;
 
-// Workgroup-wide (kSelThreads threads): the first bin of `hist` at which acc + running weight exceeds `budget`.
+// Workgroup-wide (THREADS threads): the first bin of `hist` at which acc + running weight exceeds `budget`.
 // Returns false when the whole histogram fits. All threads get the same answer.
 // *below = largest non-empty bin before the found one, or -1.
 // The histogram is the sum of COPIES arrays of kSelBins counters.
-template <int COPIES>
+template <int COPIES, int THREADS>
 __device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long long acc,
                                 unsigned long long budget, unsigned* digit, unsigned long long* acc_out,
                                 int* below) {
-  __shared__ unsigned long long wsum[kSelThreads / 64];
+  __shared__ unsigned long long wsum[THREADS / 64];
   __shared__ unsigned s_digit;
   __shared__ unsigned long long s_acc;
   __shared__ int s_found, s_below;
-  constexpr int PER = kSelBins / kSelThreads;
+  constexpr int PER = kSelBins / THREADS;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  static_assert(PER % 4 == 0, "whole 16-byte pieces");
   unsigned h[PER];
   unsigned long long tot = 0;
 #pragma unroll
@@ -342,7 +344,10 @@ __device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long
 #pragma unroll
   for (int c = 0; c < COPIES; ++c)  // all loads at once
 #pragma unroll
-    for (int j = 0; j < PER; ++j) h[j] += hist[c * kSelBins + tid * PER + j];
+    for (int j = 0; j < PER; j += 4) {
+      const uint4 v = *reinterpret_cast<const uint4*>(hist + c * kSelBins + tid * PER + j);
+      h[j] += v.x; h[j + 1] += v.y; h[j + 2] += v.z; h[j + 3] += v.w;
+    }
 #pragma unroll
   for (int j = 0; j < PER; ++j) tot += h[j];
   unsigned long long inc = tot;
@@ -395,7 +400,7 @@ __device__ inline float sel_last_digit(const SelState* __restrict__ st) {
     unsigned d2;
     unsigned long long a2;
     int below;
-    if (sel_pick<1>(st->hist[1], fd.acc, fd.budget, &d2, &a2, &below)) {
+    if (sel_pick<1, kSelThreads>(st->hist[1], fd.acc, fd.budget, &d2, &a2, &below)) {
       const unsigned over = (fd.prefix << 10) | d2;
       const unsigned lo_key = below >= 0 ? ((fd.prefix << 10) | (unsigned)below) : st->lo_out;
       const float hi = key_float(over);

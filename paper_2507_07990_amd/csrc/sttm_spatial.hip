@@ -737,7 +737,8 @@ void launch_node_levels(const Geo& g, const int32_t* node_map, uint8_t* node_lev
 // next one resolves one digit only.
 // Input: keys[video][per_video] (0 = not an element), weights (NULL = 1 for every element).
 // ------------------------------------------------------------------------------------------------
-constexpr int kSelPer = 8;   // elements per thread and pass
+constexpr int kPassThreads = 512;  // threads of a search pass
+constexpr int kSelPer = 4;         // elements per thread and pass
 
 __device__ inline int sel_shift(int pass) { return pass == 0 ? 21 : (pass == 1 ? 10 : 0); }
 __device__ inline int sel_width(int pass) { return pass == 2 ? 10 : 11; }
@@ -772,28 +773,37 @@ __global__ __launch_bounds__(256) void k_select_reset(SelState* st) {
 // starts from what the first one left in the state -- and bins its slice of the keys under the prefix found
 // so far; the workgroup of slice 0 leaves the prefix for the next launch.
 template <int PASS>  // 1 or 2
-__global__ __launch_bounds__(kSelThreads) void k_select_pass(Geo g, const uint32_t* __restrict__ keys,
+__global__ __launch_bounds__(kPassThreads) void k_select_pass(Geo g, const uint32_t* __restrict__ keys,
                                                              const uint8_t* __restrict__ weights, int per_video,
                                                              const int* __restrict__ target, int base_const,
                                                              const int32_t* __restrict__ node_map,
                                                              SelState* __restrict__ states) {
   __shared__ unsigned hist[kSelBins];
+  __shared__ uint32_t s_key[kSelPer][kPassThreads];  // (each thread reads back what it wrote: lets the loop below stay one copy)
+  __shared__ uint8_t s_w[kSelPer][kPassThreads];
+  __shared__ unsigned s_lo;
   const int b = blockIdx.y, tid = threadIdx.x;
+  if (tid == 0) s_lo = 0;
   SelState* st = states + b;
   // the slice's keys do not depend on the search: their loads fly while the digit is being found
   const uint32_t* kv = keys + (size_t)b * per_video;
   const uint8_t* wv = weights ? weights + (size_t)b * per_video : nullptr;
-  const int j0 = blockIdx.x * (kSelThreads * kSelPer);
+  const int j0 = blockIdx.x * (kPassThreads * kSelPer);
   uint32_t key[kSelPer];
   unsigned w[kSelPer];
 #pragma unroll
   for (int u = 0; u < kSelPer; ++u) {
-    const int j = j0 + u * kSelThreads + tid;
+    const int j = j0 + u * kPassThreads + tid;
     key[u] = j < per_video ? kv[j] : 0u;
     w[u] = 1u;
     if (wv) w[u] = j < per_video ? wv[j] : 0u;
   }
-  for (int j = tid; j < kSelBins; j += kSelThreads) hist[j] = 0;
+#pragma unroll
+  for (int u = 0; u < kSelPer; ++u) {
+    s_key[u][tid] = key[u];
+    s_w[u][tid] = (uint8_t)w[u];
+  }
+  for (int j = tid; j < kSelBins; j += kPassThreads) hist[j] = 0;
   SelFound fd;
   if (PASS == 1) {
     const int base = sel_base(g, b, base_const, node_map);
@@ -808,8 +818,8 @@ __global__ __launch_bounds__(kSelThreads) void k_select_pass(Geo g, const uint32
   if (fd.rc == 0) {  // uniform over the workgroup
     unsigned d;
     unsigned long long a2;
-    const bool hit = PASS == 1 ? sel_pick<kSelCopies>(st->hist0[0], fd.acc, fd.budget, &d, &a2, nullptr)
-                               : sel_pick<1>(st->hist[0], fd.acc, fd.budget, &d, &a2, nullptr);
+    const bool hit = PASS == 1 ? sel_pick<kSelCopies, kPassThreads>(st->hist0[0], fd.acc, fd.budget, &d, &a2, nullptr)
+                               : sel_pick<1, kPassThreads>(st->hist[0], fd.acc, fd.budget, &d, &a2, nullptr);
     if (hit) {
       fd.prefix = (fd.prefix << sel_width(PASS - 1)) | d;
       fd.acc = a2;
@@ -823,21 +833,21 @@ __global__ __launch_bounds__(kSelThreads) void k_select_pass(Geo g, const uint32
     const unsigned prefix = fd.prefix;
     const int shift = sel_shift(PASS), width = sel_width(PASS);
     unsigned lo = 0;  // key 0 is below every real value
-#pragma unroll
+#pragma unroll 1
     for (int u = 0; u < kSelPer; ++u) {
-      if (w[u] == 0) key[u] = 0;
-      const unsigned top = key[u] >> (shift + width);
-      const bool valid = key[u] != 0 && top == prefix;
-      wave_hist_add(hist, valid, (key[u] >> shift) & ((1u << width) - 1u), w[u]);
-      if (PASS == 2 && key[u] != 0 && top < prefix && key[u] > lo) lo = key[u];
+      const unsigned wu = s_w[u][tid], k = wu ? s_key[u][tid] : 0u;
+      const unsigned top = k >> (shift + width);
+      wave_hist_add(hist, k != 0 && top == prefix, (k >> shift) & ((1u << width) - 1u), wu);
+      if (PASS == 2 && top < prefix && k > lo) lo = k;
     }
     if (PASS == 2) {
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) lo = max(lo, (unsigned)__shfl_xor((int)lo, o, 64));
-      if ((tid & 63) == 0 && lo) atomicMax(&st->lo_out, lo);
+      if ((tid & 63) == 0 && lo) atomicMax(&s_lo, lo);
     }
     __syncthreads();
-    for (int j = tid; j < kSelBins; j += kSelThreads)
+    if (PASS == 2 && tid == 0 && s_lo) atomicMax(&st->lo_out, s_lo);
+    for (int j = tid; j < kSelBins; j += kPassThreads)
       if (hist[j]) atomicAdd(&st->hist[PASS - 1][j], hist[j]);
   }
 }
@@ -852,14 +862,14 @@ __global__ __launch_bounds__(kSelThreads) void k_select_tau(const SelState* __re
 static void launch_select(const Geo& g, const uint32_t* keys, const uint8_t* weights, int per_video,
                           const int* target, int base_const, const int32_t* node_map, SelState* st, bool dirty,
                           float* tau, hipStream_t s) {
-  const int slices = per_video > 0 ? (per_video + kSelThreads * kSelPer - 1) / (kSelThreads * kSelPer) : 1;
-  const dim3 grid(slices, g.B), block(kSelThreads);
+  const int slices = per_video > 0 ? (per_video + kPassThreads * kSelPer - 1) / (kPassThreads * kSelPer) : 1;
+  const dim3 grid(slices, g.B), block(kPassThreads);
   if (dirty) hipLaunchKernelGGL(k_select_reset, dim3(g.B), dim3(256), 0, s, st);
   hipLaunchKernelGGL(k_select_pass<1>, grid, block, 0, s, g, keys, weights, per_video, target, base_const,
                      node_map, st);
   hipLaunchKernelGGL(k_select_pass<2>, grid, block, 0, s, g, keys, weights, per_video, target, base_const,
                      node_map, st);
-  if (tau) hipLaunchKernelGGL(k_select_tau, dim3(g.B), block, 0, s, st, tau);
+  if (tau) hipLaunchKernelGGL(k_select_tau, dim3(g.B), dim3(kSelThreads), 0, s, st, tau);
 }
 
 void launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
