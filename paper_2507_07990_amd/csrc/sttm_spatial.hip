@@ -28,6 +28,17 @@ __device__ __forceinline__ void tile_load(typename Row<DT>::Raw (&raw)[16], cons
   }
 }
 
+// The same for one 2x2 block (q1) of the tile.
+template <int DT>
+__device__ __forceinline__ void block_load(typename Row<DT>::Raw (&raw)[4], const typename Row<DT>::Elem* fbase,
+                                           int W, int D, int ty, int tx, int th, int tw, int q1) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int dy = min((q1 >> 1) * 2 + (k >> 1), th - 1), dx = min((q1 & 1) * 2 + (k & 1), tw - 1);
+    raw[k] = *reinterpret_cast<const typename Row<DT>::Raw*>(fbase + (size_t)((ty + dy) * W + tx + dx) * D);
+  }
+}
+
 // Zeroes what tile_load fetched for cells beyond the edge and for lanes beyond the last channel.
 template <int DT>
 __device__ __forceinline__ void tile_mask(typename Row<DT>::Raw (&raw)[16], int th, int tw, bool act) {
@@ -90,6 +101,27 @@ __device__ __forceinline__ float staged_row_sum(const float* tbs, int row) {
   return ((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w));
 }
 
+// Sum and per-lane scalars of one 2x2 block: its per-channel sum in S1, and nd = squared norms of its four cells, then
+// each cell . the block's sum. A cell's dot product with the sum is the sum of its dot products with the block's four
+// cells, which come straight from the packed rows (no element is widened for them). Rows of cells beyond the edge and
+// lanes beyond the last channel must be zero (tile_mask).
+template <int DT>
+__device__ __forceinline__ void block_stats(const typename Row<DT>::Raw* raw, float (&S1)[Row<DT>::VEC], float (&nd)[8]) {
+  typedef Row<DT> R;
+#pragma unroll
+  for (int v = 0; v < R::VEC; ++v) S1[v] = 0.f;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) R::add_row(raw[k], S1);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) nd[k] = R::dot(raw[k], raw[k]);  // (zero rows give zero)
+  const float p01 = R::dot(raw[0], raw[1]), p02 = R::dot(raw[0], raw[2]), p03 = R::dot(raw[0], raw[3]);
+  const float p12 = R::dot(raw[1], raw[2]), p13 = R::dot(raw[1], raw[3]), p23 = R::dot(raw[2], raw[3]);
+  nd[4] = (nd[0] + p01) + (p02 + p03);
+  nd[5] = (nd[1] + p01) + (p12 + p13);
+  nd[6] = (nd[2] + p02) + (p12 + p23);
+  nd[7] = (nd[3] + p03) + (p13 + p23);
+}
+
 // Sums and per-lane scalars of one tile: returns the tile's per-channel sum in S2 and stages the tile's scalars --
 // batch q1 (rows 8 q1 .. 8 q1 + 7): squared norms of the four cells of 2x2 block q1, then each cell . the block's
 // sum; p1[q1]: block sum . tile sum, left to the caller to stage (zero for cells and blocks beyond the edge).
@@ -107,22 +139,8 @@ __device__ __forceinline__ void tile_stats(const typename Row<DT>::Raw (&raw)[16
 #pragma unroll
     for (int v = 0; v < VEC; ++v) S1[q1][v] = 0.f;
     if ((q1 >> 1) * 2 >= th || (q1 & 1) * 2 >= tw) continue;  // block beyond the edge (wave-uniform)
-    // the block's sum, channel by channel; a cell's dot product with it is the sum of the cell's dot products with
-    // the block's four cells, which come straight from the packed rows (no element is widened for them)
-#pragma unroll
-    for (int k = 0; k < 4; ++k) R::add_row(raw[q1 * 4 + k], S1[q1]);
     float nd[8];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) nd[k] = R::dot(raw[q1 * 4 + k], raw[q1 * 4 + k]);  // (zero rows give zero)
-    {
-      const float p01 = R::dot(raw[q1 * 4 + 0], raw[q1 * 4 + 1]), p02 = R::dot(raw[q1 * 4 + 0], raw[q1 * 4 + 2]);
-      const float p03 = R::dot(raw[q1 * 4 + 0], raw[q1 * 4 + 3]), p12 = R::dot(raw[q1 * 4 + 1], raw[q1 * 4 + 2]);
-      const float p13 = R::dot(raw[q1 * 4 + 1], raw[q1 * 4 + 3]), p23 = R::dot(raw[q1 * 4 + 2], raw[q1 * 4 + 3]);
-      nd[4] = (nd[0] + p01) + (p02 + p03);
-      nd[5] = (nd[1] + p01) + (p12 + p13);
-      nd[6] = (nd[2] + p02) + (p12 + p23);
-      nd[7] = (nd[3] + p03) + (p13 + p23);
-    }
+    block_stats<DT>(raw + q1 * 4, S1[q1], nd);
     stage8(tbs, q1, lane, nd);
 #pragma unroll
     for (int v = 0; v < VEC; ++v) S2[v] += S1[q1][v];
@@ -163,6 +181,31 @@ __device__ __forceinline__ void wait_loads_but(int newer) {
   if (newer >= 16) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)" ::: "memory");
   else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 #endif
+}
+
+// Which (frame, unit, chunk) a workgroup of a 1-D grid works on; false = none. With the frame-to-frame dot products a
+// tile is asked for by two workgroups: its own frame's and the one of the frame before. Workgroups go to the eight dies
+// round-robin by their index; each die gets a contiguous range of frames and walks it in order, two frames at a time
+// with the same (unit, chunk) of both next to each other, so that the two requests come from the same die within a few
+// microseconds of each other and the second one is served by that die's L2. (With frame after frame the 144 workgroups
+// a frame of 18x24 tokens at D = 8192 has lay between the two: 2.44 GB fetched, 357 us; in pairs 331 us. Groups of 4 to
+// 16 frames: 335-345 us, and up to 7 us slower at 512 frames of 13x13, D = 3584, where pairs cost nothing.)
+constexpr int kPyrGroup = 2;
+__device__ __forceinline__ bool pyramid_place(const Geo& g, int NU, int& f, int& u, int& chunk) {
+  const int per_die = (g.F + 7) / 8, die = blockIdx.x & 7;
+  int slot = blockIdx.x >> 3;
+  const int fi = slot % kPyrGroup;
+  slot /= kPyrGroup;
+  chunk = slot % g.nC;
+  slot /= g.nC;
+  u = slot % NU;
+  const int fl = (slot / NU) * kPyrGroup + fi;
+  f = die * per_die + fl;
+  return fl < per_die && f < g.F;
+}
+static unsigned pyramid_grid(const Geo& g) {
+  const unsigned pairs = ((g.F + 7) / 8 + kPyrGroup - 1) / kPyrGroup;  // per die
+  return 8u * pairs * kPyrGroup * (unsigned)(unit_cols(g) * unit_rows(g) * g.nC);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -208,18 +251,7 @@ __global__ __launch_bounds__(64, 2) void k_pyramid_stats(Geo g, const void* __re
   const int NU = unit_cols(g) * unit_rows(g), lane = threadIdx.x;
   int chunk, u, f;
   if (CC) {
-    // With the frame-to-frame dot products a tile is asked for by two workgroups: its own frame's and the one of the
-    // frame before. Workgroups go to the eight dies round-robin by their index; each die gets a contiguous range of
-    // frames and walks it in order, so the two requests come from the same die within a few microseconds of each
-    // other and the second one is served by that die's L2.
-    const int per_die = (g.F + 7) / 8, die = blockIdx.x & 7;
-    int slot = blockIdx.x >> 3;
-    chunk = slot % g.nC;
-    slot /= g.nC;
-    u = slot % NU;
-    const int fl = slot / NU;
-    f = die * per_die + fl;
-    if (fl >= per_die || f >= g.F) return;
+    if (!pyramid_place(g, NU, f, u, chunk)) return;
   } else {
     chunk = blockIdx.x;
     u = blockIdx.y;
@@ -404,33 +436,222 @@ __global__ __launch_bounds__(64, 2) void k_pyramid_stats(Geo g, const void* __re
         reinterpret_cast<const float4*>(st)[lane];
 }
 
+// ------------------------------------------------------------------------------------------------
+// k_pyramid_tiles: the same pass for small inputs, with the same results bit for bit. A workgroup of k_pyramid_stats is
+// one wavefront that walks its four tiles one after the other, about 5 us each whatever else runs; with fewer of them
+// than the chip holds a few times over that chain is the pass. Here the four tiles of a unit are four wavefronts of one
+// workgroup: each reads its tile and, four rows at a time, the partner tile, the first eight partner rows requested with
+// the tile's own; the tiles' sums meet in LDS for the unit's sum. No row buffer for a next tile is needed, which leaves
+// three wavefronts per SIMD.
+// (8x8 tokens, 8 frames, D = 64, fp32: 22.4 -> 7.9 us; one image of 24x24, D = 1152: 18.4 -> 7.0; 64 frames of 16x16,
+// D = 1152: 26.2 -> 14.3; of 13x13, D = 3584: 29.1 -> 24.5. Where the chip is full the longer-lived wavefronts with their
+// prefetch are better: 512 frames of 13x13 161 against 163 us, 1024 of 27x27 at D = 1152 442 against 501, 180 of 18x24 at
+// D = 8192 354 against 372.)
+// ------------------------------------------------------------------------------------------------
+template <int DT, int CC>  // CC: 0 = statistics only, 1 = + cell-to-cell dot products, 2 = + the same for levels 1 and 2
+__global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __restrict__ feats_v,
+                                                          float* __restrict__ part, float* __restrict__ nsum,
+                                                          SelState* __restrict__ sel) {
+  typedef Row<DT> R;
+  typedef typename R::Raw Raw;
+  constexpr int VEC = R::VEC;
+  __shared__ __attribute__((aligned(16))) float stage[4][kStageRows * kStageStride];
+  __shared__ __attribute__((aligned(16))) float st[kUnitScalars];
+  __shared__ float4 tsum[4][VEC / 4][64];  // the four tiles' sums
+  const int UX = unit_cols(g), NU = UX * unit_rows(g), lane = threadIdx.x & 63;
+  int f, u, chunk;
+  if (!pyramid_place(g, NU, f, u, chunk)) return;  // (the whole workgroup)
+  // (which wavefront -- and so which SIMD -- gets which tile rotates: in a ragged unit the first tile is the fullest)
+  const int q2 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6) + u + f + chunk) & 3;
+  float* tbs = stage[q2];
+  const int ch0 = chunk * g.cch + lane * VEC;
+  const bool act = ch0 < g.D;
+  const int H = g.H, W = g.W, L = g.L;
+  const int y3 = (u / UX) * 8, x3 = (u % UX) * 8;
+  const int ty = y3 + (q2 >> 1) * 4, tx = x3 + (q2 & 1) * 4;
+  const int th = max(0, min(4, H - ty)), tw = max(0, min(4, W - tx));  // valid rows / columns of the tile
+  const bool has_next = CC && f % g.T != g.T - 1;
+  if (chunk == 0 && u == 0 && f % g.T == 0) sel_clear(sel + f / g.T);  // this video's budget search starts afresh
+  float S2[VEC];
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) S2[v] = 0.f;
+  if (th > 0 && tw > 0) {
+    const typename R::Elem* fbase =
+        reinterpret_cast<const typename R::Elem*>(feats_v) + (size_t)f * g.HW * g.D + (act ? ch0 : 0);
+    const typename R::Elem* nbase = fbase + (size_t)g.HW * g.D;
+    Raw raw[16];
+    tile_load<DT>(raw, fbase, W, g.D, ty, tx, th, tw);
+    Raw pr[2][4];  // rows of the partner tile, two 2x2 blocks at a time
+    if (CC && has_next) {
+      block_load<DT>(pr[0], nbase, W, g.D, ty, tx, th, tw, 0);
+      block_load<DT>(pr[1], nbase, W, g.D, ty, tx, th, tw, 1);
+    }
+    // a full tile of a full chunk needs no masking
+    const bool ragged = th < 4 || tw < 4 || (chunk + 1) * g.cch > g.D;
+    if (ragged) tile_mask<DT>(raw, th, tw, act);
+    float S1[4][VEC];  // the tile's 2x2 block sums
+    float b4[8];  // the blocks' dot products with the tile, then (CC = 2) with the same blocks of the next frame
+    float SN2[VEC], cd[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b4[i] = 0.f;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) SN2[v] = 0.f;
+    // Block by block, so that a block's rows are done with before the next one's sums need their registers.
+#pragma unroll
+    for (int q1 = 0; q1 < 4; ++q1) {
+      const bool live = (q1 >> 1) * 2 < th && (q1 & 1) * 2 < tw;  // (wave-uniform)
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) S1[q1][v] = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) cd[(q1 & 1) * 4 + k] = 0.f;
+      if (live) {
+        float nd[8];
+        block_stats<DT>(raw + q1 * 4, S1[q1], nd);
+        stage8(tbs, q1, lane, nd);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) S2[v] += S1[q1][v];
+        if (CC && has_next) {
+          // x_c(t) . x_c(t+1) for the block's cells: where both frames keep single cells the temporal stage needs
+          // nothing else (Sec. 3.3 compares node features; a cell's feature is its own row).
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (ragged) {  // (a clamped request repeated another cell; a lane beyond the last channel read channel 0)
+              const bool in = (q1 >> 1) * 2 + (k >> 1) < th && (q1 & 1) * 2 + (k & 1) < tw && act;
+              if (!in) pr[q1 & 1][k] = R::zero();
+            }
+            cd[(q1 & 1) * 4 + k] = R::dot(raw[q1 * 4 + k], pr[q1 & 1][k]);
+          }
+          if (CC >= 2) {
+            // The same for the tile's 2x2 blocks and for the tile itself: S_n(t) . S_n(t+1), what the temporal
+            // stage needs where both frames keep the same node n at level 1 or 2: the block's sum with the sum of the
+            // partner block's four rows, the tile's sum with the sum of the partner blocks.
+            float SN1[VEC], d1 = 0.f;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) SN1[v] = 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) R::add_row(pr[q1 & 1][k], SN1);
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+              d1 = fmaf(S1[q1][v], SN1[v], d1);
+              SN2[v] += SN1[v];
+            }
+            b4[4 + q1] = d1;
+          }
+        }
+      }
+      if (CC && has_next) {
+        if (q1 < 2) block_load<DT>(pr[q1], nbase, W, g.D, ty, tx, th, tw, 2 + q1);
+        if (q1 & 1) stage8(tbs, 5 + (q1 >> 1), lane, cd);
+      }
+    }
+#pragma unroll
+    for (int q1 = 0; q1 < 4; ++q1) {
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) b4[q1] = fmaf(S1[q1][v], S2[v], b4[q1]);
+    }
+    if (CC >= 2 && has_next) {
+      float t8[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t8[i] = 0.f;
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) t8[0] = fmaf(S2[v], SN2[v], t8[0]);
+      stage8(tbs, 7, lane, t8);
+    }
+#pragma unroll
+    for (int v = 0; v < VEC; v += 4) tsum[q2][v / 4][lane] = make_float4(S2[v], S2[v + 1], S2[v + 2], S2[v + 3]);
+    stage8(tbs, 4, lane, b4);
+    // row r of the staging area is added up by lane r and goes to its place in the unit's block (zero where the
+    // row stands for nothing: beyond the edge, above the root level, no next frame)
+    wave_lds_fence();
+    if (lane < 57) {
+      const int r = lane;
+      bool live;
+      int dst;
+      if (r < 32 || (r >= 40 && r < 56)) {  // a cell's row: norm, dot with its block, or with the next frame
+        const int q1 = r < 32 ? r >> 3 : (r - 40) >> 2, k = r & 3;
+        live = (q1 >> 1) * 2 + (k >> 1) < th && (q1 & 1) * 2 + (k & 1) < tw;
+        if (r < 32 && (r & 4)) live = live && 0 < L;
+        if (r >= 40) live = live && has_next;
+        dst = r < 32 ? q2 * kTileRows + ((r & 4) ? 16 : 0) + q1 * 4 + k : kUnitCellDots + q2 * 16 + (r - 40);
+      } else if (r < 40) {  // a 2x2 block's row: dot with the tile, or with the next frame
+        const int q1 = r & 3;
+        live = (q1 >> 1) * 2 < th && (q1 & 1) * 2 < tw;
+        live = live && (r < 36 ? 1 < L : (CC >= 2 && has_next));
+        dst = r < 36 ? q2 * kTileRows + 32 + q1 : kUnitNodeDots + q2 * 8 + q1;
+      } else {  // the tile with the next frame's
+        live = CC >= 2 && has_next;
+        dst = kUnitNodeDots + q2 * 8 + 4;
+      }
+      st[dst] = live ? staged_row_sum(tbs, r) : 0.f;
+    }
+  } else {
+#pragma unroll
+    for (int v = 0; v < VEC; v += 4) tsum[q2][v / 4][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (lane < kTileRows) st[q2 * kTileRows + lane] = 0.f;
+    if (lane < 16) st[kUnitCellDots + q2 * 16 + lane] = 0.f;
+    if (lane < 5) st[kUnitNodeDots + q2 * 8 + lane] = 0.f;
+  }
+  if (lane >= 5 && lane < 8) st[kUnitNodeDots + q2 * 8 + lane] = 0.f;
+  if (q2 == 0 && lane < kUnitCellDots - 4 * kTileRows - 4) st[4 * kTileRows + 4 + lane] = 0.f;
+  __syncthreads();
+  // level-2 dot products of the four tiles with the unit's sum
+  float d2 = 0.f;
+  if (L >= 3) {
+    float S3[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; v += 4) {
+      float4 s = tsum[0][v / 4][lane];
+#pragma unroll
+      for (int q = 1; q < 4; ++q) {
+        const float4 t = tsum[q][v / 4][lane];
+        s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+      }
+      S3[v] = s.x; S3[v + 1] = s.y; S3[v + 2] = s.z; S3[v + 3] = s.w;
+      if (q2 == v / 4 && act)  // a wavefront per four channels of the lanes stores the unit's sum
+        *reinterpret_cast<float4*>(nsum + ((size_t)f * (g.NN - g.lvl_base[3]) + (y3 >> 3) * (g.P >> 3) + (x3 >> 3)) * g.D + ch0 + v) = s;
+    }
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) d2 = fmaf(S2[v], S3[v], d2);
+    const float one[8] = {d2, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    stage8(tbs, 0, lane, one);
+    wave_lds_fence();
+    if (lane == 0) d2 = staged_row_sum(tbs, 0);
+  }
+  if (lane == 0) st[4 * kTileRows + q2] = d2;
+  // the workgroup's scalars leave in one piece: whole, aligned 128-byte lines that no other workgroup touches
+  __syncthreads();
+  if (threadIdx.x < kUnitScalars / 4)
+    reinterpret_cast<float4*>(part + ((size_t)(f * g.nC + chunk) * NU + u) * kUnitScalars)[threadIdx.x] =
+        reinterpret_cast<const float4*>(st)[threadIdx.x];
+}
+
+// Up to this many workgroups (units x chunks x frames) of k_pyramid_stats the pass is given to k_pyramid_tiles. The chip
+// holds 2048 of them at a time, and the two kernels cost the same at about two and a half fillings (5040 workgroups, 180
+// frames of 14x14 at D = 3584: 63.3 against 62.8 us; 2700: 42.8 against 35.5; 14336: 161 against 163).
+constexpr long long kPyrTilesMax = 4096;
+
+template <int DT, int CC>
+static void launch_pyramid_dt(const Geo& g, const void* feats, float* part, float* nsum, SelState* sel, hipStream_t s) {
+  const long long units = (long long)unit_cols(g) * unit_rows(g) * g.F;
+  if (units * g.nC <= kPyrTilesMax)
+    hipLaunchKernelGGL((k_pyramid_tiles<DT, CC>), dim3(pyramid_grid(g)), dim3(256), 0, s, g, feats, part, nsum, sel);
+  else
+    hipLaunchKernelGGL((k_pyramid_stats<DT, CC>), CC ? dim3(pyramid_grid(g)) : dim3(g.nC, unit_cols(g) * unit_rows(g), g.F),
+                       dim3(64), 0, s, g, feats, part, nsum, sel);
+}
+
 template <int CC>
 static void launch_pyramid_cc(const Geo& g, const void* feats, float* part, float* nsum, SelState* sel, hipStream_t s) {
-  const int NU = unit_cols(g) * unit_rows(g);
-  const dim3 grid((unsigned)(8 * ((g.F + 7) / 8) * NU * g.nC)), block(64);
-  if (g.dtype == 1)
-    hipLaunchKernelGGL((k_pyramid_stats<1, CC>), grid, block, 0, s, g, feats, part, nsum, sel);
-  else if (g.dtype == 2)
-    hipLaunchKernelGGL((k_pyramid_stats<2, CC>), grid, block, 0, s, g, feats, part, nsum, sel);
-  else
-    hipLaunchKernelGGL((k_pyramid_stats<0, CC>), grid, block, 0, s, g, feats, part, nsum, sel);
+  if (g.dtype == 1) launch_pyramid_dt<1, CC>(g, feats, part, nsum, sel, s);
+  else if (g.dtype == 2) launch_pyramid_dt<2, CC>(g, feats, part, nsum, sel, s);
+  else launch_pyramid_dt<0, CC>(g, feats, part, nsum, sel, s);
 }
 
 void launch_pyramid_stats(const Geo& g, const void* feats, int cell_dots, float* part, float* nsum, SelState* sel,
                           hipStream_t s) {
-  if (cell_dots >= 2) {
-    launch_pyramid_cc<2>(g, feats, part, nsum, sel, s);
-  } else if (cell_dots == 1) {
-    launch_pyramid_cc<1>(g, feats, part, nsum, sel, s);
-  } else {
-    const dim3 grid(g.nC, unit_cols(g) * unit_rows(g), g.F), block(64);
-    if (g.dtype == 1)
-      hipLaunchKernelGGL((k_pyramid_stats<1, 0>), grid, block, 0, s, g, feats, part, nsum, sel);
-    else if (g.dtype == 2)
-      hipLaunchKernelGGL((k_pyramid_stats<2, 0>), grid, block, 0, s, g, feats, part, nsum, sel);
-    else
-      hipLaunchKernelGGL((k_pyramid_stats<0, 0>), grid, block, 0, s, g, feats, part, nsum, sel);
-  }
+  if (cell_dots >= 2) launch_pyramid_cc<2>(g, feats, part, nsum, sel, s);
+  else if (cell_dots == 1) launch_pyramid_cc<1>(g, feats, part, nsum, sel, s);
+  else launch_pyramid_cc<0>(g, feats, part, nsum, sel, s);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -684,6 +684,55 @@ def test_randomized_shapes_and_settings(lib):
         assert info["K"] >= 1
 
 
+@pytest.mark.parametrize("H,W,D,dtype,R,tau_s,cell_dots", [
+    (13, 13, 520, "bf16", 1, 0.0, 0),    # ragged tiles, second chunk almost empty; no next-frame products
+    (13, 13, 520, "bf16", 1, 0.0, 1),
+    (13, 13, 520, "bf16", 4, -2.0, 2),   # every 4x4 block is one node in every frame
+    (11, 6, 1032, "f16", 8, -2.0, 2),    # every 2x2 block (11 rows: half blocks at the edge)
+    (5, 9, 264, "f32", 16, -2.0, 1),     # single cells only; a unit with one column
+    (27, 27, 72, "f32", 1, 0.0, 2),
+])
+def test_both_pyramid_kernels_give_the_same_bits(lib, H, W, D, dtype, R, tau_s, cell_dots):
+    """Small inputs take the kernel with four wavefronts per unit, large ones the one with one: the same videos, alone
+    and in a batch large enough, must give identical tables (norms and similarities are sums in a fixed order)."""
+    import torch
+    T = 3
+    dt, tt, per = {"bf16": (lib.STTM_BF16, torch.bfloat16, 512), "f16": (lib.STTM_F16, torch.float16, 512),
+                   "f32": (lib.STTM_F32, torch.float32, 256)}[dtype]
+    blocks = T * ((H + 7) // 8) * ((W + 7) // 8) * ((D + per - 1) // per)   # of one video
+    B = 4096 // blocks + 2
+    gen = torch.Generator(device="cuda:0").manual_seed(H * W + D)
+    x = torch.randn(B, 1, 1, 1, D, device="cuda:0", generator=gen)
+    x = (x + torch.randn(B, T, H, W, D, device="cuda:0", generator=gen)).to(tt).contiguous()
+
+    def tables(v):
+        b, NN, n = v.shape[0], lib.sttm_nodes_per_frame(H, W, R), v.shape[0] * T * H * W
+        s = lib.Sttm(0)
+        s.sttm_set_cell_dots(cell_dots)
+        s.ensure_workspace(b, T, H, W, D, dt, R)
+        node_map = torch.empty(n, dtype=torch.int32, device="cuda:0")
+        level = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        s.sttm_spatial_quadtree(v, dt, b, T, H, W, D, R, [tau_s], node_map, level)
+        s.sttm_temporal_stats(v, node_map, level)
+        out = []
+        for table in (lib.STTM_TBL_NORM2, lib.STTM_TBL_CHILD_SIM, lib.STTM_TBL_MIN_SIM):
+            t = torch.empty(b * T * NN, device="cuda:0")
+            s.sttm_export(table, t)
+            out.append(t.view(b, -1))
+        e = torch.empty(n, device="cuda:0")
+        s.sttm_export(lib.STTM_TBL_BEST_SIM, e)
+        kept = node_map == torch.arange(n, dtype=torch.int32, device="cuda:0")
+        kept.view(b, T, -1)[:, 0] = False                  # (the first frame has no similarities)
+        out.append(torch.where(kept, e, torch.zeros_like(e)).view(b, -1))
+        torch.cuda.synchronize()
+        return out
+
+    big = tables(x)
+    for b in (0, B // 2, B - 1):
+        for t_big, t_small in zip(big, tables(x[b:b + 1].contiguous())):
+            assert torch.equal(t_big[b], t_small[0])
+
+
 @pytest.mark.parametrize("seed,B,T,H,W,D,dtype,R", [
     (60, 1, 3, 32, 32, 8, "f32", 2),       # four roots at level 4: nothing above them
     (61, 1, 2, 17, 9, 2056, "f32", 1),     # level-4 and level-5 nodes partly beyond the edge, more columns than threads
