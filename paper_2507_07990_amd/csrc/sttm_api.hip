@@ -141,8 +141,17 @@ void* static_scratch_on(int device, hipError_t* err) {
 }
 }  // namespace
 
+// Host memory that the device writes directly: what a call hands back to the caller is there when the stream has been
+// synchronised, without a copy from the device into pageable memory (a staged transfer of its own).
+constexpr int kHostTaus = 1024;
+struct HostOut {
+  int32_t k;
+  float tau[kHostTaus];
+};
+
 struct sttm_ctx {
   int device = 0;
+  HostOut* host_out = nullptr;  // NULL if it could not be had: results are copied then
   char* static_scratch = nullptr;  // this device's copy of the static scratch array
   hipStream_t stream = nullptr;
   char* ws = nullptr;
@@ -195,6 +204,7 @@ ReduceBuffers reduce_buffers(char* base, const Layout& l) {
   rb.bigw = i32(l.bigw);
   rb.biglist = i32(l.biglist);
   rb.zpos = i32(l.zpos);
+  rb.host_k = nullptr;
   return rb;
 }
 
@@ -250,9 +260,15 @@ bool same_shape(const Geo& g, int dtype, int B, int T, int H, int W, int D, int 
   return g.dtype == dtype && g.B == B && g.T == T && g.H == H && g.W == W && g.D == D && g.R == root_grid;
 }
 
-int upload_tau(sttm_ctx* c, const float* host, float* dev, std::vector<float>* staging) {
+// The caller's thresholds: as a launch argument (`given`) where they fit one, else copied to the device.
+int take_tau(sttm_ctx* c, const float* host, float* dev, std::vector<float>* staging, TauArgs* given) {
   for (int b = 0; b < c->g.B; ++b)
     if (host[b] != host[b]) return fail(c, STTM_ERR_ARG, "threshold is NaN");
+  if (c->g.B <= kTauArgs) {
+    given->n = c->g.B;
+    std::memcpy(given->v, host, c->g.B * sizeof(float));
+    return STTM_OK;
+  }
   staging->assign(host, host + c->g.B);
   STTM_HIP(c, hipMemcpyAsync(dev, staging->data(), c->g.B * sizeof(float), hipMemcpyHostToDevice, c->stream));
   return STTM_OK;
@@ -352,11 +368,21 @@ int sttm_create(sttm_ctx** out, int device, void* hip_stream) {
     delete c;
     return STTM_ERR_HIP;
   }
+  // (relaxed: an allocation must not end a stream capture that runs meanwhile)
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  void* host = nullptr;
+  if (relaxed && hipHostMalloc(&host, sizeof(HostOut), hipHostMallocDefault) == hipSuccess)
+    c->host_out = static_cast<HostOut*>(host);
+  else
+    (void)hipGetLastError();
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
   *out = c;
   return STTM_OK;
 }
 
 int sttm_destroy(sttm_ctx* ctx) {
+  if (ctx && ctx->host_out) (void)hipHostFree(ctx->host_out);
   if (ctx)
     for (auto& v : ctx->ev)
       for (auto& p : v) { (void)hipEventDestroy(p.a); (void)hipEventDestroy(p.b); }
@@ -455,12 +481,13 @@ int sttm_spatial_quadtree(sttm_ctx* ctx, const void* feats_dev, int dtype, int B
   if (!node_map_dev) return fail(ctx, STTM_ERR_NULL, "node_map is NULL");
   STTM_HIP(ctx, hipSetDevice(ctx->device));
   int rc;
+  TauArgs given = {};
   if (tau_s_host) {
     rc = check_feats(ctx, feats_dev);
     if (rc) return rc;
     rc = bind_shape(ctx, dtype, B, T, H, W, D, root_grid);
     if (rc) return rc;
-    rc = upload_tau(ctx, tau_s_host, at<float>(ctx, ctx->lay.tau_s), &ctx->h_tau_s);
+    rc = take_tau(ctx, tau_s_host, at<float>(ctx, ctx->lay.tau_s), &ctx->h_tau_s, &given);
     if (rc) return rc;
     ctx->have_tau_s = true;
     ctx->tau_s_pending = false;
@@ -474,7 +501,7 @@ int sttm_spatial_quadtree(sttm_ctx* ctx, const void* feats_dev, int dtype, int B
     if (!ctx->have_tau_s)
       return fail(ctx, STTM_ERR_STATE, "no spatial threshold chosen (call sttm_budget_threshold first)");
   }
-  launch_spatial_decide(ctx->g, at<float>(ctx, ctx->lay.m), at<float>(ctx, ctx->lay.tau_s),
+  launch_spatial_decide(ctx->g, at<float>(ctx, ctx->lay.m), at<float>(ctx, ctx->lay.tau_s), given,
                         ctx->tau_s_pending ? at<SelState>(ctx, ctx->lay.sel_s) : nullptr, node_map_dev, node_level_dev,
                         ctx->stream);
   ctx->tau_s_pending = false;  // the kernel has left the threshold in the workspace
@@ -513,8 +540,9 @@ int sttm_temporal_merge(sttm_ctx* ctx, const void* feats_dev, const int32_t* nod
   STTM_HIP(ctx, hipSetDevice(ctx->device));
   int rc = temporal_prepare(ctx, feats_dev, node_map_dev, &node_level_dev);
   if (rc) return rc;
+  TauArgs given = {};
   if (tau_t_host) {
-    rc = upload_tau(ctx, tau_t_host, at<float>(ctx, ctx->lay.tau_t), &ctx->h_tau_t);
+    rc = take_tau(ctx, tau_t_host, at<float>(ctx, ctx->lay.tau_t), &ctx->h_tau_t, &given);
     if (rc) return rc;
     rc = run_temporal_stats(ctx, feats_dev, node_map_dev, node_level_dev);
     if (rc) return rc;
@@ -528,7 +556,7 @@ int sttm_temporal_merge(sttm_ctx* ctx, const void* feats_dev, const int32_t* nod
       return fail(ctx, STTM_ERR_STATE, "the temporal statistics in the workspace were computed for another node map");
   }
   launch_temporal_parent(ctx->g, ctx->match_mode, node_map_dev, node_level_dev, at<float>(ctx, ctx->lay.sig),
-                         at<float>(ctx, ctx->lay.tau_t),
+                         at<float>(ctx, ctx->lay.tau_t), given,
                          ctx->tau_t_pending ? at<SelState>(ctx, ctx->lay.sel_t) : nullptr,
                          at<int32_t>(ctx, ctx->lay.parent), at<int32_t>(ctx, ctx->lay.ptr_a), ctx->stream);
   ctx->tau_t_pending = false;
@@ -572,14 +600,15 @@ int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_ho
   // When the caller does not ask for the value, the last digit of the search is resolved by the kernel that uses the
   // threshold (one launch less); otherwise by a launch of its own.
   float* tau_now = tau_out_host ? tau_dev : nullptr;
+  float* host_tau = tau_out_host && ctx->host_out && g.B <= kHostTaus ? ctx->host_out->tau : nullptr;
   if (spatial) {
     launch_select_spatial(g, at<uint32_t>(ctx, ctx->lay.sel_key_s), at<uint8_t>(ctx, ctx->lay.sel_w_s),
-                          target_dev, at<SelState>(ctx, ctx->lay.sel_s), ctx->sel_s_dirty, tau_now, ctx->stream);
+                          target_dev, at<SelState>(ctx, ctx->lay.sel_s), ctx->sel_s_dirty, tau_now, host_tau, ctx->stream);
     ctx->sel_s_dirty = true;
     ctx->tau_s_pending = tau_now == nullptr;
   } else {
     launch_select_temporal(g, ctx->node_map_temporal, at<uint32_t>(ctx, ctx->lay.sel_key_t), target_dev,
-                           at<SelState>(ctx, ctx->lay.sel_t), ctx->sel_t_dirty, tau_now, ctx->stream);
+                           at<SelState>(ctx, ctx->lay.sel_t), ctx->sel_t_dirty, tau_now, host_tau, ctx->stream);
     ctx->sel_t_dirty = true;
     ctx->tau_t_pending = tau_now == nullptr;
   }
@@ -587,8 +616,10 @@ int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_ho
   if (rc) return rc;
   if (stage == STTM_STAGE_SPATIAL) ctx->have_tau_s = true; else ctx->have_tau_t = true;
   if (tau_out_host) {
-    STTM_HIP(ctx, hipMemcpyAsync(tau_out_host, tau_dev, g.B * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
+    if (!host_tau)
+      STTM_HIP(ctx, hipMemcpyAsync(tau_out_host, tau_dev, g.B * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
     STTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    if (host_tau) std::memcpy(tau_out_host, host_tau, g.B * sizeof(float));
   }
   return STTM_OK;
 }
@@ -615,7 +646,8 @@ int sttm_reduce(sttm_ctx* ctx, const void* feats_dev, const int32_t* cluster_ids
                 "a partition was given but the workspace holds no stage-1 statistics of these features");
   if (reinterpret_cast<uintptr_t>(merged_dev) & 15) return fail(ctx, STTM_ERR_ARG, "merged must be 16-byte aligned");
   STTM_HIP(ctx, hipSetDevice(ctx->device));
-  const ReduceBuffers rb = reduce_buffers(ctx->ws, ctx->lay);
+  ReduceBuffers rb = reduce_buffers(ctx->ws, ctx->lay);
+  if (n_out_host && ctx->host_out) rb.host_k = &ctx->host_out->k;
   const bool zscan = ctx->order == STTM_ORDER_ZSCAN;
   ctx->cluster_ids_reduced = nullptr;
   launch_reduce_prepare(ctx->g, cluster_ids_dev, node_map_dev, node_level_dev, capacity, out_ids_dev, offsets_dev,
@@ -633,8 +665,9 @@ int sttm_reduce(sttm_ctx* ctx, const void* feats_dev, const int32_t* cluster_ids
   ctx->reduced_zscan = zscan;
   if (n_out_host) {
     int32_t k = 0;
-    STTM_HIP(ctx, hipMemcpyAsync(&k, rb.kdev, sizeof k, hipMemcpyDeviceToHost, ctx->stream));
+    if (!rb.host_k) STTM_HIP(ctx, hipMemcpyAsync(&k, rb.kdev, sizeof k, hipMemcpyDeviceToHost, ctx->stream));
     STTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    if (rb.host_k) k = *rb.host_k;
     *n_out_host = k;
     if (k > capacity) {
       char buf[128];

@@ -422,16 +422,25 @@ void launch_pyramid_stats(const Geo& g, const void* feats, int cell_dots, float*
 // Also works out the levels above an 8x8 unit from the stored unit sums (extends `nsum`).
 void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float* nrm2, float* sim, float* m,
                              uint32_t* sel_key, uint8_t* sel_w, SelState* sel, hipStream_t s);
+// Thresholds a caller has named, handed to the kernels that use them as a launch argument (n = 0: none). A copy from the
+// caller's memory to the device is a stream operation of its own: 2.5-5 us there and about as much on the host.
+constexpr int kTauArgs = 32;
+struct TauArgs {
+  int n;
+  float v[kTauArgs];
+};
+// `given`: if it holds thresholds the kernel takes them from there (and leaves them in `tau` for later readers).
 // `pending` (may be NULL): the search states of a budget search whose last digit has not been resolved yet; the
 // kernel then works the threshold out itself (and leaves it in `tau` for later readers) instead of reading `tau`.
-void launch_spatial_decide(const Geo& g, const float* m, float* tau, const SelState* pending, int32_t* node_map,
-                           uint8_t* node_level, hipStream_t s);
+void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauArgs& given, const SelState* pending,
+                           int32_t* node_map, uint8_t* node_level, hipStream_t s);
 // `dirty`: the state has been searched since its statistics pass (levels 1-2 must be cleared first).
+// `host_tau` (may be NULL): host memory the device can write, which receives the thresholds as well.
 // `tau` == NULL: the last digit is left to the kernel that uses the threshold (see `pending` above).
 void launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
-                           SelState* state, bool dirty, float* tau, hipStream_t s);
+                           SelState* state, bool dirty, float* tau, float* host_tau, hipStream_t s);
 void launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
-                            SelState* state, bool dirty, float* tau, hipStream_t s);
+                            SelState* state, bool dirty, float* tau, float* host_tau, hipStream_t s);
 inline size_t select_state_bytes(int B) { return (size_t)B * sizeof(SelState); }
 // `sel`: the temporal search states [B]; cleared here, level 0 filled by launch_temporal_resolve.
 // `skip_same`: 0 = every pair is computed here; 1 = pairs of two single cells are left out, 2 = also pairs of the same
@@ -471,8 +480,8 @@ void launch_temporal_resolve(const Geo& g, int match, int same_level, const int3
                              const float* pd_part, const float* cell_part, const float* nrm2, float* sig, float* e,
                              uint32_t* sel_key, SelState* sel, int* item_count, hipStream_t s);
 void launch_temporal_parent(const Geo& g, int match, const int32_t* node_map, const uint8_t* node_level,
-                            const float* sig, float* tau, const SelState* pending, int32_t* parent, int32_t* ptr,
-                            hipStream_t s);
+                            const float* sig, float* tau, const TauArgs& given, const SelState* pending, int32_t* parent,
+                            int32_t* ptr, hipStream_t s);
 void launch_roots(const Geo& g, int32_t* ptr_a, int32_t* ptr_b, const int32_t* node_map, int32_t* cluster_ids,
                   hipStream_t s);
 void launch_node_levels(const Geo& g, const int32_t* node_map, uint8_t* node_level, hipStream_t s);
@@ -492,6 +501,7 @@ struct ReduceBuffers {
   int32_t* seg;         // [N+1] first list position of every output row
   int32_t* kdev;        // [4] number of clusters, length of the live list, length of the big-cluster list
   int32_t* zpos;        // [N] output row of every cluster rank under the Z-shaped scan
+  int32_t* host_k;      // host memory the device can write, receives the number of clusters (or NULL)
   int32_t* biglist;     // [big clusters][4] output row, first list position, end of the list, unused
   float* bigpart;       // [gather items][2][D] partial sums of clusters with more than 64 list slots
   int32_t* bigw;        // [gather items][2] member cells behind those partial sums

@@ -263,6 +263,7 @@ struct SortArgs {
   int32_t* rank;
   const int32_t* tile_roots;
   int32_t* kdev;  // [0] = K, [1] = list length
+  int32_t* host_k;  // K once more, in host memory (or NULL)
   int32_t* out_ids;
   int64_t* offsets;
   int64_t capacity;
@@ -367,6 +368,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(SortArgs a) {
       if (FIRST) {
         const int all = s_roots[1];
         a.kdev[0] = all;
+        if (a.host_k) *a.host_k = all;
         a.kdev[1] = live;
         a.offsets[a.B] = all;
         if (LAST) a.seg[all] = live;
@@ -938,7 +940,7 @@ void launch_reduce_prepare(const Geo& g, const int32_t* cluster_ids, const int32
     a.keys = kin; a.vals = vin; a.keys_out = kout; a.vals_out = last ? rb.order : vout;
     a.hist = rb.hist; a.tot = rb.tot;
     a.cluster_ids = cluster_ids; a.rank = rb.rank; a.tile_roots = rb.tile_roots;
-    a.kdev = rb.kdev; a.out_ids = zscan ? nullptr : out_ids; a.offsets = offsets; a.capacity = capacity;
+    a.kdev = rb.kdev; a.host_k = rb.host_k; a.out_ids = zscan ? nullptr : out_ids; a.offsets = offsets; a.capacity = capacity;
     a.per_video = g.T * g.HW; a.B = g.B;
     a.orow = rb.orow; a.seg = rb.seg;
     if (first && last) hipLaunchKernelGGL((k_sort_pass<true, true>), grid, block, 0, s, a);

@@ -885,14 +885,14 @@ void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float
 // walks down from its root: the first node on the path whose smallest child similarity exceeds tau_S is kept.
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kSelThreads) void k_spatial_decide(Geo g, const float* __restrict__ m,
-                                                                float* __restrict__ tau,
+                                                                float* __restrict__ tau, TauArgs given,
                                                                 const SelState* __restrict__ pending,
                                                                 int32_t* __restrict__ node_map,
                                                                 uint8_t* __restrict__ node_level) {
   const int b = blockIdx.y, per_video = g.T * g.HW;
   float t;
-  if (pending) {  // the budget search left its last digit to this kernel
-    t = sel_last_digit(pending + b);
+  if (pending || given.n) {  // the budget search left its last digit to this kernel, or the caller named the threshold
+    t = given.n ? given.v[b] : sel_last_digit(pending + b);
     if (blockIdx.x == 0 && threadIdx.x == 0) tau[b] = t;
   } else {
     t = tau[b];
@@ -911,11 +911,11 @@ __global__ __launch_bounds__(kSelThreads) void k_spatial_decide(Geo g, const flo
   if (node_level) node_level[i] = (uint8_t)lvl;
 }
 
-void launch_spatial_decide(const Geo& g, const float* m, float* tau, const SelState* pending, int32_t* node_map,
-                           uint8_t* node_level, hipStream_t s) {
+void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauArgs& given, const SelState* pending,
+                           int32_t* node_map, uint8_t* node_level, hipStream_t s) {
   const int per_video = g.T * g.HW;
   hipLaunchKernelGGL(k_spatial_decide, dim3((per_video + kSelThreads - 1) / kSelThreads, g.B), dim3(kSelThreads), 0, s,
-                     g, m, tau, pending, node_map, node_level);
+                     g, m, tau, given, pending, node_map, node_level);
 }
 
 // Recovers node levels from a node map (callers may pass node_level == NULL to the temporal stage).
@@ -1075,14 +1075,17 @@ __global__ __launch_bounds__(kPassThreads) void k_select_pass(Geo g, const uint3
 
 // Last digit as a launch of its own (when the caller wants the threshold back).
 __global__ __launch_bounds__(kSelThreads) void k_select_tau(const SelState* __restrict__ states,
-                                                            float* __restrict__ tau) {
+                                                            float* __restrict__ tau, float* __restrict__ host_tau) {
   const float t = sel_last_digit(states + blockIdx.x);
-  if (threadIdx.x == 0) tau[blockIdx.x] = t;
+  if (threadIdx.x == 0) {
+    tau[blockIdx.x] = t;
+    if (host_tau) host_tau[blockIdx.x] = t;
+  }
 }
 
 static void launch_select(const Geo& g, const uint32_t* keys, const uint8_t* weights, int per_video,
                           const int* target, int base_const, const int32_t* node_map, SelState* st, bool dirty,
-                          float* tau, hipStream_t s) {
+                          float* tau, float* host_tau, hipStream_t s) {
   const int slices = per_video > 0 ? (per_video + kPassThreads * kSelPer - 1) / (kPassThreads * kSelPer) : 1;
   const dim3 grid(slices, g.B), block(kPassThreads);
   if (dirty) hipLaunchKernelGGL(k_select_reset, dim3(g.B), dim3(256), 0, s, st);
@@ -1090,21 +1093,21 @@ static void launch_select(const Geo& g, const uint32_t* keys, const uint8_t* wei
                      node_map, st);
   hipLaunchKernelGGL(k_select_pass<2>, grid, block, 0, s, g, keys, weights, per_video, target, base_const,
                      node_map, st);
-  if (tau) hipLaunchKernelGGL(k_select_tau, dim3(g.B), dim3(kSelThreads), 0, s, st, tau);
+  if (tau) hipLaunchKernelGGL(k_select_tau, dim3(g.B), dim3(kSelThreads), 0, s, st, tau, host_tau);
 }
 
 void launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
-                           SelState* state, bool dirty, float* tau, hipStream_t s) {
+                           SelState* state, bool dirty, float* tau, float* host_tau, hipStream_t s) {
   int roots = 0;
   for (int ry = 0; ry < g.R; ++ry)
     for (int rx = 0; rx < g.R; ++rx) roots += node_exists(g, g.L, ry, rx);
   const int per_video = g.T * (g.NN - g.lvl_base[1]);
-  launch_select(g, keys, weights, per_video, target, roots * g.T, nullptr, state, dirty, tau, s);
+  launch_select(g, keys, weights, per_video, target, roots * g.T, nullptr, state, dirty, tau, host_tau, s);
 }
 
 void launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
-                            SelState* state, bool dirty, float* tau, hipStream_t s) {
-  launch_select(g, keys, nullptr, g.T * g.HW, target, 0, node_map, state, dirty, tau, s);
+                            SelState* state, bool dirty, float* tau, float* host_tau, hipStream_t s) {
+  launch_select(g, keys, nullptr, g.T * g.HW, target, 0, node_map, state, dirty, tau, host_tau, s);
 }
 
 }  // namespace sttm

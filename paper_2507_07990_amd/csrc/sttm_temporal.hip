@@ -592,7 +592,7 @@ void launch_temporal_resolve(const Geo& g, int match, int same_level, const int3
 __global__ __launch_bounds__(kSelThreads) void k_temporal_parent(Geo g, int match, const int32_t* __restrict__ node_map,
                                                          const uint8_t* __restrict__ node_level,
                                                          const float* __restrict__ sig,
-                                                         float* __restrict__ tau,
+                                                         float* __restrict__ tau, TauArgs given,
                                                          const SelState* __restrict__ pending,
                                                          int32_t* __restrict__ parent, int32_t* __restrict__ ptr) {
   __shared__ PairFrame pf;
@@ -600,8 +600,8 @@ __global__ __launch_bounds__(kSelThreads) void k_temporal_parent(Geo g, int matc
   __shared__ unsigned long long best[1024];
   const int f = blockIdx.x, HW = g.HW;
   float th;
-  if (pending) {  // the budget search left its last digit to this kernel
-    th = sel_last_digit(pending + f / g.T);
+  if (pending || given.n) {  // the budget search left its last digit to this kernel, or the caller named the threshold
+    th = given.n ? given.v[f / g.T] : sel_last_digit(pending + f / g.T);
     if (f % g.T == 0 && threadIdx.x == 0) tau[f / g.T] = th;
   } else {
     th = tau[f / g.T];
@@ -647,9 +647,9 @@ __global__ __launch_bounds__(kSelThreads) void k_temporal_parent(Geo g, int matc
 }
 
 void launch_temporal_parent(const Geo& g, int match, const int32_t* node_map, const uint8_t* node_level,
-                            const float* sig, float* tau, const SelState* pending, int32_t* parent, int32_t* ptr,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(k_temporal_parent, dim3(g.F), dim3(kSelThreads), 0, s, g, match, node_map, node_level, sig, tau,
+                            const float* sig, float* tau, const TauArgs& given, const SelState* pending, int32_t* parent,
+                            int32_t* ptr, hipStream_t s) {
+  hipLaunchKernelGGL(k_temporal_parent, dim3(g.F), dim3(kSelThreads), 0, s, g, match, node_map, node_level, sig, tau, given,
                      pending, parent, ptr);
 }
 

@@ -742,3 +742,42 @@ def test_both_pyramid_kernels_give_the_same_bits(lib, H, W, D, dtype, R, tau_s, 
 def test_levels_above_the_units(lib, seed, B, T, H, W, D, dtype, R):
     _run_and_check(lib, _variant(seed, B, T, H, W, D, dtype), tau_s=0.85, tau_t=0.8, root_grid=R)
     _run_and_check(lib, _variant(seed, B, T, H, W, D, dtype, sigma=0.02), keep=0.2, root_grid=R)
+
+
+@pytest.mark.parametrize("B", [1, 32, 33, 1024, 1025])
+def test_thresholds_in_and_out_at_every_way_they_travel(lib, B):
+    """Up to 32 thresholds go to the kernels as a launch argument, more are copied; up to 1024 found ones come back
+    through host memory the device writes, more are copied: every video must get its own either way."""
+    import torch
+    T, H, W, D = 3, 4, 4, 32
+    gen = torch.Generator(device="cuda:0").manual_seed(B)
+    x = torch.randn(B, 1, 1, 1, D, device="cuda:0", generator=gen)
+    x = x + torch.linspace(0.2, 2.0, B, device="cuda:0").view(B, 1, 1, 1, 1) * torch.randn(B, T, H, W, D, device="cuda:0", generator=gen)
+    rng = np.random.default_rng(B)
+    tau_s, tau_t, keep = rng.uniform(0.2, 0.9, B), rng.uniform(0.2, 0.9, B), rng.uniform(0.2, 0.9, B)
+
+    def one(v, ts, tt, kp):
+        b, n = v.shape[0], v.shape[0] * T * H * W
+        s = lib.Sttm(0)
+        s.ensure_workspace(b, T, H, W, D, lib.STTM_F32)
+        node_map = torch.empty(n, dtype=torch.int32, device="cuda:0")
+        level = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        cluster, out_ids, counts = (torch.zeros(n, dtype=torch.int32, device="cuda:0") for _ in range(3))
+        merged, offsets = torch.empty(n, D, device="cuda:0"), torch.empty(b + 1, dtype=torch.int64, device="cuda:0")
+        s.sttm_spatial_quadtree(v, lib.STTM_F32, b, T, H, W, D, 1, ts, node_map, level)
+        s.sttm_spatial_quadtree(v, lib.STTM_F32, b, T, H, W, D, 1, None, node_map, level)   # the thresholds of the last call
+        s.sttm_temporal_merge(v, node_map, level, tt, cluster)
+        fixed = cluster.view(b, -1).clone()
+        K = s.sttm_reduce(v, cluster, node_map, level, lib.STTM_F32, n, merged, counts, out_ids, offsets)
+        assert K == int(offsets[b]) and K == int((cluster == torch.arange(n, device="cuda:0")).sum())
+        found = [s.sttm_budget_threshold(lib.STTM_STAGE_SPATIAL, kp)]
+        s.sttm_spatial_quadtree(v, lib.STTM_F32, b, T, H, W, D, 1, None, node_map, level)
+        s.sttm_temporal_stats(v, node_map, level)
+        found.append(s.sttm_budget_threshold(lib.STTM_STAGE_TEMPORAL, kp))
+        return fixed, np.stack(found)
+
+    ids, taus = one(x, tau_s, tau_t, keep)
+    for b in {0, B // 2, B - 1}:
+        ids1, taus1 = one(x[b:b + 1].contiguous(), tau_s[b:b + 1], tau_t[b:b + 1], keep[b:b + 1])
+        assert torch.equal(ids[b] - b * T * H * W, ids1[0])
+        assert (taus[:, b] == taus1[:, 0]).all()
