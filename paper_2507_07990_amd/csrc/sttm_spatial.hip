@@ -656,10 +656,10 @@ void launch_pyramid_stats(const Geo& g, const void* feats, int cell_dots, float*
 
 // ------------------------------------------------------------------------------------------------
 // k_spatial_finalize: one workgroup per frame. First the levels above the 8x8 units (UP = 1: a 16x16 grid, one node of
-// level 4; UP = 2: a 32x32 grid, four of level 4 and, if the root is one node, the one of level 5): a thread owns four
+// level 4; UP = 2: a 32x32 grid, four of level 4 and, if the root is one node, the one of level 5): a lane owns four
 // channels, loads them from all level-3 sums of the frame at once, adds the levels up in registers, stores the sums
 // next to the level-3 ones and keeps its share of the dot products child . parent, which are added up over the
-// workgroup at the end. (One wavefront per node and chunk, level by level, paid the memory latency once per node, chunk
+// wavefront and the chunks at the end. (One wavefront per node and chunk, level by level, paid the memory latency once per node, chunk
 // and level: 44 us of 180 frames of 18x24 tokens at D = 8192, 50 us of 1024 frames of 27x27 at D = 1152.)
 // Then it sums the per-chunk partials of the lower levels in chunk order, 16 bytes per thread into LDS, turns
 // them into sigma(parent, child) (Sec. 3.2: cosine between a level's nodes and their children),
@@ -668,7 +668,9 @@ void launch_pyramid_stats(const Geo& g, const void* feats, int cell_dots, float*
 constexpr int kUnitStats = 4 * kTileRows + 4;  // the scalars of a unit's block that this kernel reads
 static_assert(kUnitStats % 4 == 0, "whole 16-byte pieces");
 constexpr int kUpRows = 24;                    // dot products with a parent at level 4 (16) or 5 (4), whole batches of 8
-constexpr int kFinThreads = 512;
+// Threads of the kernel. With a 32x32 grid (1365 nodes) and no more frames than CUs, twice as many.
+constexpr int kFinThreads = 512, kFinThreadsWide = 1024, kFinWaves = kFinThreadsWide / kWave;
+constexpr int kFinWideFrames = 256;
 
 __device__ inline float dot4(const float4& a, const float4& b, float c) {
   return fmaf(a.x, b.x, fmaf(a.y, b.y, fmaf(a.z, b.z, fmaf(a.w, b.w, c))));
@@ -677,60 +679,82 @@ __device__ inline float4 add4(const float4& a, const float4& b) {
   return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
 }
 
-// The upper levels of frame f by a workgroup of kFinThreads threads; leaves the dot product of level-3 node
+// Eight sums over the wavefront at once, each by the tree of wave_sum (lane distances 32, 16, 8, 4, 2, 1): lane 8 i
+// returns the sum of scalar i. Three exchanges halve the scalars a lane carries.
+__device__ __forceinline__ float wave_sums8(const float (&v)[8], int lane) {
+  const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8;
+  float a[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = (b5 ? v[i + 4] : v[i]) + __shfl_xor(b5 ? v[i] : v[i + 4], 32, 64);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) c[i] = (b4 ? a[i + 2] : a[i]) + __shfl_xor(b4 ? a[i] : a[i + 2], 16, 64);
+  float r = (b3 ? c[1] : c[0]) + __shfl_xor(b3 ? c[0] : c[1], 8, 64);
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1) r += __shfl_xor(r, o, 64);
+  return r;
+}
+
+// The upper levels of frame f by the whole workgroup; leaves the dot product of level-3 node
 // (2 py + ky, 2 px + kx) with its parent p = (py, px) in up[4 p + 2 ky + kx], that of level-4 node p with its parent in
-// up[16 + p] (call a barrier before reading them). `red` is kUpRows * 64 floats of LDS.
+// up[16 + p] (call a barrier before reading them). A wavefront takes a chunk of the channels at a time; the chunks'
+// sums are added in chunk order. `red` is kUpRows * kFinWaves floats of LDS.
 template <int UP>
 __device__ inline void upper_levels(const Geo& g, float* nsum, int f, float* red, float* up) {
   constexpr int S4 = UP == 1 ? 1 : 2, N4 = S4 * S4;
+  constexpr int kBatches = UP == 1 ? 1 : kUpRows / 8;
   const int NB = g.NN - g.lvl_base[3], D4 = g.D >> 2, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int nwaves = blockDim.x >> 6;
   float4* rows = reinterpret_cast<float4*>(nsum + (size_t)f * NB * g.D);
   const int base4 = 4 * N4;  // nodes of level 3 come first, then level 4, then level 5
-  float tot[kUpRows];
-#pragma unroll
-  for (int i = 0; i < kUpRows; ++i) tot[i] = 0.f;
+  float all = 0.f;           // thread i < 8 kBatches: dot product i over the chunks so far
 #pragma unroll 1
-  for (int c = threadIdx.x; c < D4; c += kFinThreads) {
-    float4 a[4 * N4], s4[N4];
+  for (int c0 = 0; c0 < g.nC; c0 += nwaves) {
+    const int chunk = c0 + wave;
+    float tot[8 * kBatches];
 #pragma unroll
-    for (int i = 0; i < 4 * N4; ++i) {  // i = 4 p + k
-      const int p = i >> 2, k = i & 3, y = 2 * (p / S4) + (k >> 1), x = 2 * (p % S4) + (k & 1);
-      a[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (node_exists(g, 3, y, x)) a[i] = rows[(size_t)(y * 2 * S4 + x) * D4 + c];
+    for (int i = 0; i < 8 * kBatches; ++i) tot[i] = 0.f;
+    const int last = min(D4, (chunk + 1) * (g.cch >> 2));
+#pragma unroll 1
+    for (int c = chunk * (g.cch >> 2) + lane; c < last; c += kWave) {
+      float4 a[4 * N4], s4[N4];
+#pragma unroll
+      for (int i = 0; i < 4 * N4; ++i) {  // i = 4 p + k
+        const int p = i >> 2, k = i & 3, y = 2 * (p / S4) + (k >> 1), x = 2 * (p % S4) + (k & 1);
+        a[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (node_exists(g, 3, y, x)) a[i] = rows[(size_t)(y * 2 * S4 + x) * D4 + c];
+      }
+#pragma unroll
+      for (int p = 0; p < N4; ++p) {
+        s4[p] = add4(add4(a[4 * p], a[4 * p + 1]), add4(a[4 * p + 2], a[4 * p + 3]));
+        if (node_exists(g, 4, p / S4, p % S4)) rows[(size_t)(base4 + p) * D4 + c] = s4[p];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) tot[4 * p + k] = dot4(a[4 * p + k], s4[p], tot[4 * p + k]);
+      }
+      if (UP == 2 && g.L >= 5) {
+        const float4 s5 = add4(add4(s4[0], s4[1 % N4]), add4(s4[2 % N4], s4[3 % N4]));
+        rows[(size_t)(base4 + N4) * D4 + c] = s5;
+#pragma unroll
+        for (int p = 0; p < N4; ++p) tot[(16 + p) % (8 * kBatches)] = dot4(s4[p], s5, tot[(16 + p) % (8 * kBatches)]);
+      }
     }
 #pragma unroll
-    for (int p = 0; p < N4; ++p) {
-      s4[p] = add4(add4(a[4 * p], a[4 * p + 1]), add4(a[4 * p + 2], a[4 * p + 3]));
-      if (node_exists(g, 4, p / S4, p % S4)) rows[(size_t)(base4 + p) * D4 + c] = s4[p];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) tot[4 * p + k] = dot4(a[4 * p + k], s4[p], tot[4 * p + k]);
+    for (int i = 0; i < kBatches; ++i) {
+      const float v[8] = {tot[8 * i], tot[8 * i + 1], tot[8 * i + 2], tot[8 * i + 3],
+                          tot[8 * i + 4], tot[8 * i + 5], tot[8 * i + 6], tot[8 * i + 7]};
+      const float r = wave_sums8(v, lane);
+      if ((lane & 7) == 0) red[(8 * i + (lane >> 3)) * kFinWaves + wave] = r;
     }
-    if (UP == 2 && g.L >= 5) {
-      const float4 s5 = add4(add4(s4[0], s4[1 % N4]), add4(s4[2 % N4], s4[3 % N4]));
-      rows[(size_t)(base4 + N4) * D4 + c] = s5;
-#pragma unroll
-      for (int p = 0; p < N4; ++p) tot[16 + p] = dot4(s4[p], s5, tot[16 + p]);
+    __syncthreads();
+    if ((int)threadIdx.x < 8 * kBatches) {
+      for (int w = 0; w < nwaves; ++w) all += red[threadIdx.x * kFinWaves + w];  // (zero beyond the last chunk)
     }
+    __syncthreads();
   }
-  constexpr int kBatches = UP == 1 ? 1 : kUpRows / 8;
-#pragma unroll
-  for (int i = 0; i < kBatches; ++i) {
-    const float v[8] = {tot[8 * i], tot[8 * i + 1], tot[8 * i + 2], tot[8 * i + 3],
-                        tot[8 * i + 4], tot[8 * i + 5], tot[8 * i + 6], tot[8 * i + 7]};
-    red[(8 * i + (lane & 7)) * 64 + wave * 8 + (lane >> 3)] = group_sums8(v, lane);
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < 8 * kBatches) {
-    const float4* r = reinterpret_cast<const float4*>(red + threadIdx.x * 64);
-    float4 s = r[0];
-#pragma unroll
-    for (int j = 1; j < 16; ++j) s = add4(s, r[j]);
-    up[threadIdx.x] = (s.x + s.y) + (s.z + s.w);
-  }
+  if ((int)threadIdx.x < 8 * kBatches) up[threadIdx.x] = all;
 }
 
 template <int UP>
-__global__ __launch_bounds__(kFinThreads) void k_spatial_finalize(Geo g, const float* __restrict__ part,
+__global__ __launch_bounds__(UP == 2 ? kFinThreadsWide : kFinThreads) void k_spatial_finalize(Geo g, const float* __restrict__ part,
                                                                   float* __restrict__ nsum, float* __restrict__ nrm2,
                                                                   float* __restrict__ sim, float* __restrict__ m,
                                                                   uint32_t* __restrict__ sel_key,
@@ -738,7 +762,7 @@ __global__ __launch_bounds__(kFinThreads) void k_spatial_finalize(Geo g, const f
                                                                   SelState* __restrict__ sel) {
   STTM_DYNAMIC_LDS(float, sm);
   __shared__ unsigned h0[kSelBins];
-  __shared__ __attribute__((aligned(16))) float red[UP ? kUpRows * 64 : 1];
+  __shared__ __attribute__((aligned(16))) float red[UP ? kUpRows * kFinWaves : 1];
   __shared__ float up[kUpRows];
   // dynamic: the units' scalars, then per node squared norm, similarity to the parent, m, and (level, row, column)
   const int NU = unit_cols(g) * unit_rows(g), UC = unit_cols(g), tid = threadIdx.x, nthr = blockDim.x;
@@ -770,7 +794,7 @@ __global__ __launch_bounds__(kFinThreads) void k_spatial_finalize(Geo g, const f
       reinterpret_cast<float4*>(s_part)[j] = s;
     }
   }
-  if (UP) upper_levels<UP>(g, nsum, f, red, up);
+  if constexpr (UP > 0) upper_levels<UP>(g, nsum, f, red, up);
   for (int j = tid; j < kSelBins; j += nthr) h0[j] = 0;
   for (int idx = tid; idx < g.NN; idx += nthr) {
     int lvl, by, bx;
@@ -870,7 +894,7 @@ __global__ __launch_bounds__(kFinThreads) void k_spatial_finalize(Geo g, const f
 void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float* nrm2, float* sim, float* m,
                              uint32_t* sel_key, uint8_t* sel_w, SelState* sel, hipStream_t s) {
   const int up = g.L < 4 ? 0 : (g.P == 16 ? 1 : 2);
-  const int threads = g.NN <= 256 && !up ? 256 : kFinThreads;  // one node per thread where it fits
+  const int threads = up == 2 && g.F <= kFinWideFrames ? kFinThreadsWide : (g.NN <= 256 && !up ? 256 : kFinThreads);  // one node per thread where it fits
   const size_t lds = ((size_t)unit_cols(g) * unit_rows(g) * kUnitStats + 4 * (size_t)g.NN) * sizeof(float);
   if (up == 0)
     hipLaunchKernelGGL(k_spatial_finalize<0>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel);
