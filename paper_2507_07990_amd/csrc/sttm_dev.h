@@ -257,6 +257,16 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
+// The value lane `src` holds, in a scalar register (`src` is the same in all lanes). What is derived from it is known to
+// be the same in all lanes: scalar branches and scalar addresses, where a __shfl would give a vector and masked branches.
+__device__ inline int lane_value(int v, int src) {
+#ifndef STTM_HOST_EMULATION
+  return __builtin_amdgcn_readlane(v, src);
+#else
+  return __shfl(v, src, 64);
+#endif
+}
+
 // Orders LDS traffic between the lanes of one wavefront (no cross-wave synchronisation).
 __device__ inline void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -8,7 +8,7 @@ namespace sttm {
 // (y0, x0), for this lane's channels: all row loads are issued before the first one is used.
 template <int DT>
 __device__ inline void block_sum16(const typename Row<DT>::Elem* fb, int D, int W, int y0, int x0, int h, int w,
-                                   bool act, float (&S)[Row<DT>::VEC]) {
+                                   float (&S)[Row<DT>::VEC]) {
   typedef Row<DT> R;
   constexpr int VEC = R::VEC;
   typename R::Raw r[16];
@@ -16,7 +16,7 @@ __device__ inline void block_sum16(const typename Row<DT>::Elem* fb, int D, int 
   for (int i = 0; i < 16; ++i) {
     const int dy = i >> 2, dx = i & 3;
     r[i] = R::zero();
-    if (dy < h && dx < w && act) r[i] = *reinterpret_cast<const typename R::Raw*>(fb + (size_t)((y0 + dy) * W + x0 + dx) * D);
+    if (dy < h && dx < w) r[i] = *reinterpret_cast<const typename R::Raw*>(fb + (size_t)((y0 + dy) * W + x0 + dx) * D);
   }
 #pragma unroll
   for (int v = 0; v < VEC; ++v) S[v] = 0.f;
@@ -45,19 +45,20 @@ __device__ inline void block_sum16(const typename Row<DT>::Elem* fb, int D, int 
 //  * J >= 3 ("big"): the coarse sum is not recomputed: the spatial pass left the per-channel sums of all nodes
 //    at levels >= 3 in `nsum`. Pairs whose finer node is a single cell go sixteen to an item (all under the same
 //    join block), every other finer node is an item of its own.
-// The items go into kTQueues queues, frame f into queue f mod kTQueues (a workgroup reserves its stretch with one
+// The items go into kTQueues queues, each of a run of consecutive frames (a workgroup reserves its stretch with one
 // atomic on the queue's counter; with one counter for all, the five hundred atomics of a long video queued up
 // behind one another). The order of the stretches varies from run to run, what is computed for an item does not.
 //
-// k_temporal_dots, a fixed grid of four-wavefront workgroups, a fixed share of them per queue: wavefront w of a
-// queue's share takes the (item, chunk) tasks w, w + W, w + 2W, ... of that queue (a trip count known on entry),
-// loads the rows the item names, and reduces its lanes' partial dot products through LDS ([scalar][lane] rows).
-// Because every task is small and they are all alike, the pass no longer depends on how unevenly the work is
-// spread over the frame pairs (scene cuts concentrate it in a few of them).
+// k_temporal_dots, a fixed grid of four-wavefront workgroups. The queues one after the other are one list in frame
+// order; each of the eight dies takes an eighth of it, and wavefront w of the die's W the (item, chunk) tasks w, w + W,
+// w + 2W, ... of that part (a trip count known on entry): every wavefront has the same number of tasks, however unevenly
+// the work is spread over the frames (scene cuts concentrate it in a few of them), and the frame pairs that need the
+// same rows meet in one die's L2. A wavefront reads its next item while it works on the present one, loads the rows the
+// item names, and reduces its lanes' partial dot products through LDS ([scalar][lane] rows).
 // Output: pd_part[f][chunk][q].
 // ------------------------------------------------------------------------------------------------
 struct TItem {
-  int32_t f;     // frame t of the pair
+  int32_t f;     // frame t of the pair (the first two of the item's 24 16-bit words)
   int16_t type;  // 0 fast, 1 mid, 2 cells under a big block, 3 one finer node under a big block
   int16_t n;     // fast: regions (1..4); cells: cells (1..16)
   int16_t a;     // mid: top-left cell of the block; big: join block's node index counted from the first level-3 node
@@ -73,12 +74,18 @@ __host__ __device__ inline int temporal_items_per_pair(const Geo& g) { return g.
 constexpr int kFastRows = 16;
 constexpr int kBigNodes = 24;  // nodes at levels >= 3 of a 32x32 grid: 16 + 4 + 1
 constexpr int kTQueues = 64;
-constexpr int kTShare = 16;  // workgroups per queue at most
+constexpr int kTItemWords = 24, kTItemE = 6;  // 16-bit words of an item; the first of the e[]
+// Workgroups of the feature pass at most: what the chip holds at three wavefronts per SIMD, so that all start at once
+// and share the list evenly. (Two per SIMD, 1024 workgroups: 67 us for 512 frames of 13x13 at D = 3584, half the tokens
+// kept, 159 us for 1024 frames of 27x27 at D = 1152; three, 768: 55 and 130 us, 1536: 57 and 144; four per SIMD spill: 80
+// and 151. With a fixed share of the workgroups per queue, and the item read only when its turn came, 70 and 219.)
+constexpr int kTBlocks = 768;
 constexpr int kTCountStride = 32;  // ints between two queues' counters: a 128-byte line each
 
 __host__ __device__ inline int temporal_queue_items(const Geo& g) {
   return ((g.F + kTQueues - 1) / kTQueues) * temporal_items_per_pair(g);
 }
+__device__ inline int temporal_queue_of(const Geo& g, int f) { return f / ((g.F + kTQueues - 1) / kTQueues); }
 
 
 __global__ __launch_bounds__(256) void k_temporal_plan(Geo g, const uint8_t* __restrict__ node_level, int skip_same,
@@ -134,7 +141,7 @@ __global__ __launch_bounds__(256) void k_temporal_plan(Geo g, const uint8_t* __r
     ioff0[tid] = io;
     if (tid == kBigNodes) {
       const int total = ((nfast + 3) >> 2) + nmid + io + nX;
-      s_base = total ? atomicAdd(count + (f % kTQueues) * kTCountStride, total) : 0;
+      s_base = total ? atomicAdd(count + temporal_queue_of(g, f) * kTCountStride, total) : 0;
     }
   }
   __syncthreads();
@@ -151,7 +158,7 @@ __global__ __launch_bounds__(256) void k_temporal_plan(Geo g, const uint8_t* __r
   // stored in one piece needs its entry array indexed at run time, which cost more than everything else here).
   const int nfi = (nfast + 3) >> 2, nmi = nmid, n0i = ioff0[kBigNodes], nxi = nX;
   const int ntot = nfi + nmi + n0i + nxi;
-  TItem* out = items + (size_t)(f % kTQueues) * temporal_queue_items(g) + s_base;
+  TItem* out = items + (size_t)temporal_queue_of(g, f) * temporal_queue_items(g) + s_base;
   for (int idx = tid; idx < ntot * 19; idx += blockDim.x) {
     const int i = idx / 19, j = idx - i * 19 - 1;  // j = -1: the header
     int type, n = 0, a = 0, bflag = 0, ev = 0;
@@ -217,11 +224,12 @@ __device__ inline float rows16_sum(const float* tb, int lane) {
 }
 
 template <int DT>
-__global__ __launch_bounds__(256) void k_temporal_dots(Geo g, const void* __restrict__ feats_v,
+__global__ __launch_bounds__(256, 3) void k_temporal_dots(Geo g, const void* __restrict__ feats_v,
                                                        const float* __restrict__ nsum,
                                                        const TItem* __restrict__ items,
                                                        const int* __restrict__ count, float* __restrict__ pd_part) {
   typedef Row<DT> R;
+  typedef typename R::Raw Raw;
   constexpr int VEC = R::VEC;
   __shared__ float tbuf[4][kFastRows * 68];
   // (the wavefront's number is the same in all its lanes: said explicitly, so that everything derived from it --
@@ -230,53 +238,79 @@ __global__ __launch_bounds__(256) void k_temporal_dots(Geo g, const void* __rest
   const int H = g.H, W = g.W, HW = g.HW;
   const int NB = g.NN - g.lvl_base[3];
   float* tb = tbuf[wave];
-  // Workgroups go to the eight dies round-robin by their index: the workgroups of die d serve the queues 8d .. 8d+7,
-  // i.e. eight consecutive frames of every 64, so that the two frame pairs that need a frame's rows mostly meet in
-  // one L2.
-  const int slot = blockIdx.x % kTQueues, share = blockIdx.x / kTQueues;
-  static_assert(kTQueues == 64, "queue <-> die mapping below");
-  const int queue = ((slot & 7) << 3) | (slot >> 3);
-  items += (size_t)queue * temporal_queue_items(g);
-  const int ntasks = count[queue * kTCountStride] * g.nC, stride = (int)(gridDim.x / kTQueues) * 4;
-  for (int task = share * 4 + wave; task < ntasks; task += stride) {
-    const int ii = task / g.nC, chunk = task - ii * g.nC;
-    const TItem it = items[ii];  // the same for all lanes
-    const int f = it.f;
+  // where each queue's items lie in the list: lane q holds the number of items up to and including queue q's
+  static_assert(kTQueues == kWave, "a lane per queue");
+  const int mine = count[lane * kTCountStride];
+  int upto = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(upto, o, 64);
+    if (lane >= o) upto += t;
+  }
+  const int total = lane_value(upto, 63);
+  // Workgroups go to the eight dies round-robin by their index.
+  const int die = blockIdx.x & 7;
+  const int first = (int)((long long)total * die / 8), nitems = (int)((long long)total * (die + 1) / 8) - first;
+  const int ntasks = nitems * g.nC, stride = (int)(gridDim.x >> 3) * 4;
+  const int qitems = temporal_queue_items(g);
+  // the 16-bit words of the item of task t, one per lane
+  auto fetch = [&](int t) {
+    const int i = first + t / g.nC;
+    const int q = __popcll(__ballot(upto <= i));  // the queue that holds it
+    const int at = i - (lane_value(upto, q) - lane_value(mine, q));
+    const int16_t* w = reinterpret_cast<const int16_t*>(items + (size_t)q * qitems + at);
+    return (int)w[min(lane, kTItemWords - 1)];
+  };
+  int task = (int)(blockIdx.x >> 3) * 4 + wave;
+  if (task >= ntasks) return;  // (the wavefronts of a workgroup share nothing)
+  int next_words = fetch(task);
+#pragma unroll 1
+  for (; task < ntasks; task += stride) {
+    const int words = next_words, chunk = task % g.nC;
+    if (task + stride < ntasks) next_words = fetch(task + stride);
+    auto e = [&](int j) { return lane_value(words, kTItemE + j); };
+    const int f = (lane_value(words, 0) & 0xffff) | (lane_value(words, 1) << 16), type = lane_value(words, 2);
+    const int it_n = lane_value(words, 3), it_a = lane_value(words, 4);
+    const bool coarse_is_t = lane_value(words, 5) != 0;
     const int ch0 = chunk * g.cch + lane * VEC;
     const bool act = ch0 < g.D;
-    const typename R::Elem* ft =
-        reinterpret_cast<const typename R::Elem*>(feats_v) + (size_t)f * HW * g.D + (act ? ch0 : 0);
+    const int chl = act ? ch0 : 0;  // (a lane beyond the last channel reads the first ones; its share is dropped below)
+    const typename R::Elem* ft = reinterpret_cast<const typename R::Elem*>(feats_v) + (size_t)f * HW * g.D;
     const typename R::Elem* fp = ft - (size_t)HW * g.D;
+    auto row = [&](const typename R::Elem* frame, int cell) {
+      return *reinterpret_cast<const Raw*>(frame + (size_t)cell * g.D + chl);
+    };
     float* out = pd_part + (size_t)(f * g.nC + chunk) * HW;
-    if (it.type == 0) {
+    if (type == 0) {
       // ---- up to four 2x2 regions, two at a time (16 rows in flight)
-#pragma unroll
+#pragma unroll 1
       for (int half = 0; half < 2; ++half) {
-        typename R::Raw rt[2][4], rp[2][4];
+        if (half * 2 >= it_n) break;
+        Raw rt[2][4], rp[2][4];
 #pragma unroll
         for (int rr = 0; rr < 2; ++rr) {
           const int ri = half * 2 + rr;
-          const int c0 = ri < it.n ? (it.e[ri] & 1023) : -1;
+          const int c0 = ri < it_n ? (e(ri) & 1023) : HW;  // (HW: no such row)
           const int y0 = c0 / W, x0 = c0 - y0 * W;
 #pragma unroll
           for (int k = 0; k < 4; ++k) {
             const int y = y0 + (k >> 1), x = x0 + (k & 1);
             rt[rr][k] = R::zero();
             rp[rr][k] = R::zero();
-            if (c0 >= 0 && y < H && x < W && act) {
-              rt[rr][k] = *reinterpret_cast<const typename R::Raw*>(ft + (size_t)(y * W + x) * g.D);
-              rp[rr][k] = *reinterpret_cast<const typename R::Raw*>(fp + (size_t)(y * W + x) * g.D);
+            if (y < H && x < W) {
+              rt[rr][k] = row(ft, y * W + x);
+              rp[rr][k] = row(fp, y * W + x);
             }
           }
         }
 #pragma unroll
         for (int rr = 0; rr < 2; ++rr) {
           const int ri = half * 2 + rr;
-          const int e = ri < it.n ? it.e[ri] : 0;
-          const bool t_block = (e >> 10) & 1, p_block = (e >> 11) & 1;  // wave-uniform
+          const int ee = ri < it_n ? e(ri) : 0;
+          const bool t_block = (ee >> 10) & 1, p_block = (ee >> 11) & 1;  // wave-uniform
           if (!t_block && !p_block) {  // four cells against four cells: no sums needed
 #pragma unroll
-            for (int k = 0; k < 4; ++k) tb[(ri * 4 + k) * 68 + lane] = R::dot(rt[rr][k], rp[rr][k]);
+            for (int k = 0; k < 4; ++k) tb[(ri * 4 + k) * 68 + lane] = act ? R::dot(rt[rr][k], rp[rr][k]) : 0.f;
             continue;
           }
           // a frame that holds the 2x2 block takes part with the sum of its four cells
@@ -315,41 +349,35 @@ __global__ __launch_bounds__(256) void k_temporal_dots(Geo g, const void* __rest
             float d = 0.f;
 #pragma unroll
             for (int v = 0; v < VEC; ++v) d = fmaf(xa[v], xb[v], d);
-            tb[(ri * 4 + k) * 68 + lane] = d;
+            tb[(ri * 4 + k) * 68 + lane] = act ? d : 0.f;
           }
         }
-        STTM_SCHED_FENCE();  // (the second half's rows are not asked for before the first half is done with its registers)
       }
       wave_lds_fence();
       const float acc = rows16_sum(tb, lane);
-      if (lane < kFastRows) {
-        const int ri = lane >> 2, k = lane & 3;
-        if (ri < it.n) {
-          const int e = items[ii].e[ri], c0 = e & 1023;
-          const int y = c0 / W + (k >> 1), x = c0 % W + (k & 1);
-          const bool both_block = ((e >> 10) & 3) == 3;
-          if (y < H && x < W && (k == 0 || !both_block)) out[y * W + x] = acc;
-        }
+      const int ri = (lane >> 2) & 3, k = lane & 3, ee = __shfl(words, kTItemE + ri, 64);
+      if (lane < kFastRows && ri < it_n) {
+        const int c0 = ee & 1023, y = c0 / W + (k >> 1), x = c0 % W + (k & 1);
+        const bool both_block = ((ee >> 10) & 3) == 3;
+        if (y < H && x < W && (k == 0 || !both_block)) out[y * W + x] = acc;
       }
       wave_lds_fence();
-    } else if (it.type == 1) {
+    } else if (type == 1) {
       // ---- a 4x4 join block: its sum in the frame where it is one node, then every cell of the other frame dotted
       //      with it; the dot product of a finer node is the sum over its cells
-      const int c = it.a;
-      const bool coarse_is_t = it.b != 0;
-      const int y0 = c / W, x0 = c - y0 * W;
+      const int y0 = it_a / W, x0 = it_a - y0 * W;
       const typename R::Elem* coarse = coarse_is_t ? ft : fp;
       const typename R::Elem* fine = coarse_is_t ? fp : ft;
       float SA[VEC];
 #pragma unroll
       for (int v = 0; v < VEC; ++v) SA[v] = 0.f;
       {
-        typename R::Raw rc[16];
+        Raw rc[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
           const int y = y0 + (j >> 2), x = x0 + (j & 3);
           rc[j] = R::zero();
-          if (y < H && x < W && act) rc[j] = *reinterpret_cast<const typename R::Raw*>(coarse + (size_t)(y * W + x) * g.D);
+          if (y < H && x < W) rc[j] = row(coarse, y * W + x);
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
@@ -361,12 +389,12 @@ __global__ __launch_bounds__(256) void k_temporal_dots(Geo g, const void* __rest
       }
       STTM_SCHED_FENCE();  // the second sixteen rows are asked for only now: 32 in flight cost a wavefront per SIMD
       {
-        typename R::Raw rf[16];
+        Raw rf[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
           const int y = y0 + (j >> 2), x = x0 + (j & 3);
           rf[j] = R::zero();
-          if (y < H && x < W && act) rf[j] = *reinterpret_cast<const typename R::Raw*>(fine + (size_t)(y * W + x) * g.D);
+          if (y < H && x < W) rf[j] = row(fine, y * W + x);
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
@@ -375,7 +403,7 @@ __global__ __launch_bounds__(256) void k_temporal_dots(Geo g, const void* __rest
           float d = 0.f;
 #pragma unroll
           for (int v = 0; v < VEC; ++v) d = fmaf(tv[v], SA[v], d);
-          tb[j * 68 + lane] = d;
+          tb[j * 68 + lane] = act ? d : 0.f;
         }
       }
       wave_lds_fence();
@@ -384,10 +412,11 @@ __global__ __launch_bounds__(256) void k_temporal_dots(Geo g, const void* __rest
       const float s4 = (cd + __shfl_down(cd, 1, 64)) + (__shfl_down(cd, 4, 64) + __shfl_down(cd, 5, 64));  // 2x2 at lane
       float s16 = s4;  // lanes 0, 2, 8, 10 hold the four 2x2 sums
       s16 = (s16 + __shfl_down(s16, 2, 64)) + (__shfl_down(s16, 8, 64) + __shfl_down(s16, 10, 64));
+      const int lf = __shfl_down(words, kTItemE, 64);  // level of the other frame's node at the lane's cell
       if (lane < 16) {
         const int dy = lane >> 2, dx = lane & 3, y = y0 + dy, x = x0 + dx;
         if (y < H && x < W) {
-          const int cb = y * W + x, lf = items[ii].e[lane];
+          const int cb = y * W + x;
           if (lf == 0) out[cb] = cd;
           else if (lf == 1 && !(dy & 1) && !(dx & 1)) out[cb] = s4;
           else if (lf == 2 && lane == 0) out[cb] = s16;
@@ -396,22 +425,21 @@ __global__ __launch_bounds__(256) void k_temporal_dots(Geo g, const void* __rest
     } else {
       // ---- under a join block at a level >= 3: its stored sum against single cells (sixteen at a time) or against
       //      one finer node
-      const bool coarse_is_t = it.b != 0;
       const int fc = coarse_is_t ? f : f - 1;  // frame in which the join block is one node
       const typename R::Elem* fine = coarse_is_t ? fp : ft;
-      const float* srow = nsum + ((size_t)fc * NB + it.a) * g.D + (act ? ch0 : 0);
+      const float* srow = nsum + ((size_t)fc * NB + it_a) * g.D + chl;
       float S[VEC];
 #pragma unroll
       for (int v = 0; v < VEC; v += 4) {
         const float4 q = *reinterpret_cast<const float4*>(srow + v);
         S[v] = q.x; S[v + 1] = q.y; S[v + 2] = q.z; S[v + 3] = q.w;
       }
-      if (it.type == 2) {
-        typename R::Raw r[16];
+      if (type == 2) {
+        Raw r[16];
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) {
-          const int cq = jj < it.n ? it.e[jj] : it.e[0];  // (a position beyond the item's end repeats a cell and is dropped)
-          r[jj] = *reinterpret_cast<const typename R::Raw*>(fine + (size_t)cq * g.D);
+          r[jj] = R::zero();
+          if (jj < it_n) r[jj] = row(fine, e(jj));
         }
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) {
@@ -424,20 +452,24 @@ __global__ __launch_bounds__(256) void k_temporal_dots(Geo g, const void* __rest
         }
         wave_lds_fence();
         const float acc = rows16_sum(tb, lane);
-        if (lane < it.n) out[items[ii].e[lane]] = acc;
+        const int cell = __shfl_down(words, kTItemE, 64);
+        if (lane < it_n) out[cell] = acc;
         wave_lds_fence();
       } else {
-        const int q = it.e[0], lf = it.e[1];
+        const int q = e(0), lf = e(1);
         const int y = q / W, x = q - y * W;
         float SB[VEC];
         if (lf >= 3) {
           const int ff = coarse_is_t ? f - 1 : f;
-          const float* row = nsum + ((size_t)ff * NB + node_index(g, lf, y >> lf, x >> lf) - g.lvl_base[3]) * g.D;
+          const float* brow = nsum + ((size_t)ff * NB + node_index(g, lf, y >> lf, x >> lf) - g.lvl_base[3]) * g.D + chl;
 #pragma unroll
-          for (int v = 0; v < VEC; ++v) SB[v] = act ? row[ch0 + v] : 0.f;
+          for (int v = 0; v < VEC; v += 4) {
+            const float4 t = *reinterpret_cast<const float4*>(brow + v);
+            SB[v] = t.x; SB[v + 1] = t.y; SB[v + 2] = t.z; SB[v + 3] = t.w;
+          }
         } else {
           const int s = 1 << lf;
-          block_sum16<DT>(fine, g.D, W, y, x, min(s, H - y), min(s, W - x), act, SB);
+          block_sum16<DT>(fine + chl, g.D, W, y, x, min(s, H - y), min(s, W - x), SB);
         }
         float d = 0.f;
 #pragma unroll
@@ -458,13 +490,11 @@ void launch_temporal_dots(const Geo& g, const void* feats, const uint8_t* node_l
                           hipStream_t s) {
   TItem* q = reinterpret_cast<TItem*>(items);
   hipLaunchKernelGGL(k_temporal_plan, dim3(g.F), dim3(256), 0, s, g, node_level, skip_same, q, item_count, sel);
-  // enough wavefronts for about four tasks each if every pair came with all the items it can have, the same
-  // number of workgroups for every queue
-  const long long worst = (long long)temporal_queue_items(g) * g.nC;
-  long long share = (worst + 15) / 16;
-  if (share < 1) share = 1;
-  if (share > kTShare) share = kTShare;
-  const dim3 grid((unsigned)(share * kTQueues)), block(256);
+  // enough wavefronts for about four tasks each if every pair came with all the items it can have; whole rounds of dies
+  const long long worst = (long long)g.F * temporal_items_per_pair(g) * g.nC;
+  long long blocks = (worst + 15) / 16;
+  blocks = blocks < kTBlocks ? (blocks + 7) / 8 * 8 : kTBlocks;
+  const dim3 grid((unsigned)blocks), block(256);
   if (g.dtype == 1)
     hipLaunchKernelGGL(k_temporal_dots<1>, grid, block, 0, s, g, feats, nsum, q, item_count, pd_part);
   else if (g.dtype == 2)
