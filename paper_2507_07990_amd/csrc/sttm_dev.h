@@ -19,6 +19,15 @@
 #define STTM_SCHED_FENCE() ((void)0)
 #endif
 
+// A value in a scalar / vector register that the compiler must take as new from here on.
+#ifndef STTM_HOST_EMULATION
+#define STTM_OPAQUE_S(x) asm volatile("" : "+s"(x))
+#define STTM_OPAQUE_V(x) asm volatile("" : "+v"(x))
+#else
+#define STTM_OPAQUE_S(x) ((void)(x))
+#define STTM_OPAQUE_V(x) ((void)(x))
+#endif
+
 namespace sttm {
 
 constexpr int kWave = 64;

@@ -496,32 +496,37 @@ __device__ inline Slot describe(const Geo& g, const int32_t* __restrict__ node_m
   return e;
 }
 
+// A lane's 16 bytes of a slot (kind and idx are the same in all lanes, chl is the lane's first channel): one request
+// whichever table the slot lives in. This is the last use of a feature row, and node sums are read once as well.
 template <int DT>
-__device__ inline typename Row<DT>::Raw load_slot(const void* feats, const float* nsum, int D, int ch0, int kind,
+__device__ inline typename Row<DT>::Raw load_slot(const void* feats, const float* nsum, int D, int chl, int kind,
                                                   int idx) {
   typedef Row<DT> R;
-  if (kind == 0)  // a feature row: this is its last use
-    return load_once(reinterpret_cast<const typename R::Raw*>(reinterpret_cast<const typename R::Elem*>(feats) +
-                                                              (size_t)idx * D + ch0));
-  return *reinterpret_cast<const typename R::Raw*>(nsum + (size_t)idx * D + ch0 + (kind - 1) * 4);
+  const size_t first = (size_t)idx * D;
+  const char* row = kind == 0 ? static_cast<const char*>(feats) + first * sizeof(typename R::Elem)
+                              : reinterpret_cast<const char*>(nsum) + (first + (kind - 1) * 4) * sizeof(float);
+  const unsigned off = (unsigned)chl * (kind == 0 ? (unsigned)sizeof(typename R::Elem) : (unsigned)sizeof(float));
+  return load_once(reinterpret_cast<const typename R::Raw*>(row + off));
 }
 
 template <int DT>
 __device__ inline void acc_slot(const float4& r, int, float (&acc)[4]) {  // fp32 rows and node sums share a layout
   acc[0] += r.x; acc[1] += r.y; acc[2] += r.z; acc[3] += r.w;
 }
+// (Three steps, each skipped or not: as one choice of three the sums came out of it in three sets of registers and were
+// moved back into one, eight moves a slot. The node sum's two halves add to different channels, so their order is free.)
 template <int DT>
 __device__ inline void acc_slot(const uint4& r, int kind, float (&acc)[8]) {
-  if (kind == 0) {
-    Row<DT>::add_row(r, acc);
-  } else {
-    const float f0 = __uint_as_float(r.x), f1 = __uint_as_float(r.y);
-    const float f2 = __uint_as_float(r.z), f3 = __uint_as_float(r.w);
-    if (kind == 1) {
-      acc[0] += f0; acc[1] += f1; acc[2] += f2; acc[3] += f3;
-    } else {
-      acc[4] += f0; acc[5] += f1; acc[6] += f2; acc[7] += f3;
-    }
+  if (kind == 0) Row<DT>::add_row(r, acc);
+  const float f0 = __uint_as_float(r.x), f1 = __uint_as_float(r.y);
+  const float f2 = __uint_as_float(r.z), f3 = __uint_as_float(r.w);
+  if (kind == 1) {
+    STTM_OPAQUE_S(kind);  // (keeps this a branch; the additions are not made by every slot and dropped)
+    acc[0] += f0; acc[1] += f1; acc[2] += f2; acc[3] += f3;
+  }
+  if (kind == 2) {
+    STTM_OPAQUE_S(kind);
+    acc[4] += f0; acc[5] += f1; acc[6] += f2; acc[7] += f3;
   }
 }
 
@@ -575,9 +580,15 @@ __device__ inline void store_partial(float* o, const float (&acc)[VEC]) {
   for (int v = 0; v < VEC; v += 4) *reinterpret_cast<float4*>(o + v) = make_float4(acc[v], acc[v + 1], acc[v + 2], acc[v + 3]);
 }
 
+// What a slot asks for is decided for all slots at once, a lane each, and kept as bit masks in scalar registers: per
+// slot only its loads, additions and row stores are left, on scalar branches and addresses. The counts, and which
+// items hold shares of a big cluster, are written by the lanes together. (Read from lane to lane per slot, by masked
+// branches, the kernel was 31 KB of code, now 17: 8 frames of 8x8 tokens 13.1 -> 8.8 us, 96 of 11x19 in fp32 33 -> 26; and it
+// issues less: 1024 frames of 27x27 at D = 1152 306 -> 266 us (1.72 GB, 6.5 TB/s), 512 of 13x13 at D = 3584 140 -> 134.)
 template <int DT, int ODT>
 __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
   typedef Row<DT> R;
+  typedef typename R::Raw Raw;
   constexpr int VEC = R::VEC;
   // one-wavefront workgroups; consecutive ones take the chunks of one item
   const int nw = gather_waves(g), wave = blockIdx.x % nw, item = blockIdx.x / nw, lane = threadIdx.x;
@@ -603,97 +614,106 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
       row_v = a.zpos ? a.zpos[rank_l] : rank_l;
     }
   }
-  Slot tnext;  // lanes 0..kTail-1: the positions p0 + kItem ... described above
-  tnext.kind = __shfl(sv.kind, kItem + (lane & (kTail - 1)), 64);
-  tnext.idx = __shfl(sv.idx, kItem + (lane & (kTail - 1)), 64);
-  tnext.weight = __shfl(sv.weight, kItem + (lane & (kTail - 1)), 64);
+  const bool big = end_v - beg_v > kBig;
+  const bool use = pl < p1 && (beg_v >= p0 || big);  // (else the tail of a cluster that an earlier item finishes)
+  // a cluster of one cell whose row is written in the type it came in: the mean is the row itself
+  const bool one = DT == ODT && use && end_v - beg_v == 1 && sv.kind == 0;
+  const bool closes = use && !one && !big && pl + 1 == end_v;
+  const bool share = use && big && (pl + 1 == end_v || pl + 1 == p1);  // ends this item's share of a big cluster
+  const bool fits = row_v < a.capacity;
+  // member cells of the slot's cluster from its first slot in this item up to the slot
+  int members = use ? sv.weight : 0;
+#pragma unroll
+  for (int o = 1; o < kItem; o <<= 1) {
+    const int t = __shfl_up(members, o, 64);
+    if (lane >= o) members += t;
+  }
+  members -= __shfl(members, max(beg_v - p0, 0) - 1, 64) * (beg_v > p0);
+  unsigned use_m = (unsigned)__ballot(use), one_m = (unsigned)__ballot(one && fits);
+  unsigned add_m = (unsigned)__ballot(use && !one), mean_m = (unsigned)__ballot(closes && fits);
+  unsigned share_m = (unsigned)__ballot(share), end_m = share_m | (unsigned)__ballot(closes);
+  int inv_v = (int)__float_as_uint(1.f / (float)members);
+  if (wave == 0) {
+    if ((one || closes) && fits && a.counts) a.counts[row_v] = members;
+    if (share) {
+      const int slot = beg_v < p0 ? 0 : 1;
+      a.bigw[item * 2 + slot] = members;
+      if (slot == 1) a.biglist[atomicAdd(a.bigcount, 1)] = make_int4(row_v, beg_v, end_v, 0);
+    }
+  }
+  // the cluster still open after the item's last position (the item is full then)
+  const int lastj = p1 - 1 - p0;
+  const bool open = (add_m >> lastj & 1u) && !(end_m >> lastj & 1u);
+#pragma unroll 1
   for (int chunk = wave; chunk < g.nC; chunk += nw) {
     const int ch0 = chunk * g.cch + lane * VEC;
     const bool act = ch0 < g.D;
-    // issue every load of the positions this item adds up: clusters starting here, and big ones
-    typename R::Raw raw[kItem];
+    const int chl = act ? ch0 : 0;  // (a lane beyond the last channel reads the row's first channels and drops them)
+    // (The slots' bits and numbers are taken from these registers where they are used: a copy the compiler cannot look
+    // through, or it takes all of them out of the loop -- which has one round unless a row has more than 16 chunks --
+    // and runs out of scalar registers.)
+    STTM_OPAQUE_S(use_m); STTM_OPAQUE_S(one_m); STTM_OPAQUE_S(add_m);
+    STTM_OPAQUE_S(mean_m); STTM_OPAQUE_S(share_m); STTM_OPAQUE_S(end_m);
+    STTM_OPAQUE_V(sv.kind); STTM_OPAQUE_V(sv.idx); STTM_OPAQUE_V(row_v); STTM_OPAQUE_V(inv_v); STTM_OPAQUE_V(beg_v);
+    Raw raw[kItem];
 #pragma unroll
     for (int j = 0; j < kItem; ++j) {
-      const int beg = __shfl(beg_v, j, 64), end = __shfl(end_v, j, 64);
-      const int kind = __shfl(sv.kind, j, 64), idx = __shfl(sv.idx, j, 64);
       raw[j] = R::zero();
-      const bool use = p0 + j < p1 && (beg >= p0 || end - beg > kBig);  // wave-uniform
-      if (use && act) raw[j] = load_slot<DT>(a.feats, a.nsum, g.D, ch0, kind, idx);
+      if (use_m >> j & 1u)
+        raw[j] = load_slot<DT>(a.feats, a.nsum, g.D, chl, lane_value(sv.kind, j), lane_value(sv.idx, j));
     }
     float acc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
-    int members = 0, open_row = -1, open_end = 0;  // the cluster still open after the item's last position
 #pragma unroll
     for (int j = 0; j < kItem; ++j) {
-      const int beg = __shfl(beg_v, j, 64), end = __shfl(end_v, j, 64), row = __shfl(row_v, j, 64);
-      const int kind = __shfl(sv.kind, j, 64), wgt = __shfl(sv.weight, j, 64);
-      const bool big = end - beg > kBig;
-      const bool use = p0 + j < p1 && (beg >= p0 || big);
-      const int p = p0 + j;
-      // a cluster of one cell whose row is written in the type it came in: the mean is the row itself
-      const bool one = (DT == ODT) && use && !big && beg == p && end == p + 1 && kind == 0;
-      if (one) {
-        if (row < a.capacity) {
-          if (act) store_once(reinterpret_cast<typename R::Raw*>(
-                                  reinterpret_cast<typename R::Elem*>(a.merged) + (size_t)row * g.D + ch0), raw[j]);
-          if (chunk == 0 && lane == 0 && a.counts) a.counts[row] = 1;
+      if (one_m >> j & 1u) {
+        Raw* o = reinterpret_cast<Raw*>(reinterpret_cast<typename R::Elem*>(a.merged) + (size_t)lane_value(row_v, j) * g.D + chl);
+        if (act) store_once(o, raw[j]);
+      }
+      if (add_m >> j & 1u) acc_slot<DT>(raw[j], lane_value(sv.kind, j), acc);
+      if (end_m >> j & 1u) {
+        if (mean_m >> j & 1u) {
+          const size_t off = (size_t)lane_value(row_v, j) * g.D + ch0;
+          const float inv = __uint_as_float((unsigned)lane_value(inv_v, j));
+          if (act) store_mean<DT, ODT>(a.merged, off, acc, inv);
+        } else if (share_m >> j & 1u) {
+          const int slot = lane_value(beg_v, j) < p0 ? 0 : 1;
+          if (act) store_partial<VEC>(a.bigpart + ((size_t)item * 2 + slot) * g.D + ch0, acc);
         }
-      } else if (use) {
-        acc_slot<DT>(raw[j], kind, acc);
-        members += wgt;
-        const bool closes = p + 1 == end, last = p + 1 == p1;
-        if (big) {
-          if (closes || last) {  // this item's share of a big cluster
-            const int slot = beg < p0 ? 0 : 1;
-            if (act) store_partial<VEC>(a.bigpart + ((size_t)item * 2 + slot) * g.D + ch0, acc);
-            if (chunk == 0 && lane == 0) {
-              a.bigw[item * 2 + slot] = members;
-              if (slot == 1) a.biglist[atomicAdd(a.bigcount, 1)] = make_int4(row, beg, end, 0);
-            }
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
-            members = 0;
-          }
-        } else if (closes) {
-          if (row < a.capacity) {
-            if (act) store_mean<DT, ODT>(a.merged, (size_t)row * g.D + ch0, acc, 1.f / (float)members);
-            if (chunk == 0 && lane == 0 && a.counts) a.counts[row] = members;
-          }
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
-          members = 0;
-        } else if (last) {
-          open_row = row;
-          open_end = end;
-        }
+        for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
       }
     }
-    if (open_row >= 0) {
-      // the last cluster runs past the item: finish it from the list, kTail loads in flight
+    if (open) {
+      // the last cluster runs past the item: finish it from the list, kTail loads in flight (the first kTail positions
+      // after the item are already described, by lanes kItem ...)
+      const int open_row = lane_value(row_v, kItem - 1), open_end = lane_value(end_v, kItem - 1);
+      int total = lane_value(members, kItem - 1);
+      Slot ts = sv;
+      int first = kItem;  // lane of the batch's first position
+#pragma unroll 1
       for (int q = p1; q < open_end; q += kTail) {
-        Slot ts = {0, 0, 0};
-        if (q == p1) ts = tnext;  // (an open cluster means the item is full: p1 == p0 + kItem)
-        else if (lane < kTail && q + lane < open_end) ts = describe<DT>(g, a.node_map, a.lvl, a.order[q + lane]);
-        typename R::Raw tr[kTail];
+        Raw tr[kTail];
 #pragma unroll
         for (int u = 0; u < kTail; ++u) {
-          const int kd = __shfl(ts.kind, u, 64), ix = __shfl(ts.idx, u, 64);
           tr[u] = R::zero();
-          if (q + u < open_end && act) tr[u] = load_slot<DT>(a.feats, a.nsum, g.D, ch0, kd, ix);
+          if (q + u < open_end)
+            tr[u] = load_slot<DT>(a.feats, a.nsum, g.D, chl, lane_value(ts.kind, first + u), lane_value(ts.idx, first + u));
         }
 #pragma unroll
-        for (int u = 0; u < kTail; ++u) {
-          const int kd = __shfl(ts.kind, u, 64), wg = __shfl(ts.weight, u, 64);
+        for (int u = 0; u < kTail; ++u)
           if (q + u < open_end) {
-            acc_slot<DT>(tr[u], kd, acc);
-            members += wg;
+            acc_slot<DT>(tr[u], lane_value(ts.kind, first + u), acc);
+            total += lane_value(ts.weight, first + u);
           }
-        }
+        first = 0;
+        if (lane < kTail && q + kTail + lane < open_end)
+          ts = describe<DT>(g, a.node_map, a.lvl, a.order[q + kTail + lane]);
       }
       if (open_row < a.capacity) {
-        if (act) store_mean<DT, ODT>(a.merged, (size_t)open_row * g.D + ch0, acc, 1.f / (float)members);
-        if (chunk == 0 && lane == 0 && a.counts) a.counts[open_row] = members;
+        if (act) store_mean<DT, ODT>(a.merged, (size_t)open_row * g.D + ch0, acc, 1.f / (float)total);
+        if (chunk == 0 && lane == 0 && a.counts) a.counts[open_row] = total;
       }
     }
   }
