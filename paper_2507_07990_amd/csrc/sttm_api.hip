@@ -147,11 +147,65 @@ constexpr int kHostTaus = 1024;
 struct HostOut {
   int32_t k;
   float tau[kHostTaus];
+  HostOut* next;  // in the list of idle blocks
 };
+
+namespace {
+// The blocks of contexts that are gone, kept for later contexts of the same device: a free would end a stream capture
+// that runs meanwhile and waits for the work of every other context, and a context may go at any time (a garbage
+// collection). At most kIdleBlocks (256 KB) are kept per device; more are freed.
+constexpr int kIdleBlocks = 64;
+std::mutex g_idle_mutex;
+HostOut* g_idle[kMaxDevices] = {};
+int g_idle_count[kMaxDevices] = {};
+
+// While one lives, the thread's calls do not count as unsafe for a stream capture: an allocation or a free of pinned
+// memory must not end one that runs meanwhile. `ok` is false if the runtime refused.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  bool ok;
+  RelaxedCapture() : ok(hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {}
+  ~RelaxedCapture() {
+    if (ok) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+
+// A block for a context on `device`, or NULL if there is none to be had.
+HostOut* take_host_out(int device) {
+  {
+    std::lock_guard<std::mutex> lock(g_idle_mutex);
+    if (HostOut* p = g_idle[device]) {
+      g_idle[device] = p->next;
+      --g_idle_count[device];
+      return p;
+    }
+  }
+  RelaxedCapture relaxed;
+  void* p = nullptr;
+  if (relaxed.ok && hipHostMalloc(&p, sizeof(HostOut), hipHostMallocDefault) == hipSuccess) return static_cast<HostOut*>(p);
+  (void)hipGetLastError();
+  return nullptr;
+}
+
+void give_host_out(int device, HostOut* p) {
+  {
+    std::lock_guard<std::mutex> lock(g_idle_mutex);
+    if (g_idle_count[device] < kIdleBlocks) {
+      p->next = g_idle[device];
+      g_idle[device] = p;
+      ++g_idle_count[device];
+      return;
+    }
+  }
+  RelaxedCapture relaxed;
+  if (!relaxed.ok || hipHostFree(p) != hipSuccess) (void)hipGetLastError();  // (the block stays allocated then)
+}
+}  // namespace
 
 struct sttm_ctx {
   int device = 0;
   HostOut* host_out = nullptr;  // NULL if it could not be had: results are copied then
+  bool host_out_busy = false;   // kernels that write it were launched and have not been waited for (the call failed)
   char* static_scratch = nullptr;  // this device's copy of the static scratch array
   hipStream_t stream = nullptr;
   char* ws = nullptr;
@@ -368,21 +422,14 @@ int sttm_create(sttm_ctx** out, int device, void* hip_stream) {
     delete c;
     return STTM_ERR_HIP;
   }
-  // (relaxed: an allocation must not end a stream capture that runs meanwhile)
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-  void* host = nullptr;
-  if (relaxed && hipHostMalloc(&host, sizeof(HostOut), hipHostMallocDefault) == hipSuccess)
-    c->host_out = static_cast<HostOut*>(host);
-  else
-    (void)hipGetLastError();
-  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  c->host_out = take_host_out(device);
   *out = c;
   return STTM_OK;
 }
 
 int sttm_destroy(sttm_ctx* ctx) {
-  if (ctx && ctx->host_out) (void)hipHostFree(ctx->host_out);
+  // (a block that a failed call's kernels may still write is not handed on)
+  if (ctx && ctx->host_out && !ctx->host_out_busy) give_host_out(ctx->device, ctx->host_out);
   if (ctx)
     for (auto& v : ctx->ev)
       for (auto& p : v) { (void)hipEventDestroy(p.a); (void)hipEventDestroy(p.b); }
@@ -601,6 +648,7 @@ int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_ho
   // threshold (one launch less); otherwise by a launch of its own.
   float* tau_now = tau_out_host ? tau_dev : nullptr;
   float* host_tau = tau_out_host && ctx->host_out && g.B <= kHostTaus ? ctx->host_out->tau : nullptr;
+  if (host_tau) ctx->host_out_busy = true;
   if (spatial) {
     launch_select_spatial(g, at<uint32_t>(ctx, ctx->lay.sel_key_s), at<uint8_t>(ctx, ctx->lay.sel_w_s),
                           target_dev, at<SelState>(ctx, ctx->lay.sel_s), ctx->sel_s_dirty, tau_now, host_tau, ctx->stream);
@@ -619,6 +667,7 @@ int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_ho
     if (!host_tau)
       STTM_HIP(ctx, hipMemcpyAsync(tau_out_host, tau_dev, g.B * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
     STTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    ctx->host_out_busy = false;
     if (host_tau) std::memcpy(tau_out_host, host_tau, g.B * sizeof(float));
   }
   return STTM_OK;
@@ -647,7 +696,10 @@ int sttm_reduce(sttm_ctx* ctx, const void* feats_dev, const int32_t* cluster_ids
   if (reinterpret_cast<uintptr_t>(merged_dev) & 15) return fail(ctx, STTM_ERR_ARG, "merged must be 16-byte aligned");
   STTM_HIP(ctx, hipSetDevice(ctx->device));
   ReduceBuffers rb = reduce_buffers(ctx->ws, ctx->lay);
-  if (n_out_host && ctx->host_out) rb.host_k = &ctx->host_out->k;
+  if (n_out_host && ctx->host_out) {
+    rb.host_k = &ctx->host_out->k;
+    ctx->host_out_busy = true;
+  }
   const bool zscan = ctx->order == STTM_ORDER_ZSCAN;
   ctx->cluster_ids_reduced = nullptr;
   launch_reduce_prepare(ctx->g, cluster_ids_dev, node_map_dev, node_level_dev, capacity, out_ids_dev, offsets_dev,
@@ -667,6 +719,7 @@ int sttm_reduce(sttm_ctx* ctx, const void* feats_dev, const int32_t* cluster_ids
     int32_t k = 0;
     if (!rb.host_k) STTM_HIP(ctx, hipMemcpyAsync(&k, rb.kdev, sizeof k, hipMemcpyDeviceToHost, ctx->stream));
     STTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    ctx->host_out_busy = false;
     if (rb.host_k) k = *rb.host_k;
     *n_out_host = k;
     if (k > capacity) {

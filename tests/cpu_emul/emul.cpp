@@ -7,6 +7,8 @@ dim3 g_blockDim, g_gridDim;
 thread_local Wave* t_wave = nullptr;
 pthread_barrier_t g_block_bar;
 alignas(16) float g_dynamic_lds[40960];  // 160 KB, the LDS of one CU
+Pinned g_pinned;
+thread_local hipStreamCaptureMode t_capture_mode = hipStreamCaptureModeGlobal;
 
 void launch(dim3 grid, dim3 block, void (*body)(void*), void* closure) {
   const unsigned nthreads = block.x * block.y * block.z;
@@ -44,3 +46,8 @@ void launch(dim3 grid, dim3 block, void (*body)(void*), void* closure) {
 }
 }  // namespace hip_emul
 
+extern "C" void hip_emul_pinned(int out[3]) {
+  out[0] = hip_emul::g_pinned.allocated;
+  out[1] = hip_emul::g_pinned.freed;
+  out[2] = hip_emul::g_pinned.unguarded;
+}

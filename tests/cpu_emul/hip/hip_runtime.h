@@ -196,10 +196,32 @@ inline hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind
   return hipSuccess;
 }
 enum hipStreamCaptureMode { hipStreamCaptureModeGlobal = 0, hipStreamCaptureModeThreadLocal = 1, hipStreamCaptureModeRelaxed = 2 };
-inline hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) { return hipSuccess; }
+namespace hip_emul {
+// What tests ask about pinned memory (hip_emul_pinned in emul.cpp): blocks allocated and freed so far, and how many of
+// those calls were made while the thread was not in the relaxed capture mode, where they end a capture that runs.
+struct Pinned { int allocated, freed, unguarded; };
+extern Pinned g_pinned;
+extern thread_local hipStreamCaptureMode t_capture_mode;
+inline void pinned_call(int* which) {
+  ++*which;
+  if (t_capture_mode != hipStreamCaptureModeRelaxed) ++g_pinned.unguarded;
+}
+}  // namespace hip_emul
+inline hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
+  std::swap(*m, hip_emul::t_capture_mode);
+  return hipSuccess;
+}
 enum { hipHostMallocDefault = 0 };
-inline hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = malloc(n); return *p ? hipSuccess : (hipError_t)2; }
-inline hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
+inline hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  hip_emul::pinned_call(&hip_emul::g_pinned.allocated);
+  *p = malloc(n);
+  return *p ? hipSuccess : (hipError_t)2;
+}
+inline hipError_t hipHostFree(void* p) {
+  hip_emul::pinned_call(&hip_emul::g_pinned.freed);
+  free(p);
+  return hipSuccess;
+}
 inline hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
 inline hipError_t hipEventCreate(hipEvent_t* e) { *e = nullptr; return hipSuccess; }
 inline hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }

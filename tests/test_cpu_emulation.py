@@ -132,3 +132,35 @@ def test_emulated_kernels_run_clean_under_address_and_undefined_behaviour_saniti
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
     assert r.stdout.count("case ") == 2
     assert "runtime error" not in r.stderr and "AddressSanitizer" not in r.stderr
+
+
+def test_emulated_contexts_leave_the_runtime_alone_when_they_go(emul):
+    """Destroying a context must not call the runtime's host allocator: outside the relaxed capture mode that ends a
+    stream capture running on any other stream, and a free waits for the work of every context. A block goes to the
+    next context instead; of many idle ones only a bounded number is kept, the rest freed in the relaxed mode."""
+    import ctypes as C
+    lib = emul[0].load()
+    lib.sttm_destroy.argtypes = [C.c_void_p]
+
+    def pinned():
+        out = (C.c_int * 3)()
+        lib.hip_emul_pinned(out)
+        return list(out)
+
+    def create(n):
+        hs = [C.c_void_p() for _ in range(n)]
+        assert all(lib.sttm_create(C.byref(h), 0, None) == 0 for h in hs)
+        return hs
+
+    def destroy(hs):
+        assert all(lib.sttm_destroy(h) == 0 for h in hs)
+
+    _, freed, unguarded = pinned()
+    destroy(create(2))
+    assert pinned()[1:] == [freed, unguarded]          # nothing freed, no call outside the relaxed mode
+    allocated = pinned()[0]
+    destroy(create(2))
+    assert pinned() == [allocated, freed, unguarded]   # the same two blocks again
+    destroy(create(200))
+    allocated, freed, after = pinned()
+    assert after == unguarded and 0 < allocated - freed <= 64

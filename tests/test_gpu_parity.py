@@ -781,3 +781,44 @@ def test_thresholds_in_and_out_at_every_way_they_travel(lib, B):
         ids1, taus1 = one(x[b:b + 1].contiguous(), tau_s[b:b + 1], tau_t[b:b + 1], keep[b:b + 1])
         assert torch.equal(ids[b] - b * T * H * W, ids1[0])
         assert (taus[:, b] == taus1[:, 0]).all()
+
+
+def test_contexts_come_and_go_while_another_stream_captures(lib):
+    """Creating and destroying contexts must not end a graph capture that runs on another stream (in the mode that any
+    unsafe call of any thread ends): the captured work still replays and gives the eager result every time."""
+    import torch
+    feats = wl.generate(wl.small_variant(wl.CONFIGS[0], T=4))
+    r = P.run_gpu(lib, feats, tau_s=0.8, tau_t=0.8)
+    B, T, H, W, D = feats.shape
+    N, x = B * T * H * W, r.feats_dev
+    cl = torch.from_numpy(r.cluster_ids.reshape(-1)).cuda()
+    idle = [lib.Sttm(0) for _ in range(3)]
+    stream = torch.cuda.Stream()
+    ctx = lib.Sttm(0, stream_ptr=stream.cuda_stream)
+
+    def outputs():
+        return (torch.zeros(N, D, device="cuda:0"), torch.zeros(N, dtype=torch.int32, device="cuda:0"),
+                torch.zeros(N, dtype=torch.int32, device="cuda:0"), torch.zeros(B + 1, dtype=torch.int64, device="cuda:0"))
+
+    def reduce(out):
+        ctx.sttm_reduce_noalloc(x, lib.STTM_F32, B, T, H, W, D, cl, lib.STTM_F32, N, *out)
+
+    want, got = outputs(), outputs()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        reduce(want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode="global"):
+        idle.pop().close()
+        reduce(got)
+        fresh = lib.Sttm(0, stream_ptr=stream.cuda_stream)
+        idle.pop().close()
+        fresh.close()
+    for _ in range(3):
+        for t in got:
+            t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(want, got)) and int(got[3][B]) == r.K
