@@ -1,5 +1,6 @@
 // Host-thread executor behind tests/cpu_emul/hip/hip_runtime.h (test infrastructure only).
 #include <hip/hip_runtime.h>
+#include <string>
 
 namespace hip_emul {
 thread_local dim3 t_threadIdx, t_blockIdx;
@@ -9,6 +10,9 @@ pthread_barrier_t g_block_bar;
 alignas(16) float g_dynamic_lds[40960];  // 160 KB, the LDS of one CU
 Pinned g_pinned;
 thread_local hipStreamCaptureMode t_capture_mode = hipStreamCaptureModeGlobal;
+
+static std::vector<std::pair<std::string, dim3>> g_launches;
+void note_launch(const char* kernel, dim3 grid) { g_launches.emplace_back(kernel, grid); }
 
 void launch(dim3 grid, dim3 block, void (*body)(void*), void* closure) {
   const unsigned nthreads = block.x * block.y * block.z;
@@ -50,4 +54,19 @@ extern "C" void hip_emul_pinned(int out[3]) {
   out[0] = hip_emul::g_pinned.allocated;
   out[1] = hip_emul::g_pinned.freed;
   out[2] = hip_emul::g_pinned.unguarded;
+}
+
+// Grid of the last launch, since the last call with NULL, whose kernel's name as written at the launch contains `kernel`;
+// false if there was none.
+extern "C" int hip_emul_last_grid(const char* kernel, unsigned grid[3]) {
+  if (!kernel) {
+    hip_emul::g_launches.clear();
+    return 0;
+  }
+  for (auto it = hip_emul::g_launches.rbegin(); it != hip_emul::g_launches.rend(); ++it)
+    if (it->first.find(kernel) != std::string::npos) {
+      grid[0] = it->second.x; grid[1] = it->second.y; grid[2] = it->second.z;
+      return 1;
+    }
+  return 0;
 }

@@ -61,6 +61,7 @@ inline uint64_t exchange(uint64_t v, int src_lane) {
   return r;
 }
 void launch(dim3 grid, dim3 block, void (*body)(void*), void* closure);
+void note_launch(const char* kernel, dim3 grid);  // what hip_emul_last_grid (emul.cpp) answers from
 }  // namespace hip_emul
 
 #define threadIdx (hip_emul::t_threadIdx)
@@ -238,4 +239,4 @@ inline void hip_emul_launch(void (*k)(P...), dim3 grid, dim3 block, size_t, hipS
   }, &c);
 }
 #define hipLaunchKernelGGL(kernel, grid, block, lds, stream, ...) \
-  hip_emul_launch(kernel, grid, block, lds, stream, __VA_ARGS__)
+  (hip_emul::note_launch(#kernel, grid), hip_emul_launch(kernel, grid, block, lds, stream, __VA_ARGS__))

@@ -164,3 +164,19 @@ def test_emulated_contexts_leave_the_runtime_alone_when_they_go(emul):
     destroy(create(200))
     allocated, freed, after = pinned()
     assert after == unguarded and 0 < allocated - freed <= 64
+
+
+@pytest.mark.parametrize("B,T,cell_dots", [(1, 1, 1), (3, 1, 1), (1, 2, 0)])
+def test_emulated_pyramid_grid_without_frame_pairs_has_no_idle_workgroups(emul, B, T, cell_dots):
+    """Where no two workgroups share rows (single images, frame-to-frame products off) the pass is numbered plainly: as
+    many workgroups as there are (frame, unit, chunk) triples, which the hardware deals to all dies in turn. A grid laid
+    out in one range of frames per die would put a single image on one of the eight."""
+    import ctypes as C
+    run_cpu, _ = emul
+    H, W, D = 9, 10, 72                                # 4 units of 8x8, fp32: one chunk of 64 x 4 channels
+    lib = run_cpu.load()
+    lib.hip_emul_last_grid(None, None)
+    run_cpu.run_cpu(wl.generate(_variant(89, B, T, H, W, D, "f32")), tau_s=0.5, tau_t=0.5, cell_dots=cell_dots, lib=lib)
+    grid = (C.c_uint * 3)()
+    assert lib.hip_emul_last_grid(b"k_pyramid", grid)
+    assert grid[0] * grid[1] * grid[2] == B * T * 4
