@@ -78,7 +78,8 @@ constexpr int kTItemWords = 24, kTItemE = 6;  // 16-bit words of an item; the fi
 // Workgroups of the feature pass at most: what the chip holds at three wavefronts per SIMD, so that all start at once
 // and share the list evenly. (Two per SIMD, 1024 workgroups: 67 us for 512 frames of 13x13 at D = 3584, half the tokens
 // kept, 159 us for 1024 frames of 27x27 at D = 1152; three, 768: 55 and 130 us, 1536: 57 and 144; four per SIMD spill: 80
-// and 151. With a fixed share of the workgroups per queue, and the item read only when its turn came, 70 and 219.)
+// and 151. Three hold 168 registers, which the 16-bit instances use to the last one; none of them spills. With a fixed
+// share of the workgroups per queue, and the item read only when its turn came, 70 and 219.)
 constexpr int kTBlocks = 768;
 constexpr int kTCountStride = 32;  // ints between two queues' counters: a 128-byte line each
 
@@ -355,8 +356,10 @@ __global__ __launch_bounds__(256, 3) void k_temporal_dots(Geo g, const void* __r
       }
       wave_lds_fence();
       const float acc = rows16_sum(tb, lane);
-      const int ri = (lane >> 2) & 3, k = lane & 3, ee = __shfl(words, kTItemE + ri, 64);
-      if (lane < kFastRows && ri < it_n) {
+      int row_l = lane;  // (what is derived from it is worked out here: kept through the loop it does not fit the registers)
+      STTM_OPAQUE_V(row_l);
+      const int ri = (row_l >> 2) & 3, k = row_l & 3, ee = __shfl(words, kTItemE + ri, 64);
+      if (row_l < kFastRows && ri < it_n) {
         const int c0 = ee & 1023, y = c0 / W + (k >> 1), x = c0 % W + (k & 1);
         const bool both_block = ((ee >> 10) & 3) == 3;
         if (y < H && x < W && (k == 0 || !both_block)) out[y * W + x] = acc;
@@ -413,8 +416,10 @@ __global__ __launch_bounds__(256, 3) void k_temporal_dots(Geo g, const void* __r
       float s16 = s4;  // lanes 0, 2, 8, 10 hold the four 2x2 sums
       s16 = (s16 + __shfl_down(s16, 2, 64)) + (__shfl_down(s16, 8, 64) + __shfl_down(s16, 10, 64));
       const int lf = __shfl_down(words, kTItemE, 64);  // level of the other frame's node at the lane's cell
-      if (lane < 16) {
-        const int dy = lane >> 2, dx = lane & 3, y = y0 + dy, x = x0 + dx;
+      int cell_l = lane;  // (as above)
+      STTM_OPAQUE_V(cell_l);
+      if (cell_l < 16) {
+        const int dy = cell_l >> 2, dx = cell_l & 3, y = y0 + dy, x = x0 + dx;
         if (y < H && x < W) {
           const int cb = y * W + x;
           if (lf == 0) out[cb] = cd;

@@ -2,6 +2,7 @@
 import ctypes
 import os
 import re
+import struct
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -35,3 +36,43 @@ def test_host_side_geometry_helpers():
     assert b.sttm_workspace_bytes(1, 8, 8, 8, 64, b.STTM_F32, 1) > 0
     assert b.sttm_workspace_bytes(1, 8, 8, 8, 60, b.STTM_F32, 1) == 0     # D % 8
     assert b.sttm_workspace_bytes(1, 8, 8, 8, 64, 7, 1) == 0
+
+
+def _kernel_metadata(path):
+    """The metadata of every kernel in a library built by hipcc: its offload bundles, the code objects in them, the
+    AMDGPU metadata note (type 32, MessagePack) of each."""
+    import msgpack
+    blob, magic, kernels = open(path, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", []
+    for m in re.finditer(magic, blob):
+        at = m.start() + len(magic)
+        count, = struct.unpack_from("<Q", blob, at)
+        at += 8
+        for _ in range(count):
+            off, size, n = struct.unpack_from("<QQQ", blob, at)
+            triple = blob[at + 24:at + 24 + n]
+            at += 24 + n
+            elf = blob[m.start() + off:m.start() + off + size]
+            if not triple.endswith(b"gfx950"):
+                continue
+            phoff, = struct.unpack_from("<Q", elf, 0x20)
+            phsize, phnum = struct.unpack_from("<HH", elf, 0x36)
+            for i in range(phnum):
+                kind, _, start, _, _, length = struct.unpack_from("<IIQQQQ", elf, phoff + i * phsize)
+                while kind == 4 and length >= 12:      # PT_NOTE
+                    namesz, descsz, note = struct.unpack_from("<III", elf, start)
+                    desc = start + 12 + (namesz + 3) // 4 * 4
+                    if note == 32:
+                        kernels += msgpack.unpackb(elf[desc:desc + descsz])["amdhsa.kernels"]
+                    step = desc + (descsz + 3) // 4 * 4 - start
+                    start, length = start + step, length - step
+    return kernels
+
+
+def test_no_kernel_uses_scratch_memory():
+    """Spilled vector registers or indexed private arrays: a trip to memory in the middle of a kernel, and scratch memory
+    that the runtime has to allocate behind the library's back."""
+    from paper_2507_07990_amd import binding
+    kernels = _kernel_metadata(binding.LIB_PATH)
+    assert len(kernels) > 50
+    assert {k[".name"]: k[".private_segment_fixed_size"] for k in kernels
+            if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]} == {}
