@@ -634,7 +634,11 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
 // Up to this many workgroups (units x chunks x frames) of k_pyramid_stats the pass is given to k_pyramid_tiles. The chip
 // holds 2048 of them at a time, and the two kernels cost the same at about two and a half fillings (5040 workgroups, 180
 // frames of 14x14 at D = 3584: 63.3 against 62.8 us; 2700: 42.8 against 35.5; 14336: 161 against 163).
-constexpr long long kPyrTilesMax = 4096;
+// (The host-thread build of the tests sets 0, for k_pyramid_stats on inputs that are small enough for it.)
+#ifndef STTM_PYR_TILES_MAX
+#define STTM_PYR_TILES_MAX 4096
+#endif
+constexpr long long kPyrTilesMax = STTM_PYR_TILES_MAX;
 
 template <int DT, int CC>
 static void launch_pyramid_dt(const Geo& g, const void* feats, float* part, float* nsum, SelState* sel, hipStream_t s) {

@@ -8,37 +8,37 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(os.path.dirname(HERE))
 CSRC = os.path.join(ROOT, "paper_2507_07990_amd", "csrc")
 LIB = os.path.join(HERE, "libsttm_cpu.so")
+LIB_LARGE = os.path.join(HERE, "libsttm_cpu_large.so")  # every input takes the pyramid kernel of the large ones
+LARGE = ["-DSTTM_PYR_TILES_MAX=0"]
 SOURCES = ["sttm_api.hip", "sttm_spatial.hip", "sttm_temporal.hip", "sttm_reduce.hip"]
-
-
 SANITIZE_EXE = os.path.join(HERE, "sanitize_run")
+SANITIZE_EXE_LARGE = os.path.join(HERE, "sanitize_run_large")
 
 
-def build_sanitized(verbose: bool = False) -> str:
+def _compile(flags, extra_sources, out, verbose):
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-pthread", "-I", HERE, "-I", CSRC, "-Wno-unknown-pragmas",
+           "-Wno-attributes"] + flags
+    for s in [os.path.join(CSRC, s) for s in SOURCES] + [os.path.join(HERE, s) for s in ["emul.cpp"] + extra_sources]:
+        cmd += ["-x", "c++", s]
+    cmd += ["-o", out]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True)
+    return out
+
+
+def build_sanitized(verbose: bool = False, large: bool = False) -> str:
     """tests/cpu_emul/sanitize_main.cpp and the library's sources in one executable, under AddressSanitizer and
     UndefinedBehaviorSanitizer (any report ends the run with a non-zero status)."""
-    cmd = ["g++", "-std=c++17", "-O1", "-g", "-pthread", "-I", HERE, "-I", CSRC, "-Wno-unknown-pragmas", "-Wno-attributes",
-           "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer"]
-    for s in SOURCES:
-        cmd += ["-x", "c++", os.path.join(CSRC, s)]
-    cmd += ["-x", "c++", os.path.join(HERE, "emul.cpp"), "-x", "c++", os.path.join(HERE, "sanitize_main.cpp"),
-            "-o", SANITIZE_EXE]
-    if verbose:
-        print(" ".join(cmd))
-    subprocess.run(cmd, check=True)
-    return SANITIZE_EXE
+    flags = ["-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer"]
+    return _compile(flags + (LARGE if large else []), ["sanitize_main.cpp"],
+                    SANITIZE_EXE_LARGE if large else SANITIZE_EXE, verbose)
 
 
-def build(verbose: bool = False) -> str:
-    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fPIC", "-shared", "-pthread", "-I", HERE, "-I", CSRC,
-           "-Wno-unknown-pragmas", "-Wno-attributes"]
-    for s in SOURCES:
-        cmd += ["-x", "c++", os.path.join(CSRC, s)]
-    cmd += ["-x", "c++", os.path.join(HERE, "emul.cpp"), "-o", LIB]
-    if verbose:
-        print(" ".join(cmd))
-    subprocess.run(cmd, check=True)
-    return LIB
+def build(verbose: bool = False, large: bool = False) -> str:
+    # (two of these live in one process: -fno-gnu-unique keeps the statics of their template functions apart)
+    return _compile(["-fPIC", "-shared", "-fno-gnu-unique"] + (LARGE if large else []), [], LIB_LARGE if large else LIB,
+                    verbose)
 
 
 if __name__ == "__main__":

@@ -19,18 +19,19 @@ class Result:
 
 def _aligned(nbytes, align=256, garbage=False):
     raw = np.zeros(nbytes + align, dtype=np.uint8)
-    if garbage:  # device memory is not zero-initialised: make reads of never-written words visible
-        raw[:] = np.random.default_rng(12345).integers(0, 256, size=raw.size, dtype=np.uint8)
     off = (-raw.ctypes.data) % align
-    return raw[off:off + nbytes]
+    view = raw[off:off + nbytes]
+    if garbage:  # device memory is not zero-initialised: make reads of never-written words visible (the same in every run)
+        view[:] = np.random.default_rng(12345).integers(0, 256, size=nbytes, dtype=np.uint8)
+    return view
 
 
 def _p(a):
     return C.c_void_p(a.ctypes.data) if a is not None else None
 
 
-def load():
-    lib = C.CDLL(LIB)
+def load(path=LIB):
+    lib = C.CDLL(path)
     lib.sttm_workspace_bytes.restype = C.c_size_t
     lib.sttm_last_error.restype = C.c_char_p
     lib.sttm_last_error.argtypes = [C.c_void_p]

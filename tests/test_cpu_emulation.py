@@ -2,6 +2,7 @@
 
 Not a product path: the stand-in runs one OS thread per GPU thread so that the control flow, indexing and
 synchronisation of the kernels can be exercised (and debugged with host tools) where there is no GPU."""
+import ctypes
 import math
 import shutil
 
@@ -122,34 +123,76 @@ def test_emulated_temporal_work_lists_at_their_largest(emul):
     P.check_reduce(feats, r, tm, False)
 
 
+@pytest.fixture(scope="module")
+def large(emul):
+    """The build in which every input takes the pyramid kernel of the large ones."""
+    from tests.cpu_emul import build_cpu
+    return emul[0].load(build_cpu.build(large=True))
+
+
+@pytest.mark.parametrize("seed,B,T,H,W,D,dtype,kw", [
+    (90, 1, 3, 8, 8, 16, "f32", dict(tau_s=0.8, tau_t=0.8)),
+    (91, 2, 3, 5, 6, 24, "bf16", dict(keep=0.5)),
+    (92, 1, 2, 9, 9, 16, "bf16", dict(tau_s=0.2, tau_t=0.2, cell_dots=0)),
+    (93, 1, 3, 8, 8, 24, "f16", dict(tau_s=0.7, tau_t=0.7, cell_dots=2)),
+    (94, 1, 2, 17, 18, 16, "f32", dict(tau_s=0.3, tau_t=0.3)),
+    (97, 1, 2, 14, 14, 24, "bf16", dict(tau_s=0.8, tau_t=0.7, root_grid=4, cell_dots=2)),
+    (98, 1, 3, 9, 7, 520, "bf16", dict(tau_s=0.95, tau_t=0.6)),     # a second chunk with one live lane
+    (88, 3, 1, 13, 11, 24, "f16", dict(tau_s=0.6, tau_t=0.6)),      # single images: a three-dimensional grid
+])
+def test_emulated_pyramid_kernel_of_large_inputs(emul, large, seed, B, T, H, W, D, dtype, kw):
+    """Inputs that a host-thread run can afford take k_pyramid_tiles; here k_pyramid_stats works on them instead: parity
+    with the oracle, and every table and output the same bit for bit as from the other kernel. (What a table holds where
+    nothing is defined is the workspace's filling, the same in both.)"""
+    run_cpu, fake = emul
+    small = run_cpu.load()
+    feats = wl.generate(_variant(seed, B, T, H, W, D, dtype))
+    r = []
+    for lib, kernel, other in ((large, b"k_pyramid_stats", b"k_pyramid_tiles"), (small, b"k_pyramid_tiles", b"k_pyramid_stats")):
+        grid = (ctypes.c_uint * 3)()
+        lib.hip_emul_last_grid(None, None)
+        r.append(run_cpu.run_cpu(feats, lib=lib, **kw))
+        assert lib.hip_emul_last_grid(kernel, grid) and not lib.hip_emul_last_grid(other, grid)
+    oracle_kw = {k: v for k, v in kw.items() if k != "cell_dots"}
+    P.check_parity(fake, feats, r[0], **oracle_kw)
+    for name, a in vars(r[0]).items():
+        if isinstance(a, np.ndarray):
+            np.testing.assert_array_equal(a, getattr(r[1], name), err_msg=name)
+
+
 def test_emulated_kernels_run_clean_under_address_and_undefined_behaviour_sanitizers():
     """The host-thread build with -fsanitize=address,undefined (any report aborts): both dtypes, fixed thresholds and
-    a budget, every output in a heap block of its exact size, the workspace of exactly sttm_workspace_bytes()."""
+    a budget, every output in a heap block of its exact size, the workspace of exactly sttm_workspace_bytes(); once
+    with the pyramid kernel of small inputs and once with that of large ones."""
     import subprocess
+    from concurrent.futures import ThreadPoolExecutor
     from tests.cpu_emul import build_cpu
-    exe = build_cpu.build_sanitized()
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
-    assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
-    assert r.stdout.count("case ") == 2
-    assert "runtime error" not in r.stderr and "AddressSanitizer" not in r.stderr
+
+    def one(is_large):
+        return subprocess.run([build_cpu.build_sanitized(large=is_large)], capture_output=True, text=True, timeout=600)
+
+    with ThreadPoolExecutor(2) as pool:
+        for r in pool.map(one, (False, True)):
+            assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
+            assert r.stdout.count("case ") == 2
+            assert "runtime error" not in r.stderr and "AddressSanitizer" not in r.stderr
 
 
 def test_emulated_contexts_leave_the_runtime_alone_when_they_go(emul):
     """Destroying a context must not call the runtime's host allocator: outside the relaxed capture mode that ends a
     stream capture running on any other stream, and a free waits for the work of every context. A block goes to the
     next context instead; of many idle ones only a bounded number is kept, the rest freed in the relaxed mode."""
-    import ctypes as C
     lib = emul[0].load()
-    lib.sttm_destroy.argtypes = [C.c_void_p]
+    lib.sttm_destroy.argtypes = [ctypes.c_void_p]
 
     def pinned():
-        out = (C.c_int * 3)()
+        out = (ctypes.c_int * 3)()
         lib.hip_emul_pinned(out)
         return list(out)
 
     def create(n):
-        hs = [C.c_void_p() for _ in range(n)]
-        assert all(lib.sttm_create(C.byref(h), 0, None) == 0 for h in hs)
+        hs = [ctypes.c_void_p() for _ in range(n)]
+        assert all(lib.sttm_create(ctypes.byref(h), 0, None) == 0 for h in hs)
         return hs
 
     def destroy(hs):
@@ -171,12 +214,11 @@ def test_emulated_pyramid_grid_without_frame_pairs_has_no_idle_workgroups(emul, 
     """Where no two workgroups share rows (single images, frame-to-frame products off) the pass is numbered plainly: as
     many workgroups as there are (frame, unit, chunk) triples, which the hardware deals to all dies in turn. A grid laid
     out in one range of frames per die would put a single image on one of the eight."""
-    import ctypes as C
     run_cpu, _ = emul
     H, W, D = 9, 10, 72                                # 4 units of 8x8, fp32: one chunk of 64 x 4 channels
     lib = run_cpu.load()
     lib.hip_emul_last_grid(None, None)
     run_cpu.run_cpu(wl.generate(_variant(89, B, T, H, W, D, "f32")), tau_s=0.5, tau_t=0.5, cell_dots=cell_dots, lib=lib)
-    grid = (C.c_uint * 3)()
+    grid = (ctypes.c_uint * 3)()
     assert lib.hip_emul_last_grid(b"k_pyramid", grid)
     assert grid[0] * grid[1] * grid[2] == B * T * 4
