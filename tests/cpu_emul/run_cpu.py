@@ -39,7 +39,9 @@ def load(path=LIB):
 
 
 def run_cpu(feats, *, tau_s=None, tau_t=None, keep=None, root_grid=1, out_dtype=None, lib=None, use_nodes=True,
-            match=0, order=0, positions=False, defer_tau=False, cell_dots=1, node_map_override=None):
+            match=0, order=0, positions=False, defer_tau=False, cell_dots=1, node_map_override=None, again=False):
+    """again: every call with thresholds is repeated without, i.e. with those that the first one left in the workspace (the
+    first one's results are kept in `first`)."""
     lib = lib or load()
     B, T, H, W, D = feats.shape
     dt = STTM_BF16 if feats.dtype == np.uint16 else (STTM_F16 if feats.dtype == np.float16 else STTM_F32)
@@ -56,6 +58,8 @@ def run_cpu(feats, *, tau_s=None, tau_t=None, keep=None, root_grid=1, out_dtype=
     chk(lib.sttm_set_cell_dots(h, cell_dots))
     need = lib.sttm_workspace_bytes(B, T, H, W, D, dt, root_grid)
     ws = _aligned(need, garbage=True)
+    if again:  # a threshold that is not there reads as NaN: it would split everything and link nothing
+        ws[:] = 255
     chk(lib.sttm_set_workspace(h, _p(ws), C.c_size_t(need)))
     x = _aligned(feats.nbytes, 16)
     x[:] = np.ascontiguousarray(feats).view(np.uint8).reshape(-1)
@@ -75,6 +79,10 @@ def run_cpu(feats, *, tau_s=None, tau_t=None, keep=None, root_grid=1, out_dtype=
     else:
         chk(lib.sttm_spatial_quadtree(h, _p(x), dt, B, T, H, W, D, root_grid, farr(tau_s), _p(node_map),
                                       _p(node_level)))
+        if again:
+            r.first = [node_map.copy(), node_level.copy()]
+            node_map[:], node_level[:] = -1, 77
+            chk(lib.sttm_spatial_quadtree(h, _p(x), dt, B, T, H, W, D, root_grid, None, _p(node_map), _p(node_level)))
     lib.sttm_nodes_per_frame.restype = C.c_int
     NN = lib.sttm_nodes_per_frame(H, W, root_grid)
     tbl = np.zeros(B * T * NN, np.float32)
@@ -95,6 +103,10 @@ def run_cpu(feats, *, tau_s=None, tau_t=None, keep=None, root_grid=1, out_dtype=
         chk(lib.sttm_temporal_merge(h, _p(x), _p(node_map), _p(node_level), None, _p(cluster)))
     else:
         chk(lib.sttm_temporal_merge(h, _p(x), _p(node_map), _p(node_level), farr(tau_t), _p(cluster)))
+        if again:
+            r.first.append(cluster.copy())
+            cluster[:] = -1
+            chk(lib.sttm_temporal_merge(h, _p(x), _p(node_map), _p(node_level), None, _p(cluster)))
     t32 = np.zeros(N, np.float32)
     chk(lib.sttm_export(h, 3, _p(t32), C.c_size_t(t32.nbytes)))
     r.pair_sim = t32.copy()

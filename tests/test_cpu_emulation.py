@@ -93,6 +93,18 @@ def test_emulated_temporal_pass_without_the_cell_dot_products(emul, kw):
     P.check_parity(fake, feats, a, **kw)
 
 
+@pytest.mark.parametrize("B", [2, 33])
+def test_emulated_thresholds_named_by_the_caller_stay_for_later_calls(emul, B):
+    """As a launch argument (up to 32) or copied: a later call without thresholds finds every video's own."""
+    run_cpu, _ = emul
+    feats = wl.generate(_variant(87, B, 2, 2, 4, 8, "f32"))
+    rng = np.random.default_rng(B)
+    r = run_cpu.run_cpu(feats, tau_s=rng.uniform(-0.5, 0.7, B), tau_t=rng.uniform(-0.5, 0.5, B), again=True)
+    for a, b in zip(r.first, (r.node_map, r.node_level, r.cluster_ids)):
+        assert (a == b.reshape(-1)).all()
+    assert (r.node_level > 0).any() and (r.cluster_ids != r.node_map).any()
+
+
 def _uniform_partition(T, H, W, levels):
     """Node map and levels of a video whose frame t consists of the aligned blocks of level levels[t] only."""
     nm = np.empty((1, T, H, W), np.int32)

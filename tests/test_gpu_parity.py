@@ -759,15 +759,25 @@ def test_thresholds_in_and_out_at_every_way_they_travel(lib, B):
     def one(v, ts, tt, kp):
         b, n = v.shape[0], v.shape[0] * T * H * W
         s = lib.Sttm(0)
-        s.ensure_workspace(b, T, H, W, D, lib.STTM_F32)
+        # (a threshold that was never left in the workspace reads as NaN there: it would split everything, link nothing)
+        s.sttm_set_workspace(torch.full((lib.sttm_workspace_bytes(b, T, H, W, D, lib.STTM_F32),), 255, dtype=torch.uint8,
+                                        device="cuda:0"))
         node_map = torch.empty(n, dtype=torch.int32, device="cuda:0")
         level = torch.empty(n, dtype=torch.uint8, device="cuda:0")
         cluster, out_ids, counts = (torch.zeros(n, dtype=torch.int32, device="cuda:0") for _ in range(3))
         merged, offsets = torch.empty(n, D, device="cuda:0"), torch.empty(b + 1, dtype=torch.int64, device="cuda:0")
         s.sttm_spatial_quadtree(v, lib.STTM_F32, b, T, H, W, D, 1, ts, node_map, level)
+        first = node_map.clone(), level.clone()
+        node_map.fill_(-1), level.fill_(77)
         s.sttm_spatial_quadtree(v, lib.STTM_F32, b, T, H, W, D, 1, None, node_map, level)   # the thresholds of the last call
+        assert torch.equal(node_map, first[0]) and torch.equal(level, first[1])
         s.sttm_temporal_merge(v, node_map, level, tt, cluster)
         fixed = cluster.view(b, -1).clone()
+        cluster.fill_(-1)
+        s.sttm_temporal_merge(v, node_map, level, None, cluster)                            # the same in the temporal stage
+        assert torch.equal(cluster.view(b, -1), fixed)
+        if b > 1:                                          # (thresholds that differ from NaN's in what they do)
+            assert bool((level > 0).any()) and bool((cluster != node_map).any())
         K = s.sttm_reduce(v, cluster, node_map, level, lib.STTM_F32, n, merged, counts, out_ids, offsets)
         assert K == int(offsets[b]) and K == int((cluster == torch.arange(n, device="cuda:0")).sum())
         found = [s.sttm_budget_threshold(lib.STTM_STAGE_SPATIAL, kp)]
