@@ -302,11 +302,7 @@ int bind_shape(sttm_ctx* c, int dtype, int B, int T, int H, int W, int D, int ro
   c->have_spatial = c->have_tau_s = c->have_temporal = c->have_tau_t = false;
   c->tau_s_pending = c->tau_t_pending = false;
   c->cluster_ids_reduced = nullptr;
-  if (!same) {
-    c->target_s_on_device = c->target_t_on_device = false;  // the layout moved: upload targets again
-    // the work queue of the temporal pass starts empty (afterwards every pass leaves it empty behind itself)
-    STTM_HIP(c, hipMemsetAsync(at<int>(c, c->lay.tcount), 0, temporal_count_bytes(), c->stream));
-  }
+  if (!same) c->target_s_on_device = c->target_t_on_device = false;  // the layout moved: upload targets again
   return STTM_OK;
 }
 
@@ -360,7 +356,7 @@ int run_spatial_stats(sttm_ctx* c, const void* feats) {
                           at<float>(c, c->lay.nrm2),
                           at<float>(c, c->lay.sim),
                           at<float>(c, c->lay.m), at<uint32_t>(c, c->lay.sel_key_s), at<uint8_t>(c, c->lay.sel_w_s),
-                          at<SelState>(c, c->lay.sel_s), c->stream);
+                          at<SelState>(c, c->lay.sel_s), at<int>(c, c->lay.tcount), c->stream);
   int rc = after_launch(c);
   if (rc == STTM_OK) {
     c->sel_s_dirty = false;

@@ -438,9 +438,17 @@ __device__ inline float sel_last_digit(const SelState* __restrict__ st) {
 // 2 = and S_n(t) . S_n(t+1) of every 2x2 and 4x4 block n.
 void launch_pyramid_stats(const Geo& g, const void* feats, int cell_dots, float* part, float* nsum, SelState* sel,
                           hipStream_t s);
+// The counters of the temporal pass's work queues. They are empty when the pass begins: the spatial stage clears them, and
+// so does the pass itself when it is over. (Not by a memset when a shape is bound: one recorded into a graph has given
+// wrong results on replays, and a graph recorded later would count on memory that another shape may have used since.)
+constexpr int kTQueues = 64;
+constexpr int kTCountStride = 32;  // ints between two queues' counters: a 128-byte line each
+__device__ inline void temporal_clear(int* item_count, int tid) {
+  if (tid < kTQueues) item_count[tid * kTCountStride] = 0;
+}
 // Also works out the levels above an 8x8 unit from the stored unit sums (extends `nsum`).
 void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float* nrm2, float* sim, float* m,
-                             uint32_t* sel_key, uint8_t* sel_w, SelState* sel, hipStream_t s);
+                             uint32_t* sel_key, uint8_t* sel_w, SelState* sel, int* item_count, hipStream_t s);
 // Thresholds a caller has named, handed to the kernels that use them as a launch argument (n = 0: none). A copy from the
 // caller's memory to the device is a stream operation of its own: 2.5-5 us there and about as much on the host.
 constexpr int kTauArgs = 32;
@@ -464,8 +472,7 @@ inline size_t select_state_bytes(int B) { return (size_t)B * sizeof(SelState); }
 // `sel`: the temporal search states [B]; cleared here, level 0 filled by launch_temporal_resolve.
 // `skip_same`: 0 = every pair is computed here; 1 = pairs of two single cells are left out, 2 = also pairs of the same
 // 2x2 or 4x4 block in both frames (their dot products are in the spatial pass's `part`).
-// `items` (temporal_items_bytes() of them) / `item_count`: the work queue of the pass; the count must be zero on
-// entry (launch_temporal_resolve leaves it so).
+// `items` (temporal_items_bytes() of them) / `item_count`: the work queues of the pass (see temporal_clear).
 void launch_temporal_dots(const Geo& g, const void* feats, const uint8_t* node_level, const float* nsum,
                           int skip_same, float* pd_part, SelState* sel, void* items, int* item_count,
                           hipStream_t s);

@@ -771,7 +771,7 @@ __global__ __launch_bounds__(UP == 2 ? kFinThreadsWide : kFinThreads) void k_spa
                                                                   float* __restrict__ sim, float* __restrict__ m,
                                                                   uint32_t* __restrict__ sel_key,
                                                                   uint8_t* __restrict__ sel_w,
-                                                                  SelState* __restrict__ sel) {
+                                                                  SelState* __restrict__ sel, int* __restrict__ item_count) {
   STTM_DYNAMIC_LDS(float, sm);
   __shared__ unsigned h0[kSelBins];
   __shared__ __attribute__((aligned(16))) float red[UP ? kUpRows * kFinWaves : 1];
@@ -785,6 +785,7 @@ __global__ __launch_bounds__(UP == 2 ? kFinThreadsWide : kFinThreads) void k_spa
   int* s_pos = reinterpret_cast<int*>(s_m + g.NN);
   const int f = blockIdx.x;
   const size_t fo = (size_t)f * g.NN;
+  if (f == 0) temporal_clear(item_count, tid);
   {
     constexpr int kPieces = kUnitStats / 4;
     const float4* p4 = reinterpret_cast<const float4*>(part) + (size_t)f * g.nC * NU * (kUnitScalars / 4);
@@ -904,16 +905,16 @@ __global__ __launch_bounds__(UP == 2 ? kFinThreadsWide : kFinThreads) void k_spa
 }
 
 void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float* nrm2, float* sim, float* m,
-                             uint32_t* sel_key, uint8_t* sel_w, SelState* sel, hipStream_t s) {
+                             uint32_t* sel_key, uint8_t* sel_w, SelState* sel, int* item_count, hipStream_t s) {
   const int up = g.L < 4 ? 0 : (g.P == 16 ? 1 : 2);
   const int threads = up == 2 && g.F <= kFinWideFrames ? kFinThreadsWide : (g.NN <= 256 && !up ? 256 : kFinThreads);  // one node per thread where it fits
   const size_t lds = ((size_t)unit_cols(g) * unit_rows(g) * kUnitStats + 4 * (size_t)g.NN) * sizeof(float);
   if (up == 0)
-    hipLaunchKernelGGL(k_spatial_finalize<0>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel);
+    hipLaunchKernelGGL(k_spatial_finalize<0>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel, item_count);
   else if (up == 1)
-    hipLaunchKernelGGL(k_spatial_finalize<1>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel);
+    hipLaunchKernelGGL(k_spatial_finalize<1>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel, item_count);
   else
-    hipLaunchKernelGGL(k_spatial_finalize<2>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel);
+    hipLaunchKernelGGL(k_spatial_finalize<2>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel, item_count);
 }
 
 // ------------------------------------------------------------------------------------------------

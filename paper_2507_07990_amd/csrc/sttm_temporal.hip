@@ -73,7 +73,6 @@ static_assert(sizeof(TItem) == 48, "three 16-byte pieces");
 __host__ __device__ inline int temporal_items_per_pair(const Geo& g) { return g.P * g.P / 4 + g.P * g.P / 64 + 4; }
 constexpr int kFastRows = 16;
 constexpr int kBigNodes = 24;  // nodes at levels >= 3 of a 32x32 grid: 16 + 4 + 1
-constexpr int kTQueues = 64;
 constexpr int kTItemWords = 24, kTItemE = 6;  // 16-bit words of an item; the first of the e[]
 // Workgroups of the feature pass at most: what the chip holds at three wavefronts per SIMD, so that all start at once
 // and share the list evenly. (Two per SIMD, 1024 workgroups: 67 us for 512 frames of 13x13 at D = 3584, half the tokens
@@ -81,7 +80,6 @@ constexpr int kTItemWords = 24, kTItemE = 6;  // 16-bit words of an item; the fi
 // and 151. Three hold 168 registers, which the 16-bit instances use to the last one; none of them spills. With a fixed
 // share of the workgroups per queue, and the item read only when its turn came, 70 and 219.)
 constexpr int kTBlocks = 768;
-constexpr int kTCountStride = 32;  // ints between two queues' counters: a 128-byte line each
 
 __host__ __device__ inline int temporal_queue_items(const Geo& g) {
   return ((g.F + kTQueues - 1) / kTQueues) * temporal_items_per_pair(g);
@@ -551,7 +549,7 @@ __global__ __launch_bounds__(256) void k_temporal_resolve(Geo g, int match, int 
   __shared__ unsigned ekey[1024];
   __shared__ unsigned h0[kSelBins];
   const int f = blockIdx.x, HW = g.HW, W = g.W;
-  if (f == 0 && threadIdx.x < kTQueues) item_count[threadIdx.x * kTCountStride] = 0;  // the feature pass is over: its queues are empty for the next one
+  if (f == 0) temporal_clear(item_count, threadIdx.x);  // the feature pass is over: its queues are empty for the next one
   if (f % g.T == 0) {
     for (int c = threadIdx.x; c < HW; c += blockDim.x) sel_key[(size_t)f * HW + c] = 0;
     return;

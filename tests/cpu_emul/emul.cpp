@@ -9,6 +9,7 @@ thread_local Wave* t_wave = nullptr;
 pthread_barrier_t g_block_bar;
 alignas(16) float g_dynamic_lds[40960];  // 160 KB, the LDS of one CU
 Pinned g_pinned;
+int g_memsets = 0;
 thread_local hipStreamCaptureMode t_capture_mode = hipStreamCaptureModeGlobal;
 
 static std::vector<std::pair<std::string, dim3>> g_launches;
@@ -70,3 +71,5 @@ extern "C" int hip_emul_last_grid(const char* kernel, unsigned grid[3]) {
     }
   return 0;
 }
+
+extern "C" int hip_emul_memsets() { return hip_emul::g_memsets; }  // hipMemsetAsync calls so far

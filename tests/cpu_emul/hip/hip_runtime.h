@@ -223,7 +223,12 @@ inline hipError_t hipHostFree(void* p) {
   free(p);
   return hipSuccess;
 }
-inline hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { memset(d, v, n); return hipSuccess; }
+namespace hip_emul { extern int g_memsets; }
+inline hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
+  ++hip_emul::g_memsets;
+  memset(d, v, n);
+  return hipSuccess;
+}
 inline hipError_t hipEventCreate(hipEvent_t* e) { *e = nullptr; return hipSuccess; }
 inline hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 inline hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }

@@ -234,3 +234,13 @@ def test_emulated_pyramid_grid_without_frame_pairs_has_no_idle_workgroups(emul, 
     grid = (ctypes.c_uint * 3)()
     assert lib.hip_emul_last_grid(b"k_pyramid", grid)
     assert grid[0] * grid[1] * grid[2] == B * T * 4
+
+
+def test_emulated_pass_issues_no_memset(emul):
+    """A memset recorded into a graph has given wrong results on replays after the first: whatever a caller may capture
+    clears memory in kernels, the work queues of the temporal pass on a new shape (its first call) among it."""
+    run_cpu, _ = emul
+    lib = run_cpu.load()
+    before = lib.hip_emul_memsets()
+    run_cpu.run_cpu(wl.generate(_variant(86, 1, 2, 3, 3, 8, "f32")), tau_s=0.5, tau_t=0.5, lib=lib)
+    assert lib.hip_emul_memsets() == before

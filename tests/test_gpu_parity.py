@@ -832,3 +832,54 @@ def test_contexts_come_and_go_while_another_stream_captures(lib):
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(want, got)) and int(got[3][B]) == r.K
+
+
+def test_whole_pass_replayed_from_a_graph(lib):
+    """A fixed-threshold pass captured on a context that has never run: every replay gives the eager result, with other
+    shapes processed by the same context, in the same workspace, between the replays."""
+    import torch
+    shape, other = (1, 6, 13, 11, 264), (2, 3, 9, 20, 72)
+    stream = torch.cuda.Stream()
+
+    def make(shape, seed):
+        B, T, H, W, D = shape
+        n = B * T * H * W
+        feats = wl.generate(_variant(seed, B, T, H, W, D, "bf16"))
+        x = torch.from_numpy(feats.view(np.int16)).to("cuda:0").view(torch.bfloat16)
+        out = [torch.zeros(n, dtype=torch.int32, device="cuda:0"), torch.zeros(n, dtype=torch.uint8, device="cuda:0"),
+               torch.zeros(n, dtype=torch.int32, device="cuda:0"), torch.zeros(n, D, dtype=torch.bfloat16, device="cuda:0"),
+               torch.zeros(n, dtype=torch.int32, device="cuda:0"), torch.zeros(n, dtype=torch.int32, device="cuda:0"),
+               torch.zeros(B + 1, dtype=torch.int64, device="cuda:0")]
+        return x, out
+
+    def run(ctx, shape, x, out):
+        node_map, level, cluster, merged, counts, out_ids, offsets = out
+        ctx.sttm_spatial_quadtree(x, lib.STTM_BF16, *shape, 1, [0.8], node_map, level)
+        ctx.sttm_temporal_merge(x, node_map, level, [0.8], cluster)
+        ctx.sttm_reduce(x, cluster, node_map, level, lib.STTM_BF16, len(cluster), merged, counts, out_ids, offsets,
+                        want_n=False)
+
+    need = max(lib.sttm_workspace_bytes(*s, lib.STTM_BF16) for s in (shape, other))
+    x, got = make(shape, 1)
+    y, spare = make(other, 2)
+    want = [t.clone() for t in got]
+    eager = lib.Sttm(0, stream_ptr=stream.cuda_stream)
+    eager.ensure_workspace(*shape, lib.STTM_BF16)
+    ctx = lib.Sttm(0, stream_ptr=stream.cuda_stream)
+    ctx.sttm_set_workspace(torch.full((need,), 255, dtype=torch.uint8, device="cuda:0"))
+    torch.cuda.synchronize()
+    run(eager, shape, x, want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        run(ctx, shape, x, got)
+    for _ in range(4):
+        run(ctx, other, y, spare)
+        for t in got:
+            t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(want, got))
+    K = int(want[6][-1])
+    assert 1 < K < len(want[2]) and bool((want[1] > 0).any())
