@@ -22,6 +22,9 @@
  *   - "host" pointers are ordinary host memory, read or written before the call returns.
  *   - all work is enqueued on the context's stream; calls return before the GPU finishes unless they
  *     hand a value back through a host pointer (documented per call), in which case they synchronise the stream.
+ *   - in a stream capture, explicit thresholds of up to 32 videos are recorded by value. With more videos, and for the
+ *     targets of a budget search, the recorded copy reads a buffer of the context again at every replay: such a graph
+ *     is replayed only while the context lives and has not been given other thresholds (targets) since.
  *   - feats is contiguous [B, T, H, W, D] (D fastest), B independent videos; tokens are addressed by the
  *     flat cell index i = ((b*T + t)*H + y)*W + x.  Requirements: 1 <= H, W <= 32; D % 8 == 0;
  *     B*T <= 65535 frames; B*T*H*W < 2^31; root_grid a power of two <= P, P = smallest power of two >= max(H, W).

@@ -11,14 +11,6 @@
 #define STTM_DYNAMIC_LDS(T, name) T* name = reinterpret_cast<T*>(hip_emul::g_dynamic_lds)
 #endif
 
-// Keeps the instruction scheduler from moving anything across this point (used where hoisting the next batch of
-// loads above the work on the current one would cost more registers than the overlap is worth).
-#ifndef STTM_HOST_EMULATION
-#define STTM_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
-#else
-#define STTM_SCHED_FENCE() ((void)0)
-#endif
-
 // A value in a scalar / vector register that the compiler must take as new from here on.
 #ifndef STTM_HOST_EMULATION
 #define STTM_OPAQUE_S(x) asm volatile("" : "+s"(x))

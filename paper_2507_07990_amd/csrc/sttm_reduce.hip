@@ -168,11 +168,6 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const int32_t* __res
   for (int d = tid; d < DIG; d += kSortThreads) hist[(size_t)b * DIG + d] = cnt[d];
 }
 
-__global__ __launch_bounds__(256) void k_fill_i32(int n, int32_t* __restrict__ p, int32_t v) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
 // Large inputs only: turns every column (digit) of hist[tile][digit] into its exclusive prefix over the
 // tiles and leaves the column total in tot[digit].
 __global__ __launch_bounds__(256) void k_sort_colscan(int nb, int DIG, int32_t* __restrict__ hist,

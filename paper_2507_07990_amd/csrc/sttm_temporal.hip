@@ -388,7 +388,7 @@ __global__ __launch_bounds__(256, 3) void k_temporal_dots(Geo g, const void* __r
           for (int v = 0; v < VEC; ++v) SA[v] += tv[v];
         }
       }
-      STTM_SCHED_FENCE();  // the second sixteen rows are asked for only now: 32 in flight cost a wavefront per SIMD
+      // (the compiler asks for these sixteen rows before it adds up the first sixteen: all 32 are in flight, and fit)
       {
         Raw rf[16];
 #pragma unroll
