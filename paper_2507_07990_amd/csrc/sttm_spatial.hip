@@ -443,7 +443,7 @@ __global__ __launch_bounds__(64, 2) void k_pyramid_stats(Geo g, const void* __re
 // workgroup: each reads its tile and, four rows at a time, the partner tile, the first eight partner rows requested with
 // the tile's own; the tiles' sums meet in LDS for the unit's sum. No row buffer for a next tile is needed, which leaves
 // three wavefronts per SIMD.
-// (8x8 tokens, 8 frames, D = 64, fp32: 22.4 -> 7.9 us; one image of 24x24, D = 1152: 18.4 -> 7.0; 64 frames of 16x16,
+// (8x8 tokens, 8 frames, D = 64, fp32: 22.4 -> 7.9 us; one image of 24x24, D = 1152: 18.4 -> 6.5; 64 frames of 16x16,
 // D = 1152: 26.2 -> 14.3; of 13x13, D = 3584: 29.1 -> 24.5. Where the chip is full the longer-lived wavefronts with their
 // prefetch are better: 512 frames of 13x13 161 against 163 us, 1024 of 27x27 at D = 1152 442 against 501, 180 of 18x24 at
 // D = 8192 354 against 372.)
