@@ -101,6 +101,45 @@ template <uint32_t LO, uint32_t HI>
 inline void opaque_pairs(uint32_t& lo, uint32_t& hi) { lo = LO; hi = HI; }
 #endif
 
+// ---- widening sums on the matrix cores ---------------------------------------------------------------------
+// S[0..3] += the four 16-bit channels a lane holds in two registers, as a product of the 4x4 identity with the lanes'
+// channels (v_mfma_f32_4x4x4_16b: sixteen products side by side, four lanes each; a lane's column is its own channels, and
+// row i of the result is its register i). One instruction on an otherwise idle pipe instead of four on the vector one; the
+// same bits for every finite input, subnormal ones included (4 x 10^6 random sums compared for either type). Where a value
+// is an infinity or a NaN, all four of the lane's sums are undefined.
+// `ident`: this lane's row of the identity (identity_row).
+#ifndef STTM_HOST_EMULATION
+typedef float sttm_sum4 __attribute__((ext_vector_type(4)));
+template <uint32_t ONE>
+__device__ inline uint2 identity_row() {
+  const unsigned i = threadIdx.x & 3;
+  return make_uint2(i == 0 ? ONE : (i == 1 ? ONE << 16 : 0u), i == 2 ? ONE : (i == 3 ? ONE << 16 : 0u));
+}
+__device__ inline sttm_sum4 widen_add_bf16(uint2 ident, uint32_t lo, uint32_t hi, sttm_sum4 s) {
+  typedef short quad __attribute__((ext_vector_type(4)));
+  return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(quad, ident), __builtin_bit_cast(quad, make_uint2(lo, hi)), s, 0, 0, 0);
+}
+__device__ inline sttm_sum4 widen_add_f16(uint2 ident, uint32_t lo, uint32_t hi, sttm_sum4 s) {
+  typedef _Float16 quad __attribute__((ext_vector_type(4)));
+  return __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(quad, ident), __builtin_bit_cast(quad, make_uint2(lo, hi)), s, 0, 0, 0);
+}
+#else
+struct sttm_sum4 {
+  float v[4];
+  float& operator[](int i) { return v[i]; }
+};
+template <uint32_t ONE>
+inline uint2 identity_row() { return make_uint2(0u, 0u); }
+inline sttm_sum4 widen_add_bf16(uint2, uint32_t lo, uint32_t hi, sttm_sum4 s) {
+  for (int i = 0; i < 4; ++i) s[i] += __uint_as_float((i < 2 ? lo : hi) >> 16 * (i & 1) << 16);
+  return s;
+}
+inline sttm_sum4 widen_add_f16(uint2, uint32_t lo, uint32_t hi, sttm_sum4 s) {
+  for (int i = 0; i < 4; ++i) s[i] += __half2float(__ushort_as_half((unsigned short)((i < 2 ? lo : hi) >> 16 * (i & 1))));
+  return s;
+}
+#endif
+
 // ---- feature row access: one lane owns `VEC` consecutive channels ------------------------------------
 template <int DT> struct Row;  // DT: 0 = f32, 1 = bf16, 2 = f16
 
@@ -119,6 +158,14 @@ template <> struct Row<0> {
   // S += the row's channels
   __device__ static inline void add_row(const Raw& r, float (&S)[4]) {
     S[0] += r.x; S[1] += r.y; S[2] += r.z; S[3] += r.w;
+  }
+  // S = the sum of four rows, added up in their order (`ident`: see identity_row; not needed here)
+  __device__ static inline uint2 ident() { return make_uint2(0u, 0u); }
+  __device__ static inline void sum4(uint2, const Raw* r, float (&S)[4]) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) S[v] = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) add_row(r[k], S);
   }
 };
 
@@ -151,6 +198,21 @@ template <> struct Row<1> {
       S[2 * j + 1] = dot2_bf16(w[j], khi, S[2 * j + 1]);
     }
   }
+  // S = the sum of four rows, added up in their order
+  __device__ static inline uint2 ident() { return identity_row<0x3f80u>(); }
+  __device__ static inline void sum4(uint2 ident, const Raw* r, float (&S)[8]) {
+    sttm_sum4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      lo = widen_add_bf16(ident, r[k].x, r[k].y, lo);
+      hi = widen_add_bf16(ident, r[k].z, r[k].w, hi);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      S[v] = lo[v];
+      S[v + 4] = hi[v];
+    }
+  }
 };
 
 template <> struct Row<2> {
@@ -176,6 +238,21 @@ template <> struct Row<2> {
     for (int j = 0; j < 4; ++j) {
       S[2 * j] = dot2_f16(w[j], klo, S[2 * j]);
       S[2 * j + 1] = dot2_f16(w[j], khi, S[2 * j + 1]);
+    }
+  }
+  // S = the sum of four rows, added up in their order
+  __device__ static inline uint2 ident() { return identity_row<0x3c00u>(); }
+  __device__ static inline void sum4(uint2 ident, const Raw* r, float (&S)[8]) {
+    sttm_sum4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      lo = widen_add_f16(ident, r[k].x, r[k].y, lo);
+      hi = widen_add_f16(ident, r[k].z, r[k].w, hi);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      S[v] = lo[v];
+      S[v + 4] = hi[v];
     }
   }
 };
@@ -204,6 +281,43 @@ __device__ inline void store_once(float4* p, const float4& v) {
 #else
 template <class T> inline T load_once(const T* p) { return *p; }
 template <class T> inline void store_once(T* p, const T& v) { *p = v; }
+#endif
+
+// A stretch of global memory with its length: a load beyond it gives zeros and fetches nothing, a store beyond it is
+// dropped, by the hardware's own check of every access against the length. Address = base + uniform + lane.
+#ifndef STTM_HOST_EMULATION
+typedef __amdgpu_buffer_rsrc_t Window;
+__device__ __forceinline__ Window make_window(const void* base, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+template <class Raw>
+__device__ __forceinline__ Raw window_load_once(Window w, unsigned lane_off, unsigned uniform_off) {
+  return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b128(w, (int)lane_off, (int)uniform_off, 2));  // (2: non-temporal)
+}
+__device__ __forceinline__ void window_store(Window w, unsigned lane_off, unsigned uniform_off, const float (&v)[1]) {
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), w, (int)lane_off, (int)uniform_off, 0);
+}
+__device__ __forceinline__ void window_store(Window w, unsigned lane_off, unsigned uniform_off, const float (&v)[2]) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 d = {__float_as_uint(v[0]), __float_as_uint(v[1])};
+  __builtin_amdgcn_raw_buffer_store_b64(d, w, (int)lane_off, (int)uniform_off, 0);
+}
+#else
+struct Window { char* base; unsigned bytes; };
+inline Window make_window(const void* base, unsigned bytes) {
+  return {static_cast<char*>(const_cast<void*>(base)), bytes};
+}
+template <class Raw>
+inline Raw window_load_once(const Window& w, unsigned lane_off, unsigned uniform_off) {
+  Raw r;
+  memset(&r, 0, sizeof r);
+  if ((uint64_t)lane_off + uniform_off + sizeof r <= w.bytes) memcpy(&r, w.base + uniform_off + lane_off, sizeof r);
+  return r;
+}
+template <int N>
+inline void window_store(const Window& w, unsigned lane_off, unsigned uniform_off, const float (&v)[N]) {
+  if ((uint64_t)lane_off + uniform_off + sizeof v <= w.bytes) memcpy(w.base + uniform_off + lane_off, v, sizeof v);
+}
 #endif
 
 __device__ inline uint32_t f32_to_f16_rne(float f) { return (uint32_t)__half_as_ushort(__float2half_rn(f)); }

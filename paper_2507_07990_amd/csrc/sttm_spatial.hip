@@ -1,6 +1,7 @@
 // Spatial stage (Sec. 3.2): pyramid sums, squared norms, parent-child cosine similarities, the
 // coarse-to-fine decision, and the budget-driven threshold for it.
 #include "sttm_dev.h"
+#include <type_traits>
 
 namespace sttm {
 
@@ -106,12 +107,10 @@ __device__ __forceinline__ float staged_row_sum(const float* tbs, int row) {
 // cells, which come straight from the packed rows (no element is widened for them). Rows of cells beyond the edge and
 // lanes beyond the last channel must be zero (tile_mask).
 template <int DT>
-__device__ __forceinline__ void block_stats(const typename Row<DT>::Raw* raw, float (&S1)[Row<DT>::VEC], float (&nd)[8]) {
+__device__ __forceinline__ void block_stats(uint2 ident, const typename Row<DT>::Raw* raw, float (&S1)[Row<DT>::VEC],
+                                            float (&nd)[8]) {
   typedef Row<DT> R;
-#pragma unroll
-  for (int v = 0; v < R::VEC; ++v) S1[v] = 0.f;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) R::add_row(raw[k], S1);
+  R::sum4(ident, raw, S1);
 #pragma unroll
   for (int k = 0; k < 4; ++k) nd[k] = R::dot(raw[k], raw[k]);  // (zero rows give zero)
   const float p01 = R::dot(raw[0], raw[1]), p02 = R::dot(raw[0], raw[2]), p03 = R::dot(raw[0], raw[3]);
@@ -120,67 +119,6 @@ __device__ __forceinline__ void block_stats(const typename Row<DT>::Raw* raw, fl
   nd[5] = (nd[1] + p01) + (p12 + p13);
   nd[6] = (nd[2] + p02) + (p12 + p23);
   nd[7] = (nd[3] + p03) + (p13 + p23);
-}
-
-// Sums and per-lane scalars of one tile: returns the tile's per-channel sum in S2 and stages the tile's scalars --
-// batch q1 (rows 8 q1 .. 8 q1 + 7): squared norms of the four cells of 2x2 block q1, then each cell . the block's
-// sum; p1[q1]: block sum . tile sum, left to the caller to stage (zero for cells and blocks beyond the edge).
-// The rows must be zero for cells beyond the edge and for lanes beyond the last channel (tile_mask).
-template <int DT>
-__device__ __forceinline__ void tile_stats(const typename Row<DT>::Raw (&raw)[16], float* tbs, int lane, int th, int tw,
-                                           float (&p1)[4], float (&S2)[Row<DT>::VEC],
-                                           float (&S1)[4][Row<DT>::VEC]) {
-  typedef Row<DT> R;
-  constexpr int VEC = R::VEC;
-#pragma unroll
-  for (int v = 0; v < VEC; ++v) S2[v] = 0.f;
-#pragma unroll
-  for (int q1 = 0; q1 < 4; ++q1) {
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) S1[q1][v] = 0.f;
-    if ((q1 >> 1) * 2 >= th || (q1 & 1) * 2 >= tw) continue;  // block beyond the edge (wave-uniform)
-    float nd[8];
-    block_stats<DT>(raw + q1 * 4, S1[q1], nd);
-    stage8(tbs, q1, lane, nd);
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) S2[v] += S1[q1][v];
-  }
-#pragma unroll
-  for (int q1 = 0; q1 < 4; ++q1) {
-    float d1 = 0.f;
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) d1 = fmaf(S1[q1][v], S2[v], d1);
-    p1[q1] = d1;
-  }
-}
-
-// Asks for 16 bytes per lane straight into LDS: lane l's piece lands at byte address lds_row + 16 l of the
-// workgroup's LDS (`lds_row` is the same in all lanes). No registers are involved; it completes in order with the
-// wavefront's other loads. Written as an instruction of its own (the register that carries the LDS address is
-// saved and put back) so that the compiler, which would wait for every load in flight at the next use of any loaded
-// register once it has seen such a request, goes on counting the ordinary loads exactly; the wavefront waits for
-// these rows itself (wait_loads_but) before it reads them.
-template <class Elem>
-__device__ __forceinline__ void load_row_to_lds(void* lds_base, int row_bytes, const Elem* src_lane, int lane) {
-#ifndef STTM_HOST_EMULATION
-  const unsigned dst = (unsigned)(size_t)(__attribute__((address_space(3))) void*)lds_base + (unsigned)row_bytes;
-  unsigned keep;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
-               : "=&s"(keep)
-               : "v"(src_lane), "s"(dst)
-               : "memory");
-#else
-  memcpy(static_cast<char*>(lds_base) + row_bytes + 16 * lane, src_lane, 16);
-#endif
-}
-
-// Waits until at most `newer` (0 or 16) of the wavefront's loads are still on their way (they complete in issue
-// order), and until its earlier LDS traffic is through.
-__device__ __forceinline__ void wait_loads_but(int newer) {
-#ifndef STTM_HOST_EMULATION
-  if (newer >= 16) asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)" ::: "memory");
-  else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-#endif
 }
 
 // Which (frame, unit, chunk) a workgroup of a 1-D grid works on; false = none. With the frame-to-frame dot products a
@@ -209,244 +147,12 @@ static unsigned pyramid_grid(const Geo& g) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// k_pyramid_stats: the one pass over the features of the spatial stage.
-//
-// One workgroup per (chunk, unit, frame) -- a 3-D grid, or a 1-D grid decoded die by die when the frame-to-frame dot
-// products are wanted (template parameter CC, see below); a workgroup is ONE wavefront that owns a "unit" = an 8x8
-// cell block (level 3) of one frame for one chunk of the token rows. Units at the ragged edge of the grid are
-// smaller, but every workgroup is a single wavefront, so the hardware dispatcher evens the load out. A lane owns VEC
-// consecutive channels, so all pyramid sums are private to the lane and only scalars are reduced across lanes:
-// three exchanges between lanes leave eight partial sums per scalar, which go through a small LDS area
-// ([scalar][8]) to the lane that adds them up.
-// The unit is walked quadrant by quadrant: 4 tiles (4x4, level 2) of 4 level-1 blocks of 4 cells. The row
-// loads of the next tile are issued before the current one is worked on; cells and blocks beyond the
-// grid's edge cost no arithmetic (the tests are wave-uniform) and no memory traffic (their loads hit a row
-// the tile has just fetched).
-// Scalars: the squared norm of every cell, and for every node below the root the dot product of its sum
-// with its parent's sum. (The squared norm of a parent is the sum of its children's dot products with it,
-// which the finalize kernel adds up.)
-// With CC the wavefront also needs each tile of the next frame, for x_c(t) . x_c(t+1) of the tile's cells (the dot
-// products the temporal stage needs where both frames keep single cells): its 16 rows are asked for straight into
-// LDS as soon as the tile's own rows have arrived -- no registers are held for them -- travel while the tile's
-// statistics are worked out, and are read back for the dot products.
-// Output: part[f][chunk][unit][kUnitScalars] = the workgroup's scalars, partial over this chunk's channels, written
-//         as one block: per tile 16 squared norms, 16 cell and 4 level-1 dot products (child sum . parent sum), then
-//         the 4 level-2 dot products, then per tile the 16 cell-to-cell dot products and the 4 + 1 of its blocks and
-//         itself (zeros without CC); the levels from 3 up are the finalize kernel's when the pyramid is taller than
-//         a unit;
-//         nsum[f][node - first level-3 node][D] = the per-channel sums of the level-3 nodes (fp32), which
-//         the later stages read instead of re-adding up to 64 token rows.
-// (Two wavefronts per SIMD asked for: the CC = 2 instances would otherwise take a few registers more than half the
-// file and run alone on their SIMD.)
-// ------------------------------------------------------------------------------------------------
-template <int DT, int CC>  // CC: 0 = statistics only, 1 = + cell-to-cell dot products, 2 = + the same for levels 1 and 2
-__global__ __launch_bounds__(64, 2) void k_pyramid_stats(Geo g, const void* __restrict__ feats_v,
-                                                         float* __restrict__ part, float* __restrict__ nsum,
-                                                         SelState* __restrict__ sel) {
-  typedef Row<DT> R;
-  constexpr int VEC = R::VEC;
-  __shared__ __attribute__((aligned(16))) float tbs[kStageRows * kStageStride];
-  __shared__ __attribute__((aligned(16))) float st[kUnitScalars];
-  __shared__ typename R::Raw pbuf[CC ? 16 * 64 : 1];  // the partner tile (the same tile of frame t + 1), as loaded
-  const int NU = unit_cols(g) * unit_rows(g), lane = threadIdx.x;
-  int chunk, u, f;
-  if (CC) {
-    if (!pyramid_place(g, NU, f, u, chunk)) return;
-  } else {
-    chunk = blockIdx.x;
-    u = blockIdx.y;
-    f = blockIdx.z;
-  }
-  const int ch0 = chunk * g.cch + lane * VEC;
-  const bool act = ch0 < g.D;
-  const int H = g.H, W = g.W, L = g.L;
-  const typename R::Elem* fbase =
-      reinterpret_cast<const typename R::Elem*>(feats_v) + (size_t)f * g.HW * g.D + (act ? ch0 : 0);
-  const int UX = (W + 7) >> 3;  // units per row that hold valid cells
-  const int y3 = (u / UX) * 8, x3 = (u % UX) * 8;
-  const int vh = min(8, H - y3), vw = min(8, W - x3);  // valid rows / columns of the unit
-
-  const bool has_next = CC && f % g.T != g.T - 1;
-  const typename R::Elem* nbase = has_next ? fbase + (size_t)g.HW * g.D : fbase;
-  typename R::Raw bufA[16], bufB[16];
-  tile_load<DT>(bufA, fbase, W, g.D, y3, x3, min(vh, 4), min(vw, 4));
-  if (chunk == 0 && u == 0 && f % g.T == 0) sel_clear(sel + f / g.T);  // this video's budget search starts afresh
-  float S3[VEC], S2[4][VEC];
-#pragma unroll
-  for (int v = 0; v < VEC; ++v) S3[v] = 0.f;
-#pragma unroll
-  for (int q2 = 0; q2 < 4; ++q2) {
-    const int th = max(0, min(4, vh - (q2 >> 1) * 4)), tw = max(0, min(4, vw - (q2 & 1) * 4));
-    const bool some = th > 0 && tw > 0;
-    // the tile's own rows are waited for here (nothing newer is in flight at this point); a full tile of a full
-    // chunk needs no masking
-    const bool ragged = th < 4 || tw < 4 || (chunk + 1) * g.cch > g.D;
-    if (some && ragged) tile_mask<DT>((q2 & 1) ? bufB : bufA, th, tw, act);
-    if (CC && has_next && some) {
-      // the partner tile, with the same clamping as the tile's own loads: sixteen requests, whatever the edge
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int q1 = i >> 2, k = i & 3;
-        const int dy = min((q1 >> 1) * 2 + (k >> 1), th - 1), dx = min((q1 & 1) * 2 + (k & 1), tw - 1);
-        load_row_to_lds(pbuf, i * 1024,
-                        nbase + (size_t)((y3 + (q2 >> 1) * 4 + dy) * W + x3 + (q2 & 1) * 4 + dx) * g.D, lane);
-      }
-    }
-    if (q2 < 3) {
-      // the next tile's rows fly while this one is worked on; a tile wholly beyond the edge reads the
-      // first tile again instead (nothing is done with it), so that the loads stay unconditional
-      const int n = q2 + 1;
-      const int nh = max(0, min(4, vh - (n >> 1) * 4)), nw = max(0, min(4, vw - (n & 1) * 4));
-      const bool none = nh == 0 || nw == 0;
-      tile_load<DT>((q2 & 1) ? bufA : bufB, fbase, W, g.D, none ? y3 : y3 + (n >> 1) * 4,
-                    none ? x3 : x3 + (n & 1) * 4, none ? 1 : nh, none ? 1 : nw);
-    }
-    if (some) {
-      float S1[4][VEC];  // the tile's 2x2 block sums
-      float b4[8];  // the blocks' dot products with the tile, then (CC = 2) with the same blocks of the next frame
-#pragma unroll
-      for (int i = 0; i < 8; ++i) b4[i] = 0.f;
-      {
-        float p1[4];
-        tile_stats<DT>((q2 & 1) ? bufB : bufA, tbs, lane, th, tw, p1, S2[q2], S1);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b4[i] = p1[i];
-      }
-      if (CC && has_next) {
-        // x_c(t) . x_c(t+1) for the tile's cells: where both frames keep single cells the temporal stage needs
-        // nothing else (Sec. 3.3 compares node features; a cell's feature is its own row).
-        wait_loads_but(q2 < 3 ? 16 : 0);  // the partner rows are there; the next tile's may still be on their way
-        float SN2[VEC];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) SN2[v] = 0.f;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          float cd[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) cd[i] = 0.f;
-#pragma unroll
-          for (int qq = 0; qq < 2; ++qq) {
-            const int q1 = h * 2 + qq;
-            if ((q1 >> 1) * 2 >= th || (q1 & 1) * 2 >= tw) continue;
-            typename R::Raw pr[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              pr[k] = pbuf[(q1 * 4 + k) * 64 + lane];
-              if (ragged) {  // (a clamped request repeated another cell; a lane beyond the last channel read channel 0)
-                const bool in = (q1 >> 1) * 2 + (k >> 1) < th && (q1 & 1) * 2 + (k & 1) < tw && act;
-                if (!in) pr[k] = R::zero();
-              }
-              cd[qq * 4 + k] = R::dot(((q2 & 1) ? bufB : bufA)[q1 * 4 + k], pr[k]);
-            }
-            if (CC >= 2) {
-              // The same for the tile's 2x2 blocks and for the tile itself: S_n(t) . S_n(t+1), what the temporal
-              // stage needs where both frames keep the same node n at level 1 or 2: the block's sum (kept from the
-              // tile's statistics) with the sum of the partner block's four rows, the tile's sum with the sum of
-              // the partner blocks.
-              float SN1[VEC], d1 = 0.f;
-#pragma unroll
-              for (int v = 0; v < VEC; ++v) SN1[v] = 0.f;
-#pragma unroll
-              for (int k = 0; k < 4; ++k) R::add_row(pr[k], SN1);
-#pragma unroll
-              for (int v = 0; v < VEC; ++v) {
-                d1 = fmaf(S1[q1][v], SN1[v], d1);
-                SN2[v] += SN1[v];
-              }
-              b4[4 + q1] = d1;
-            }
-          }
-          stage8(tbs, 5 + h, lane, cd);
-        }
-        if (CC >= 2) {
-          float t8[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) t8[i] = 0.f;
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) t8[0] = fmaf(S2[q2][v], SN2[v], t8[0]);
-          stage8(tbs, 7, lane, t8);
-        }
-      }
-      stage8(tbs, 4, lane, b4);
-      // row r of the staging area is added up by lane r and goes to its place in the unit's block (zero where the
-      // row stands for nothing: beyond the edge, above the root level, no next frame)
-      wave_lds_fence();
-      if (lane < 57) {
-        const int r = lane;
-        bool live;
-        int dst;
-        if (r < 32 || (r >= 40 && r < 56)) {  // a cell's row: norm, dot with its block, or with the next frame
-          const int q1 = r < 32 ? r >> 3 : (r - 40) >> 2, k = r & 3;
-          live = (q1 >> 1) * 2 + (k >> 1) < th && (q1 & 1) * 2 + (k & 1) < tw;
-          if (r < 32 && (r & 4)) live = live && 0 < L;
-          if (r >= 40) live = live && has_next;
-          dst = r < 32 ? q2 * kTileRows + ((r & 4) ? 16 : 0) + q1 * 4 + k : kUnitCellDots + q2 * 16 + (r - 40);
-        } else if (r < 40) {  // a 2x2 block's row: dot with the tile, or with the next frame
-          const int q1 = r & 3;
-          live = (q1 >> 1) * 2 < th && (q1 & 1) * 2 < tw;
-          live = live && (r < 36 ? 1 < L : (CC >= 2 && has_next));
-          dst = r < 36 ? q2 * kTileRows + 32 + q1 : kUnitNodeDots + q2 * 8 + q1;
-        } else {  // the tile with the next frame's
-          live = CC >= 2 && has_next;
-          dst = kUnitNodeDots + q2 * 8 + 4;
-        }
-        st[dst] = live ? staged_row_sum(tbs, r) : 0.f;
-      }
-      wave_lds_fence();
-    } else {
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) S2[q2][v] = 0.f;
-      if (lane < kTileRows) st[q2 * kTileRows + lane] = 0.f;
-      if (lane < 16) st[kUnitCellDots + q2 * 16 + lane] = 0.f;
-      if (lane < 5) st[kUnitNodeDots + q2 * 8 + lane] = 0.f;
-    }
-    if (lane >= 5 && lane < 8) st[kUnitNodeDots + q2 * 8 + lane] = 0.f;
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) S3[v] += S2[q2][v];
-  }
-  // level-2 dot products of the four tiles with the unit's sum
-  if (lane < kUnitCellDots - 4 * kTileRows) st[4 * kTileRows + lane] = 0.f;
-  if (L >= 3) {
-    float d2[8];
-#pragma unroll
-    for (int q2 = 0; q2 < 8; ++q2) d2[q2] = 0.f;
-#pragma unroll
-    for (int q2 = 0; q2 < 4; ++q2) {
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) d2[q2] = fmaf(S2[q2][v], S3[v], d2[q2]);
-    }
-    stage8(tbs, 0, lane, d2);
-    wave_lds_fence();
-    if (lane < 4) {
-      const int q2 = lane;
-      if ((q2 >> 1) * 4 < vh && (q2 & 1) * 4 < vw) st[4 * kTileRows + q2] = staged_row_sum(tbs, lane);
-    }
-    wave_lds_fence();
-    if (act) {
-      float* o = nsum + ((size_t)f * (g.NN - g.lvl_base[3]) + (y3 >> 3) * (g.P >> 3) + (x3 >> 3)) * g.D + ch0;
-#pragma unroll
-      for (int v = 0; v < VEC; v += 4)
-        *reinterpret_cast<float4*>(o + v) = make_float4(S3[v], S3[v + 1], S3[v + 2], S3[v + 3]);
-    }
-  }
-  // the workgroup's scalars leave in one piece: whole, aligned 128-byte lines that no other workgroup touches
-  wave_lds_fence();
-  if (lane < kUnitScalars / 4)
-    reinterpret_cast<float4*>(part + ((size_t)(f * g.nC + chunk) * NU + u) * kUnitScalars)[lane] =
-        reinterpret_cast<const float4*>(st)[lane];
-}
-
-// ------------------------------------------------------------------------------------------------
-// k_pyramid_tiles: the same pass for small inputs, with the same results bit for bit. A workgroup of k_pyramid_stats is
-// one wavefront that walks its four tiles one after the other, about 5 us each whatever else runs; with fewer of them
-// than the chip holds a few times over that chain is the pass. Here the four tiles of a unit are four wavefronts of one
-// workgroup: each reads its tile and, four rows at a time, the partner tile, the first eight partner rows requested with
-// the tile's own; the tiles' sums meet in LDS for the unit's sum. No row buffer for a next tile is needed, which leaves
-// three wavefronts per SIMD.
-// (8x8 tokens, 8 frames, D = 64, fp32: 22.4 -> 7.9 us; one image of 24x24, D = 1152: 18.4 -> 6.5; 64 frames of 16x16,
-// D = 1152: 26.2 -> 14.3; of 13x13, D = 3584: 29.1 -> 24.5. Where the chip is full the longer-lived wavefronts with their
-// prefetch are better: 512 frames of 13x13 161 against 163 us, 1024 of 27x27 at D = 1152 442 against 501, 180 of 18x24 at
-// D = 8192 354 against 372.)
+// k_pyramid_tiles: the same pass with a workgroup for every frame, the same results bit for bit: for small inputs, and
+// where no frame-to-frame products are wanted. The four tiles of a unit are four wavefronts: each reads its tile and, four
+// rows at a time, the partner tile (the same tile of the next frame), the first eight partner rows requested with the
+// tile's own; the tiles' sums meet in LDS for the unit's sum. Three wavefronts per SIMD.
+// (8 frames of 8x8 tokens, D = 64, fp32: 7.9 us; one image of 24x24, D = 1152: 5.9; 64 frames of 16x16, D = 1152: 15.6,
+// of 13x13, D = 3584: 23.6 and 28.2 by k_pyramid_stats.)
 // ------------------------------------------------------------------------------------------------
 template <int DT, int CC>  // CC: 0 = statistics only, 1 = + cell-to-cell dot products, 2 = + the same for levels 1 and 2
 __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __restrict__ feats_v,
@@ -495,6 +201,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
     // a full tile of a full chunk needs no masking
     const bool ragged = th < 4 || tw < 4 || (chunk + 1) * g.cch > g.D;
     if (ragged) tile_mask<DT>(raw, th, tw, act);
+    const uint2 ident = R::ident();
     float S1[4][VEC];  // the tile's 2x2 block sums
     float b4[8];  // the blocks' dot products with the tile, then (CC = 2) with the same blocks of the next frame
     float SN2[VEC], cd[8];
@@ -512,7 +219,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
       for (int k = 0; k < 4; ++k) cd[(q1 & 1) * 4 + k] = 0.f;
       if (live) {
         float nd[8];
-        block_stats<DT>(raw + q1 * 4, S1[q1], nd);
+        block_stats<DT>(ident, raw + q1 * 4, S1[q1], nd);
         stage8(tbs, q1, lane, nd);
 #pragma unroll
         for (int v = 0; v < VEC; ++v) S2[v] += S1[q1][v];
@@ -532,10 +239,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
             // stage needs where both frames keep the same node n at level 1 or 2: the block's sum with the sum of the
             // partner block's four rows, the tile's sum with the sum of the partner blocks.
             float SN1[VEC], d1 = 0.f;
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) SN1[v] = 0.f;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) R::add_row(pr[q1 & 1][k], SN1);
+            R::sum4(ident, pr[q1 & 1], SN1);
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
               d1 = fmaf(S1[q1][v], SN1[v], d1);
@@ -631,9 +335,305 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
         reinterpret_cast<const float4*>(st)[threadIdx.x];
 }
 
-// Up to this many workgroups (units x chunks x frames) of k_pyramid_stats the pass is given to k_pyramid_tiles. The chip
-// holds 2048 of them at a time, and the two kernels cost the same at about two and a half fillings (5040 workgroups, 180
-// frames of 14x14 at D = 3584: 63.3 against 62.8 us; 2700: 42.8 against 35.5; 14336: 161 against 163).
+// ------------------------------------------------------------------------------------------------
+// k_pyramid_stats: the one pass over the features of the spatial stage, for videos that fill the chip.
+//
+// A workgroup owns a "unit" = an 8x8 cell block (level 3) for one chunk of the token rows, and walks through a run of
+// frames; its four wavefronts own the unit's four 4x4 tiles (level 2). A lane owns VEC consecutive channels, so all
+// pyramid sums are private to the lane and only scalars are reduced across lanes: three exchanges between lanes leave
+// eight partial sums per scalar, which go through a small LDS area ([scalar][8]) to the lane that adds them up.
+// Scalars: the squared norm of every cell, and for every node below the root the dot product of its sum
+// with its parent's sum. (The squared norm of a parent is the sum of its children's dot products with it,
+// which the finalize kernel adds up.) With CC also x_c(t) . x_c(t+1) of the cells (the dot products the temporal stage
+// needs where both frames keep single cells), with CC = 2 the same of the 2x2 blocks and of the tiles.
+// A row is read once: the next frame's rows, wanted for those products, are the next step's own. Six places of four rows
+// (one 2x2 block each) hold the frame's blocks and, two blocks ahead of the arithmetic, the next frame's; a block that is
+// done with gives its place to the one six further on, so that the places' roles come round every three frames, which are
+// written out one after the other. A cell beyond the edge, or a lane beyond the last channel, is beyond the window its
+// load is checked against and reads as zero without a request to memory; no load or store of the walk is under a
+// condition, so what is in flight is a compile-time fact and only the block that is needed is waited for. The tiles' sums
+// meet in LDS, two frames' worth of places: one barrier a frame.
+// Output: part[f][chunk][unit][kUnitScalars] = the workgroup's scalars, partial over this chunk's channels: per tile 16
+//         squared norms, 16 cell and 4 level-1 dot products (child sum . parent sum), then the 4 level-2 dot products,
+//         then per tile the 16 cell-to-cell dot products and the 4 + 1 of its blocks and itself (zeros without CC); the
+//         levels from 3 up are the finalize kernel's when the pyramid is taller than a unit;
+//         nsum[f][node - first level-3 node][D] = the per-channel sums of the level-3 nodes (fp32), which
+//         the later stages read instead of re-adding up to 64 token rows.
+// What bounds it: memory. 512 frames of 13x13 at D = 3584 in bf16, 653 MB read and 44 MB written in 145 us: 138 without
+// the arithmetic, 124 without the stores, 111 without either. 180 frames of 18x24 at D = 8192: 1.31 GB and 79 MB in 255 us
+// (5.4 TB/s). (A wavefront that took a unit's tiles one after the other and asked for the next frame's rows as well, from
+// the cache its neighbour had just filled: 168 and 325 us, 172 with CC = 2 on the former.) The loads are marked
+// non-temporal: 158 and 286 us without. Eight places and two wavefronts per SIMD: 147 and 313. Two or three rounds of
+// workgroups with shorter runs read more rows twice: 154 and 161 us.
+// ------------------------------------------------------------------------------------------------
+constexpr int kWalkSlots = 6, kWalkPeriod = 3;  // places of a block's rows; frames after which their roles are the same again
+// Workgroups of one round: three wavefronts per SIMD. While a run stays this many frames long (3 % of the rows read twice)
+// there are more rounds, which even out what ragged units need: 1024 frames of 27x27 at D = 1152, 416 us in one round and
+// 400 in two. (The host-thread build of the tests asks for few, so that it has runs of more than one frame.)
+#ifndef STTM_WALK_GROUPS
+#ifdef STTM_HOST_EMULATION
+#define STTM_WALK_GROUPS 2
+#else
+#define STTM_WALK_GROUPS 768
+#endif
+#endif
+constexpr int kWalkGroups = STTM_WALK_GROUPS, kWalkRounds = 3, kWalkLongRun = 32;
+static int walk_segments(const Geo& g) {
+  const long long columns = (long long)unit_cols(g) * unit_rows(g) * g.nC;
+  long long s = max(kWalkGroups / columns, min(kWalkRounds * kWalkGroups / columns, (long long)(g.F / kWalkLongRun)));
+  return (int)max(1ll, min(s, (long long)g.F));
+}
+
+// One scalar of the wavefront: row `row` of the staging area gets its eight partial sums, added up as group_sums8 does.
+__device__ __forceinline__ void stage1(float* tbs, int row, int lane, float v) {
+#ifndef STTM_HOST_EMULATION
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));  // quad_perm [1,0,3,2]
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));  // quad_perm [2,3,0,1]
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true)); // row_half_mirror
+#else
+  v += __shfl_xor(v, 1, 64);
+  v += __shfl_xor(v, 2, 64);
+  v += __shfl_xor(v, 4, 64);
+#endif
+  if ((lane & 7) == 0) tbs[row * kStageStride + (lane >> 3)] = v;
+}
+
+template <int DT, int CC>  // CC: 0 = statistics only, 1 = + cell-to-cell dot products, 2 = + the same for levels 1 and 2
+__global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __restrict__ feats_v,
+                                                          float* __restrict__ part, float* __restrict__ nsum,
+                                                          SelState* __restrict__ sel, int segs) {
+  typedef Row<DT> R;
+  typedef typename R::Raw Raw;
+  constexpr int VEC = R::VEC;
+  __shared__ __attribute__((aligned(16))) float stage[4][kStageRows * kStageStride];
+  __shared__ __attribute__((aligned(16))) float st[3][kUnitScalars];
+  __shared__ __attribute__((aligned(16))) float4 tsum[2][4][VEC / 4][64];  // the four tiles' sums
+  __shared__ float4 early[CC >= 2 ? 4 : 1][2][VEC / 4][64];  // sums of a tile's first two blocks, when registers are short
+  const int H = g.H, W = g.W, L = g.L;
+  const int UX = unit_cols(g), NU = UX * unit_rows(g), tid = threadIdx.x, lane = tid & 63;
+  int rest = blockIdx.x;
+  const int chunk = rest % g.nC;
+  rest /= g.nC;
+  const int u = rest % NU, seg = rest / NU;
+  const int f0 = (int)((long long)g.F * seg / segs), f1 = (int)((long long)g.F * (seg + 1) / segs);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // (which wavefront -- and so which SIMD -- gets which tile rotates: in a ragged unit the first tile is the fullest)
+  const int q2 = __builtin_amdgcn_readfirstlane(wave + u + seg + chunk) & 3;
+  float* tbs = stage[q2];
+  const int ch0 = chunk * g.cch + lane * VEC;
+  const int y3 = (u / UX) * 8, x3 = (u % UX) * 8;
+  const int ty = y3 + (q2 >> 1) * 4, tx = x3 + (q2 & 1) * 4;
+  const int th = max(0, min(4, H - ty)), tw = max(0, min(4, W - tx));  // valid rows / columns of the tile
+  if (chunk == 0 && u == 0)  // the budget searches of the videos that begin here start afresh
+    for (int b = (f0 + g.T - 1) / g.T; b * g.T < f1; ++b) sel_clear(sel + b);
+  for (int i = tid; i < 3 * kUnitScalars; i += 256) (&st[0][0])[i] = 0.f;
+  for (int i = tid; i < 2 * 4 * (VEC / 4) * 64; i += 256) (&tsum[0][0][0][0])[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  __syncthreads();
+
+  const unsigned row_bytes = (unsigned)g.D * (unsigned)sizeof(typename R::Elem), frame_bytes = row_bytes * (unsigned)g.HW;
+  const unsigned voff = ch0 < g.D ? (unsigned)ch0 * (unsigned)sizeof(typename R::Elem) : frame_bytes;
+  // the channels of the unit's sum that this lane stores, and the first one's place in a tile's sum in LDS
+  const int own = (wave * 64 + lane) * (VEC / 4), pick = VEC == 4 ? own : ((own >> 2) & 1) * 256 + (own >> 3) * 4 + (own & 3);
+  const unsigned noff = (unsigned)(chunk * g.cch + own) * 4u;
+  unsigned soff[16];  // rows of the tile, wave-uniform; beyond the edge: past the window
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int q1 = i >> 2, k = i & 3, dy = (q1 >> 1) * 2 + (k >> 1), dx = (q1 & 1) * 2 + (k & 1);
+    soff[i] = dy < th && dx < tw ? (unsigned)((ty + dy) * W + tx + dx) * row_bytes : frame_bytes;
+  }
+  // the last frame whose rows are needed: one past the run, if it belongs to the same video
+  const int flast = CC && f1 < g.F && f1 % g.T != 0 ? f1 : f1 - 1;
+  // where the frame being worked on is: its scalars and its unit's sum; the next frame's rows, those of the one after it
+  // (never beyond flast: the loads are issued whatever they are for); how many frames of the video come after it
+  float* part_f = part + ((size_t)(f0 * g.nC + chunk) * NU + u) * kUnitScalars;
+  const size_t part_step = (size_t)g.nC * NU * kUnitScalars, nsum_step = (size_t)(g.NN - g.lvl_base[3]) * g.D;
+  float* nsum_f = nsum + (size_t)f0 * nsum_step + (size_t)((y3 >> 3) * (g.P >> 3) + (x3 >> 3)) * g.D;
+  const char* rows0 = reinterpret_cast<const char*>(feats_v) + (size_t)f0 * frame_bytes;
+  const char* rows1 = rows0 + (f0 + 1 <= flast ? frame_bytes : 0u);
+  const char* rows2 = rows1 + (f0 + 2 <= flast ? frame_bytes : 0u);
+  int after = g.T - 1 - f0 % g.T;
+  auto load_block = [&](Raw (&dst)[4], const Window& w, int q1) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dst[k] = window_load_once<Raw>(w, voff, soff[q1 * 4 + k]);
+  };
+  // what lane r < 57 adds up: row r of the staging area, and where it goes
+  const int r = lane;
+  bool live = false;
+  int dst = kUnitNodeDots + q2 * 8 + 4;
+  if (r < 32 || (r >= 40 && r < 56)) {  // a cell's row: norm, dot with its block, or with the next frame
+    const int q1 = r < 32 ? r >> 3 : (r - 40) >> 2, k = r & 3;
+    live = (q1 >> 1) * 2 + (k >> 1) < th && (q1 & 1) * 2 + (k & 1) < tw;
+    if (r < 32 && (r & 4)) live = live && 0 < L;
+    dst = r < 32 ? q2 * kTileRows + ((r & 4) ? 16 : 0) + q1 * 4 + k : kUnitCellDots + q2 * 16 + (r - 40);
+  } else if (r < 40) {  // a 2x2 block's row: dot with the tile, or with the next frame
+    const int q1 = r & 3;
+    live = (q1 >> 1) * 2 < th && (q1 & 1) * 2 < tw;
+    live = live && (r < 36 ? 1 < L : CC >= 2);
+    dst = r < 36 ? q2 * kTileRows + 32 + q1 : kUnitNodeDots + q2 * 8 + q1;
+  } else {  // the tile with the next frame's
+    live = CC >= 2;
+  }
+
+  // The second half of a frame, by all four wavefronts: the unit's sum, the tiles' dot products with it.
+  auto unit_half = [&](int f, int buf3, int buf2, const float (&S2)[VEC], bool some) {
+    __syncthreads();
+    // what the frame before left, its last entries made before this barrier
+    {
+      const Window w = make_window(f > f0 ? part_f - part_step : part_f, f > f0 ? kUnitScalars * 4u : 0u);
+      const float v[1] = {st[buf3 == 0 ? 2 : buf3 - 1][tid]};
+      window_store(w, (unsigned)(tid * 4), 0u, v);
+    }
+    if (L >= 3) {
+      float S3[VEC];
+#pragma unroll
+      for (int v = 0; v < VEC; v += 4) {
+        float4 s = tsum[buf2][0][v / 4][lane];
+#pragma unroll
+        for (int q = 1; q < 4; ++q) {
+          const float4 t = tsum[buf2][q][v / 4][lane];
+          s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+        }
+        S3[v] = s.x; S3[v + 1] = s.y; S3[v + 2] = s.z; S3[v + 3] = s.w;
+      }
+      if (some) {
+        float d2 = 0.f;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) d2 = fmaf(S2[v], S3[v], d2);
+        stage1(tbs, 0, lane, d2);
+        wave_lds_fence();
+        if (lane == 0) st[buf3][4 * kTileRows + q2] = staged_row_sum(tbs, 0);
+        wave_lds_fence();
+      }
+      // a quarter of the sum's channels each
+      const Window w = make_window(nsum_f, (unsigned)g.D * (unsigned)sizeof(float));
+      float v[VEC / 4];
+      const float* t = reinterpret_cast<const float*>(&tsum[buf2][0][0][0]) + pick;
+#pragma unroll
+      for (int i = 0; i < VEC / 4; ++i)
+        v[i] = ((t[i] + t[VEC * 64 + i]) + t[2 * VEC * 64 + i]) + t[3 * VEC * 64 + i];
+      window_store(w, noff, 0u, v);
+    }
+    part_f += part_step;
+    nsum_f += nsum_step;
+  };
+
+  if (th > 0 && tw > 0) {
+    const uint2 ident = R::ident();
+    Raw s[kWalkSlots][4];  // rows of a 2x2 block each: the frame's own blocks, those of the next one as they arrive
+    {
+      const Window w0 = make_window(rows0, frame_bytes), w1 = make_window(rows1, frame_bytes);
+#pragma unroll
+      for (int n = 0; n < kWalkSlots; ++n) load_block(s[n], n < 4 ? w0 : w1, n & 3);
+    }
+    auto frame = [&](auto phase, int f, int buf3, int buf2) {
+      constexpr int P = decltype(phase)::value;
+      const bool has_next = CC && after > 0;
+      const Window w1 = make_window(rows1, frame_bytes), w2 = make_window(rows2, frame_bytes);
+      float S1[4][VEC], S2[VEC];  // the tile's 2x2 block sums, its sum
+      float b4[8];  // the blocks' dot products with the tile, then (CC = 2) with the same blocks of the next frame
+      float SN2[VEC], cd[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) b4[i] = 0.f;
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) S2[v] = SN2[v] = 0.f;
+#pragma unroll
+      for (int q1 = 0; q1 < 4; ++q1) {
+        Raw(&own)[4] = s[(4 * P + q1) % kWalkSlots];
+        Raw(&nxt)[4] = s[(4 * P + q1 + 4) % kWalkSlots];
+        const bool in = (q1 >> 1) * 2 < th && (q1 & 1) * 2 < tw;  // (wave-uniform)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) S1[q1][v] = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) cd[(q1 & 1) * 4 + k] = 0.f;
+        if (in) {
+          float nd[8];
+          block_stats<DT>(ident, own, S1[q1], nd);
+          stage8(tbs, q1, lane, nd);
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) S2[v] += S1[q1][v];
+          if (CC >= 2 && q1 < 2) {
+#pragma unroll
+            for (int v = 0; v < VEC; v += 4)
+              early[q2][q1][v / 4][lane] = make_float4(S1[q1][v], S1[q1][v + 1], S1[q1][v + 2], S1[q1][v + 3]);
+          }
+          if (CC && has_next) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) cd[(q1 & 1) * 4 + k] = R::dot(own[k], nxt[k]);
+            if (CC >= 2) {
+              float SN1[VEC], d1 = 0.f;
+              R::sum4(ident, nxt, SN1);
+#pragma unroll
+              for (int v = 0; v < VEC; ++v) {
+                d1 = fmaf(S1[q1][v], SN1[v], d1);
+                SN2[v] += SN1[v];
+              }
+              b4[4 + q1] = d1;
+            }
+          }
+        }
+        // the block's rows are done with: their place goes to the block kWalkSlots further on
+        load_block(own, q1 + kWalkSlots - 4 < 4 ? w1 : w2, (q1 + kWalkSlots) & 3);
+        if (CC && (q1 & 1) && has_next) stage8(tbs, 5 + (q1 >> 1), lane, cd);
+      }
+#pragma unroll
+      for (int q1 = 0; q1 < 4; ++q1) {
+        if (CC >= 2 && q1 < 2) {
+          if ((q1 & 1) * 2 >= tw) continue;  // (no such block, nothing was kept)
+#pragma unroll
+          for (int v = 0; v < VEC; v += 4) {
+            const float4 k = early[q2][q1][v / 4][lane];
+            b4[q1] = fmaf(k.w, S2[v + 3], fmaf(k.z, S2[v + 2], fmaf(k.y, S2[v + 1], fmaf(k.x, S2[v], b4[q1]))));
+          }
+        } else {
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) b4[q1] = fmaf(S1[q1][v], S2[v], b4[q1]);
+        }
+      }
+      if (CC >= 2 && has_next) {
+        float t = 0.f;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) t = fmaf(S2[v], SN2[v], t);
+        stage1(tbs, 56, lane, t);
+      }
+#pragma unroll
+      for (int v = 0; v < VEC; v += 4) tsum[buf2][q2][v / 4][lane] = make_float4(S2[v], S2[v + 1], S2[v + 2], S2[v + 3]);
+      stage8(tbs, 4, lane, b4);
+      wave_lds_fence();
+      if (lane < 57) st[buf3][dst] = live && (lane < 36 || has_next) ? staged_row_sum(tbs, lane) : 0.f;
+      wave_lds_fence();
+      unit_half(f, buf3, buf2, S2, true);
+      rows1 = rows2;
+      rows2 += f + 3 <= flast ? frame_bytes : 0u;
+      after = after ? after - 1 : g.T - 1;
+    };
+    static_assert(kWalkPeriod * 4 % kWalkSlots == 0, "the places' roles come round");
+    int f = f0, buf3 = 0;
+#pragma unroll 1
+    while (true) {
+      auto next = [&] { buf3 = buf3 == 2 ? 0 : buf3 + 1; return ++f == f1; };
+      frame(std::integral_constant<int, 0>(), f, buf3, (f - f0) & 1);
+      if (next()) break;
+      frame(std::integral_constant<int, 1>(), f, buf3, (f - f0) & 1);
+      if (next()) break;
+      frame(std::integral_constant<int, 2>(), f, buf3, (f - f0) & 1);
+      if (next()) break;
+    }
+  } else {
+    float none[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) none[v] = 0.f;
+#pragma unroll 1
+    for (int f = f0; f < f1; ++f) unit_half(f, (f - f0) % 3, (f - f0) & 1, none, false);
+  }
+  __syncthreads();
+  (part_f - part_step)[tid] = st[(f1 - 1 - f0) % 3][tid];
+}
+
+// Up to this many (unit, chunk, frame) triples the pass is given to k_pyramid_tiles, beyond it to k_pyramid_stats, whose
+// runs get too short below: 2800 triples (100 frames of 13x13, D = 3584) 34 against 38 us, 3072 (256 of 16x16, D = 1152,
+// CC = 2) 43 and 43, 4200 (150 of 13x13) 54 and 53, 5600 69 and 66, 9600 (800 of 16x16) 125 and 110.
+// Without frame-to-frame products nothing is read twice, and k_pyramid_tiles needs 95 registers, for five wavefronts per
+// SIMD: it takes all (128 images of 24x24, D = 1152: 40 against 54 us; 512 frames of 13x13, D = 3584: 127 and 146).
 // (The host-thread build of the tests sets 0, for k_pyramid_stats on inputs that are small enough for it.)
 #ifndef STTM_PYR_TILES_MAX
 #define STTM_PYR_TILES_MAX 4096
@@ -646,10 +646,16 @@ static void launch_pyramid_dt(const Geo& g, const void* feats, float* part, floa
   // Without the frame-to-frame products no two workgroups share rows: a plain grid, dealt to all dies in turn. (In ranges
   // of frames per die one image is one die's work: 32x32 tokens at D = 8192, fp32, 34.8 against 11.0 us.)
   const dim3 grid = CC ? dim3(pyramid_grid(g)) : dim3(g.nC, NU, g.F);
-  if ((long long)NU * g.F * g.nC <= kPyrTilesMax)
-    hipLaunchKernelGGL((k_pyramid_tiles<DT, CC>), grid, dim3(256), 0, s, g, feats, part, nsum, sel);
-  else
-    hipLaunchKernelGGL((k_pyramid_stats<DT, CC>), grid, dim3(64), 0, s, g, feats, part, nsum, sel);
+  if constexpr (CC > 0 || kPyrTilesMax == 0) {
+    const long long frame_bytes = (long long)g.HW * g.D * (g.dtype == 0 ? 4 : 2);  // (a window's offsets are 32 bits wide)
+    if ((long long)NU * g.F * g.nC > kPyrTilesMax && frame_bytes < 1ll << 31) {
+      const int segs = walk_segments(g);
+      hipLaunchKernelGGL((k_pyramid_stats<DT, CC>), dim3((unsigned)(segs * NU * g.nC)), dim3(256), 0, s, g, feats, part,
+                         nsum, sel, segs);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_pyramid_tiles<DT, CC>), grid, dim3(256), 0, s, g, feats, part, nsum, sel);
 }
 
 template <int CC>

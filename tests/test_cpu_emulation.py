@@ -172,6 +172,22 @@ def test_emulated_pyramid_kernel_of_large_inputs(emul, large, seed, B, T, H, W, 
             np.testing.assert_array_equal(a, getattr(r[1], name), err_msg=name)
 
 
+@pytest.mark.parametrize("seed,B,T,H,W,D,dtype,cell_dots", [
+    (101, 1, 9, 5, 7, 24, "bf16", 2),      # two runs of one video: the second's first frame is read by the first as well
+    (102, 1, 7, 9, 5, 264, "f32", 1),      # one run per column; a unit of one row, a second chunk of two lanes
+    (103, 3, 5, 12, 4, 16, "f16", 2),      # runs across the ends of videos; a tile beyond the edge
+    (104, 5, 2, 3, 3, 8, "bf16", 1),       # level 2 is the root's: no unit sums
+])
+def test_emulated_walk_through_runs_of_frames(emul, large, seed, B, T, H, W, D, dtype, cell_dots):
+    """Runs of more frames than the block places need to come round (three), against the kernel without runs, bit for bit."""
+    run_cpu, _ = emul
+    feats = wl.generate(_variant(seed, B, T, H, W, D, dtype))
+    a, b = (run_cpu.run_cpu(feats, lib=lib, tau_s=0.8, tau_t=0.7, cell_dots=cell_dots) for lib in (large, run_cpu.load()))
+    for name, x in vars(a).items():
+        if isinstance(x, np.ndarray):
+            np.testing.assert_array_equal(x, getattr(b, name), err_msg=name)
+
+
 def test_emulated_kernels_run_clean_under_address_and_undefined_behaviour_sanitizers():
     """The host-thread build with -fsanitize=address,undefined (any report aborts): both dtypes, fixed thresholds and
     a budget, every output in a heap block of its exact size, the workspace of exactly sttm_workspace_bytes(); once
