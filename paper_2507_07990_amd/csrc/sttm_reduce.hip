@@ -20,6 +20,20 @@ constexpr int kSortThreads = 512;
 constexpr int kSortPer = kSortTile / kSortThreads;
 constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kMaxDigitBits = 11;
+// The list of an input of up to this many cells is made by one launch (k_list_small), each workgroup for a range of ids.
+// (The host-thread build of the tests that takes the large inputs' kernels takes the sort passes as well.)
+#ifndef STTM_LIST_MAX
+#if defined(STTM_PYR_TILES_MAX) && STTM_PYR_TILES_MAX == 0
+#define STTM_LIST_MAX 0
+#else
+#define STTM_LIST_MAX 65535
+#endif
+#endif
+constexpr int kListMax = STTM_LIST_MAX;
+static_assert(kListMax < 65536, "cells and counts in 16 bits");
+constexpr int kListThreads = 1024, kListWaves = kListThreads / kWave;
+constexpr int kListBits = 8, kListRange = 1 << kListBits;
+constexpr int kListBatch = 4;  // cells per lane whose loads are in flight together
 constexpr int kItem = 16;  // list positions per gather item
 constexpr int kBig = 64;   // clusters with more list slots than this are summed item by item, then combined
 constexpr int kTail = 8;
@@ -41,7 +55,7 @@ static SortPlan sort_plan(int N) {
   SortPlan p;
   int bits = 1;
   while ((1ll << bits) < (long long)N) ++bits;  // keys 0..N-1
-  p.passes = (bits + kMaxDigitBits - 1) / kMaxDigitBits;
+  p.passes = max(2, (bits + kMaxDigitBits - 1) / kMaxDigitBits);
   p.dbits = (bits + p.passes - 1) / p.passes;
   if (p.dbits < 2) p.dbits = 2;  // a histogram row is read in pieces of four digits
   p.nb = (N + kSortTile - 1) / kSortTile;
@@ -366,7 +380,6 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(SortArgs a) {
         if (a.host_k) *a.host_k = all;
         a.kdev[1] = live;
         a.offsets[a.B] = all;
-        if (LAST) a.seg[all] = live;
       } else if (LAST) {
         a.seg[a.kdev[0]] = n;
       }
@@ -443,6 +456,217 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(SortArgs a) {
     wave_lds_fence();
     if (r + 1 < kSortPer && key[r] >= 0 && ((same[r] >> lane) >> 1) == 0)  // highest lane of its digit group advances the cursor
       atomicAdd(&mycur[digit >> 1], (unsigned)__popcll(same[r]) << half);
+    wave_lds_fence();
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
+// k_list_small: all of the integer plumbing of a small input in one launch. A workgroup owns kListRange consecutive cluster
+// ids. It looks at every cell of the input, counts the list elements and the roots that come before its ids, and keeps the
+// cells of its own ids, in index order; these it then puts into the list by a stable counting sort in LDS. No workgroup
+// waits for another: what they would have to tell each other every one finds out by itself, at 5 bytes to 9 a cell from
+// the caches. A wavefront takes a run of consecutive cells, so the order of equal keys is the order of the cells.
+// Writes what the sort passes write (rank, list, output row of every position, first position of every row, out_ids,
+// offsets, totals).
+// What bounds it: the look over all cells by every workgroup, two rounds of loads per thousand cells and wavefront, and the
+// first fetch of its code. Against preparation, scatter, histogram and second scatter as launches of their own: 64 frames of
+// 13x13 (10816 cells) 25.9 -> 9.4 us, of 16x16 26.3 -> 12.0, 96 of 11x19 27.7 -> 14.0, 180 of 14x14 (35280) 26.6 -> 17.6, six
+// clips of 7500 cells 26.8 -> 21.7; at 65000 cells the two are about even. (Ranges of 512 or 1024 ids 0.3 and 2 us more;
+// elements left with the wavefront that found them 29 us for the six clips, 20.6 for the 180 frames: the members of a range's
+// clusters lie close together.)
+// ------------------------------------------------------------------------------------------------
+struct ListArgs {
+  int n, W, HW, both_halves;  // both_halves: a stored node sum takes two list elements (16-bit input)
+  int cap;                    // cells per wavefront, a multiple of 64
+  const int32_t* cluster_ids;
+  const int32_t* node_map;    // the stage-1 partition, or both NULL
+  const uint8_t* node_level;
+  int32_t* rank;
+  int32_t* kdev;
+  int32_t* host_k;
+  int32_t* out_ids;
+  int64_t* offsets;
+  int64_t capacity;
+  int per_video, B;
+  int32_t* order;
+  int32_t* orow;
+  int32_t* seg;
+};
+
+__global__ __launch_bounds__(kListThreads) void k_list_small(ListArgs a) {
+  STTM_DYNAMIC_LDS(uint16_t, list);                // [wavefront][cap] cells of the own ids
+  __shared__ unsigned cur[kListWaves * kListRange / 2];  // [wavefront][two ids to a word] counts, then cursors
+  __shared__ int s_base[kListRange], s_rank[kListRange];
+  __shared__ int s_roots[kListWaves], s_below[kListWaves], s_len[kListWaves];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lo = blockIdx.x * kListRange, hi = min(a.n, lo + kListRange);
+  const int c0 = wave * a.cap, c1 = min(a.n, c0 + a.cap);
+  const unsigned long long before = (1ull << lane) - 1ull;
+  const int own = lo + tid;  // the cell of the own range that this thread ranks
+  const int own_cid = tid < kListRange && own < hi ? a.cluster_ids[own] : -1;
+  for (int d = tid; d < kListWaves * kListRange / 2; d += kListThreads) cur[d] = 0;
+  __syncthreads();
+
+  unsigned* mycur = cur + wave * (kListRange / 2);
+  uint16_t* mylist = list + wave * a.cap;
+  int nlist = 0, below = 0, roots = 0;  // (the same in all lanes of a wavefront)
+#pragma unroll 1
+  for (int j0 = c0; j0 < c1; j0 += kListBatch * 64) {
+    int cid[kListBatch], rep[kListBatch], lv[kListBatch];
+#pragma unroll
+    for (int u = 0; u < kListBatch; ++u) {  // all loads first
+      const int i = min(j0 + u * 64 + lane, a.n - 1);
+      cid[u] = a.cluster_ids[i];
+      rep[u] = lv[u] = 0;
+      if (a.node_map) {
+        rep[u] = a.node_map[i];
+        lv[u] = a.node_level[i];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kListBatch; ++u) {
+      const int i0 = j0 + u * 64, i = i0 + lane;
+      if (i0 >= c1) continue;
+      if (i0 + 64 > c1 && i >= c1) cid[u] = 0x7fffffff;  // (no id; only the input's last cells end inside a row of lanes)
+      if (i0 < lo) roots += __popcll(__ballot(cid[u] == i));
+      unsigned long long dropped = __ballot(lv[u] >= 3 && i != rep[u]);
+      if (dropped) {
+        // of a node with a stored sum only its top-left cell stays and, where that takes two elements, its next cell in
+        // raster order: the one to the right, or in a node of one column the one below
+        const int past = i - rep[u];
+        const bool second = past == 1 || ((a.W & 7) == 1 && past == a.W && i % a.HW % a.W == a.W - 1);
+        const bool drop = lv[u] >= 3 && past != 0 && !(a.both_halves && second);
+        dropped = __ballot(drop);
+        if (drop) cid[u] = 0x7fffffff;
+      }
+      if (i0 < lo) {  // (whole rows of lanes; a cell's id is at most its own)
+        below += 64 - __popcll(dropped);
+      } else {
+        below += __popcll(__ballot(cid[u] < lo));
+        const unsigned d = (unsigned)(cid[u] - lo);
+        const bool mine = d < (unsigned)(hi - lo);
+        const unsigned long long m = __ballot(mine);
+        if (m) {
+          if (mine) mylist[nlist + __popcll(m & before)] = (uint16_t)i;
+          nlist += __popcll(m);
+        }
+      }
+    }
+  }
+  // ranks of the range's roots
+  const unsigned long long is_root = __ballot(tid < kListRange && own < hi && own_cid == own);
+  if (lane == 0) {
+    s_roots[wave] = roots;
+    s_below[wave] = below;
+    s_len[wave] = nlist;
+    if (wave < kListRange / 64) s_base[wave] = __popcll(is_root);  // (its place is not in use yet)
+  }
+  __syncthreads();
+  int roots_before = 0, start = 0, in_range = 0, mine_before = 0;
+#pragma unroll
+  for (int w = 0; w < kListWaves; ++w) {
+    roots_before += s_roots[w];
+    start += s_below[w];
+    if (w < kListRange / 64) {
+      if (w < wave) mine_before += s_base[w];
+      in_range += s_base[w];
+    }
+  }
+  if (tid < kListRange) {
+    const int rk = roots_before + mine_before + __popcll(is_root & before);
+    s_rank[tid] = rk;
+    if (own < hi) {
+      a.rank[own] = rk;
+      if (own_cid == own && a.out_ids && rk < a.capacity) a.out_ids[rk] = own;
+      if (own % a.per_video == 0) a.offsets[own / a.per_video] = rk;
+    }
+  }
+  // The elements found are dealt out anew, the same number to every wavefront, in their order: those of a range of ids lie
+  // close together, often all in one or two wavefronts' cells.
+  int upto[kListWaves], all = 0;  // elements found up to and including each wavefront's
+#pragma unroll
+  for (int w = 0; w < kListWaves; ++w) {
+    all += s_len[w];
+    upto[w] = __builtin_amdgcn_readfirstlane(all);
+  }
+  const int q0 = (int)((unsigned)all * (unsigned)wave / kListWaves), q1 = (int)((unsigned)all * (unsigned)(wave + 1) / kListWaves);
+  auto element = [&](int q) {  // element q + lane, or -1
+    int finder = 0, first = 0;
+#pragma unroll
+    for (int w = 0; w < kListWaves - 1; ++w)
+      if (q + lane >= upto[w]) {
+        finder = w + 1;
+        first = upto[w];
+      }
+    return q + lane < q1 ? (int)list[finder * a.cap + (q + lane - first)] : -1;
+  };
+  int e0 = -1, key0 = 0;  // the first ones are kept
+#pragma unroll 1
+  for (int q = q0; q < q1; q += 64) {
+    const int e = element(q), key = e >= 0 ? a.cluster_ids[e] : 0, d = key - lo;
+    if (e >= 0) atomicAdd(&mycur[d >> 1], 1u << ((d & 1) * 16));
+    if (q == q0) {
+      e0 = e;
+      key0 = key;
+    }
+  }
+  __syncthreads();
+  // counts of the wavefronts -> where each one's elements of an id begin
+  int two[2] = {0, 0};
+  if (tid < kListRange / 2) {
+    unsigned run = 0;
+#pragma unroll
+    for (int w = 0; w < kListWaves; ++w) {
+      const unsigned c = cur[w * (kListRange / 2) + tid];
+      cur[w * (kListRange / 2) + tid] = run;
+      run += c;
+    }
+    two[0] = (int)(run & 0xffffu);
+    two[1] = (int)(run >> 16);
+  }
+  int sum;
+  const int ex = block_exclusive_scan<kListWaves>(two[0] + two[1], &sum);  // (its barriers: everybody is done with s_base)
+  if (tid < kListRange / 2) {
+    s_base[2 * tid] = start + ex;
+    s_base[2 * tid + 1] = start + ex + two[0];
+  }
+  if (tid == 0) {
+    if (blockIdx.x == 0) a.kdev[2] = 0;  // the list of big clusters starts empty
+    if (hi == a.n) {
+      const int k = roots_before + in_range;
+      a.kdev[0] = k;
+      if (a.host_k) *a.host_k = k;
+      a.kdev[1] = start + all;
+      a.offsets[a.B] = k;
+      a.seg[k] = start + all;
+    }
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int q = q0; q < q1; q += 64) {
+    int e = e0, key = key0;
+    if (q != q0) {
+      e = element(q);
+      key = e >= 0 ? a.cluster_ids[e] : 0;
+    }
+    const int d = key - lo;
+    unsigned long long same = __ballot(e >= 0);
+#pragma unroll
+    for (int bit = 0; bit < kListBits; ++bit) {
+      const bool one = (d >> bit) & 1;
+      const unsigned long long m = __ballot(one);
+      same &= one ? m : ~m;
+    }
+    if (e >= 0) {
+      const int half = (d & 1) * 16, rk = s_rank[d];
+      const int dst = s_base[d] + (int)((mycur[d >> 1] >> half) & 0xffffu) + __popcll(same & before);
+      a.order[dst] = e;
+      a.orow[dst] = rk;
+      if (key == e) a.seg[rk] = dst;
+    }
+    wave_lds_fence();
+    if (e >= 0 && ((same >> lane) >> 1) == 0)  // highest lane of its id's group advances the cursor
+      atomicAdd(&mycur[d >> 1], (unsigned)__popcll(same) << ((d & 1) * 16));
     wave_lds_fence();
   }
 }
@@ -932,6 +1156,21 @@ void launch_reduce_prepare(const Geo& g, const int32_t* cluster_ids, const int32
                            const uint8_t* node_level, int64_t capacity, int32_t* out_ids, int64_t* offsets,
                            const ReduceBuffers& rb, bool zscan, hipStream_t s) {
   const int N = g.N;
+  if (N <= kListMax) {
+    ListArgs a;
+    a.n = N; a.W = g.W; a.HW = g.HW; a.both_halves = g.vec == 8;
+    a.cap = (N + kListThreads - 1) / kListThreads * kWave;
+    a.cluster_ids = cluster_ids; a.node_map = node_map; a.node_level = node_level;
+    a.rank = rb.rank; a.kdev = rb.kdev; a.host_k = rb.host_k;
+    a.out_ids = zscan ? nullptr : out_ids; a.offsets = offsets; a.capacity = capacity;
+    a.per_video = g.T * g.HW; a.B = g.B;
+    a.order = rb.order; a.orow = rb.orow; a.seg = rb.seg;
+    hipLaunchKernelGGL(k_list_small, dim3((N + kListRange - 1) / kListRange), dim3(kListThreads),
+                       (size_t)kListWaves * a.cap * sizeof(uint16_t), s, a);
+    if (zscan)
+      hipLaunchKernelGGL(k_zorder, dim3(g.F), dim3(256), 0, s, g, cluster_ids, rb.rank, capacity, rb.zpos, out_ids);
+    return;
+  }
   const SortPlan pl = sort_plan(N);
   const int DIG = 1 << pl.dbits;
   const dim3 grid(pl.nb), block(kSortThreads);
@@ -958,8 +1197,7 @@ void launch_reduce_prepare(const Geo& g, const int32_t* cluster_ids, const int32
     a.kdev = rb.kdev; a.host_k = rb.host_k; a.out_ids = zscan ? nullptr : out_ids; a.offsets = offsets; a.capacity = capacity;
     a.per_video = g.T * g.HW; a.B = g.B;
     a.orow = rb.orow; a.seg = rb.seg;
-    if (first && last) hipLaunchKernelGGL((k_sort_pass<true, true>), grid, block, 0, s, a);
-    else if (first) hipLaunchKernelGGL((k_sort_pass<true, false>), grid, block, 0, s, a);
+    if (first) hipLaunchKernelGGL((k_sort_pass<true, false>), grid, block, 0, s, a);
     else if (last) hipLaunchKernelGGL((k_sort_pass<false, true>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_sort_pass<false, false>), grid, block, 0, s, a);
     kin = kout;

@@ -733,6 +733,41 @@ def test_both_pyramid_kernels_give_the_same_bits(lib, H, W, D, dtype, R, tau_s, 
             assert torch.equal(t_big[b], t_small[0])
 
 
+@pytest.mark.parametrize("T,H,W,labels", [
+    (1, 1, 1, "own"), (1, 7, 9, "random"), (1, 8, 8, "one"), (5, 13, 1, "random"),       # 1, 63, 64, 65 cells
+    (1, 15, 17, "random"), (1, 16, 16, "own"), (257, 1, 1, "one"), (12, 32, 32, "random"),  # around 256 ids of a workgroup
+    (64, 32, 32, "one"), (257, 15, 17, "one"), (257, 15, 17, "random"), (64, 32, 32, "random"),  # 65535 cells, and 65536
+])
+def test_member_lists_of_every_size(lib, T, H, W, labels):
+    """Up to 65535 cells the member lists are made by one launch, beyond that by sort passes: rows, counts, ids and the
+    clusters' means for labellings with no structure, every cell for itself, and all cells in one cluster. Whole numbers of
+    at most 255 in at most 2^16 cells: their fp32 sums stay below 2^24 and are exact in any order."""
+    import torch
+    N, D = T * H * W, 8
+    rng = np.random.default_rng(N)
+    first = {"own": np.arange(N), "one": np.zeros(N, np.int64), "random": rng.integers(0, max(1, N // 3), N)}[labels]
+    _, where, ids = np.unique(first, return_index=True, return_inverse=True)
+    cluster = where[ids].astype(np.int32)                    # a cluster's id is its smallest member
+    x = rng.integers(-255, 256, (N, D)).astype(np.float32)
+    s = lib.Sttm(0)
+    put = lambda a: torch.from_numpy(a).to("cuda:0")         # noqa: E731
+    merged = torch.full((N, D), 7.0, device="cuda:0")
+    counts, out_ids = (torch.full((N,), -1, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    offsets = torch.full((2,), -1, dtype=torch.int64, device="cuda:0")
+    s.sttm_reduce_noalloc(put(x), lib.STTM_F32, 1, T, H, W, D, put(cluster), lib.STTM_F32, N, merged, counts, out_ids, offsets)
+    roots, rank, size = np.unique(cluster, return_inverse=True, return_counts=True)
+    K = len(roots)
+    assert offsets.tolist() == [0, K]
+    np.testing.assert_array_equal(out_ids[:K].cpu().numpy(), roots)
+    np.testing.assert_array_equal(counts[:K].cpu().numpy(), size)
+    assert (counts[K:] == -1).all() and (out_ids[K:] == -1).all() and (merged[K:] == 7.0).all()
+    sums = np.zeros((K, D))
+    np.add.at(sums, rank, x.astype(np.float64))
+    inv = (np.float32(1) / size.astype(np.float32))[:, None]
+    want = sums.astype(np.float32) * inv
+    np.testing.assert_allclose(merged[:K].cpu().numpy(), want, rtol=2.0 ** -22, atol=0)
+
+
 @pytest.mark.parametrize("seed,B,T,H,W,D,dtype,R", [
     (60, 1, 3, 32, 32, 8, "f32", 2),       # four roots at level 4: nothing above them
     (61, 1, 2, 17, 9, 2056, "f32", 1),     # level-4 and level-5 nodes partly beyond the edge, more columns than threads
