@@ -18,7 +18,7 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-  size_t part, nsum, nrm2, sim, m, sel_key_s, sel_w_s, sel_key_t, tau_s, tau_t, target_s, target_t, sel_s, sel_t, lvl,
+  size_t part, nsum, nrm2, sim, m, sel_key_s, sel_w_s, sel_key_t, tau_s, tau_t, target_s, target_t, sel_s, sel_t, list_key_s, list_w_s, list_key_t, lvl,
       titems, tcount, pd_part, sig, e, parent, ptr_a, ptr_b;
   size_t rank, key_a, val_a, key_b, val_b, order, orow, hist, tot, gsum, tile_roots, seg, kdev,
       bigpart, bigw, biglist, zpos, possum, poscnt;
@@ -97,6 +97,9 @@ Layout make_layout(const Geo& g) {
   l.target_t = take(g.B * sizeof(int));
   l.sel_s = take(select_state_bytes(g.B));
   l.sel_t = take(select_state_bytes(g.B));
+  l.list_key_s = take((size_t)g.B * select_elements(g, true) * sizeof(uint32_t));
+  l.list_w_s = take((size_t)g.B * select_elements(g, true));
+  l.list_key_t = take((size_t)g.B * select_elements(g, false) * sizeof(uint32_t));
   l.lvl = take(N);
   l.titems = take(temporal_items_bytes(g));
   l.tcount = take(temporal_count_bytes());
@@ -214,7 +217,8 @@ struct sttm_ctx {
   Geo g{};
   Layout lay{};
   bool have_spatial = false, have_tau_s = false, have_temporal = false, have_tau_t = false;
-  bool tau_s_pending = false, tau_t_pending = false;  // the budget search left its last digit to the consumer kernel
+  bool tau_s_pending = false, tau_t_pending = false;  // a budget search was left to the kernel that uses its threshold:
+  SelSearch search_s{}, search_t{};                   // this one
   int match_mode = STTM_MATCH_FIRST_PASSING, order = STTM_ORDER_RASTER;
   int cell_dots = 1;       // setting: the spatial pass also emits frame-to-frame dot products (0 no, 1 cells, 2 + 2x2 / 4x4 blocks)
   int have_cell_dots = 0;  // what the statistics in the workspace were computed with
@@ -545,7 +549,7 @@ int sttm_spatial_quadtree(sttm_ctx* ctx, const void* feats_dev, int dtype, int B
       return fail(ctx, STTM_ERR_STATE, "no spatial threshold chosen (call sttm_budget_threshold first)");
   }
   launch_spatial_decide(ctx->g, at<float>(ctx, ctx->lay.m), at<float>(ctx, ctx->lay.tau_s), given,
-                        ctx->tau_s_pending ? at<SelState>(ctx, ctx->lay.sel_s) : nullptr, node_map_dev, node_level_dev,
+                        ctx->tau_s_pending ? ctx->search_s : SelSearch{}, node_map_dev, node_level_dev,
                         ctx->stream);
   ctx->tau_s_pending = false;  // the kernel has left the threshold in the workspace
   return after_launch(ctx);
@@ -600,7 +604,7 @@ int sttm_temporal_merge(sttm_ctx* ctx, const void* feats_dev, const int32_t* nod
   }
   launch_temporal_parent(ctx->g, ctx->match_mode, node_map_dev, node_level_dev, at<float>(ctx, ctx->lay.sig),
                          at<float>(ctx, ctx->lay.tau_t), given,
-                         ctx->tau_t_pending ? at<SelState>(ctx, ctx->lay.sel_t) : nullptr,
+                         ctx->tau_t_pending ? ctx->search_t : SelSearch{},
                          at<int32_t>(ctx, ctx->lay.parent), at<int32_t>(ctx, ctx->lay.ptr_a), ctx->stream);
   ctx->tau_t_pending = false;
   launch_roots(ctx->g, at<int32_t>(ctx, ctx->lay.ptr_a), at<int32_t>(ctx, ctx->lay.ptr_b), node_map_dev,
@@ -640,22 +644,27 @@ int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_ho
     on_device = true;
   }
   float* tau_dev = at<float>(ctx, spatial ? ctx->lay.tau_s : ctx->lay.tau_t);
-  // When the caller does not ask for the value, the last digit of the search is resolved by the kernel that uses the
-  // threshold (one launch less); otherwise by a launch of its own.
-  float* tau_now = tau_out_host ? tau_dev : nullptr;
+  // When the caller does not ask for the value, the search is carried out (or, of a large input, finished) by the kernel
+  // that uses the threshold; otherwise by a launch of its own.
   float* host_tau = tau_out_host && ctx->host_out && g.B <= kHostTaus ? ctx->host_out->tau : nullptr;
   if (host_tau) ctx->host_out_busy = true;
+  SelSearch search;
   if (spatial) {
-    launch_select_spatial(g, at<uint32_t>(ctx, ctx->lay.sel_key_s), at<uint8_t>(ctx, ctx->lay.sel_w_s),
-                          target_dev, at<SelState>(ctx, ctx->lay.sel_s), ctx->sel_s_dirty, tau_now, host_tau, ctx->stream);
+    search = launch_select_spatial(g, at<uint32_t>(ctx, ctx->lay.sel_key_s), at<uint8_t>(ctx, ctx->lay.sel_w_s), target_dev,
+                                   at<SelState>(ctx, ctx->lay.sel_s), ctx->sel_s_dirty,
+                                   at<uint32_t>(ctx, ctx->lay.list_key_s), at<uint8_t>(ctx, ctx->lay.list_w_s), ctx->stream);
     ctx->sel_s_dirty = true;
-    ctx->tau_s_pending = tau_now == nullptr;
+    ctx->search_s = search;
+    ctx->tau_s_pending = tau_out_host == nullptr;
   } else {
-    launch_select_temporal(g, ctx->node_map_temporal, at<uint32_t>(ctx, ctx->lay.sel_key_t), target_dev,
-                           at<SelState>(ctx, ctx->lay.sel_t), ctx->sel_t_dirty, tau_now, host_tau, ctx->stream);
+    search = launch_select_temporal(g, ctx->node_map_temporal, at<uint32_t>(ctx, ctx->lay.sel_key_t), target_dev,
+                                    at<SelState>(ctx, ctx->lay.sel_t), ctx->sel_t_dirty,
+                                    at<uint32_t>(ctx, ctx->lay.list_key_t), ctx->stream);
     ctx->sel_t_dirty = true;
-    ctx->tau_t_pending = tau_now == nullptr;
+    ctx->search_t = search;
+    ctx->tau_t_pending = tau_out_host == nullptr;
   }
+  if (tau_out_host) launch_select_tau(g, search, tau_dev, host_tau, ctx->stream);
   rc = after_launch(ctx);
   if (rc) return rc;
   if (stage == STTM_STAGE_SPATIAL) ctx->have_tau_s = true; else ctx->have_tau_t = true;

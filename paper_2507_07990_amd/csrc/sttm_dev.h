@@ -390,28 +390,35 @@ __device__ inline void wave_lds_fence() {
 }
 
 // ---- budget search state (one per video and stage) ---------------------------------------------------
-// Token count as a function of the threshold is K(tau) = base + sum_j w_j [v_j <= tau]; the search is an
-// MSB-first radix select (11 + 11 + 10 bits) over the order-preserving integer image of v.
+// Token count as a function of the threshold is K(tau) = base + sum_j w_j [v_j <= tau]. The search is for the smallest v at
+// which K exceeds the target and for the largest v below it. The kernels that make the values count their weight in a
+// histogram of kSelBins bins (sel_bin); the bin in which K exceeds the target is picked from that, and of the few values
+// in that bin the one is found exactly.
 constexpr int kSelBins = 2048;
-// What a search pass found, handed to the next launch so that it does not have to derive it again.
+// The bin of a value, by its key: any function that never decreases would do. Equal steps in the logarithm of 1.125 - v,
+// 512 to the octave: 2.4e-4 wide at v = 1, where the similarities of still scenes crowd, 1e-3 at a half, 2e-3 at zero,
+// everything below -0.9 together.
+__device__ inline unsigned sel_bin(uint32_t key);
+// What the first pass over a large input found.
 struct SelFound {
   unsigned long long budget;  // target - base
-  unsigned long long acc;     // weight of the keys below the prefix
-  unsigned prefix;            // leading digits of the searched key found so far
+  unsigned long long acc;     // weight of the keys in the bins before the picked one
   int rc;                     // 0 = searching, 1 = everything fits (tau = 1), 2 = the base alone exceeds the target
+  int pad;
 };
-// The level-0 histogram is fed by hundreds of workgroups whose values fall into a handful of bins; it is kept
+// The histogram is fed by hundreds of workgroups whose values may crowd in a few bins; it is kept
 // in kSelCopies copies, one per accelerator die (workgroups go to the dies round-robin by their index), so that
 // the hot counters stay in one die's L2 instead of travelling between the dies with every atomic.
 constexpr int kSelCopies = 8;
 struct alignas(16) SelState {
-  unsigned hist0[kSelCopies][kSelBins];  // weight per leading digit over all elements; the copies add up
-  unsigned hist[2][kSelBins];            // second and third digit under the found prefix
-  unsigned lo_out;             // largest key whose leading 22 bits are below the found prefix (0 = none)
-  unsigned pad0[3];
-  SelFound found[2];           // after the first / second digit
-  unsigned pad[16];
+  unsigned hist0[kSelCopies][kSelBins];  // weight per bin over all elements; the copies add up
+  unsigned count;              // large inputs: elements of the picked bin, listed beside the state
+  unsigned lo;                 // and the largest key in the bins before it (0 = none)
+  unsigned pad0[2];
+  SelFound found;
+  unsigned pad[22];
 };
+static_assert(sizeof(SelState) % 128 == 0, "whole lines");
 
 // One workgroup zeroes a state.
 __device__ inline void sel_clear(SelState* st) {
@@ -420,7 +427,7 @@ __device__ inline void sel_clear(SelState* st) {
 }
 
 // Adds w to hist[digit] for the lanes with valid set; every lane of the wavefront must call it. The two
-// most frequent leading digits of the wavefront are combined before the atomic (real similarities sit in
+// most frequent digits of the wavefront are combined before the atomic (real similarities sit in
 // tight clusters, which would otherwise serialise on one LDS word); whatever is left goes through plain
 // LDS atomics.
 __device__ inline void wave_hist_add(unsigned* hist, bool valid, unsigned digit, unsigned w) {
@@ -438,8 +445,8 @@ __device__ inline void wave_hist_add(unsigned* hist, bool valid, unsigned digit,
   if ((todo >> (threadIdx.x & 63)) & 1ull) atomicAdd(&hist[digit], w);
 }
 
-// Adds a workgroup's LDS histogram of leading digits to the state's level-0 histogram (call after a barrier).
-__device__ inline void sel_flush_level0(SelState* st, const unsigned* lds_hist) {
+// Adds a workgroup's LDS histogram of bins to the state's (call after a barrier).
+__device__ inline void sel_flush_bins(SelState* st, const unsigned* lds_hist) {
   unsigned* dst = st->hist0[blockIdx.x % kSelCopies];
   for (int j = threadIdx.x; j < kSelBins; j += blockDim.x)
     if (lds_hist[j]) atomicAdd(&dst[j], lds_hist[j]);
@@ -449,16 +456,14 @@ constexpr int kSelThreads = 256;
 
 // Workgroup-wide (THREADS threads): the first bin of `hist` at which acc + running weight exceeds `budget`.
 // Returns false when the whole histogram fits. All threads get the same answer.
-// *below = largest non-empty bin before the found one, or -1.
 // The histogram is the sum of COPIES arrays of kSelBins counters.
 template <int COPIES, int THREADS>
 __device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long long acc,
-                                unsigned long long budget, unsigned* digit, unsigned long long* acc_out,
-                                int* below) {
+                                unsigned long long budget, unsigned* digit, unsigned long long* acc_out) {
   __shared__ unsigned long long wsum[THREADS / 64];
   __shared__ unsigned s_digit;
   __shared__ unsigned long long s_acc;
-  __shared__ int s_found, s_below;
+  __shared__ int s_found;
   constexpr int PER = kSelBins / THREADS;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   static_assert(PER % 4 == 0, "whole 16-byte pieces");
@@ -481,7 +486,7 @@ __device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long
     const unsigned long long t = __shfl_up(inc, o, 64);
     if (lane >= o) inc += t;
   }
-  if (tid == 0) { s_found = 0; s_below = -1; }
+  if (tid == 0) s_found = 0;
   if (lane == 63) wsum[wave] = inc;
   __syncthreads();
   unsigned long long ex = acc + inc - tot;
@@ -497,49 +502,163 @@ __device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long
   }
   __syncthreads();
   const bool found = s_found != 0;
-  if (found && below) {
-    int mine = -1;  // largest non-empty bin below the found one: per thread, per wavefront, then one LDS atomic each
-#pragma unroll
-    for (int j = 0; j < PER; ++j)
-      if (h[j] && tid * PER + j < (int)s_digit) mine = tid * PER + j;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mine = max(mine, __shfl_xor(mine, o, 64));
-    if (lane == 0 && mine >= 0) atomicMax(&s_below, mine);
-    __syncthreads();
-    *below = s_below;
-  }
   *digit = s_digit;
   *acc_out = s_acc;
   __syncthreads();
   return found;
 }
 
-// Last digit of a budget search, by a workgroup of kSelThreads threads: tau = midpoint between the searched key
-// and the largest key below it. All threads get the value.
-__device__ inline float sel_last_digit(const SelState* __restrict__ st) {
-  const SelFound fd = st->found[1];
-  float t = 1.f;
-  if (fd.rc == 2) {
-    t = -2.f;
-  } else if (fd.rc == 0) {  // uniform over the workgroup
-    unsigned d2;
-    unsigned long long a2;
-    int below;
-    if (sel_pick<1, kSelThreads>(st->hist[1], fd.acc, fd.budget, &d2, &a2, &below)) {
-      const unsigned over = (fd.prefix << 10) | d2;
-      const unsigned lo_key = below >= 0 ? ((fd.prefix << 10) | (unsigned)below) : st->lo_out;
-      const float hi = key_float(over);
-      const float lof = lo_key ? key_float(lo_key) : -2.f;
-      t = 0.5f * (lof + hi);
-      if (!(t < hi)) t = lof;
-    }
+__device__ inline unsigned sel_bin(uint32_t key) {
+  const float t = 1.125f - key_float(key);  // (at least 0.125: similarities are at most 1)
+  return 2047u - (unsigned)min(max((int)(__float_as_uint(t) - 0x3e000000u) >> 14, 0), 2047);
+}
+
+// A budget search that the kernel using its threshold carries out.
+struct SelSearch {
+  const SelState* states;  // [videos]; NULL: no search is pending
+  const uint32_t* keys;    // [videos][per_video]: all elements' keys (0 = not an element) if `whole`, else those of the
+  const uint8_t* weights;  // picked bin; weights of the elements (NULL = 1 each)
+  int per_video;
+  bool whole;              // a small input: nothing has been picked yet
+  const int* target;       // [videos]
+  int base_const;          // base of the step function: spatial = roots of all frames
+  const int32_t* node_map; // temporal: the kept nodes of the video's first frame are counted here
+};
+
+// Kept nodes of a video's first frame, by the whole workgroup.
+__device__ inline int sel_base(const Geo& g, int b, int base_const, const int32_t* node_map) {
+  if (!node_map) return base_const;
+  __shared__ int s_base;
+  if (threadIdx.x == 0) s_base = 0;
+  __syncthreads();
+  int c = 0;
+  for (int j = threadIdx.x; j < g.HW; j += blockDim.x) {
+    const int i = b * g.T * g.HW + j;
+    c += (node_map[i] == i);
   }
+  if (c) atomicAdd(&s_base, c);
+  __syncthreads();
+  const int r = s_base;
+  __syncthreads();
+  return r;
+}
+__device__ inline SelFound sel_begin(const Geo& g, int b, const int* target, int base_const, const int32_t* node_map) {
+  const long long budget = (long long)target[b] - sel_base(g, b, base_const, node_map);
+  SelFound fd;
+  fd.budget = budget < 0 ? 0ull : (unsigned long long)budget;
+  fd.acc = 0;
+  fd.rc = budget < 0 ? 2 : 0;
+  fd.pad = 0;
+  return fd;
+}
+
+constexpr int kSelList = 2048;  // elements a search keeps in LDS; of more it reads the keys again in every round
+
+// tau of video b, by a workgroup of kSelThreads threads: midpoint between the searched key and the largest key below it.
+// All threads get the value. The range of keys is cut into 256 pieces, of which one is picked, until it is one key: two
+// rounds for the elements of a bin, however many of them are equal.
+__device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
+  __shared__ uint32_t s_key[kSelList];
+  __shared__ uint8_t s_w[kSelList];
+  __shared__ unsigned hist[kSelThreads];
+  __shared__ unsigned wsum[kSelThreads / 64];
+  __shared__ unsigned s_lo, s_not_min, s_max, s_total, s_piece, s_acc;  // (s_not_min: the complement of the smallest key)
+  const uint32_t* keys = q.keys + (size_t)b * q.per_video;
+  const uint8_t* weights = q.weights ? q.weights + (size_t)b * q.per_video : nullptr;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  SelFound fd;
+  int count = q.per_video;
+  if (tid == 0) s_lo = s_not_min = s_max = s_total = 0;
+  if (q.whole) {
+    fd = sel_begin(g, b, q.target, q.base_const, q.node_map);
+  } else {
+    fd = q.states[b].found;
+    count = (int)q.states[b].count;
+    if (tid == 0) s_lo = q.states[b].lo;
+  }
+  if (fd.rc) return fd.rc == 1 ? 1.f : -2.f;  // uniform over the workgroup
+  __syncthreads();
+  unsigned kmin = 0xffffffffu, kmax = 0, total = 0;
+#pragma unroll 4
+  for (int j = tid; j < count; j += kSelThreads) {
+    const uint32_t k = keys[j];
+    const unsigned w = k == 0 ? 0u : (weights ? weights[j] : 1u);
+    if (j < kSelList) {
+      s_key[j] = k;
+      s_w[j] = (uint8_t)w;
+    }
+    if (k) kmin = min(kmin, k);
+    kmax = max(kmax, k);
+    total += w;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    kmin = min(kmin, (unsigned)__shfl_xor((int)kmin, o, 64));
+    kmax = max(kmax, (unsigned)__shfl_xor((int)kmax, o, 64));
+    total += (unsigned)__shfl_xor((int)total, o, 64);
+  }
+  if (lane == 0) {
+    atomicMax(&s_not_min, ~kmin);
+    atomicMax(&s_max, kmax);
+    atomicAdd(&s_total, total);
+  }
+  __syncthreads();
+  if (fd.acc + s_total <= fd.budget) return 1.f;  // (a small input all of which fits)
+  const bool kept = count <= kSelList;
+  unsigned a = ~s_not_min, z = s_max, room = (unsigned)(fd.budget - fd.acc);  // weight that still fits before key a
+#pragma unroll 1
+  while (a != z) {
+    const int shift = max(0, 24 - __builtin_clz(z - a));
+    hist[tid] = 0;
+    __syncthreads();
+#pragma unroll 2
+    for (int j = tid; j < count; j += kSelThreads) {
+      const uint32_t k = kept ? s_key[j] : keys[j];
+      if (k >= a && k <= z) atomicAdd(&hist[(k - a) >> shift], kept ? (unsigned)s_w[j] : (weights ? (unsigned)weights[j] : 1u));
+    }
+    __syncthreads();
+    const unsigned h = hist[tid];
+    unsigned inc = h;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned t = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += t;
+    }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    unsigned ex = inc - h;
+    for (int w = 0; w < wave; ++w) ex += wsum[w];
+    if (ex <= room && ex + h > room) {
+      s_piece = (unsigned)tid;
+      s_acc = ex;
+    }
+    __syncthreads();
+    a += s_piece << shift;
+    z = min(z, a + ((1u << shift) - 1u));
+    room -= s_acc;
+  }
+  // (an element may still lie below the searched key in its bin)
+  unsigned under = 0;
+#pragma unroll 2
+  for (int j = tid; j < count; j += kSelThreads) {
+    const uint32_t k = kept ? s_key[j] : keys[j];
+    if (k < a) under = max(under, k);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) under = max(under, (unsigned)__shfl_xor((int)under, o, 64));
+  if (lane == 0 && under) atomicMax(&s_lo, under);
+  __syncthreads();
+  const unsigned lo_key = s_lo;
+  const float hi = key_float(a);
+  const float lof = lo_key ? key_float(lo_key) : -2.f;
+  float t = 0.5f * (lof + hi);
+  if (!(t < hi)) t = lof;
   return t;
 }
 
 // ---- launchers (defined in the .hip files; all asynchronous on `s`) ------------------------------------
 
-// `sel`: the spatial search states [B]; cleared by the statistics pass, level 0 filled by the finalize kernel.
+// `sel`: the spatial search states [B]; cleared by the statistics pass, the histogram filled by the finalize kernel.
 // `cell_dots`: 1 = also leave x_c(t) . x_c(t+1) of every cell in `part` (the temporal stage then skips those pairs);
 // 2 = and S_n(t) . S_n(t+1) of every 2x2 and 4x4 block n.
 void launch_pyramid_stats(const Geo& g, const void* feats, int cell_dots, float* part, float* nsum, SelState* sel,
@@ -563,19 +682,24 @@ struct TauArgs {
   float v[kTauArgs];
 };
 // `given`: if it holds thresholds the kernel takes them from there (and leaves them in `tau` for later readers).
-// `pending` (may be NULL): the search states of a budget search whose last digit has not been resolved yet; the
-// kernel then works the threshold out itself (and leaves it in `tau` for later readers) instead of reading `tau`.
-void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauArgs& given, const SelState* pending,
+// `pending`: a budget search that has not been carried out yet (or states == NULL); the kernel then works the threshold out
+// itself (and leaves it in `tau` for later readers) instead of reading `tau`.
+void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauArgs& given, const SelSearch& pending,
                            int32_t* node_map, uint8_t* node_level, hipStream_t s);
-// `dirty`: the state has been searched since its statistics pass (levels 1-2 must be cleared first).
+// Begins a budget search and says how it goes on. A small input is left to whoever uses the threshold; of a large one the
+// elements of the right bin are listed (`list_key`, `list_w`: [videos][select_elements()]).
+// `dirty`: the state has been searched since its statistics pass (the list must be emptied first).
+SelSearch launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
+                                SelState* state, bool dirty, uint32_t* list_key, uint8_t* list_w, hipStream_t s);
+SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
+                                 SelState* state, bool dirty, uint32_t* list_key, hipStream_t s);
+// Carries a search out now, for a caller who wants the thresholds back.
 // `host_tau` (may be NULL): host memory the device can write, which receives the thresholds as well.
-// `tau` == NULL: the last digit is left to the kernel that uses the threshold (see `pending` above).
-void launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
-                           SelState* state, bool dirty, float* tau, float* host_tau, hipStream_t s);
-void launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
-                            SelState* state, bool dirty, float* tau, float* host_tau, hipStream_t s);
+void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s);
+// Elements per video of a spatial / temporal search: what its list has room for.
+int select_elements(const Geo& g, bool spatial);
 inline size_t select_state_bytes(int B) { return (size_t)B * sizeof(SelState); }
-// `sel`: the temporal search states [B]; cleared here, level 0 filled by launch_temporal_resolve.
+// `sel`: the temporal search states [B]; cleared here, the histogram filled by launch_temporal_resolve.
 // `skip_same`: 0 = every pair is computed here; 1 = pairs of two single cells are left out, 2 = also pairs of the same
 // 2x2 or 4x4 block in both frames (their dot products are in the spatial pass's `part`).
 // `items` (temporal_items_bytes() of them) / `item_count`: the work queues of the pass (see temporal_clear).
@@ -612,7 +736,7 @@ void launch_temporal_resolve(const Geo& g, int match, int same_level, const int3
                              const float* pd_part, const float* cell_part, const float* nrm2, float* sig, float* e,
                              uint32_t* sel_key, SelState* sel, int* item_count, hipStream_t s);
 void launch_temporal_parent(const Geo& g, int match, const int32_t* node_map, const uint8_t* node_level,
-                            const float* sig, float* tau, const TauArgs& given, const SelState* pending, int32_t* parent,
+                            const float* sig, float* tau, const TauArgs& given, const SelSearch& pending, int32_t* parent,
                             int32_t* ptr, hipStream_t s);
 void launch_roots(const Geo& g, int32_t* ptr_a, int32_t* ptr_b, const int32_t* node_map, int32_t* cluster_ids,
                   hipStream_t s);

@@ -904,10 +904,10 @@ __global__ __launch_bounds__(UP == 2 ? kFinThreadsWide : kFinThreads) void k_spa
       sel_key[o] = key;
       sel_w[o] = (uint8_t)wgt;
     }
-    wave_hist_add(h0, wgt != 0, key >> 21, wgt);
+    wave_hist_add(h0, wgt != 0, sel_bin(key), wgt);
   }
   __syncthreads();
-  sel_flush_level0(sel + f / g.T, h0);
+  sel_flush_bins(sel + f / g.T, h0);
 }
 
 void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float* nrm2, float* sim, float* m,
@@ -929,13 +929,13 @@ void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kSelThreads) void k_spatial_decide(Geo g, const float* __restrict__ m,
                                                                 float* __restrict__ tau, TauArgs given,
-                                                                const SelState* __restrict__ pending,
+                                                                SelSearch pending,
                                                                 int32_t* __restrict__ node_map,
                                                                 uint8_t* __restrict__ node_level) {
   const int b = blockIdx.y, per_video = g.T * g.HW;
   float t;
-  if (pending || given.n) {  // the budget search left its last digit to this kernel, or the caller named the threshold
-    t = given.n ? given.v[b] : sel_last_digit(pending + b);
+  if (pending.states || given.n) {  // the budget search was left to this kernel, or the caller named the threshold
+    t = given.n ? given.v[b] : sel_threshold(g, pending, b);
     if (blockIdx.x == 0 && threadIdx.x == 0) tau[b] = t;
   } else {
     t = tau[b];
@@ -954,7 +954,7 @@ __global__ __launch_bounds__(kSelThreads) void k_spatial_decide(Geo g, const flo
   if (node_level) node_level[i] = (uint8_t)lvl;
 }
 
-void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauArgs& given, const SelState* pending,
+void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauArgs& given, const SelSearch& pending,
                            int32_t* node_map, uint8_t* node_level, hipStream_t s) {
   const int per_video = g.T * g.HW;
   hipLaunchKernelGGL(k_spatial_decide, dim3((per_video + kSelThreads - 1) / kSelThreads, g.B), dim3(kSelThreads), 0, s,
@@ -990,167 +990,129 @@ void launch_node_levels(const Geo& g, const int32_t* node_map, uint8_t* node_lev
 }
 
 // ------------------------------------------------------------------------------------------------
-// Budget-driven thresholds. Token count as a function of the threshold is the step function
-// K(tau) = base + sum_j w_j [v_j <= tau]. An MSB-first radix select (11 + 11 + 10 bits) over the
-// order-preserving integer image of v finds the smallest value whose cumulative weight exceeds
-// target - base, then the largest value below it; tau is the midpoint of the two.
-// The level-0 histogram is filled by the statistics pass of the stage; two launches follow, grid
-// (slices, videos): every workgroup finds the next digit from the (complete) histogram of the level before
-// and bins its slice under the prefix (the second also collects the largest key below the prefix); a last
-// small launch resolves the last digit and writes tau. Each launch leaves what it found in the state, so the
-// next one resolves one digit only.
+// Budget-driven thresholds (see SelState). The statistics pass of the stage has filled the histogram of bins;
+// k_select_list, grid (slices, videos), picks the bin and lists its elements, and every workgroup of the kernel that uses
+// the threshold finds the value among those (sel_threshold). Where a video has no more elements than such a workgroup
+// keeps in LDS anyway, it is given all of them and no launch is made for the search.
 // Input: keys[video][per_video] (0 = not an element), weights (NULL = 1 for every element).
+// What it costs is launches and dependent loads. Against a radix search of 11 + 11 + 10 bits, two launches and the last
+// digit in the kernel that uses the threshold (the first bits of a float tell similarities apart badly: four bins from a
+// half to one), both searches of a pass with those kernels, us: 64 frames of 13x13 35 -> 27, 512 of 13x13 39 -> 27, 180 of
+// 18x24 40 -> 28; one image with the value handed back 21 -> 13. (One workgroup for every video up to 16384 elements instead
+// of the list: 15 us more at 64 frames.)
 // ------------------------------------------------------------------------------------------------
-constexpr int kPassThreads = 512;  // threads of a search pass
-constexpr int kSelPer = 4;         // elements per thread and pass
+// (The host-thread build of the tests that takes the large inputs' kernels lists the elements of every search.)
+#ifndef STTM_SEL_WHOLE
+#if STTM_PYR_TILES_MAX == 0
+#define STTM_SEL_WHOLE 0
+#else
+#define STTM_SEL_WHOLE kSelList
+#endif
+#endif
+constexpr int kSelWhole = STTM_SEL_WHOLE;
+constexpr int kPassThreads = 512;  // threads of the listing pass
+constexpr int kSelPer = 4;         // elements per thread
 
-__device__ inline int sel_shift(int pass) { return pass == 0 ? 21 : (pass == 1 ? 10 : 0); }
-__device__ inline int sel_width(int pass) { return pass == 2 ? 10 : 11; }
-
-// base of the step function: spatial = constant (roots * T), temporal = kept nodes of the video's first frame
-__device__ inline int sel_base(const Geo& g, int b, int base_const, const int32_t* node_map) {
-  if (!node_map) return base_const;
-  __shared__ int s_base;
-  if (threadIdx.x == 0) s_base = 0;
-  __syncthreads();
-  int c = 0;
-  for (int j = threadIdx.x; j < g.HW; j += blockDim.x) {
-    const int i = b * g.T * g.HW + j;
-    c += (node_map[i] == i);
-  }
-  if (c) atomicAdd(&s_base, c);
-  __syncthreads();
-  const int r = s_base;
-  __syncthreads();
-  return r;
-}
-
-// Clears what a search leaves behind (levels 1-2, the lower neighbour); level 0 stays.
 __global__ __launch_bounds__(256) void k_select_reset(SelState* st) {
-  SelState* s = st + blockIdx.x;
-  for (int j = threadIdx.x; j < kSelBins; j += blockDim.x) s->hist[0][j] = s->hist[1][j] = 0;
-  if (threadIdx.x == 0) s->lo_out = 0;
+  if (threadIdx.x == 0) st[blockIdx.x].count = st[blockIdx.x].lo = 0;
 }
 
-// One digit of the search per launch, grid (slices, videos). Every workgroup finds the digit of level
-// PASS - 1 from that level's (complete) histogram -- the first launch also works out the budget, the second
-// starts from what the first one left in the state -- and bins its slice of the keys under the prefix found
-// so far; the workgroup of slice 0 leaves the prefix for the next launch.
-template <int PASS>  // 1 or 2
-__global__ __launch_bounds__(kPassThreads) void k_select_pass(Geo g, const uint32_t* __restrict__ keys,
+__global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint32_t* __restrict__ keys,
                                                              const uint8_t* __restrict__ weights, int per_video,
                                                              const int* __restrict__ target, int base_const,
                                                              const int32_t* __restrict__ node_map,
-                                                             SelState* __restrict__ states) {
-  __shared__ unsigned hist[kSelBins];
-  __shared__ uint32_t s_key[kSelPer][kPassThreads];  // (each thread reads back what it wrote: lets the loop below stay one copy)
-  __shared__ uint8_t s_w[kSelPer][kPassThreads];
-  __shared__ unsigned s_lo;
+                                                             SelState* __restrict__ states,
+                                                             uint32_t* __restrict__ list_key,
+                                                             uint8_t* __restrict__ list_w) {
+  __shared__ unsigned s_lo, s_n, s_at;
   const int b = blockIdx.y, tid = threadIdx.x;
-  if (tid == 0) s_lo = 0;
+  if (tid == 0) s_lo = s_n = 0;
   SelState* st = states + b;
-  // the slice's keys do not depend on the search: their loads fly while the digit is being found
+  // the slice's keys do not depend on the search: their loads fly while the bin is being found
   const uint32_t* kv = keys + (size_t)b * per_video;
-  const uint8_t* wv = weights ? weights + (size_t)b * per_video : nullptr;
   const int j0 = blockIdx.x * (kPassThreads * kSelPer);
   uint32_t key[kSelPer];
-  unsigned w[kSelPer];
 #pragma unroll
   for (int u = 0; u < kSelPer; ++u) {
     const int j = j0 + u * kPassThreads + tid;
     key[u] = j < per_video ? kv[j] : 0u;
-    w[u] = 1u;
-    if (wv) w[u] = j < per_video ? wv[j] : 0u;
   }
+  SelFound fd = sel_begin(g, b, target, base_const, node_map);
+  unsigned bin = 0;
+  if (fd.rc == 0 && !sel_pick<kSelCopies, kPassThreads>(st->hist0[0], 0ull, fd.budget, &bin, &fd.acc)) fd.rc = 1;
+  if (blockIdx.x == 0 && tid == 0) st->found = fd;
+  if (fd.rc) return;  // uniform over the workgroup
+  __syncthreads();
+  unsigned lo = 0, place[kSelPer];  // key 0 is below every real value
 #pragma unroll
   for (int u = 0; u < kSelPer; ++u) {
-    s_key[u][tid] = key[u];
-    s_w[u][tid] = (uint8_t)w[u];
+    const unsigned at = key[u] ? sel_bin(key[u]) : kSelBins;
+    place[u] = 0xffffffffu;
+    if (at == bin) place[u] = atomicAdd(&s_n, 1u);
+    else if (at < bin) lo = max(lo, key[u]);
   }
-  for (int j = tid; j < kSelBins; j += kPassThreads) hist[j] = 0;
-  SelFound fd;
-  if (PASS == 1) {
-    const int base = sel_base(g, b, base_const, node_map);
-    const long long budget = (long long)target[b] - base;
-    fd.budget = budget < 0 ? 0ull : (unsigned long long)budget;
-    fd.acc = 0;
-    fd.prefix = 0;
-    fd.rc = budget < 0 ? 2 : 0;
-  } else {
-    fd = st->found[0];
-  }
-  if (fd.rc == 0) {  // uniform over the workgroup
-    unsigned d;
-    unsigned long long a2;
-    const bool hit = PASS == 1 ? sel_pick<kSelCopies, kPassThreads>(st->hist0[0], fd.acc, fd.budget, &d, &a2, nullptr)
-                               : sel_pick<1, kPassThreads>(st->hist[0], fd.acc, fd.budget, &d, &a2, nullptr);
-    if (hit) {
-      fd.prefix = (fd.prefix << sel_width(PASS - 1)) | d;
-      fd.acc = a2;
-    } else {
-      fd.rc = 1;
-    }
-  }
-  if (blockIdx.x == 0 && tid == 0) st->found[PASS - 1] = fd;
-  __syncthreads();  // the LDS histogram is clear
-  if (fd.rc == 0) {
-    const unsigned prefix = fd.prefix;
-    const int shift = sel_shift(PASS), width = sel_width(PASS);
-    unsigned lo = 0;  // key 0 is below every real value
-#pragma unroll 1
-    for (int u = 0; u < kSelPer; ++u) {
-      const unsigned wu = s_w[u][tid], k = wu ? s_key[u][tid] : 0u;
-      const unsigned top = k >> (shift + width);
-      wave_hist_add(hist, k != 0 && top == prefix, (k >> shift) & ((1u << width) - 1u), wu);
-      if (PASS == 2 && top < prefix && k > lo) lo = k;
-    }
-    if (PASS == 2) {
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) lo = max(lo, (unsigned)__shfl_xor((int)lo, o, 64));
-      if ((tid & 63) == 0 && lo) atomicMax(&s_lo, lo);
-    }
-    __syncthreads();
-    if (PASS == 2 && tid == 0 && s_lo) atomicMax(&st->lo_out, s_lo);
-    for (int j = tid; j < kSelBins; j += kPassThreads)
-      if (hist[j]) atomicAdd(&st->hist[PASS - 1][j], hist[j]);
+  for (int o = 32; o > 0; o >>= 1) lo = max(lo, (unsigned)__shfl_xor((int)lo, o, 64));
+  if ((tid & 63) == 0 && lo) atomicMax(&s_lo, lo);
+  __syncthreads();
+  if (tid == 0) {
+    if (s_lo) atomicMax(&st->lo, s_lo);
+    s_at = s_n ? atomicAdd(&st->count, s_n) : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kSelPer; ++u) {
+    if (place[u] == 0xffffffffu) continue;
+    const size_t o = (size_t)b * per_video + s_at + place[u];
+    list_key[o] = key[u];
+    if (weights) list_w[o] = weights[(size_t)b * per_video + j0 + u * kPassThreads + tid];
   }
 }
 
-// Last digit as a launch of its own (when the caller wants the threshold back).
-__global__ __launch_bounds__(kSelThreads) void k_select_tau(const SelState* __restrict__ states,
-                                                            float* __restrict__ tau, float* __restrict__ host_tau) {
-  const float t = sel_last_digit(states + blockIdx.x);
+// The whole search as a launch of its own (when the caller wants the threshold back).
+__global__ __launch_bounds__(kSelThreads) void k_select_tau(Geo g, SelSearch search, float* __restrict__ tau,
+                                                            float* __restrict__ host_tau) {
+  const float t = sel_threshold(g, search, blockIdx.x);
   if (threadIdx.x == 0) {
     tau[blockIdx.x] = t;
     if (host_tau) host_tau[blockIdx.x] = t;
   }
 }
 
-static void launch_select(const Geo& g, const uint32_t* keys, const uint8_t* weights, int per_video,
-                          const int* target, int base_const, const int32_t* node_map, SelState* st, bool dirty,
-                          float* tau, float* host_tau, hipStream_t s) {
-  const int slices = per_video > 0 ? (per_video + kPassThreads * kSelPer - 1) / (kPassThreads * kSelPer) : 1;
-  const dim3 grid(slices, g.B), block(kPassThreads);
+static SelSearch launch_select(const Geo& g, const uint32_t* keys, const uint8_t* weights, int per_video,
+                               const int* target, int base_const, const int32_t* node_map, SelState* st, bool dirty,
+                               uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
+  SelSearch q = {st, keys, weights, per_video, true, target, base_const, node_map};
+  if (per_video <= kSelWhole) return q;
+  const dim3 grid((per_video + kPassThreads * kSelPer - 1) / (kPassThreads * kSelPer), g.B), block(kPassThreads);
   if (dirty) hipLaunchKernelGGL(k_select_reset, dim3(g.B), dim3(256), 0, s, st);
-  hipLaunchKernelGGL(k_select_pass<1>, grid, block, 0, s, g, keys, weights, per_video, target, base_const,
-                     node_map, st);
-  hipLaunchKernelGGL(k_select_pass<2>, grid, block, 0, s, g, keys, weights, per_video, target, base_const,
-                     node_map, st);
-  if (tau) hipLaunchKernelGGL(k_select_tau, dim3(g.B), dim3(kSelThreads), 0, s, st, tau, host_tau);
+  hipLaunchKernelGGL(k_select_list, grid, block, 0, s, g, keys, weights, per_video, target, base_const, node_map, st,
+                     list_key, list_w);
+  q.keys = list_key;
+  q.weights = weights ? list_w : nullptr;
+  q.whole = false;
+  return q;
 }
 
-void launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
-                           SelState* state, bool dirty, float* tau, float* host_tau, hipStream_t s) {
+int select_elements(const Geo& g, bool spatial) { return g.T * (spatial ? g.NN - g.lvl_base[1] : g.HW); }
+
+SelSearch launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
+                                SelState* state, bool dirty, uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
   int roots = 0;
   for (int ry = 0; ry < g.R; ++ry)
     for (int rx = 0; rx < g.R; ++rx) roots += node_exists(g, g.L, ry, rx);
-  const int per_video = g.T * (g.NN - g.lvl_base[1]);
-  launch_select(g, keys, weights, per_video, target, roots * g.T, nullptr, state, dirty, tau, host_tau, s);
+  return launch_select(g, keys, weights, select_elements(g, true), target, roots * g.T, nullptr, state, dirty, list_key,
+                       list_w, s);
 }
 
-void launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
-                            SelState* state, bool dirty, float* tau, float* host_tau, hipStream_t s) {
-  launch_select(g, keys, nullptr, g.T * g.HW, target, 0, node_map, state, dirty, tau, host_tau, s);
+SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
+                                 SelState* state, bool dirty, uint32_t* list_key, hipStream_t s) {
+  return launch_select(g, keys, nullptr, select_elements(g, false), target, 0, node_map, state, dirty, list_key, nullptr,
+                       s);
+}
+
+void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s) {
+  hipLaunchKernelGGL(k_select_tau, dim3(g.B), dim3(kSelThreads), 0, s, g, search, tau, host_tau);
 }
 
 }  // namespace sttm

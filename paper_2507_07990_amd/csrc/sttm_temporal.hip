@@ -600,10 +600,10 @@ __global__ __launch_bounds__(256) void k_temporal_resolve(Geo g, int match, int 
       }
       sel_key[i] = key;
     }
-    wave_hist_add(h0, key != 0, key >> 21, 1u);
+    wave_hist_add(h0, key != 0, sel_bin(key), 1u);
   }
   __syncthreads();
-  sel_flush_level0(sel + f / g.T, h0);
+  sel_flush_bins(sel + f / g.T, h0);
 }
 
 void launch_temporal_resolve(const Geo& g, int match, int same_level, const int32_t* node_map,
@@ -626,15 +626,15 @@ __global__ __launch_bounds__(kSelThreads) void k_temporal_parent(Geo g, int matc
                                                          const uint8_t* __restrict__ node_level,
                                                          const float* __restrict__ sig,
                                                          float* __restrict__ tau, TauArgs given,
-                                                         const SelState* __restrict__ pending,
+                                                         SelSearch pending,
                                                          int32_t* __restrict__ parent, int32_t* __restrict__ ptr) {
   __shared__ PairFrame pf;
   __shared__ int par[1024];
   __shared__ unsigned long long best[1024];
   const int f = blockIdx.x, HW = g.HW;
   float th;
-  if (pending || given.n) {  // the budget search left its last digit to this kernel, or the caller named the threshold
-    th = given.n ? given.v[f / g.T] : sel_last_digit(pending + f / g.T);
+  if (pending.states || given.n) {  // the budget search was left to this kernel, or the caller named the threshold
+    th = given.n ? given.v[f / g.T] : sel_threshold(g, pending, f / g.T);
     if (f % g.T == 0 && threadIdx.x == 0) tau[f / g.T] = th;
   } else {
     th = tau[f / g.T];
@@ -680,7 +680,7 @@ __global__ __launch_bounds__(kSelThreads) void k_temporal_parent(Geo g, int matc
 }
 
 void launch_temporal_parent(const Geo& g, int match, const int32_t* node_map, const uint8_t* node_level,
-                            const float* sig, float* tau, const TauArgs& given, const SelState* pending, int32_t* parent,
+                            const float* sig, float* tau, const TauArgs& given, const SelSearch& pending, int32_t* parent,
                             int32_t* ptr, hipStream_t s) {
   hipLaunchKernelGGL(k_temporal_parent, dim3(g.F), dim3(kSelThreads), 0, s, g, match, node_map, node_level, sig, tau, given,
                      pending, parent, ptr);

@@ -733,6 +733,80 @@ def test_both_pyramid_kernels_give_the_same_bits(lib, H, W, D, dtype, R, tau_s, 
             assert torch.equal(t_big[b], t_small[0])
 
 
+def _searched(values, weights, base, target):
+    """The budget rule on fp32 values: midpoint between the first value at which the count exceeds the target and the
+    largest value below it."""
+    if base > target:
+        return np.float32(-2)
+    v, at = np.unique(values, return_inverse=True)
+    total = base + np.cumsum(np.bincount(at, weights=weights))
+    over = np.nonzero(total > target)[0]
+    if not len(over):
+        return np.float32(1)
+    hi, lo = v[over[0]], v[over[0] - 1] if over[0] else np.float32(-2)
+    t = np.float32(0.5) * np.float32(lo + hi)
+    return t if t < hi else lo
+
+
+@pytest.mark.parametrize("T,noise,D", [
+    (8, 1.0, 64),       # 2048 cells, 680 nodes above them: no list for either search
+    (9, 1.0, 64),       # 2304 cells, more than a workgroup keeps: the elements of the picked bin are listed
+    (32, 0.02, 512),    # all similarities within a few hundredths of one
+    (200, 0.003, 512),  # and within 1e-4: more elements in the picked bin than a workgroup keeps
+    (60, 0.0, 64),      # nothing but ties
+])
+def test_budget_searches_are_exact(lib, T, noise, D):
+    """The thresholds found, against the rule applied to the similarity tables the library exports: the same fp32 values,
+    whatever the spread of the similarities and the way the search takes; once handed back and once left to the kernel
+    that uses it."""
+    import torch
+    H = W = 16
+    N, L = T * H * W, 4
+    gen = torch.Generator(device="cuda:0").manual_seed(T)
+    x = torch.randn(1, 1, 1, D, device="cuda:0", generator=gen) + noise * torch.randn(T, H, W, D, device="cuda:0", generator=gen)
+    x = x.contiguous()
+    s = lib.Sttm(0)
+    s.ensure_workspace(1, T, H, W, D, lib.STTM_F32, 1)
+    nm, cl = (torch.empty(N, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    nl = torch.empty(N, dtype=torch.uint8, device="cuda:0")
+    sh = (lib.STTM_F32, 1, T, H, W, D, 1)
+    s.sttm_spatial_stats(x, *sh)
+    m = torch.empty(T * 341, device="cuda:0")
+    s.sttm_export(lib.STTM_TBL_MIN_SIM, m)
+    m = m.cpu().numpy().reshape(T, 341)
+    values, up = [], np.full((T, 1, 1), -2, np.float32)
+    for level in range(L, 0, -1):                            # the largest m on the way from the root
+        side = 16 >> level
+        at = lib.sttm_node_index(H, W, 1, level, 0, 0)
+        up = np.maximum(up, m[:, at:at + side * side].reshape(T, side, side))
+        values.append(up.ravel())
+        up = up.repeat(2, 1).repeat(2, 2)
+    values = np.concatenate(values)
+    for keep in (0.03, 0.2, 0.5, 0.9, 1.0):
+        want = _searched(values, np.full(len(values), 3), T, int(np.floor(np.sqrt(keep) * N)))
+        tau = s.sttm_budget_threshold(lib.STTM_STAGE_SPATIAL, keep)[0]
+        assert tau == want, keep
+        s.sttm_spatial_quadtree(x, *sh, None, nm, nl)
+        given = nm.clone()
+        s.sttm_budget_threshold(lib.STTM_STAGE_SPATIAL, keep, want_tau=False)
+        s.sttm_spatial_quadtree(x, *sh, None, nm, nl)
+        assert torch.equal(nm, given)
+    s.sttm_spatial_quadtree(x, *sh, [1.0], nm, nl)           # single cells
+    s.sttm_temporal_stats(x, nm, nl)
+    e = torch.empty(N, device="cuda:0")
+    s.sttm_export(lib.STTM_TBL_BEST_SIM, e)
+    e = e.cpu().numpy()[H * W:]
+    for keep in (0.01, 0.3, 0.5, 0.95, 1.0):
+        want = _searched(e, np.ones(len(e)), H * W, int(np.floor(keep * N)))
+        tau = s.sttm_budget_threshold(lib.STTM_STAGE_TEMPORAL, keep)[0]
+        assert tau == want, keep
+        s.sttm_temporal_merge(x, nm, nl, None, cl)
+        given = cl.clone()
+        s.sttm_budget_threshold(lib.STTM_STAGE_TEMPORAL, keep, want_tau=False)
+        s.sttm_temporal_merge(x, nm, nl, None, cl)
+        assert torch.equal(cl, given)
+
+
 @pytest.mark.parametrize("T,H,W,labels", [
     (1, 1, 1, "own"), (1, 7, 9, "random"), (1, 8, 8, "one"), (5, 13, 1, "random"),       # 1, 63, 64, 65 cells
     (1, 15, 17, "random"), (1, 16, 16, "own"), (257, 1, 1, "one"), (12, 32, 32, "random"),  # around 256 ids of a workgroup
