@@ -18,7 +18,7 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-  size_t part, nsum, nrm2, sim, m, sel_key_s, sel_w_s, sel_key_t, tau_s, tau_t, target_s, target_t, sel_s, sel_t, list_key_s, list_w_s, list_key_t, lvl,
+  size_t part, nsum, nrm2, sim, m, sel_key_s, sel_w_s, sel_key_t, tau_s, tau_t, target_s, target_t, sel_s, sel_t, list_key_s, list_w_s, list_key_t, list_w_t, lvl,
       titems, tcount, pd_part, sig, e, parent, ptr_a, ptr_b;
   size_t rank, key_a, val_a, key_b, val_b, order, orow, hist, tot, gsum, tile_roots, seg, kdev,
       bigpart, bigw, biglist, zpos, possum, poscnt;
@@ -100,6 +100,7 @@ Layout make_layout(const Geo& g) {
   l.list_key_s = take((size_t)g.B * select_elements(g, true) * sizeof(uint32_t));
   l.list_w_s = take((size_t)g.B * select_elements(g, true));
   l.list_key_t = take((size_t)g.B * select_elements(g, false) * sizeof(uint32_t));
+  l.list_w_t = take((size_t)g.B * select_elements(g, false));
   l.lvl = take(N);
   l.titems = take(temporal_items_bytes(g));
   l.tcount = take(temporal_count_bytes());
@@ -659,7 +660,7 @@ int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_ho
   } else {
     search = launch_select_temporal(g, ctx->node_map_temporal, at<uint32_t>(ctx, ctx->lay.sel_key_t), target_dev,
                                     at<SelState>(ctx, ctx->lay.sel_t), ctx->sel_t_dirty,
-                                    at<uint32_t>(ctx, ctx->lay.list_key_t), ctx->stream);
+                                    at<uint32_t>(ctx, ctx->lay.list_key_t), at<uint8_t>(ctx, ctx->lay.list_w_t), ctx->stream);
     ctx->sel_t_dirty = true;
     ctx->search_t = search;
     ctx->tau_t_pending = tau_out_host == nullptr;

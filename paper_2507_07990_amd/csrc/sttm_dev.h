@@ -395,9 +395,9 @@ __device__ inline void wave_lds_fence() {
 // histogram of kSelBins bins (sel_bin); the bin in which K exceeds the target is picked from that, and of the few values
 // in that bin the one is found exactly.
 constexpr int kSelBins = 2048;
-// The bin of a value, by its key: any function that never decreases would do. Equal steps in the logarithm of 1.125 - v,
-// 512 to the octave: 2.4e-4 wide at v = 1, where the similarities of still scenes crowd, 1e-3 at a half, 2e-3 at zero,
-// everything below -0.9 together.
+// The bin of a value, by its key: any function that never decreases would do. Equal steps in the logarithm of
+// 1 + 2^-14 - v, 128 to the octave: 5e-7 wide at v = 1, where the similarities of still scenes crowd, 6e-5 at 0.99, 4e-3 at
+// a half, 8e-3 below zero.
 __device__ inline unsigned sel_bin(uint32_t key);
 // What the first pass over a large input found.
 struct SelFound {
@@ -509,8 +509,8 @@ __device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long
 }
 
 __device__ inline unsigned sel_bin(uint32_t key) {
-  const float t = 1.125f - key_float(key);  // (at least 0.125: similarities are at most 1)
-  return 2047u - (unsigned)min(max((int)(__float_as_uint(t) - 0x3e000000u) >> 14, 0), 2047);
+  const float t = 1.00006103515625f - key_float(key);  // (at least 2^-14: similarities are at most 1)
+  return 2047u - (unsigned)min(max((int)(__float_as_uint(t) - 0x38800000u) >> 16, 0), 2047);
 }
 
 // A budget search that the kernel using its threshold carries out.
@@ -552,7 +552,7 @@ __device__ inline SelFound sel_begin(const Geo& g, int b, const int* target, int
   return fd;
 }
 
-constexpr int kSelList = 2048;  // elements a search keeps in LDS; of more it reads the keys again in every round
+constexpr int kSelList = 4096;  // elements a search keeps in LDS; of more it reads the keys again in every round
 
 // tau of video b, by a workgroup of kSelThreads threads: midpoint between the searched key and the largest key below it.
 // All threads get the value. The range of keys is cut into 256 pieces, of which one is picked, until it is one key: two
@@ -579,18 +579,35 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
   if (fd.rc) return fd.rc == 1 ? 1.f : -2.f;  // uniform over the workgroup
   __syncthreads();
   unsigned kmin = 0xffffffffu, kmax = 0, total = 0;
-#pragma unroll 4
-  for (int j = tid; j < count; j += kSelThreads) {
-    const uint32_t k = keys[j];
-    const unsigned w = k == 0 ? 0u : (weights ? weights[j] : 1u);
+  // every key with its weight from memory, eight loads of either in flight
+  auto read = [&](auto use) {
+    constexpr int kBatch = 8;
+#pragma unroll 1
+    for (int j0 = tid; j0 < count; j0 += kBatch * kSelThreads) {
+      uint32_t k[kBatch];
+      unsigned w[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int j = min(j0 + u * kSelThreads, count - 1);
+        k[u] = keys[j];
+        w[u] = weights ? (unsigned)weights[j] : 1u;
+      }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (j0 + u * kSelThreads < count) use(j0 + u * kSelThreads, k[u], w[u]);
+    }
+  };
+  read([&](int j, uint32_t k, unsigned w) {
     if (j < kSelList) {
       s_key[j] = k;
       s_w[j] = (uint8_t)w;
     }
-    if (k) kmin = min(kmin, k);
+    if (k) {
+      kmin = min(kmin, k);
+      total += w;
+    }
     kmax = max(kmax, k);
-    total += w;
-  }
+  });
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     kmin = min(kmin, (unsigned)__shfl_xor((int)kmin, o, 64));
@@ -611,10 +628,14 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
     const int shift = max(0, 24 - __builtin_clz(z - a));
     hist[tid] = 0;
     __syncthreads();
+    auto count_in = [&](int, uint32_t k, unsigned w) {
+      if (k >= a && k <= z) atomicAdd(&hist[(k - a) >> shift], w);
+    };
+    if (kept) {
 #pragma unroll 2
-    for (int j = tid; j < count; j += kSelThreads) {
-      const uint32_t k = kept ? s_key[j] : keys[j];
-      if (k >= a && k <= z) atomicAdd(&hist[(k - a) >> shift], kept ? (unsigned)s_w[j] : (weights ? (unsigned)weights[j] : 1u));
+      for (int j = tid; j < count; j += kSelThreads) count_in(j, s_key[j], s_w[j]);
+    } else {
+      read(count_in);
     }
     __syncthreads();
     const unsigned h = hist[tid];
@@ -639,10 +660,14 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
   }
   // (an element may still lie below the searched key in its bin)
   unsigned under = 0;
-#pragma unroll 2
-  for (int j = tid; j < count; j += kSelThreads) {
-    const uint32_t k = kept ? s_key[j] : keys[j];
+  auto below = [&](int, uint32_t k, unsigned) {
     if (k < a) under = max(under, k);
+  };
+  if (kept) {
+#pragma unroll 2
+    for (int j = tid; j < count; j += kSelThreads) below(j, s_key[j], 0u);
+  } else {
+    read(below);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) under = max(under, (unsigned)__shfl_xor((int)under, o, 64));
@@ -692,7 +717,7 @@ void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauAr
 SelSearch launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
                                 SelState* state, bool dirty, uint32_t* list_key, uint8_t* list_w, hipStream_t s);
 SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
-                                 SelState* state, bool dirty, uint32_t* list_key, hipStream_t s);
+                                 SelState* state, bool dirty, uint32_t* list_key, uint8_t* list_w, hipStream_t s);
 // Carries a search out now, for a caller who wants the thresholds back.
 // `host_tau` (may be NULL): host memory the device can write, which receives the thresholds as well.
 void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s);

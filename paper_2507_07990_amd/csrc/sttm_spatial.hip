@@ -1006,7 +1006,7 @@ void launch_node_levels(const Geo& g, const int32_t* node_map, uint8_t* node_lev
 #if STTM_PYR_TILES_MAX == 0
 #define STTM_SEL_WHOLE 0
 #else
-#define STTM_SEL_WHOLE kSelList
+#define STTM_SEL_WHOLE 2048
 #endif
 #endif
 constexpr int kSelWhole = STTM_SEL_WHOLE;
@@ -1032,10 +1032,12 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
   const uint32_t* kv = keys + (size_t)b * per_video;
   const int j0 = blockIdx.x * (kPassThreads * kSelPer);
   uint32_t key[kSelPer];
+  unsigned w[kSelPer];
 #pragma unroll
   for (int u = 0; u < kSelPer; ++u) {
     const int j = j0 + u * kPassThreads + tid;
     key[u] = j < per_video ? kv[j] : 0u;
+    w[u] = weights && j < per_video ? weights[(size_t)b * per_video + j] : 1u;
   }
   SelFound fd = sel_begin(g, b, target, base_const, node_map);
   unsigned bin = 0;
@@ -1047,9 +1049,25 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
 #pragma unroll
   for (int u = 0; u < kSelPer; ++u) {
     const unsigned at = key[u] ? sel_bin(key[u]) : kSelBins;
+    if (at < bin) lo = max(lo, key[u]);
     place[u] = 0xffffffffu;
-    if (at == bin) place[u] = atomicAdd(&s_n, 1u);
-    else if (at < bin) lo = max(lo, key[u]);
+    // Equal keys of the wavefront's 64 become one element (for the two most frequent of them): still scenes are full of
+    // them, and so are the scores of a node's descendants, which are the node's.
+    const int lane = tid & 63;
+    unsigned long long todo = __ballot(at == bin);
+#pragma unroll 1
+    for (int it = 0; it < 2 && __popcll(todo) > 8; ++it) {
+      const int leader = __ffsll((long long)todo) - 1;
+      const bool mine = at == bin && key[u] == (uint32_t)__shfl((int)key[u], leader, 64);
+      const unsigned long long m = __ballot(mine);
+      const unsigned sum = __popcll(__ballot(mine && (w[u] & 1))) + 2u * __popcll(__ballot(mine && (w[u] & 2)));
+      if (lane == leader) {
+        place[u] = atomicAdd(&s_n, 1u);
+        w[u] = sum;
+      }
+      todo &= ~m;
+    }
+    if ((todo >> lane) & 1ull) place[u] = atomicAdd(&s_n, 1u);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) lo = max(lo, (unsigned)__shfl_xor((int)lo, o, 64));
@@ -1065,7 +1083,7 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
     if (place[u] == 0xffffffffu) continue;
     const size_t o = (size_t)b * per_video + s_at + place[u];
     list_key[o] = key[u];
-    if (weights) list_w[o] = weights[(size_t)b * per_video + j0 + u * kPassThreads + tid];
+    list_w[o] = (uint8_t)w[u];  // (at most 64 elements of weight 3)
   }
 }
 
@@ -1089,7 +1107,7 @@ static SelSearch launch_select(const Geo& g, const uint32_t* keys, const uint8_t
   hipLaunchKernelGGL(k_select_list, grid, block, 0, s, g, keys, weights, per_video, target, base_const, node_map, st,
                      list_key, list_w);
   q.keys = list_key;
-  q.weights = weights ? list_w : nullptr;
+  q.weights = list_w;
   q.whole = false;
   return q;
 }
@@ -1106,8 +1124,8 @@ SelSearch launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_
 }
 
 SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
-                                 SelState* state, bool dirty, uint32_t* list_key, hipStream_t s) {
-  return launch_select(g, keys, nullptr, select_elements(g, false), target, 0, node_map, state, dirty, list_key, nullptr,
+                                 SelState* state, bool dirty, uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
+  return launch_select(g, keys, nullptr, select_elements(g, false), target, 0, node_map, state, dirty, list_key, list_w,
                        s);
 }
 
