@@ -123,15 +123,11 @@ int sttm_invalidate(sttm_ctx* ctx);
 int sttm_set_match_mode(sttm_ctx* ctx, int mode);
 /* Row order of sttm_reduce and sttm_positions (sttm_order); applies to the calls that follow. */
 int sttm_set_output_order(sttm_ctx* ctx, int order);
-/* level = 1 (the default): the spatial statistics pass also computes x_c(t) . x_c(t+1) for every cell c and frame t
- * (Sec. 3.3 compares the features of overlapping nodes of consecutive frames; where both nodes are single cells
- * that is this dot product), and the temporal pass leaves those pairs out instead of reading both rows again.
- * level = 2: the same also for every 2x2 and 4x4 block (S_n(t) . S_n(t+1), used where both frames keep the same
- * node n at level 1 or 2). level = 0 keeps the two passes separate. Each level makes the statistics pass slower
- * and the temporal pass faster: 1 pays wherever many tokens stay unmerged in space, 2 where many of them merge
- * spatially. (A pass over a 512-frame video, 1 against 2: equal where 45 % of the tokens are kept; at 50 % 0.413 against
- * 0.414 ms, at 40 % 0.404 against 0.399, at 30 % 0.417 against 0.395, at 10 % 0.440 against 0.394. 0 was nowhere the
- * fastest: 0.481, 0.461 and 0.436 at 50, 30 and 10 %.) Results agree to rounding. Takes effect with the next
+/* level = 1 (the default) or 2: the spatial statistics pass also computes S_n(t) . S_n(t+1) for every cell, 2x2 and 4x4
+ * block n and frame t (Sec. 3.3 compares the features of overlapping nodes of consecutive frames; where both frames
+ * keep the same node n at one of these levels that is this dot product), and the temporal pass leaves those pairs out
+ * instead of reading their rows again. (The two values mean the same: without the blocks the statistics pass would take
+ * as long.) level = 0 keeps the two passes separate. Results agree to rounding. Takes effect with the next
  * statistics pass (sttm_spatial_stats / sttm_spatial_quadtree with thresholds). */
 int sttm_set_cell_dots(sttm_ctx* ctx, int level);
 
@@ -156,7 +152,7 @@ int sttm_spatial_quadtree(sttm_ctx* ctx, const void* feats_dev, int dtype, int B
  * one per node (tables PAIR_SIM, BEST_SIM). node_map / node_level as produced by stage 1 (any valid quadtree
  * partition per frame is accepted). Needs the stage-1 statistics of the same feats in the workspace: feats_dev must
  * be the buffer the last statistics pass read (STTM_ERR_STATE otherwise; the norms, the sums of large nodes and the
- * cell-to-cell dot products come from that pass). Asynchronous. */
+ * frame-to-frame dot products come from that pass). Asynchronous. */
 int sttm_temporal_stats(sttm_ctx* ctx, const void* feats_dev, const int32_t* node_map_dev,
                         const uint8_t* node_level_dev);
 

@@ -221,8 +221,8 @@ struct sttm_ctx {
   bool tau_s_pending = false, tau_t_pending = false;  // a budget search was left to the kernel that uses its threshold:
   SelSearch search_s{}, search_t{};                   // this one
   int match_mode = STTM_MATCH_FIRST_PASSING, order = STTM_ORDER_RASTER;
-  int cell_dots = 1;       // setting: the spatial pass also emits frame-to-frame dot products (0 no, 1 cells, 2 + 2x2 / 4x4 blocks)
-  int have_cell_dots = 0;  // what the statistics in the workspace were computed with
+  bool cell_dots = true;        // setting: the spatial pass also emits frame-to-frame dot products
+  bool have_cell_dots = false;  // what the statistics in the workspace were computed with
   const int32_t* cluster_ids_reduced = nullptr;  // cluster ids of the last reduce call (NULL: none since the shape was bound)
   bool reduced_zscan = false;
   const void* feats_spatial = nullptr;
@@ -354,7 +354,7 @@ int after_launch(sttm_ctx* c) { return hip_check(c, hipGetLastError(), "kernel l
 int run_spatial_stats(sttm_ctx* c, const void* feats) {
   {
     Timed t(c, STTM_KERNEL_PYRAMID_STATS);
-    launch_pyramid_stats(c->g, feats, c->g.T > 1 ? c->cell_dots : 0, at<float>(c, c->lay.part),
+    launch_pyramid_stats(c->g, feats, c->g.T > 1 && c->cell_dots, at<float>(c, c->lay.part),
                          at<float>(c, c->lay.nsum), at<SelState>(c, c->lay.sel_s), c->stream);
   }
   launch_spatial_finalize(c->g, at<float>(c, c->lay.part), at<float>(c, c->lay.nsum),
@@ -368,7 +368,7 @@ int run_spatial_stats(sttm_ctx* c, const void* feats) {
     c->have_spatial = true;
     c->have_temporal = false;
     c->feats_spatial = feats;
-    c->have_cell_dots = c->g.T > 1 ? c->cell_dots : 0;
+    c->have_cell_dots = c->g.T > 1 && c->cell_dots;
   }
   return rc;
 }
@@ -380,7 +380,7 @@ int run_temporal_stats(sttm_ctx* c, const void* feats, const int32_t* node_map, 
                          at<float>(c, c->lay.pd_part), at<SelState>(c, c->lay.sel_t), at<char>(c, c->lay.titems),
                          at<int>(c, c->lay.tcount), c->stream);
   }
-  launch_temporal_resolve(c->g, c->match_mode, c->have_cell_dots == 2 ? 2 : 0, node_map, node_level,
+  launch_temporal_resolve(c->g, c->match_mode, node_map, node_level,
                           at<float>(c, c->lay.pd_part),
                           c->have_cell_dots ? at<float>(c, c->lay.part) : nullptr, at<float>(c, c->lay.nrm2),
                           at<float>(c, c->lay.sig), at<float>(c, c->lay.e), at<uint32_t>(c, c->lay.sel_key_t),
@@ -481,7 +481,7 @@ int sttm_invalidate(sttm_ctx* ctx) {
   if (!ctx) return STTM_ERR_NULL;
   ctx->have_spatial = ctx->have_tau_s = ctx->have_temporal = ctx->have_tau_t = false;
   ctx->tau_s_pending = ctx->tau_t_pending = false;
-  ctx->have_cell_dots = 0;
+  ctx->have_cell_dots = false;
   ctx->feats_spatial = nullptr;
   ctx->node_map_temporal = nullptr;
   ctx->cluster_ids_reduced = nullptr;
@@ -500,7 +500,7 @@ int sttm_set_match_mode(sttm_ctx* ctx, int mode) {
 int sttm_set_cell_dots(sttm_ctx* ctx, int on) {
   if (!ctx) return STTM_ERR_NULL;
   if (on < 0 || on > 2) return fail(ctx, STTM_ERR_ARG, "cell dots: 0, 1 or 2");
-  ctx->cell_dots = on;  // takes effect with the next spatial statistics pass
+  ctx->cell_dots = on > 0;  // takes effect with the next spatial statistics pass
   return STTM_OK;
 }
 

@@ -684,9 +684,8 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
 // ---- launchers (defined in the .hip files; all asynchronous on `s`) ------------------------------------
 
 // `sel`: the spatial search states [B]; cleared by the statistics pass, the histogram filled by the finalize kernel.
-// `cell_dots`: 1 = also leave x_c(t) . x_c(t+1) of every cell in `part` (the temporal stage then skips those pairs);
-// 2 = and S_n(t) . S_n(t+1) of every 2x2 and 4x4 block n.
-void launch_pyramid_stats(const Geo& g, const void* feats, int cell_dots, float* part, float* nsum, SelState* sel,
+// `pairs`: also leave S_n(t) . S_n(t+1) of every cell, 2x2 and 4x4 block n in `part` (the temporal stage then skips those).
+void launch_pyramid_stats(const Geo& g, const void* feats, bool pairs, float* part, float* nsum, SelState* sel,
                           hipStream_t s);
 // The counters of the temporal pass's work queues. They are empty when the pass begins: the spatial stage clears them, and
 // so does the pass itself when it is over. (Not by a memset when a shape is bound: one recorded into a graph has given
@@ -725,11 +724,11 @@ void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float*
 int select_elements(const Geo& g, bool spatial);
 inline size_t select_state_bytes(int B) { return (size_t)B * sizeof(SelState); }
 // `sel`: the temporal search states [B]; cleared here, the histogram filled by launch_temporal_resolve.
-// `skip_same`: 0 = every pair is computed here; 1 = pairs of two single cells are left out, 2 = also pairs of the same
-// 2x2 or 4x4 block in both frames (their dot products are in the spatial pass's `part`).
+// `skip_same`: pairs of the same cell, 2x2 or 4x4 block in both frames are left out (their dot products are in the
+// spatial pass's `part`).
 // `items` (temporal_items_bytes() of them) / `item_count`: the work queues of the pass (see temporal_clear).
 void launch_temporal_dots(const Geo& g, const void* feats, const uint8_t* node_level, const float* nsum,
-                          int skip_same, float* pd_part, SelState* sel, void* items, int* item_count,
+                          bool skip_same, float* pd_part, SelState* sel, void* items, int* item_count,
                           hipStream_t s);
 size_t temporal_items_bytes(const Geo& g);
 size_t temporal_count_bytes();
@@ -755,9 +754,8 @@ inline __host__ __device__ int unit_rows(const Geo& g) { return (g.H + 7) >> 3; 
 // fp32 sums of the pyramid nodes at levels >= 3: [F][nsum_nodes][D]
 inline size_t nsum_nodes(const Geo& g) { return g.L >= 3 ? (size_t)(g.NN - g.lvl_base[3]) : 0; }
 // `match`: destination rule (0 = top-left-most passing, 1 = the one under the top-left cell only, 2 = most similar).
-// `cell_part`: the spatial pass's `part` when it holds frame-to-frame dot products (else NULL), `same_level`: of the
-// same node in both frames up to this level (0 = single cells only, 2 = up to 4x4 blocks).
-void launch_temporal_resolve(const Geo& g, int match, int same_level, const int32_t* node_map, const uint8_t* node_level,
+// `cell_part`: the spatial pass's `part` when it holds frame-to-frame dot products (else NULL).
+void launch_temporal_resolve(const Geo& g, int match, const int32_t* node_map, const uint8_t* node_level,
                              const float* pd_part, const float* cell_part, const float* nrm2, float* sig, float* e,
                              uint32_t* sel_key, SelState* sel, int* item_count, hipStream_t s);
 void launch_temporal_parent(const Geo& g, int match, const int32_t* node_map, const uint8_t* node_level,

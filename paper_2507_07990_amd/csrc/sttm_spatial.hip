@@ -154,7 +154,7 @@ static unsigned pyramid_grid(const Geo& g) {
 // (8 frames of 8x8 tokens, D = 64, fp32: 7.9 us; one image of 24x24, D = 1152: 5.9; 64 frames of 16x16, D = 1152: 15.6,
 // of 13x13, D = 3584: 23.6 and 28.2 by k_pyramid_stats.)
 // ------------------------------------------------------------------------------------------------
-template <int DT, int CC>  // CC: 0 = statistics only, 1 = + cell-to-cell dot products, 2 = + the same for levels 1 and 2
+template <int DT, bool CC>  // CC: with the frame-to-frame dot products of cells, 2x2 blocks and tiles
 __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __restrict__ feats_v,
                                                           float* __restrict__ part, float* __restrict__ nsum,
                                                           SelState* __restrict__ sel) {
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
     if (ragged) tile_mask<DT>(raw, th, tw, act);
     const uint2 ident = R::ident();
     float S1[4][VEC];  // the tile's 2x2 block sums
-    float b4[8];  // the blocks' dot products with the tile, then (CC = 2) with the same blocks of the next frame
+    float b4[8];  // the blocks' dot products with the tile, then with the same blocks of the next frame
     float SN2[VEC], cd[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) b4[i] = 0.f;
@@ -234,19 +234,17 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
             }
             cd[(q1 & 1) * 4 + k] = R::dot(raw[q1 * 4 + k], pr[q1 & 1][k]);
           }
-          if (CC >= 2) {
-            // The same for the tile's 2x2 blocks and for the tile itself: S_n(t) . S_n(t+1), what the temporal
-            // stage needs where both frames keep the same node n at level 1 or 2: the block's sum with the sum of the
-            // partner block's four rows, the tile's sum with the sum of the partner blocks.
-            float SN1[VEC], d1 = 0.f;
-            R::sum4(ident, pr[q1 & 1], SN1);
+          // The same for the tile's 2x2 blocks and for the tile itself: S_n(t) . S_n(t+1), what the temporal
+          // stage needs where both frames keep the same node n at level 1 or 2: the block's sum with the sum of the
+          // partner block's four rows, the tile's sum with the sum of the partner blocks.
+          float SN1[VEC], d1 = 0.f;
+          R::sum4(ident, pr[q1 & 1], SN1);
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-              d1 = fmaf(S1[q1][v], SN1[v], d1);
-              SN2[v] += SN1[v];
-            }
-            b4[4 + q1] = d1;
+          for (int v = 0; v < VEC; ++v) {
+            d1 = fmaf(S1[q1][v], SN1[v], d1);
+            SN2[v] += SN1[v];
           }
+          b4[4 + q1] = d1;
         }
       }
       if (CC && has_next) {
@@ -259,7 +257,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
 #pragma unroll
       for (int v = 0; v < VEC; ++v) b4[q1] = fmaf(S1[q1][v], S2[v], b4[q1]);
     }
-    if (CC >= 2 && has_next) {
+    if (CC && has_next) {
       float t8[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) t8[i] = 0.f;
@@ -286,10 +284,10 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
       } else if (r < 40) {  // a 2x2 block's row: dot with the tile, or with the next frame
         const int q1 = r & 3;
         live = (q1 >> 1) * 2 < th && (q1 & 1) * 2 < tw;
-        live = live && (r < 36 ? 1 < L : (CC >= 2 && has_next));
+        live = live && (r < 36 ? 1 < L : has_next);
         dst = r < 36 ? q2 * kTileRows + 32 + q1 : kUnitNodeDots + q2 * 8 + q1;
       } else {  // the tile with the next frame's
-        live = CC >= 2 && has_next;
+        live = has_next;
         dst = kUnitNodeDots + q2 * 8 + 4;
       }
       st[dst] = live ? staged_row_sum(tbs, r) : 0.f;
@@ -344,8 +342,8 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
 // eight partial sums per scalar, which go through a small LDS area ([scalar][8]) to the lane that adds them up.
 // Scalars: the squared norm of every cell, and for every node below the root the dot product of its sum
 // with its parent's sum. (The squared norm of a parent is the sum of its children's dot products with it,
-// which the finalize kernel adds up.) With CC also x_c(t) . x_c(t+1) of the cells (the dot products the temporal stage
-// needs where both frames keep single cells), with CC = 2 the same of the 2x2 blocks and of the tiles.
+// which the finalize kernel adds up.) With CC also x_c(t) . x_c(t+1) of the cells and the same of the 2x2 blocks and the
+// tiles: what the temporal stage needs where both frames keep the same node.
 // A row is read once: the next frame's rows, wanted for those products, are the next step's own. Six places of four rows
 // (one 2x2 block each) hold the frame's blocks and, two blocks ahead of the arithmetic, the next frame's; a block that is
 // done with gives its place to the one six further on, so that the places' roles come round every three frames, which are
@@ -398,7 +396,7 @@ __device__ __forceinline__ void stage1(float* tbs, int row, int lane, float v) {
   if ((lane & 7) == 0) tbs[row * kStageStride + (lane >> 3)] = v;
 }
 
-template <int DT, int CC>  // CC: 0 = statistics only, 1 = + cell-to-cell dot products, 2 = + the same for levels 1 and 2
+template <int DT, bool CC>  // CC: with the frame-to-frame dot products of cells, 2x2 blocks and tiles
 __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __restrict__ feats_v,
                                                           float* __restrict__ part, float* __restrict__ nsum,
                                                           SelState* __restrict__ sel, int segs) {
@@ -408,7 +406,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
   __shared__ __attribute__((aligned(16))) float stage[4][kStageRows * kStageStride];
   __shared__ __attribute__((aligned(16))) float st[3][kUnitScalars];
   __shared__ __attribute__((aligned(16))) float4 tsum[2][4][VEC / 4][64];  // the four tiles' sums
-  __shared__ float4 early[CC >= 2 ? 4 : 1][2][VEC / 4][64];  // sums of a tile's first two blocks, when registers are short
+  __shared__ float4 early[CC ? 4 : 1][2][VEC / 4][64];  // sums of a tile's first two blocks, when registers are short
   const int H = g.H, W = g.W, L = g.L;
   const int UX = unit_cols(g), NU = UX * unit_rows(g), tid = threadIdx.x, lane = tid & 63;
   int rest = blockIdx.x;
@@ -468,10 +466,10 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
   } else if (r < 40) {  // a 2x2 block's row: dot with the tile, or with the next frame
     const int q1 = r & 3;
     live = (q1 >> 1) * 2 < th && (q1 & 1) * 2 < tw;
-    live = live && (r < 36 ? 1 < L : CC >= 2);
+    live = live && (r < 36 ? 1 < L : CC);
     dst = r < 36 ? q2 * kTileRows + 32 + q1 : kUnitNodeDots + q2 * 8 + q1;
   } else {  // the tile with the next frame's
-    live = CC >= 2;
+    live = CC;
   }
 
   // The second half of a frame, by all four wavefronts: the unit's sum, the tiles' dot products with it.
@@ -530,7 +528,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
       const bool has_next = CC && after > 0;
       const Window w1 = make_window(rows1, frame_bytes), w2 = make_window(rows2, frame_bytes);
       float S1[4][VEC], S2[VEC];  // the tile's 2x2 block sums, its sum
-      float b4[8];  // the blocks' dot products with the tile, then (CC = 2) with the same blocks of the next frame
+      float b4[8];  // the blocks' dot products with the tile, then with the same blocks of the next frame
       float SN2[VEC], cd[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) b4[i] = 0.f;
@@ -551,7 +549,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
           stage8(tbs, q1, lane, nd);
 #pragma unroll
           for (int v = 0; v < VEC; ++v) S2[v] += S1[q1][v];
-          if (CC >= 2 && q1 < 2) {
+          if (CC && q1 < 2) {
 #pragma unroll
             for (int v = 0; v < VEC; v += 4)
               early[q2][q1][v / 4][lane] = make_float4(S1[q1][v], S1[q1][v + 1], S1[q1][v + 2], S1[q1][v + 3]);
@@ -559,16 +557,14 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
           if (CC && has_next) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) cd[(q1 & 1) * 4 + k] = R::dot(own[k], nxt[k]);
-            if (CC >= 2) {
-              float SN1[VEC], d1 = 0.f;
-              R::sum4(ident, nxt, SN1);
+            float SN1[VEC], d1 = 0.f;
+            R::sum4(ident, nxt, SN1);
 #pragma unroll
-              for (int v = 0; v < VEC; ++v) {
-                d1 = fmaf(S1[q1][v], SN1[v], d1);
-                SN2[v] += SN1[v];
-              }
-              b4[4 + q1] = d1;
+            for (int v = 0; v < VEC; ++v) {
+              d1 = fmaf(S1[q1][v], SN1[v], d1);
+              SN2[v] += SN1[v];
             }
+            b4[4 + q1] = d1;
           }
         }
         // the block's rows are done with: their place goes to the block kWalkSlots further on
@@ -577,7 +573,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
       }
 #pragma unroll
       for (int q1 = 0; q1 < 4; ++q1) {
-        if (CC >= 2 && q1 < 2) {
+        if (CC && q1 < 2) {
           if ((q1 & 1) * 2 >= tw) continue;  // (no such block, nothing was kept)
 #pragma unroll
           for (int v = 0; v < VEC; v += 4) {
@@ -589,7 +585,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
           for (int v = 0; v < VEC; ++v) b4[q1] = fmaf(S1[q1][v], S2[v], b4[q1]);
         }
       }
-      if (CC >= 2 && has_next) {
+      if (CC && has_next) {
         float t = 0.f;
 #pragma unroll
         for (int v = 0; v < VEC; ++v) t = fmaf(S2[v], SN2[v], t);
@@ -630,8 +626,8 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
 }
 
 // Up to this many (unit, chunk, frame) triples the pass is given to k_pyramid_tiles, beyond it to k_pyramid_stats, whose
-// runs get too short below: 2800 triples (100 frames of 13x13, D = 3584) 34 against 38 us, 3072 (256 of 16x16, D = 1152,
-// CC = 2) 43 and 43, 4200 (150 of 13x13) 54 and 53, 5600 69 and 66, 9600 (800 of 16x16) 125 and 110.
+// runs get too short below: 2800 triples (100 frames of 13x13, D = 3584) 34 against 38 us, 3072 (256 of 16x16, D = 1152)
+// 43 and 43, 4200 (150 of 13x13) 54 and 53, 5600 69 and 66, 9600 (800 of 16x16) 125 and 110.
 // Without frame-to-frame products nothing is read twice, and k_pyramid_tiles needs 95 registers, for five wavefronts per
 // SIMD: it takes all (128 images of 24x24, D = 1152: 40 against 54 us; 512 frames of 13x13, D = 3584: 127 and 146).
 // (The host-thread build of the tests sets 0, for k_pyramid_stats on inputs that are small enough for it.)
@@ -640,13 +636,13 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
 #endif
 constexpr long long kPyrTilesMax = STTM_PYR_TILES_MAX;
 
-template <int DT, int CC>
+template <int DT, bool CC>
 static void launch_pyramid_dt(const Geo& g, const void* feats, float* part, float* nsum, SelState* sel, hipStream_t s) {
   const int NU = unit_cols(g) * unit_rows(g);
   // Without the frame-to-frame products no two workgroups share rows: a plain grid, dealt to all dies in turn. (In ranges
   // of frames per die one image is one die's work: 32x32 tokens at D = 8192, fp32, 34.8 against 11.0 us.)
   const dim3 grid = CC ? dim3(pyramid_grid(g)) : dim3(g.nC, NU, g.F);
-  if constexpr (CC > 0 || kPyrTilesMax == 0) {
+  if constexpr (CC || kPyrTilesMax == 0) {
     const long long frame_bytes = (long long)g.HW * g.D * (g.dtype == 0 ? 4 : 2);  // (a window's offsets are 32 bits wide)
     if ((long long)NU * g.F * g.nC > kPyrTilesMax && frame_bytes < 1ll << 31) {
       const int segs = walk_segments(g);
@@ -658,18 +654,17 @@ static void launch_pyramid_dt(const Geo& g, const void* feats, float* part, floa
   hipLaunchKernelGGL((k_pyramid_tiles<DT, CC>), grid, dim3(256), 0, s, g, feats, part, nsum, sel);
 }
 
-template <int CC>
+template <bool CC>
 static void launch_pyramid_cc(const Geo& g, const void* feats, float* part, float* nsum, SelState* sel, hipStream_t s) {
   if (g.dtype == 1) launch_pyramid_dt<1, CC>(g, feats, part, nsum, sel, s);
   else if (g.dtype == 2) launch_pyramid_dt<2, CC>(g, feats, part, nsum, sel, s);
   else launch_pyramid_dt<0, CC>(g, feats, part, nsum, sel, s);
 }
 
-void launch_pyramid_stats(const Geo& g, const void* feats, int cell_dots, float* part, float* nsum, SelState* sel,
+void launch_pyramid_stats(const Geo& g, const void* feats, bool pairs, float* part, float* nsum, SelState* sel,
                           hipStream_t s) {
-  if (cell_dots >= 2) launch_pyramid_cc<2>(g, feats, part, nsum, sel, s);
-  else if (cell_dots == 1) launch_pyramid_cc<1>(g, feats, part, nsum, sel, s);
-  else launch_pyramid_cc<0>(g, feats, part, nsum, sel, s);
+  if (pairs) launch_pyramid_cc<true>(g, feats, part, nsum, sel, s);
+  else launch_pyramid_cc<false>(g, feats, part, nsum, sel, s);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -39,7 +39,7 @@ __device__ inline void block_sum16(const typename Row<DT>::Elem* fb, int D, int 
 //  * J <= 1 ("fast"): aligned 2x2 regions in which both frames' nodes are single cells or the 2x2 block; four
 //    regions per item.
 //  * J == 2 ("mid"): one 4x4 block per item.
-//    With `skip_same` the regions (1: of single cells; 2: also 2x2 and 4x4 blocks) that are the same node
+//    With `skip_same` the regions (of single cells, 2x2 and 4x4 blocks) that are the same node
 //    in both frames are left out: the spatial pass has already formed those dot products (k_temporal_resolve
 //    reads them from its table).
 //  * J >= 3 ("big"): the coarse sum is not recomputed: the spatial pass left the per-channel sums of all nodes
@@ -87,7 +87,7 @@ __host__ __device__ inline int temporal_queue_items(const Geo& g) {
 __device__ inline int temporal_queue_of(const Geo& g, int f) { return f / ((g.F + kTQueues - 1) / kTQueues); }
 
 
-__global__ __launch_bounds__(256) void k_temporal_plan(Geo g, const uint8_t* __restrict__ node_level, int skip_same,
+__global__ __launch_bounds__(256) void k_temporal_plan(Geo g, const uint8_t* __restrict__ node_level, bool skip_same,
                                                        TItem* __restrict__ items, int* __restrict__ count,
                                                        SelState* __restrict__ sel) {
   __shared__ uint8_t lvl_t[1024], lvl_p[1024];
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256) void k_temporal_plan(Geo g, const uint8_t* __r
     const bool join_head = !(y & ((1 << J) - 1)) && !(x & ((1 << J) - 1));
     // (where both frames keep the same node at a level <= 2 there is nothing to do when the spatial pass left
     // those dot products)
-    const bool same_done = a == bb && (skip_same >= 2 || (skip_same == 1 && a == 0));
+    const bool same_done = skip_same && a == bb;
     if (J <= 1) {
       if (!(y & 1) && !(x & 1) && !same_done) fast[atomicAdd(&nfast, 1)] = (int16_t)c;
     } else if (J == 2) {
@@ -489,7 +489,7 @@ size_t temporal_items_bytes(const Geo& g) { return (size_t)kTQueues * temporal_q
 size_t temporal_count_bytes() { return (size_t)kTQueues * kTCountStride * sizeof(int); }
 
 void launch_temporal_dots(const Geo& g, const void* feats, const uint8_t* node_level, const float* nsum,
-                          int skip_same, float* pd_part, SelState* sel, void* items, int* item_count,
+                          bool skip_same, float* pd_part, SelState* sel, void* items, int* item_count,
                           hipStream_t s) {
   TItem* q = reinterpret_cast<TItem*>(items);
   hipLaunchKernelGGL(k_temporal_plan, dim3(g.F), dim3(256), 0, s, g, node_level, skip_same, q, item_count, sel);
@@ -536,7 +536,7 @@ __device__ inline void load_pair_frame(const Geo& g, int f, const int32_t* node_
 // match = 1 (only the destination under n's top-left cell counts): that pair always lives at n's own top-left
 // cell -- n is the finer node, or the destination there is and shares the corner -- so e_n is that one entry.
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_temporal_resolve(Geo g, int match, int same_level,
+__global__ __launch_bounds__(256) void k_temporal_resolve(Geo g, int match,
                                                           const int32_t* __restrict__ node_map,
                                                           const uint8_t* __restrict__ node_level,
                                                           const float* __restrict__ pd_part,
@@ -568,7 +568,7 @@ __global__ __launch_bounds__(256) void k_temporal_resolve(Geo g, int match, int 
     float dot = 0.f;
     const float* pp = pd_part + (size_t)f * g.nC * HW + c;
     size_t cstride = HW;  // from one chunk's partial to the next
-    if (cell_part && a == b && a <= same_level) {
+    if (cell_part && a == b && a <= 2) {
       // the same node (a cell, a 2x2 or a 4x4 block) in both frames: the spatial pass of frame t-1 left the dot
       // product of its sum with the same node's sum in frame t
       const int y = c / W, x = c - y * W, NU = unit_cols(g) * unit_rows(g);
@@ -606,11 +606,11 @@ __global__ __launch_bounds__(256) void k_temporal_resolve(Geo g, int match, int 
   sel_flush_bins(sel + f / g.T, h0);
 }
 
-void launch_temporal_resolve(const Geo& g, int match, int same_level, const int32_t* node_map,
+void launch_temporal_resolve(const Geo& g, int match, const int32_t* node_map,
                              const uint8_t* node_level,
                              const float* pd_part, const float* cell_part, const float* nrm2, float* sig, float* e,
                              uint32_t* sel_key, SelState* sel, int* item_count, hipStream_t s) {
-  hipLaunchKernelGGL(k_temporal_resolve, dim3(g.F), dim3(256), 0, s, g, match, same_level, node_map, node_level, pd_part,
+  hipLaunchKernelGGL(k_temporal_resolve, dim3(g.F), dim3(256), 0, s, g, match, node_map, node_level, pd_part,
                      cell_part,
                      nrm2, sig, e, sel_key, sel, item_count);
 }
