@@ -554,14 +554,16 @@ __device__ inline SelFound sel_begin(const Geo& g, int b, const int* target, int
 
 constexpr int kSelList = 4096;  // elements a search keeps in LDS; of more it reads the keys again in every round
 
-// tau of video b, by a workgroup of kSelThreads threads: midpoint between the searched key and the largest key below it.
+// tau of video b, by a workgroup of THREADS threads (256 or more): midpoint between the searched key and the largest key below it.
 // All threads get the value. The range of keys is cut into 256 pieces, of which one is picked, until it is one key: two
 // rounds for the elements of a bin, however many of them are equal.
+template <int THREADS>
 __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
   __shared__ uint32_t s_key[kSelList];
   __shared__ uint8_t s_w[kSelList];
-  __shared__ unsigned hist[kSelThreads];
-  __shared__ unsigned wsum[kSelThreads / 64];
+  constexpr int kPieces = 256;
+  __shared__ unsigned hist[kPieces];
+  __shared__ unsigned wsum[kPieces / 64];
   __shared__ unsigned s_lo, s_not_min, s_max, s_total, s_piece, s_acc;  // (s_not_min: the complement of the smallest key)
   const uint32_t* keys = q.keys + (size_t)b * q.per_video;
   const uint8_t* weights = q.weights ? q.weights + (size_t)b * q.per_video : nullptr;
@@ -583,18 +585,18 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
   auto read = [&](auto use) {
     constexpr int kBatch = 8;
 #pragma unroll 1
-    for (int j0 = tid; j0 < count; j0 += kBatch * kSelThreads) {
+    for (int j0 = tid; j0 < count; j0 += kBatch * THREADS) {
       uint32_t k[kBatch];
       unsigned w[kBatch];
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
-        const int j = min(j0 + u * kSelThreads, count - 1);
+        const int j = min(j0 + u * THREADS, count - 1);
         k[u] = keys[j];
         w[u] = weights ? (unsigned)weights[j] : 1u;
       }
 #pragma unroll
       for (int u = 0; u < kBatch; ++u)
-        if (j0 + u * kSelThreads < count) use(j0 + u * kSelThreads, k[u], w[u]);
+        if (j0 + u * THREADS < count) use(j0 + u * THREADS, k[u], w[u]);
     }
   };
   read([&](int j, uint32_t k, unsigned w) {
@@ -626,29 +628,29 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
 #pragma unroll 1
   while (a != z) {
     const int shift = max(0, 24 - __builtin_clz(z - a));
-    hist[tid] = 0;
+    if (tid < kPieces) hist[tid] = 0;
     __syncthreads();
     auto count_in = [&](int, uint32_t k, unsigned w) {
       if (k >= a && k <= z) atomicAdd(&hist[(k - a) >> shift], w);
     };
     if (kept) {
 #pragma unroll 2
-      for (int j = tid; j < count; j += kSelThreads) count_in(j, s_key[j], s_w[j]);
+      for (int j = tid; j < count; j += THREADS) count_in(j, s_key[j], s_w[j]);
     } else {
       read(count_in);
     }
     __syncthreads();
-    const unsigned h = hist[tid];
+    const unsigned h = tid < kPieces ? hist[tid] : 0u;
     unsigned inc = h;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const unsigned t = __shfl_up(inc, o, 64);
       if (lane >= o) inc += t;
     }
-    if (lane == 63) wsum[wave] = inc;
+    if (lane == 63 && tid < kPieces) wsum[wave] = inc;
     __syncthreads();
     unsigned ex = inc - h;
-    for (int w = 0; w < wave; ++w) ex += wsum[w];
+    for (int w = 0; w < min(wave, kPieces / 64); ++w) ex += wsum[w];
     if (ex <= room && ex + h > room) {
       s_piece = (unsigned)tid;
       s_acc = ex;
@@ -665,7 +667,7 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
   };
   if (kept) {
 #pragma unroll 2
-    for (int j = tid; j < count; j += kSelThreads) below(j, s_key[j], 0u);
+    for (int j = tid; j < count; j += THREADS) below(j, s_key[j], 0u);
   } else {
     read(below);
   }

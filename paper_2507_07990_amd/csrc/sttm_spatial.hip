@@ -930,7 +930,7 @@ __global__ __launch_bounds__(kSelThreads) void k_spatial_decide(Geo g, const flo
   const int b = blockIdx.y, per_video = g.T * g.HW;
   float t;
   if (pending.states || given.n) {  // the budget search was left to this kernel, or the caller named the threshold
-    t = given.n ? given.v[b] : sel_threshold(g, pending, b);
+    t = given.n ? given.v[b] : sel_threshold<kSelThreads>(g, pending, b);
     if (blockIdx.x == 0 && threadIdx.x == 0) tau[b] = t;
   } else {
     t = tau[b];
@@ -1085,7 +1085,7 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
 // The whole search as a launch of its own (when the caller wants the threshold back).
 __global__ __launch_bounds__(kSelThreads) void k_select_tau(Geo g, SelSearch search, float* __restrict__ tau,
                                                             float* __restrict__ host_tau) {
-  const float t = sel_threshold(g, search, blockIdx.x);
+  const float t = sel_threshold<kSelThreads>(g, search, blockIdx.x);
   if (threadIdx.x == 0) {
     tau[blockIdx.x] = t;
     if (host_tau) host_tau[blockIdx.x] = t;

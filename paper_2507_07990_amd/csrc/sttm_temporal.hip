@@ -510,7 +510,7 @@ __device__ inline int node_idx_of(const Geo& g, int lvl, int y0, int x0) {
   return node_index(g, lvl, y0 >> lvl, x0 >> lvl);
 }
 
-// Per-frame view of the two partitions in LDS, shared by the two kernels below.
+// Per-frame view of the two partitions in LDS.
 struct PairFrame {
   uint8_t lvl_t[1024], lvl_p[1024];
   int16_t rep_t[1024], rep_p[1024];
@@ -616,83 +616,121 @@ void launch_temporal_resolve(const Geo& g, int match, const int32_t* node_map,
 }
 
 // ------------------------------------------------------------------------------------------------
-// k_temporal_parent: directed edge of every kept node (Sec. 3.3). Among the destinations whose similarity
-// exceeds tau_T: the one towards the top-left (smallest raster index; integer min in LDS) -- or, by `match`,
-// only the one under the node's top-left cell, or the most similar one (64-bit integer max in LDS over
-// (similarity image, reversed raster index), so ties go towards the top-left). Also seeds the
-// pointer-jumping array.
+// k_temporal_parent: directed edge of every kept node (Sec. 3.3), one workgroup per run of frames of a video. Among the
+// destinations whose similarity exceeds tau_T: the one towards the top-left (smallest raster index; integer min in LDS) --
+// or, by `match`, only the one under the node's top-left cell, or the most similar one (64-bit integer max in LDS over
+// (similarity image, reversed raster index), so ties go towards the top-left). A chain is followed through the run's frames
+// in LDS right away, so that the jumps over memory below go from run to run: `ptr` of a node is its root, or the node of
+// the frame before the run that its chain leaves the run by.
+// (With one frame to a workgroup everywhere, and a launch more for the first 23 hops of every chain, these kernels took, us:
+// 64 frames of 13x13 15.3, now 12.8, 32 videos of 32 frames of 27x27 22.0 and 16.7, 96 frames of 11x19 12.6 and 9.7, six
+// clips of 25 frames 13.2 and 9.2. Runs of 23 frames for 512 frames: 25 against 18, too few workgroups.)
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kSelThreads) void k_temporal_parent(Geo g, int match, const int32_t* __restrict__ node_map,
-                                                         const uint8_t* __restrict__ node_level,
-                                                         const float* __restrict__ sig,
-                                                         float* __restrict__ tau, TauArgs given,
-                                                         SelSearch pending,
-                                                         int32_t* __restrict__ parent, int32_t* __restrict__ ptr) {
-  __shared__ PairFrame pf;
-  __shared__ int par[1024];
-  __shared__ unsigned long long best[1024];
-  const int f = blockIdx.x, HW = g.HW;
+constexpr int kParThreads = 1024;  // of a workgroup with more than one frame
+constexpr int kParCells = 2048;  // cells of a run of more than one frame at most
+constexpr int kHops = 23;        // edges that one launch below follows
+// Frames of a run: as many as it takes for the runs of a video to be crossed by one launch, if that is few.
+static int parent_run(const Geo& g) {
+  const int needed = (g.T + kHops - 1) / kHops;
+  return needed * g.HW <= kParCells ? needed : 1;
+}
+static size_t parent_lds(const Geo& g, int run, int match) {
+  const size_t cells = (size_t)run * g.HW;
+  return cells * (match == 2 ? 8 : 4) + (cells + g.HW) * 3 + 16;
+}
+
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_temporal_parent(Geo g, int match, int run, int runs,
+                                                                 const int32_t* __restrict__ node_map,
+                                                                 const uint8_t* __restrict__ node_level,
+                                                                 const float* __restrict__ sig,
+                                                                 float* __restrict__ tau, TauArgs given,
+                                                                 SelSearch pending,
+                                                                 int32_t* __restrict__ parent, int32_t* __restrict__ ptr) {
+  // dynamic: per cell of the run the chosen destination (its place in the frame before; 64 bits wide with its similarity
+  // when the most similar one is wanted), then of the frame before the run and of the run's own frames the top-left cell
+  // and the level of every cell's node
+  STTM_DYNAMIC_LDS(unsigned long long, sm);
+  const int HW = g.HW, tid = threadIdx.x, b = blockIdx.x / runs, t0 = (blockIdx.x - b * runs) * run;
+  const int frames = min(run, g.T - t0), cells = frames * HW, f0 = b * g.T + t0, i0 = f0 * HW;
+  int* par = reinterpret_cast<int*>(sm);
+  unsigned long long* best = sm;
+  int16_t* rep = reinterpret_cast<int16_t*>(reinterpret_cast<char*>(sm) + (size_t)run * HW * (match == 2 ? 8 : 4));
+  uint8_t* lvl = reinterpret_cast<uint8_t*>(rep + (run + 1) * HW);
   float th;
   if (pending.states || given.n) {  // the budget search was left to this kernel, or the caller named the threshold
-    th = given.n ? given.v[f / g.T] : sel_threshold(g, pending, f / g.T);
-    if (f % g.T == 0 && threadIdx.x == 0) tau[f / g.T] = th;
+    th = given.n ? given.v[b] : sel_threshold<THREADS>(g, pending, b);
+    if (t0 == 0 && tid == 0) tau[b] = th;
   } else {
-    th = tau[f / g.T];
+    th = tau[b];
   }
-  if (f % g.T == 0) {
-    for (int c = threadIdx.x; c < HW; c += blockDim.x) {
-      parent[(size_t)f * HW + c] = -1;
-      ptr[(size_t)f * HW + c] = f * HW + c;
-    }
-    return;
+  for (int q = tid; q < cells + HW; q += THREADS) {  // (cell q of these tables is cell q - HW of the run)
+    if (t0 == 0 && q < HW) continue;
+    const int i = i0 - HW + q, f = i / HW;
+    rep[q] = (int16_t)(node_map[i] - f * HW);
+    lvl[q] = node_level[i];
   }
-  load_pair_frame(g, f, node_map, node_level, pf);
-  for (int c = threadIdx.x; c < HW; c += blockDim.x) {
-    par[c] = 0x7fffffff;
-    best[c] = 0ull;
+  for (int q = tid; q < cells; q += THREADS) {
+    if (match == 2) best[q] = 0ull;
+    else par[q] = 0x7fffffff;
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < HW; c += blockDim.x) {
-    const int a = pf.lvl_t[c], b = pf.lvl_p[c];
-    const int n = pf.rep_t[c], d = pf.rep_p[c];
-    if ((a <= b ? n : d) != c) continue;
-    const float v = sig[(size_t)f * HW + c];
+  for (int q = tid; q < cells; q += THREADS) {
+    const int r = q / HW, c = q - r * HW;
+    if (t0 + r == 0) continue;
+    const int a = lvl[q + HW], bb = lvl[q], n = rep[q + HW], d = rep[q];
+    if ((a <= bb ? n : d) != c) continue;  // not the top-left cell of the finer node
+    const float v = sig[i0 + q];
     if (!(v > th)) continue;
     if (match == 2)
-      atomicMax(&best[n], ((unsigned long long)float_key(v) << 32) | (unsigned)(0x7fffffff - d));
+      atomicMax(&best[r * HW + n], ((unsigned long long)float_key(v) << 32) | (unsigned)(0x7fffffff - d));
     else if (match == 0 || c == n)
-      atomicMin(&par[n], d);
+      atomicMin(&par[r * HW + n], d);
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < HW; c += blockDim.x) {
-    const int i = f * HW + c;
-    int p = -1;
-    if (pf.rep_t[c] == c) {
-      if (match == 2) {
-        if (best[c] != 0ull) p = (f - 1) * HW + (0x7fffffff - (int)(best[c] & 0xffffffffull));
-      } else if (par[c] != 0x7fffffff) {
-        p = (f - 1) * HW + par[c];
+  // the edge a cell's place holds: destination in the frame before, or -1
+  auto edge = [&](int q) {
+    if (match == 2) return best[q] ? 0x7fffffff - (int)(best[q] & 0xffffffffull) : -1;
+    return par[q] != 0x7fffffff ? par[q] : -1;
+  };
+  for (int q = tid; q < cells; q += THREADS) {
+    const int r = q / HW, c = q - r * HW;
+    int p = -1, end = q;
+    if (rep[q + HW] == c) {
+      const int d = edge(q);
+      if (d >= 0) p = i0 + (r - 1) * HW + d;
+      // along the chain until it ends or leaves the run (then `end` is a cell of the frame before the run: negative)
+      for (int h = r, e = d; e >= 0; --h) {
+        end = (h - 1) * HW + e;
+        if (h == 0) break;
+        e = edge(end);
       }
     }
-    parent[i] = p;
-    ptr[i] = p >= 0 ? p : i;
+    parent[i0 + q] = p;
+    ptr[i0 + q] = i0 + end;
   }
 }
 
 void launch_temporal_parent(const Geo& g, int match, const int32_t* node_map, const uint8_t* node_level,
                             const float* sig, float* tau, const TauArgs& given, const SelSearch& pending, int32_t* parent,
                             int32_t* ptr, hipStream_t s) {
-  hipLaunchKernelGGL(k_temporal_parent, dim3(g.F), dim3(kSelThreads), 0, s, g, match, node_map, node_level, sig, tau, given,
-                     pending, parent, ptr);
+  const int run = parent_run(g), runs = (g.T + run - 1) / run;
+  const dim3 grid(g.B * runs);
+  const size_t lds = parent_lds(g, run, match);
+  if (run > 1)
+    hipLaunchKernelGGL(k_temporal_parent<kParThreads>, grid, dim3(kParThreads), lds, s, g, match, run, runs, node_map,
+                       node_level, sig, tau, given, pending, parent, ptr);
+  else
+    hipLaunchKernelGGL(k_temporal_parent<kSelThreads>, grid, dim3(kSelThreads), lds, s, g, match, run, runs, node_map,
+                       node_level, sig, tau, given, pending, parent, ptr);
 }
 
 // ------------------------------------------------------------------------------------------------
-// Common root of every chain by pointer jumping (root finding of Sec. 3.3): every edge points one
-// frame back, so a chain has at most T-1 edges; each launch multiplies the reach by kHops.
+// Common root of every chain by pointer jumping (root finding of Sec. 3.3): every pointer is a root or leads to the run of
+// frames before; each launch multiplies the reach by kHops.
 // ------------------------------------------------------------------------------------------------
 // One launch follows up to kHops edges of the previous array, i.e. multiplies the reach by kHops; a walk stops at a
 // root (an entry that points to itself), so short chains cost a load or two.
-constexpr int kHops = 23;
 __global__ __launch_bounds__(256) void k_root_jump(int n, const int32_t* __restrict__ src,
                                                    int32_t* __restrict__ dst) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -723,8 +761,11 @@ __global__ __launch_bounds__(256) void k_root_jump_cells(int n, int hops, const 
 
 void launch_roots(const Geo& g, int32_t* ptr_a, int32_t* ptr_b, const int32_t* node_map, int32_t* cluster_ids,
                   hipStream_t s) {
-  int rounds = 0;
-  for (long long reach = 1; reach < g.T; reach *= kHops) ++rounds;
+  const int run = parent_run(g), runs = (g.T + run - 1) / run;
+  // a chain crosses every run but the first, where one more step may lead to the root
+  const long long steps = g.T == 1 ? 0 : runs;
+  int rounds = steps > 0;
+  for (long long reach = kHops; reach < steps; reach *= kHops) ++rounds;
   dim3 grid((g.N + 255) / 256), block(256);
   int32_t* src = ptr_a;
   int32_t* dst = ptr_b;

@@ -733,6 +733,44 @@ def test_both_pyramid_kernels_give_the_same_bits(lib, H, W, D, dtype, R, tau_s, 
             assert torch.equal(t_big[b], t_small[0])
 
 
+@pytest.mark.parametrize("match", [0, 1, 2])
+@pytest.mark.parametrize("T", [23, 24, 69, 70, 600])   # runs of 1, 2, 3 and 4 frames, and one frame again (27 * 81 cells)
+def test_edges_and_roots_across_runs_of_frames(lib, T, match):
+    """The edges of a video's first frames do not depend on how many frames follow (and so on the frames a workgroup takes);
+    every cell's cluster is where the edges lead from its node."""
+    import torch
+    H = W = 9
+    D = 16
+    gen = torch.Generator(device="cuda:0").manual_seed(T + match)
+    blocks = torch.randn(2, 1, 3, 3, D, device="cuda:0", generator=gen).repeat_interleave(3, 2).repeat_interleave(3, 3)
+    x = (blocks + 0.35 * torch.randn(2, T, H, W, D, device="cuda:0", generator=gen)).contiguous()
+
+    def edges(v):
+        B, t = v.shape[:2]
+        n = B * t * H * W
+        s = lib.Sttm(0)
+        s.sttm_set_match_mode(match)
+        s.ensure_workspace(B, t, H, W, D, lib.STTM_F32, 1)
+        nm, cl, pa = (torch.empty(n, dtype=torch.int32, device="cuda:0") for _ in range(3))
+        nl = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        s.sttm_spatial_quadtree(v, lib.STTM_F32, B, t, H, W, D, 1, [0.9] * B, nm, nl)
+        s.sttm_temporal_merge(v, nm, nl, [0.82] * B, cl)
+        s.sttm_export(lib.STTM_TBL_PARENT, pa)
+        return [a.cpu().numpy() for a in (nm, cl, pa)]
+
+    nm, cl, pa = edges(x)
+    root = np.where(pa >= 0, pa, np.arange(len(pa)))
+    for _ in range(10):                                      # 2^10 steps
+        root = root[root]
+    np.testing.assert_array_equal(cl, root[nm])
+    assert 0 < (pa >= 0).sum() and len(np.unique(cl)) > 2
+    short, per = min(T, 20), T * H * W
+    for b in range(2):
+        first = edges(x[b:b + 1, :short].contiguous())[2]
+        mine = pa[b * per:b * per + short * H * W]
+        np.testing.assert_array_equal(first, np.where(mine >= 0, mine - b * per, -1))
+
+
 def _searched(values, weights, base, target):
     """The budget rule on fp32 values: midpoint between the first value at which the count exceeds the target and the
     largest value below it."""
