@@ -131,10 +131,10 @@ def main() -> int:
     ap.add_argument("--no-cell-dots", action="store_true",
                     help="keep the spatial and temporal passes separate (sttm_set_cell_dots(0))")
     ap.add_argument("--cell-dots-only", action="store_true",
-                    help="keep the spatial pass to the cell-against-cell products at every budget (default: the 2x2 and "
-                         "4x4 block products ride along too when the budget keeps 35 % of the tokens or less)")
+                    help="sttm_set_cell_dots(1) at every budget (default: 2 where 35 %% of the tokens or less are kept; "
+                         "both mean the same)")
     ap.add_argument("--node-dots", action="store_true",
-                    help="frame-to-frame dot products of the 2x2 and 4x4 blocks in the spatial pass too (sttm_set_cell_dots(2))")
+                    help="sttm_set_cell_dots(2) at every budget")
     ap.add_argument("--no-node-sums", action="store_true",
                     help="reduce stage without the stage-1 partition: every cell is read again")
     ap.add_argument("--no-two-streams", action="store_true",
@@ -191,10 +191,8 @@ def main() -> int:
     s.sttm_set_output_order({"raster": 0, "zscan": 1}[args.order])
 
     def dots_level(keep):
-        """Which frame-to-frame dot products the spatial pass leaves for the temporal stage (sttm_set_cell_dots): the
-        block products (level 2) cost the spatial pass 7 us of the bench workload. Measured there, both levels take the
-        same time at a budget of 45 %, 2 is 1 % faster at 40 %, 3 % at 35 % and 5 % at 30 %; the line is drawn where
-        the gain is clear, since how much merges in space at a given budget differs between videos."""
+        """Which frame-to-frame dot products the spatial pass leaves for the temporal stage (sttm_set_cell_dots): 0 none;
+        1 and 2 mean the same, those of cells and of 2x2 and 4x4 blocks."""
         if args.no_cell_dots:
             return 0
         if args.node_dots:
@@ -404,8 +402,7 @@ def main() -> int:
                                + (f", match={args.match}" if args.match != "first_passing" else "")
                                + (f", order={args.order}" if args.order != "raster" else "")
                                + (", with position indices" if args.positions else "")
-                               + (", separate spatial and temporal passes" if args.no_cell_dots else "")
-                               + (", block dot products in the spatial pass" if head["cell_dots_level"] == 2 else ""),
+                               + (", separate spatial and temporal passes" if args.no_cell_dots else ""),
                    "tokens": N, "kept_tokens": head["kept_tokens"], "kept_fraction": head["kept_fraction"],
                    "generate_s": gen_s, "input_copies": copies},
         "roofline": head["roofline"],

@@ -738,7 +738,7 @@ size_t temporal_count_bytes();
 // as one block of kUnitScalars floats: per 4x4 tile 16 squared norms, 16 cell and 4 level-1 dot products, then the
 // 4 level-2 dot products (padded to whole 128-byte lines), then per tile the 16 dot products of its cells with the
 // same cells of the next frame, then per tile the dot products of its four 2x2 blocks and of the tile itself with the
-// same blocks of the next frame (zeros unless asked for): part[f][chunk][unit][kUnitScalars].
+// same blocks of the next frame (zeros where those products are not formed): part[f][chunk][unit][kUnitScalars].
 constexpr int kUnitScalars = 256;
 constexpr int kUnitCellDots = 160;
 constexpr int kUnitNodeDots = 224;

@@ -360,7 +360,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
 // What bounds it: memory. 512 frames of 13x13 at D = 3584 in bf16, 653 MB read and 44 MB written in 145 us: 138 without
 // the arithmetic, 124 without the stores, 111 without either. 180 frames of 18x24 at D = 8192: 1.31 GB and 79 MB in 255 us
 // (5.4 TB/s). (A wavefront that took a unit's tiles one after the other and asked for the next frame's rows as well, from
-// the cache its neighbour had just filled: 168 and 325 us, 172 with CC = 2 on the former.) The loads are marked
+// the cache its neighbour had just filled: 172 and 325 us.) The loads are marked
 // non-temporal: 158 and 286 us without. Eight places and two wavefronts per SIMD: 147 and 313. Two or three rounds of
 // workgroups with shorter runs read more rows twice: 154 and 161 us.
 // ------------------------------------------------------------------------------------------------

@@ -493,6 +493,7 @@ void launch_temporal_dots(const Geo& g, const void* feats, const uint8_t* node_l
                           hipStream_t s) {
   TItem* q = reinterpret_cast<TItem*>(items);
   hipLaunchKernelGGL(k_temporal_plan, dim3(g.F), dim3(256), 0, s, g, node_level, skip_same, q, item_count, sel);
+  if (g.T == 1) return;  // no pairs (an empty pass over them takes 2.2 us of the 98 of one image of 24x24)
   // enough wavefronts for about four tasks each if every pair came with all the items it can have; whole rounds of dies
   const long long worst = (long long)g.F * temporal_items_per_pair(g) * g.nC;
   long long blocks = (worst + 15) / 16;
