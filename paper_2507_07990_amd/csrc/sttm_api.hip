@@ -387,7 +387,7 @@ int run_temporal_stats(sttm_ctx* c, const void* feats, const int32_t* node_map, 
                           at<SelState>(c, c->lay.sel_t), at<int>(c, c->lay.tcount), c->stream);
   int rc = after_launch(c);
   // the search state of the temporal budget starts afresh with these statistics: a threshold chosen from the
-  // statistics before them (or a last digit still pending) no longer applies
+  // statistics before them (or a search still pending) no longer applies
   c->have_tau_t = c->tau_t_pending = false;
   if (rc == STTM_OK) {
     c->sel_t_dirty = false;

@@ -16,7 +16,7 @@ constexpr int kStageStride = 8;  // floats per staging row: one per group of eig
 // (th, tw >= 1). Every one of the 16 loads is issued, without a condition: a cell beyond the edge, or a lane
 // beyond the last channel, reads a valid cell of the tile again (a cache hit) and tile_mask() discards it. The
 // number of loads in flight is then known at compile time, and the wavefront can wait for this tile's rows
-// while the next tile's are still on their way.
+// while the partner tile's are still on their way.
 template <int DT>
 __device__ __forceinline__ void tile_load(typename Row<DT>::Raw (&raw)[16], const typename Row<DT>::Elem* fbase,
                                           int W, int D, int ty, int tx, int th, int tw) {
@@ -125,9 +125,8 @@ __device__ __forceinline__ void block_stats(uint2 ident, const typename Row<DT>:
 // tile is asked for by two workgroups: its own frame's and the one of the frame before. Workgroups go to the eight dies
 // round-robin by their index; each die gets a contiguous range of frames and walks it in order, two frames at a time
 // with the same (unit, chunk) of both next to each other, so that the two requests come from the same die within a few
-// microseconds of each other and the second one is served by that die's L2. (With frame after frame the 144 workgroups
-// a frame of 18x24 tokens at D = 8192 has lay between the two: 2.44 GB fetched, 357 us; in pairs 331 us. Groups of 4 to
-// 16 frames: 335-345 us, and up to 7 us slower at 512 frames of 13x13, D = 3584, where pairs cost nothing.)
+// microseconds of each other and the second one is served by that die's L2. (180 frames of 18x24 tokens at D = 8192, 144
+// workgroups a frame, frame after frame: 2.44 GB fetched, 357 us; in pairs 331. Groups of 4 to 16 frames: 335-345.)
 constexpr int kPyrGroup = 2;
 __device__ __forceinline__ bool pyramid_place(const Geo& g, int NU, int& f, int& u, int& chunk) {
   const int per_die = (g.F + 7) / 8, die = blockIdx.x & 7;
