@@ -1052,7 +1052,8 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
 #pragma unroll 1
     for (int it = 0; it < 2 && __popcll(todo) > 8; ++it) {
       const int leader = __ffsll((long long)todo) - 1;
-      const bool mine = at == bin && key[u] == (uint32_t)__shfl((int)key[u], leader, 64);
+      const uint32_t leads = (uint32_t)__shfl((int)key[u], leader, 64);  // (by all lanes, whatever their own key)
+      const bool mine = at == bin && key[u] == leads;
       const unsigned long long m = __ballot(mine);
       const unsigned sum = __popcll(__ballot(mine && (w[u] & 1))) + 2u * __popcll(__ballot(mine && (w[u] & 2)));
       if (lane == leader) {

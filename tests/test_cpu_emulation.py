@@ -188,6 +188,19 @@ def test_emulated_walk_through_runs_of_frames(emul, large, seed, B, T, H, W, D, 
             np.testing.assert_array_equal(x, getattr(b, name), err_msg=name)
 
 
+@pytest.mark.parametrize("noise", [0.0, 0.003])
+def test_emulated_search_among_many_elements_of_one_bin(emul, large, noise):
+    """Similarities that crowd in a bin or two, equal ones among them (still content): listing the bin's elements and
+    searching those gives the thresholds, the partition and the clusters that the search of a small input gives."""
+    run_cpu, _ = emul
+    rng = np.random.default_rng(11)
+    feats = (rng.standard_normal(16) + noise * rng.standard_normal((2, 4, 8, 8, 16)).round(1)).astype(np.float32)
+    feats[:, 2] = feats[:, 1]                              # a frame that repeats: its pairs are all alike
+    a, b = (run_cpu.run_cpu(feats, lib=lib, keep=0.4) for lib in (large, run_cpu.load()))
+    for name in ("tau_s", "tau_t", "node_map", "cluster_ids"):
+        np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
+
+
 def test_emulated_kernels_run_clean_under_address_and_undefined_behaviour_sanitizers():
     """The host-thread build with -fsanitize=address,undefined (any report aborts): both dtypes, fixed thresholds and
     a budget, every output in a heap block of its exact size, the workspace of exactly sttm_workspace_bytes(); once
