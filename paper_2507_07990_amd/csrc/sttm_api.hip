@@ -230,7 +230,6 @@ struct sttm_ctx {
   std::vector<float> h_tau_s, h_tau_t;         // host staging that outlives the asynchronous uploads
   std::vector<int> h_target_s, h_target_t;
   bool target_s_on_device = false, target_t_on_device = false;  // the device copy equals the host staging
-  bool sel_s_dirty = false, sel_t_dirty = false;                // searched since the statistics pass
   std::string err;
   // optional per-kernel timing of the three feature passes (HIP events on the context's stream)
   int profiling = 0;  // 0 = off, n = every n-th launch of each feature kernel is bracketed by events
@@ -364,7 +363,6 @@ int run_spatial_stats(sttm_ctx* c, const void* feats) {
                           at<SelState>(c, c->lay.sel_s), at<int>(c, c->lay.tcount), c->stream);
   int rc = after_launch(c);
   if (rc == STTM_OK) {
-    c->sel_s_dirty = false;
     c->have_spatial = true;
     c->have_temporal = false;
     c->feats_spatial = feats;
@@ -390,7 +388,6 @@ int run_temporal_stats(sttm_ctx* c, const void* feats, const int32_t* node_map, 
   // statistics before them (or a search still pending) no longer applies
   c->have_tau_t = c->tau_t_pending = false;
   if (rc == STTM_OK) {
-    c->sel_t_dirty = false;
     c->have_temporal = true;
     c->node_map_temporal = node_map;
   }
@@ -652,16 +649,14 @@ int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_ho
   SelSearch search;
   if (spatial) {
     search = launch_select_spatial(g, at<uint32_t>(ctx, ctx->lay.sel_key_s), at<uint8_t>(ctx, ctx->lay.sel_w_s), target_dev,
-                                   at<SelState>(ctx, ctx->lay.sel_s), ctx->sel_s_dirty,
+                                   at<SelState>(ctx, ctx->lay.sel_s),
                                    at<uint32_t>(ctx, ctx->lay.list_key_s), at<uint8_t>(ctx, ctx->lay.list_w_s), ctx->stream);
-    ctx->sel_s_dirty = true;
     ctx->search_s = search;
     ctx->tau_s_pending = tau_out_host == nullptr;
   } else {
     search = launch_select_temporal(g, ctx->node_map_temporal, at<uint32_t>(ctx, ctx->lay.sel_key_t), target_dev,
-                                    at<SelState>(ctx, ctx->lay.sel_t), ctx->sel_t_dirty,
+                                    at<SelState>(ctx, ctx->lay.sel_t),
                                     at<uint32_t>(ctx, ctx->lay.list_key_t), at<uint8_t>(ctx, ctx->lay.list_w_t), ctx->stream);
-    ctx->sel_t_dirty = true;
     ctx->search_t = search;
     ctx->tau_t_pending = tau_out_host == nullptr;
   }

@@ -404,7 +404,12 @@ struct SelFound {
   unsigned long long budget;  // target - base
   unsigned long long acc;     // weight of the keys in the bins before the picked one
   int rc;                     // 0 = searching, 1 = everything fits (tau = 1), 2 = the base alone exceeds the target
-  int pad;
+  int list;                   // which of the state's two lists holds the elements
+};
+// The list that such a pass makes of the picked bin; the elements themselves lie beside the state.
+struct SelList {
+  unsigned count;
+  unsigned lo;                // the largest key in the bins before the picked one (0 = none)
 };
 // The histogram is fed by hundreds of workgroups whose values may crowd in a few bins; it is kept
 // in kSelCopies copies, one per accelerator die (workgroups go to the dies round-robin by their index), so that
@@ -412,11 +417,15 @@ struct SelFound {
 constexpr int kSelCopies = 8;
 struct alignas(16) SelState {
   unsigned hist0[kSelCopies][kSelBins];  // weight per bin over all elements; the copies add up
-  unsigned count;              // large inputs: elements of the picked bin, listed beside the state
-  unsigned lo;                 // and the largest key in the bins before it (0 = none)
-  unsigned pad0[2];
+  // Large inputs. Every search appends to an empty list, however often it is made on the same statistics, also where it is
+  // replayed from a graph that was recorded without them: the searches take the two lists in turn, and each empties the
+  // other's. Whose turn it is follows from `begun`, which every workgroup of the listing pass counts up as it begins; the
+  // last one of the second search puts it back to zero.
+  SelList list[2];
+  unsigned begun;
+  unsigned pad0;
   SelFound found;
-  unsigned pad[22];
+  unsigned pad[20];
 };
 static_assert(sizeof(SelState) % 128 == 0, "whole lines");
 
@@ -548,11 +557,15 @@ __device__ inline SelFound sel_begin(const Geo& g, int b, const int* target, int
   fd.budget = budget < 0 ? 0ull : (unsigned long long)budget;
   fd.acc = 0;
   fd.rc = budget < 0 ? 2 : 0;
-  fd.pad = 0;
+  fd.list = 0;
   return fd;
 }
 
-constexpr int kSelList = 4096;  // elements a search keeps in LDS; of more it reads the keys again in every round
+// Elements a search keeps in LDS; of more it reads the keys again in every round.
+#ifndef STTM_SEL_LIST
+#define STTM_SEL_LIST 4096
+#endif
+constexpr int kSelList = STTM_SEL_LIST;
 
 // tau of video b, by a workgroup of THREADS threads (256 or more): midpoint between the searched key and the largest key below it.
 // All threads get the value. The range of keys is cut into 256 pieces, of which one is picked, until it is one key: two
@@ -575,8 +588,9 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
     fd = sel_begin(g, b, q.target, q.base_const, q.node_map);
   } else {
     fd = q.states[b].found;
-    count = (int)q.states[b].count;
-    if (tid == 0) s_lo = q.states[b].lo;
+    const SelList first = q.states[b].list[0], second = q.states[b].list[1];
+    count = min((int)(fd.list ? second.count : first.count), q.per_video);
+    if (tid == 0) s_lo = fd.list ? second.lo : first.lo;
   }
   if (fd.rc) return fd.rc == 1 ? 1.f : -2.f;  // uniform over the workgroup
   __syncthreads();
@@ -714,11 +728,10 @@ void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauAr
                            int32_t* node_map, uint8_t* node_level, hipStream_t s);
 // Begins a budget search and says how it goes on. A small input is left to whoever uses the threshold; of a large one the
 // elements of the right bin are listed (`list_key`, `list_w`: [videos][select_elements()]).
-// `dirty`: the state has been searched since its statistics pass (the list must be emptied first).
 SelSearch launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
-                                SelState* state, bool dirty, uint32_t* list_key, uint8_t* list_w, hipStream_t s);
+                                SelState* state, uint32_t* list_key, uint8_t* list_w, hipStream_t s);
 SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
-                                 SelState* state, bool dirty, uint32_t* list_key, uint8_t* list_w, hipStream_t s);
+                                 SelState* state, uint32_t* list_key, uint8_t* list_w, hipStream_t s);
 // Carries a search out now, for a caller who wants the thresholds back.
 // `host_tau` (may be NULL): host memory the device can write, which receives the thresholds as well.
 void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s);

@@ -997,19 +997,14 @@ void launch_node_levels(const Geo& g, const int32_t* node_map, uint8_t* node_lev
 // ------------------------------------------------------------------------------------------------
 // (The host-thread build of the tests that takes the large inputs' kernels lists the elements of every search.)
 #ifndef STTM_SEL_WHOLE
-#if STTM_PYR_TILES_MAX == 0
-#define STTM_SEL_WHOLE 0
-#else
 #define STTM_SEL_WHOLE 2048
 #endif
-#endif
 constexpr int kSelWhole = STTM_SEL_WHOLE;
-constexpr int kPassThreads = 512;  // threads of the listing pass
-constexpr int kSelPer = 4;         // elements per thread
-
-__global__ __launch_bounds__(256) void k_select_reset(SelState* st) {
-  if (threadIdx.x == 0) st[blockIdx.x].count = st[blockIdx.x].lo = 0;
-}
+// Threads of the listing pass, and elements per thread. (Fewer in the host-thread build: a small input has several workgroups.)
+#ifndef STTM_SEL_THREADS
+#define STTM_SEL_THREADS 512
+#endif
+constexpr int kPassThreads = STTM_SEL_THREADS, kSelPer = 4;
 
 __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint32_t* __restrict__ keys,
                                                              const uint8_t* __restrict__ weights, int per_video,
@@ -1018,7 +1013,7 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
                                                              SelState* __restrict__ states,
                                                              uint32_t* __restrict__ list_key,
                                                              uint8_t* __restrict__ list_w) {
-  __shared__ unsigned s_lo, s_n, s_at;
+  __shared__ unsigned s_lo, s_n, s_at, s_list;
   const int b = blockIdx.y, tid = threadIdx.x;
   if (tid == 0) s_lo = s_n = 0;
   SelState* st = states + b;
@@ -1033,10 +1028,20 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
     key[u] = j < per_video ? kv[j] : 0u;
     w[u] = weights && j < per_video ? weights[(size_t)b * per_video + j] : 1u;
   }
+  unsigned turn = 0;
+  if (tid == 0) turn = atomicAdd(&st->begun, 1u);
   SelFound fd = sel_begin(g, b, target, base_const, node_map);
   unsigned bin = 0;
   if (fd.rc == 0 && !sel_pick<kSelCopies, kPassThreads>(st->hist0[0], 0ull, fd.budget, &bin, &fd.acc)) fd.rc = 1;
-  if (blockIdx.x == 0 && tid == 0) st->found = fd;
+  if (tid == 0) {
+    fd.list = turn >= gridDim.x;
+    if (turn == 2 * gridDim.x - 1) atomicExch(&st->begun, 0u);  // (every workgroup of both searches has its number)
+    if (blockIdx.x == 0) {
+      st->found = fd;
+      st->list[1 - fd.list] = {0u, 0u};  // for the next search
+    }
+    s_list = fd.list;
+  }
   if (fd.rc) return;  // uniform over the workgroup
   __syncthreads();
   unsigned lo = 0, place[kSelPer];  // key 0 is below every real value
@@ -1069,13 +1074,14 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
   if ((tid & 63) == 0 && lo) atomicMax(&s_lo, lo);
   __syncthreads();
   if (tid == 0) {
-    if (s_lo) atomicMax(&st->lo, s_lo);
-    s_at = s_n ? atomicAdd(&st->count, s_n) : 0u;
+    SelList* l = &st->list[s_list];
+    if (s_lo) atomicMax(&l->lo, s_lo);
+    s_at = s_n ? atomicAdd(&l->count, s_n) : 0u;
   }
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < kSelPer; ++u) {
-    if (place[u] == 0xffffffffu) continue;
+    if (place[u] == 0xffffffffu || s_at + place[u] >= (unsigned)per_video) continue;  // (never beyond the list's room)
     const size_t o = (size_t)b * per_video + s_at + place[u];
     list_key[o] = key[u];
     list_w[o] = (uint8_t)w[u];  // (at most 64 elements of weight 3)
@@ -1093,12 +1099,11 @@ __global__ __launch_bounds__(kSelThreads) void k_select_tau(Geo g, SelSearch sea
 }
 
 static SelSearch launch_select(const Geo& g, const uint32_t* keys, const uint8_t* weights, int per_video,
-                               const int* target, int base_const, const int32_t* node_map, SelState* st, bool dirty,
+                               const int* target, int base_const, const int32_t* node_map, SelState* st,
                                uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
   SelSearch q = {st, keys, weights, per_video, true, target, base_const, node_map};
   if (per_video <= kSelWhole) return q;
   const dim3 grid((per_video + kPassThreads * kSelPer - 1) / (kPassThreads * kSelPer), g.B), block(kPassThreads);
-  if (dirty) hipLaunchKernelGGL(k_select_reset, dim3(g.B), dim3(256), 0, s, st);
   hipLaunchKernelGGL(k_select_list, grid, block, 0, s, g, keys, weights, per_video, target, base_const, node_map, st,
                      list_key, list_w);
   q.keys = list_key;
@@ -1110,18 +1115,17 @@ static SelSearch launch_select(const Geo& g, const uint32_t* keys, const uint8_t
 int select_elements(const Geo& g, bool spatial) { return g.T * (spatial ? g.NN - g.lvl_base[1] : g.HW); }
 
 SelSearch launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
-                                SelState* state, bool dirty, uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
+                                SelState* state, uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
   int roots = 0;
   for (int ry = 0; ry < g.R; ++ry)
     for (int rx = 0; rx < g.R; ++rx) roots += node_exists(g, g.L, ry, rx);
-  return launch_select(g, keys, weights, select_elements(g, true), target, roots * g.T, nullptr, state, dirty, list_key,
-                       list_w, s);
+  return launch_select(g, keys, weights, select_elements(g, true), target, roots * g.T, nullptr, state, list_key, list_w,
+                       s);
 }
 
 SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
-                                 SelState* state, bool dirty, uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
-  return launch_select(g, keys, nullptr, select_elements(g, false), target, 0, node_map, state, dirty, list_key, list_w,
-                       s);
+                                 SelState* state, uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
+  return launch_select(g, keys, nullptr, select_elements(g, false), target, 0, node_map, state, list_key, list_w, s);
 }
 
 void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s) {

@@ -10,6 +10,8 @@ pthread_barrier_t g_block_bar;
 alignas(16) float g_dynamic_lds[40960];  // 160 KB, the LDS of one CU
 Pinned g_pinned;
 int g_memsets = 0;
+bool g_recording = false;
+std::vector<std::function<void()>> g_recorded;
 thread_local hipStreamCaptureMode t_capture_mode = hipStreamCaptureModeGlobal;
 
 static std::vector<std::pair<std::string, dim3>> g_launches;
@@ -70,6 +72,16 @@ extern "C" int hip_emul_last_grid(const char* kernel, unsigned grid[3]) {
       return 1;
     }
   return 0;
+}
+
+// 1: keeps the launches that follow instead of carrying them out; 0: carries launches out again.
+extern "C" void hip_emul_record(int on) {
+  if (on) hip_emul::g_recorded.clear();
+  hip_emul::g_recording = on != 0;
+}
+extern "C" int hip_emul_replay() {
+  for (auto& run : hip_emul::g_recorded) run();
+  return (int)hip_emul::g_recorded.size();
 }
 
 extern "C" int hip_emul_memsets() { return hip_emul::g_memsets; }  // hipMemsetAsync calls so far

@@ -12,6 +12,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <functional>
 #include <thread>
 #include <tuple>
 #include <utility>
@@ -62,6 +63,10 @@ inline uint64_t exchange(uint64_t v, int src_lane) {
 }
 void launch(dim3 grid, dim3 block, void (*body)(void*), void* closure);
 void note_launch(const char* kernel, dim3 grid);  // what hip_emul_last_grid (emul.cpp) answers from
+// Launches in place of a stream capture: while `g_recording`, they are kept instead of carried out (hip_emul_record and
+// hip_emul_replay in emul.cpp).
+extern bool g_recording;
+extern std::vector<std::function<void()>> g_recorded;
 }  // namespace hip_emul
 
 #define threadIdx (hip_emul::t_threadIdx)
@@ -236,12 +241,15 @@ inline hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms =
 
 template <class... P, class... A>
 inline void hip_emul_launch(void (*k)(P...), dim3 grid, dim3 block, size_t, hipStream_t, A... args) {
-  std::tuple<P...> t(static_cast<P>(args)...);
-  struct C { void (*k)(P...); std::tuple<P...>* t; } c{k, &t};
-  hip_emul::launch(grid, block, [](void* p) {
-    C* cc = static_cast<C*>(p);
-    std::apply(cc->k, *cc->t);
-  }, &c);
+  struct C { void (*k)(P...); std::tuple<P...> t; } c{k, std::tuple<P...>(static_cast<P>(args)...)};
+  auto run = [=]() mutable {
+    hip_emul::launch(grid, block, [](void* p) {
+      C* cc = static_cast<C*>(p);
+      std::apply(cc->k, cc->t);
+    }, &c);
+  };
+  if (hip_emul::g_recording) hip_emul::g_recorded.push_back(run);
+  else run();
 }
 #define hipLaunchKernelGGL(kernel, grid, block, lds, stream, ...) \
   (hip_emul::note_launch(#kernel, grid), hip_emul_launch(kernel, grid, block, lds, stream, __VA_ARGS__))

@@ -201,6 +201,58 @@ def test_emulated_search_among_many_elements_of_one_bin(emul, large, noise):
         np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
 
 
+@pytest.mark.parametrize("B,T,H,W,keep", [
+    (1, 4, 8, 8, 0.5),       # one workgroup lists the cells
+    (2, 5, 16, 16, 0.3),     # several; the second video's list lies behind the first one's
+])
+def test_emulated_searches_can_be_recorded_and_replayed(emul, large, B, T, H, W, keep):
+    """Statistics as ordinary calls, then a budget search and the call that uses its threshold recorded and replayed: what
+    every replay gives, and the same calls made again afterwards, is what they gave when they were first made."""
+    run_cpu, _ = emul
+    D = 8
+    feats = wl.generate(_variant(105, B, T, H, W, D, "f32"))
+    N = B * T * H * W
+    h, need = ctypes.c_void_p(), large.sttm_workspace_bytes(B, T, H, W, D, 0, 1)
+    ws, x = run_cpu._aligned(need, garbage=True), run_cpu._aligned(feats.nbytes, 16)
+    x[:] = feats.view(np.uint8).reshape(-1)
+    nm, cl, nl = np.zeros(N, np.int32), np.zeros(N, np.int32), np.zeros(N, np.uint8)
+    ptr, share = run_cpu._p, (ctypes.c_double * B)(*[keep] * B)
+    shape = (0, B, T, H, W, D, 1)
+
+    def chk(rc):
+        assert rc == 0, large.sttm_last_error(h)
+
+    assert large.sttm_create(ctypes.byref(h), 0, None) == 0
+    chk(large.sttm_set_workspace(h, ptr(ws), ctypes.c_size_t(need)))
+
+    def spatial():
+        chk(large.sttm_budget_threshold(h, 0, share, None))
+        chk(large.sttm_spatial_quadtree(h, ptr(x), *shape, None, ptr(nm), ptr(nl)))
+
+    def temporal():
+        chk(large.sttm_budget_threshold(h, 1, share, None))
+        chk(large.sttm_temporal_merge(h, ptr(x), ptr(nm), ptr(nl), None, ptr(cl)))
+
+    for stats, search, out in ((lambda: chk(large.sttm_spatial_stats(h, ptr(x), *shape)), spatial, nm),
+                               (lambda: chk(large.sttm_temporal_stats(h, ptr(x), ptr(nm), ptr(nl))), temporal, cl)):
+        stats()
+        search()                                           # (the targets are on the device from here on)
+        want = out.copy()
+        stats()
+        large.hip_emul_record(1)
+        search()
+        large.hip_emul_record(0)
+        for again in range(4):
+            out[:] = -1
+            assert large.hip_emul_replay() > 1
+            np.testing.assert_array_equal(out, want, err_msg=f"replay {again}")
+        out[:] = -1
+        search()
+        np.testing.assert_array_equal(out, want)
+        assert 1 < len(np.unique(want)) < N
+    large.sttm_destroy(h)
+
+
 def test_emulated_kernels_run_clean_under_address_and_undefined_behaviour_sanitizers():
     """The host-thread build with -fsanitize=address,undefined (any report aborts): both dtypes, fixed thresholds and
     a budget, every output in a heap block of its exact size, the workspace of exactly sttm_workspace_bytes(); once

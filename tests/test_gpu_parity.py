@@ -845,6 +845,60 @@ def test_budget_searches_are_exact(lib, T, noise, D):
         assert torch.equal(cl, given)
 
 
+@pytest.mark.parametrize("B,T,noise", [
+    (1, 40, 0.3),       # 10240 cells, 3400 nodes above them: the elements of the picked bin few
+    (2, 150, 0.003),    # all similarities close to one: thousands of elements in the picked bin
+])
+def test_recorded_budget_searches_replay(lib, B, T, noise):
+    """A search and the call that uses its threshold, captured after statistics that were not: every replay gives the eager
+    result, and so do the same calls made again after the replays."""
+    import torch
+    H = W = 16
+    D, N = 64, B * T * 256
+    gen = torch.Generator(device="cuda:0").manual_seed(T)
+    x = torch.randn(B, 1, 1, 1, D, device="cuda:0", generator=gen) + noise * torch.randn(B, T, H, W, D, device="cuda:0", generator=gen)
+    x = x.contiguous()
+    stream = torch.cuda.Stream(device=0)
+    s = lib.Sttm(0, stream_ptr=stream.cuda_stream)
+    s.ensure_workspace(B, T, H, W, D, lib.STTM_F32, 1)
+    nm, cl = (torch.empty(N, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    nl = torch.empty(N, dtype=torch.uint8, device="cuda:0")
+    torch.cuda.synchronize()
+    sh = (lib.STTM_F32, B, T, H, W, D, 1)
+
+    def spatial():
+        s.sttm_budget_threshold(lib.STTM_STAGE_SPATIAL, 0.5, want_tau=False)
+        s.sttm_spatial_quadtree(x, *sh, None, nm, nl)
+
+    def temporal():
+        s.sttm_budget_threshold(lib.STTM_STAGE_TEMPORAL, 0.3, want_tau=False)
+        s.sttm_temporal_merge(x, nm, nl, None, cl)
+
+    for stats, search, out in ((lambda: s.sttm_spatial_stats(x, *sh), spatial, nm),
+                               (lambda: s.sttm_temporal_stats(x, nm, nl), temporal, cl)):
+        stats()
+        search()
+        stream.synchronize()
+        want = out.clone()
+        stats()
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            search()
+        for again in range(4):
+            out.fill_(-1)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want), again
+        out.fill_(-1)
+        torch.cuda.synchronize()
+        search()
+        stream.synchronize()
+        assert torch.equal(out, want)
+        assert 1 < len(torch.unique(want)) < N
+
+
 @pytest.mark.parametrize("T,H,W,labels", [
     (1, 1, 1, "own"), (1, 7, 9, "random"), (1, 8, 8, "one"), (5, 13, 1, "random"),       # 1, 63, 64, 65 cells
     (1, 15, 17, "random"), (1, 16, 16, "own"), (257, 1, 1, "one"), (12, 32, 32, "random"),  # around 256 ids of a workgroup
