@@ -106,7 +106,8 @@ inline void opaque_pairs(uint32_t& lo, uint32_t& hi) { lo = LO; hi = HI; }
 // channels (v_mfma_f32_4x4x4_16b: sixteen products side by side, four lanes each; a lane's column is its own channels, and
 // row i of the result is its register i). One instruction on an otherwise idle pipe instead of four on the vector one; the
 // same bits for every finite input, subnormal ones included (4 x 10^6 random sums compared for either type). Where a value
-// is an infinity or a NaN, all four of the lane's sums are undefined.
+// is an infinity or a NaN, all four of the lane's sums come out as NaN: similarities are undefined then in any case, but a
+// sum that is kept for the rows of the output is formed again by Row::add_row (unit_pair_sums).
 // `ident`: this lane's row of the identity (identity_row).
 #ifndef STTM_HOST_EMULATION
 typedef float sttm_sum4 __attribute__((ext_vector_type(4)));

@@ -121,6 +121,44 @@ __device__ __forceinline__ void block_stats(uint2 ident, const typename Row<DT>:
   nd[7] = (nd[3] + p03) + (p13 + p23);
 }
 
+// The sums over a unit of N channels from `ch` on (N and ch even), by the packed dot product and in the order of the
+// pyramid kernels: for a sum that came out as no finite number. There one broken value takes three more channels with it,
+// here at most the other one of its pair, as where the rows themselves are added up for the output.
+template <int DT, int N>
+__device__ inline void unit_pair_sums(const Geo& g, const void* frame, int y3, int x3, int ch, float (&sum)[N]) {
+  uint32_t klo, khi;
+  if (DT == 1) opaque_pairs<0x3f80u, 0x3f800000u>(klo, khi);
+  else opaque_pairs<0x3c00u, 0x3c000000u>(klo, khi);
+#pragma unroll
+  for (int n = 0; n < N; n += 2) {
+    const uint16_t* rows = static_cast<const uint16_t*>(frame) + ch + n;
+    float s3[2];
+#pragma unroll 1
+    for (int q2 = 0; q2 < 4; ++q2) {
+      float s2[2] = {0.f, 0.f};
+#pragma unroll 1
+      for (int q1 = 0; q1 < 4; ++q1) {
+        float s1[2] = {0.f, 0.f};
+#pragma unroll 1
+        for (int k = 0; k < 4; ++k) {
+          const int y = y3 + (q2 >> 1) * 4 + (q1 >> 1) * 2 + (k >> 1), x = x3 + (q2 & 1) * 4 + (q1 & 1) * 2 + (k & 1);
+          if (y >= g.H || x >= g.W) continue;
+          const uint32_t w = *reinterpret_cast<const uint32_t*>(rows + (size_t)(y * g.W + x) * g.D);
+          s1[0] = DT == 1 ? dot2_bf16(w, klo, s1[0]) : dot2_f16(w, klo, s1[0]);
+          s1[1] = DT == 1 ? dot2_bf16(w, khi, s1[1]) : dot2_f16(w, khi, s1[1]);
+        }
+        s2[0] += s1[0];
+        s2[1] += s1[1];
+      }
+      s3[0] = q2 ? s3[0] + s2[0] : s2[0];
+      s3[1] = q2 ? s3[1] + s2[1] : s2[1];
+    }
+    sum[n] = s3[0];
+    sum[n + 1] = s3[1];
+  }
+}
+__device__ inline bool finite(float v) { return (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u; }
+
 // Which (frame, unit, chunk) a workgroup of a 1-D grid works on; false = none. With the frame-to-frame dot products a
 // tile is asked for by two workgroups: its own frame's and the one of the frame before. Workgroups go to the eight dies
 // round-robin by their index; each die gets a contiguous range of frames and walks it in order, two frames at a time
@@ -314,8 +352,16 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
         s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
       }
       S3[v] = s.x; S3[v + 1] = s.y; S3[v + 2] = s.z; S3[v + 3] = s.w;
-      if (q2 == v / 4 && act)  // a wavefront per four channels of the lanes stores the unit's sum
+      if (q2 == v / 4 && act) {  // a wavefront per four channels of the lanes stores the unit's sum
+        if constexpr (DT != 0) {
+          if (!(finite(s.x) && finite(s.y) && finite(s.z) && finite(s.w))) {
+            float again[4];
+            unit_pair_sums<DT>(g, reinterpret_cast<const typename R::Elem*>(feats_v) + (size_t)f * g.HW * g.D, y3, x3, ch0 + v, again);
+            s = make_float4(again[0], again[1], again[2], again[3]);
+          }
+        }
         *reinterpret_cast<float4*>(nsum + ((size_t)f * (g.NN - g.lvl_base[3]) + (y3 >> 3) * (g.P >> 3) + (x3 >> 3)) * g.D + ch0 + v) = s;
+      }
     }
 #pragma unroll
     for (int v = 0; v < VEC; ++v) d2 = fmaf(S2[v], S3[v], d2);
@@ -508,6 +554,11 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
 #pragma unroll
       for (int i = 0; i < VEC / 4; ++i)
         v[i] = ((t[i] + t[VEC * 64 + i]) + t[2 * VEC * 64 + i]) + t[3 * VEC * 64 + i];
+      if constexpr (DT != 0) {  // (a lane beyond the last channel holds zeros)
+        if (!(finite(v[0]) && finite(v[1])))
+          unit_pair_sums<DT>(g, reinterpret_cast<const typename R::Elem*>(feats_v) + (size_t)f * g.HW * g.D, y3, x3,
+                             chunk * g.cch + own, v);
+      }
       window_store(w, noff, 0u, v);
     }
     part_f += part_step;

@@ -550,6 +550,61 @@ def test_infinite_and_nan_features_against_the_oracle(lib):
         assert (r.counts.sum() == feats[..., 0].size) and r.K == len(np.unique(tm.cluster_ids))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_infinite_and_nan_half_precision_features_against_the_oracle(lib, dtype):
+    """The same in the types whose 2x2 sums are made on the matrix cores."""
+    feats = wl.generate(_variant(41, 1, 4, 13, 13, 72, dtype))
+    bits = feats.view(np.uint16)
+    inf, sign, nan = (0x7f80, 0x8000, 0x7fc0) if dtype == "bf16" else (0x7c00, 0x8000, 0x7e00)
+    bits[0, 1, 5, 6, 3], bits[0, 2, 12, 12, 70], bits[0, 3, 0, 0, 0] = inf, inf | sign, nan
+    for kw in (dict(tau_s=0.7, tau_t=0.6), dict(tau_s=-2.0, tau_t=-2.0)):
+        r = P.run_gpu(lib, feats, **kw)
+        sp, _ = P.check_spatial(lib, feats, r, kw["tau_s"])
+        assert r.node_level[0, 1, 5, 6] == 0 and r.node_level[0, 2, 12, 12] == 0 and r.node_level[0, 3, 0, 0] == 0
+        tm, _ = P.check_temporal(lib, feats, r, sp, kw["tau_t"])
+        assert r.parent[0, 1, 5, 6] == -1 and r.parent[0, 2, 5, 6] == -1
+        assert (r.counts.sum() == feats[..., 0].size) and r.K == len(np.unique(tm.cluster_ids))
+
+
+@pytest.mark.parametrize("T", [3, 700])                    # the kernel with a workgroup per frame, and the walk
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+def test_a_broken_value_stays_with_its_channels_in_a_stored_node_sum(lib, dtype, T):
+    """The reduce call with a partition of the caller's that keeps a node with an infinite or NaN value: the rows differ
+    from those of the call that reads every cell in the order of the additions only, and what is not finite is the broken
+    value's channel and at most the other one of its pair."""
+    import torch
+    H, W, D = 13, 16, 520
+    N = T * H * W
+    dt, tt = {"bf16": (lib.STTM_BF16, torch.bfloat16), "f16": (lib.STTM_F16, torch.float16), "f32": (lib.STTM_F32, torch.float32)}[dtype]
+    gen = torch.Generator(device="cuda:0").manual_seed(T)
+    x = torch.randn(1, T, H, W, D, device="cuda:0", generator=gen).to(tt)
+    broken = [(0, 5, 6, 3, math.inf), (1, 12, 15, 519, -math.inf), (T - 1, 0, 9, 256, math.nan)]
+    for t, y, c, ch, v in broken:
+        x[0, t, y, c, ch] = v
+    yy, xx = torch.meshgrid(torch.arange(H), torch.arange(W), indexing="ij")
+    nm = (torch.arange(T)[:, None, None] * H * W + (yy // 8 * 8) * W + xx // 8 * 8).to(torch.int32).reshape(-1).to("cuda:0")
+    nl = torch.full((N,), 3, dtype=torch.uint8, device="cuda:0")
+    s = lib.Sttm(0)
+    s.ensure_workspace(1, T, H, W, D, dt, 1)
+    s.sttm_spatial_stats(x, dt, 1, T, H, W, D, 1)
+    cl = nm.clone()                                        # every 8x8 block a cluster of its own
+    rows = []
+    for node_map, level in ((nm, nl), (None, None)):
+        merged = torch.zeros(N, D, device="cuda:0")
+        counts, ids = (torch.zeros(N, dtype=torch.int32, device="cuda:0") for _ in range(2))
+        offsets = torch.zeros(2, dtype=torch.int64, device="cuda:0")
+        n = s.sttm_reduce(x, cl, node_map, level, lib.STTM_F32, N, merged, counts, ids, offsets)
+        assert n == T * 4
+        rows.append(merged[:n])
+    a, b = rows
+    whole = torch.isfinite(b)
+    assert torch.equal(torch.isfinite(a), whole)
+    torch.testing.assert_close(a[whole], b[whole], rtol=0, atol=1e-5)   # means of at most 64 values of a few units
+    want = {(t * 4 + y // 8 * 2 + c // 8, ch) for t, y, c, ch, _ in broken}
+    got = {tuple(i) for i in (~whole).nonzero().tolist()}
+    assert want <= got <= {(row, c) for row, ch in want for c in (ch, ch ^ 1)}
+
+
 def test_new_temporal_statistics_discard_the_pending_threshold(lib):
     """temporal_stats, budget (threshold left to the consumer), temporal_stats again, merge without thresholds:
     the second statistics pass starts the search afresh, so the merge must refuse instead of resolving a
