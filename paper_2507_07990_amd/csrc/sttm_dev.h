@@ -295,6 +295,12 @@ template <class Raw>
 __device__ __forceinline__ Raw window_load_once(Window w, unsigned lane_off, unsigned uniform_off) {
   return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b128(w, (int)lane_off, (int)uniform_off, 2));  // (2: non-temporal)
 }
+__device__ __forceinline__ int window_load_i32(Window w, unsigned lane_off, unsigned uniform_off) {
+  return (int)__builtin_amdgcn_raw_buffer_load_b32(w, (int)lane_off, (int)uniform_off, 0);
+}
+__device__ __forceinline__ int window_load_u8(Window w, unsigned lane_off, unsigned uniform_off) {
+  return (int)__builtin_amdgcn_raw_buffer_load_b8(w, (int)lane_off, (int)uniform_off, 0);
+}
 __device__ __forceinline__ void window_store(Window w, unsigned lane_off, unsigned uniform_off, const float (&v)[1]) {
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[0]), w, (int)lane_off, (int)uniform_off, 0);
 }
@@ -314,6 +320,14 @@ inline Raw window_load_once(const Window& w, unsigned lane_off, unsigned uniform
   memset(&r, 0, sizeof r);
   if ((uint64_t)lane_off + uniform_off + sizeof r <= w.bytes) memcpy(&r, w.base + uniform_off + lane_off, sizeof r);
   return r;
+}
+inline int window_load_i32(const Window& w, unsigned lane_off, unsigned uniform_off) {
+  int r = 0;
+  if ((uint64_t)lane_off + uniform_off + sizeof r <= w.bytes) memcpy(&r, w.base + uniform_off + lane_off, sizeof r);
+  return r;
+}
+inline int window_load_u8(const Window& w, unsigned lane_off, unsigned uniform_off) {
+  return (uint64_t)lane_off + uniform_off < w.bytes ? (int)(uint8_t)w.base[uniform_off + lane_off] : 0;
 }
 template <int N>
 inline void window_store(const Window& w, unsigned lane_off, unsigned uniform_off, const float (&v)[N]) {

@@ -20,20 +20,30 @@ constexpr int kSortThreads = 512;
 constexpr int kSortPer = kSortTile / kSortThreads;
 constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kMaxDigitBits = 11;
-// The list of an input of up to this many cells is made by one launch (k_list_small), each workgroup for a range of ids.
+// The list of an input of up to this many cells is made by one launch (k_list_small); beyond it the sort passes are as fast:
+// the reduce stage of 47,000 to 50,700 cells 40-54 us either way, of 63,488 61 by one launch and 54.
 // (The host-thread build of the tests that takes the large inputs' kernels takes the sort passes as well.)
 #ifndef STTM_LIST_MAX
 #if defined(STTM_PYR_TILES_MAX) && STTM_PYR_TILES_MAX == 0
 #define STTM_LIST_MAX 0
 #else
-#define STTM_LIST_MAX 65535
+#define STTM_LIST_MAX 49152
 #endif
 #endif
 constexpr int kListMax = STTM_LIST_MAX;
 static_assert(kListMax < 65536, "cells and counts in 16 bits");
-constexpr int kListThreads = 1024, kListWaves = kListThreads / kWave;
-constexpr int kListBits = 8, kListRange = 1 << kListBits;
-constexpr int kListBatch = 4;  // cells per lane whose loads are in flight together
+constexpr int kListThreads = 1024;
+constexpr int kListTiny = 1024, kListThreadsTiny = 256;  // of up to this many cells: 576 cells 16.9 us by 1024 threads, 16.4;
+                                                         // 2304 cells 26 and 28
+// Cells up to which the count has a word for every id: 10,816 cells 9.5 us and 9.9 by half words, 512 cells 4.6 and 4.8; 16,384
+// 12.8 and 11.7, 35,280 20.6 and 18.3 (twice the LDS to clear and to add up).
+constexpr int kListWide = kListMax < 12288 ? kListMax : 12288;
+constexpr int kListSlice = 256;  // cells that a workgroup puts into the list
+constexpr int kListBatch = 4;    // cells per lane whose loads are in flight together
+constexpr int kListPieces = 3;   // pieces of the count per lane whose loads are
+constexpr int kListRuns = kListMax / 128 * 2 + 2;  // runs of 64 ids, at most
+static_assert(kListMax == 0 || (kListRuns <= kListThreads && kListTiny / 128 * 2 + 2 <= kListThreadsTiny), "a thread per run");
+static_assert(kListSlice <= kListThreadsTiny, "a thread per cell");
 constexpr int kItem = 16;  // list positions per gather item
 constexpr int kBig = 64;   // clusters with more list slots than this are summed item by item, then combined
 constexpr int kTail = 8;
@@ -460,24 +470,66 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(SortArgs a) {
   }
 }
 
+// The value of the lane before (the first one: 0), and this lane's bit of a mask.
+#ifndef STTM_HOST_EMULATION
+__device__ inline int lane_before(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, true); }  // wave_shr:1
+__device__ inline bool from_mask(unsigned long long m, int) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+#else
+inline int lane_before(int v) { const int r = __shfl_up(v, 1, 64); return (threadIdx.x & 63) ? r : 0; }
+inline bool from_mask(unsigned long long m, int lane) { return (m >> lane) & 1ull; }
+#endif
+
+// Running sum over the lanes of each row of sixteen, and over the wavefront.
+#ifndef STTM_HOST_EMULATION
+__device__ inline unsigned row16_inclusive(unsigned v, int) {
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);  // row_shr:1 (zero from beyond the row)
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+  return v;
+}
+__device__ inline unsigned wave_inclusive(unsigned v, int lane) {
+  v = row16_inclusive(v, lane);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15, to the second and fourth row
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31, to the third and fourth
+  return v;
+}
+#else
+inline unsigned lanes_inclusive(unsigned v, int lane, int width) {
+  for (int o = 1; o < width; o <<= 1) {
+    const unsigned t = __shfl_up(v, o, 64);
+    if ((lane & (width - 1)) >= o) v += t;
+  }
+  return v;
+}
+inline unsigned row16_inclusive(unsigned v, int lane) { return lanes_inclusive(v, lane, 16); }
+inline unsigned wave_inclusive(unsigned v, int lane) { return lanes_inclusive(v, lane, 64); }
+#endif
+
 // ------------------------------------------------------------------------------------------------
-// k_list_small: all of the integer plumbing of a small input in one launch. A workgroup owns kListRange consecutive cluster
-// ids. It looks at every cell of the input, counts the list elements and the roots that come before its ids, and keeps the
-// cells of its own ids, in index order; these it then puts into the list by a stable counting sort in LDS. No workgroup
-// waits for another: what they would have to tell each other every one finds out by itself, at 5 bytes to 9 a cell from
-// the caches. A wavefront takes a run of consecutive cells, so the order of equal keys is the order of the cells.
+// k_list_small: all of the integer plumbing of a small input in one launch. A workgroup puts kListSlice consecutive cells
+// into the list. The place of an element is the number of elements with a smaller id plus that of earlier ones with the
+// same id; both come from a count of every id, which each workgroup keeps in LDS and makes by itself from all cells of the
+// input. For the earlier ones of an id it either counts the cells before its own beside all of them, 32 bits an id (WIDE),
+// or counts those before its own first, then its own, then the rest, 16 bits an id. Its own cells take their turns, a
+// wavefront after the other. Ranks come from a bit per cell, "is a root". No workgroup waits for another: what they would
+// have to tell each other every one finds out by itself, at 4 bytes a cell (9 with the partition) from the caches.
 // Writes what the sort passes write (rank, list, output row of every position, first position of every row, out_ids,
 // offsets, totals).
-// What bounds it: the look over all cells by every workgroup, two rounds of loads per thousand cells and wavefront, and the
-// first fetch of its code. Against preparation, scatter, histogram and second scatter as launches of their own: 64 frames of
-// 13x13 (10816 cells) 25.9 -> 9.4 us, of 16x16 26.3 -> 12.0, 96 of 11x19 27.7 -> 14.0, 180 of 14x14 (35280) 26.6 -> 17.6, six
-// clips of 7500 cells 26.8 -> 21.7; at 65000 cells the two are about even. (Ranges of 512 or 1024 ids 0.3 and 2 us more;
-// elements left with the wavefront that found them 29 us for the six clips, 20.6 for the 180 frames: the members of a range's
-// clusters lie close together.)
+// What bounds it: the look over all cells by every workgroup, by its instructions (about 25 vector ones for 64 cells, 16
+// wavefronts a workgroup) and the LDS atomics; by time stamps, 45,000 cells: 11 us of 18 with 3 for the sums over the count.
+// The work does not depend on the labelling: a workgroup for 256 ids that found and sorted their cells did all the work
+// alone where a still scene leaves the cells of all frames to the first frame's ids. Whole reduce stage at D = 256, us, that
+// kernel and this one: 300 still frames of 13x13 130 -> 42, 64 of them 49 -> 32; moving scenes of 92 frames of 13x13 44 -> 37,
+// 64 of 16x16 45 -> 37, 512 of 8x8 45 -> 47; the launch alone in passes of the package's workloads 9.0 -> 9.5 (10,816 cells),
+// 11.1 -> 11.7 (16,384), 14.1 -> 13.1 (20,064), 15.8 -> 18.3 (35,280), 20.4 -> 20.3 (45,000).
 // ------------------------------------------------------------------------------------------------
 struct ListArgs {
-  int n, W, HW, both_halves;  // both_halves: a stored node sum takes two list elements (16-bit input)
-  int cap;                    // cells per wavefront, a multiple of 64
+  int n, W;
+  int both_halves;        // both_halves: a stored node sum takes two list elements (16-bit input)
+  unsigned inv_w;         // where a node may be one column wide (W = 9, 17, 25): 2^32 / W rounded up, exact for 16-bit numerators
+  int words;                  // of the count
+  int id_bits;
   const int32_t* cluster_ids;
   const int32_t* node_map;    // the stage-1 partition, or both NULL
   const uint8_t* node_level;
@@ -493,181 +545,200 @@ struct ListArgs {
   int32_t* seg;
 };
 
-__global__ __launch_bounds__(kListThreads) void k_list_small(ListArgs a) {
-  STTM_DYNAMIC_LDS(uint16_t, list);                // [wavefront][cap] cells of the own ids
-  __shared__ unsigned cur[kListWaves * kListRange / 2];  // [wavefront][two ids to a word] counts, then cursors
-  __shared__ int s_base[kListRange], s_rank[kListRange];
-  __shared__ int s_roots[kListWaves], s_below[kListWaves], s_len[kListWaves];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lo = blockIdx.x * kListRange, hi = min(a.n, lo + kListRange);
-  const int c0 = wave * a.cap, c1 = min(a.n, c0 + a.cap);
-  const unsigned long long before = (1ull << lane) - 1ull;
-  const int own = lo + tid;  // the cell of the own range that this thread ranks
-  const int own_cid = tid < kListRange && own < hi ? a.cluster_ids[own] : -1;
-  for (int d = tid; d < kListWaves * kListRange / 2; d += kListThreads) cur[d] = 0;
-  __syncthreads();
+// The count's words for n ids, whole runs of 64: WIDE one for every id, with the cells before the workgroup's own in its low
+// half and all of them in its high one; otherwise id j is in the low half of word j, id words + j in the high one. (Neighbouring
+// ids are in different words: the cells of a row of lanes mostly have ids in a row, and two atomics on one word would take
+// their turns.)
+static int list_words(int n, bool wide) { return wide ? (n + 63) / 64 * 64 : (n + 127) / 128 * 64; }
 
-  unsigned* mycur = cur + wave * (kListRange / 2);
-  uint16_t* mylist = list + wave * a.cap;
-  int nlist = 0, below = 0, roots = 0;  // (the same in all lanes of a wavefront)
-#pragma unroll 1
-  for (int j0 = c0; j0 < c1; j0 += kListBatch * 64) {
-    int cid[kListBatch], rep[kListBatch], lv[kListBatch];
-#pragma unroll
-    for (int u = 0; u < kListBatch; ++u) {  // all loads first
-      const int i = min(j0 + u * 64 + lane, a.n - 1);
-      cid[u] = a.cluster_ids[i];
-      rep[u] = lv[u] = 0;
-      if (a.node_map) {
-        rep[u] = a.node_map[i];
-        lv[u] = a.node_level[i];
-      }
+template <int THREADS, bool WIDE>
+__global__ __launch_bounds__(THREADS) void k_list_small(ListArgs a) {
+  constexpr int WAVES = THREADS / kWave;
+  STTM_DYNAMIC_LDS(unsigned, count);                 // [words]
+  __shared__ __attribute__((aligned(16))) unsigned long long s_roots[kListRuns + 2];  // a bit per cell; whole batches of rows
+  __shared__ unsigned s_first[kListRuns];            // per run of 64 ids: elements (low half) and roots in the runs before it
+  __shared__ unsigned s_none[64];                    // where additions of nothing go
+  __shared__ unsigned s_wave[WAVES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lo = blockIdx.x * kListSlice, hi = min(a.n, lo + kListSlice), rows = (a.n + 63) >> 6;
+  const unsigned long long before = (1ull << lane) - 1ull;
+
+  // the id of cell i, whose node's top-left cell is rep and level lv; -1 if the cell is not an element of the list
+  auto element_id = [&](int i, int cid, int rep, int lv) {
+    // of a node with a stored sum only its top-left cell stays and, where that takes two elements, its next cell in
+    // raster order: the one to the right, or in a node of one column the one below
+    const int past = i - rep;
+    bool dropped = (lv >= 3) & ((unsigned)past > (unsigned)a.both_halves);
+    if (a.inv_w && a.both_halves) {
+      const int col = i - (int)((unsigned long long)(unsigned)i * a.inv_w >> 32) * a.W;
+      dropped &= (past != a.W) | (col != a.W - 1);
     }
+    return (!dropped & ((unsigned)cid < (unsigned)a.n)) ? cid : -1;
+  };
+  auto word = [&](int id) { return count + (WIDE ? (unsigned)id : min((unsigned)id, (unsigned)id - (unsigned)a.words)); };
+  auto low = [&](int id) { return WIDE || id < a.words; };
+
+  const int own = lo + tid;  // the cell that this thread places (of the first kListSlice threads)
+  const bool mine = tid < kListSlice && own < hi;
+  int own_cid = -1, own_rep = 0, own_lv = 0;
+  if (mine) {
+    own_cid = a.cluster_ids[own];
+    if (a.node_map) {
+      own_rep = a.node_map[own];
+      own_lv = a.node_level[own];
+    }
+  }
+  for (int d = tid; d < a.words >> 2; d += THREADS) reinterpret_cast<uint4*>(count)[d] = make_uint4(0u, 0u, 0u, 0u);
+  const int per = a.words >> 6, runs = WIDE ? per : 2 * per;
+  if (tid < runs) s_roots[tid] = 0;
+  __syncthreads();
+  const int id = mine ? element_id(own, own_cid, own_rep, own_lv) : -1;
+  int place = 0;  // of the own element among those with its id
+  unsigned long long same = 0;  // the wavefront's own cells with that id
+  const Window ids = make_window(a.cluster_ids, (unsigned)a.n * 4u), reps = make_window(a.node_map, a.node_map ? (unsigned)a.n * 4u : 0u),
+               levels = make_window(a.node_level, a.node_map ? (unsigned)a.n : 0u);
+  struct Rows { int cid[kListBatch], rep[kListBatch], lv[kListBatch]; };
+  auto load = [&](Rows& q, int r0) {  // (zeros behind the last cell)
 #pragma unroll
     for (int u = 0; u < kListBatch; ++u) {
-      const int i0 = j0 + u * 64, i = i0 + lane;
-      if (i0 >= c1) continue;
-      if (i0 + 64 > c1 && i >= c1) cid[u] = 0x7fffffff;  // (no id; only the input's last cells end inside a row of lanes)
-      if (i0 < lo) roots += __popcll(__ballot(cid[u] == i));
-      unsigned long long dropped = __ballot(lv[u] >= 3 && i != rep[u]);
-      if (dropped) {
-        // of a node with a stored sum only its top-left cell stays and, where that takes two elements, its next cell in
-        // raster order: the one to the right, or in a node of one column the one below
-        const int past = i - rep[u];
-        const bool second = past == 1 || ((a.W & 7) == 1 && past == a.W && i % a.HW % a.W == a.W - 1);
-        const bool drop = lv[u] >= 3 && past != 0 && !(a.both_halves && second);
-        dropped = __ballot(drop);
-        if (drop) cid[u] = 0x7fffffff;
+      q.cid[u] = window_load_i32(ids, (unsigned)(lane * 4 + u * 256), (unsigned)r0 * 256u);
+      q.rep[u] = q.lv[u] = 0;
+      if (a.node_map) {
+        q.rep[u] = window_load_i32(reps, (unsigned)(lane * 4 + u * 256), (unsigned)r0 * 256u);
+        q.lv[u] = window_load_u8(levels, (unsigned)(lane + u * 64), (unsigned)r0 * 64u);
       }
-      if (i0 < lo) {  // (whole rows of lanes; a cell's id is at most its own)
-        below += 64 - __popcll(dropped);
-      } else {
-        below += __popcll(__ballot(cid[u] < lo));
-        const unsigned d = (unsigned)(cid[u] - lo);
-        const bool mine = d < (unsigned)(hi - lo);
-        const unsigned long long m = __ballot(mine);
-        if (m) {
-          if (mine) mylist[nlist + __popcll(m & before)] = (uint16_t)i;
-          nlist += __popcll(m);
+    }
+  };
+  // WIDE: all rows of 64 cells. Otherwise those before the own ones, then those behind.
+#pragma unroll 1
+  for (int part = 0; part < (WIDE ? 1 : 2); ++part) {
+    const int rb = part ? (hi + 63) >> 6 : 0, r1 = WIDE || part ? rows : lo >> 6, end = min(a.n, r1 * 64);
+    // Batches of rows; workgroups of one die (they are dealt to the eight in turn) begin at different places, so that not all of
+    // them wait for the same lines to reach the die's L2.
+    const int batches = (max(0, r1 - rb) + kListBatch - 1) / kListBatch, skip = batches * (int)(blockIdx.x >> 3 & 15) >> 4;
+    auto row_of = [&](int j) { return rb + (j + skip < batches ? j + skip : j + skip - batches) * kListBatch; };
+    Rows next;
+    if (wave < batches) load(next, row_of(wave));
+    if (part == 0 && wave < kListSlice / 64) {  // (while these are on their way)
+      const unsigned long long roots = __ballot(mine && own_cid == own);
+      if (lane == 0 && (lo >> 6) + wave < rows) s_roots[(lo >> 6) + wave] = roots;
+      same = __ballot(id >= 0);
+#pragma unroll 1
+      for (int bit = 0; bit < a.id_bits; ++bit) {
+        const bool set = (id >> bit) & 1;
+        const unsigned long long m = __ballot(set);
+        same &= set ? m : ~m;
+      }
+    }
+#pragma unroll 1
+    for (int j = wave; j < batches; j += WAVES) {
+      const int r0 = row_of(j);
+      const Rows now = next;  // the next rows are on their way while these are counted
+      if (j + WAVES < batches) load(next, row_of(j + WAVES));
+      unsigned long long roots[kListBatch];
+      int e[kListBatch];
+#pragma unroll
+      for (int u = 0; u < kListBatch; ++u) {
+        const int i = (r0 + u) * 64 + lane;
+        roots[u] = __ballot(now.cid[u] == i);
+        e[u] = a.node_map ? element_id(i, now.cid[u], now.rep[u], now.lv[u]) : ((unsigned)now.cid[u] < (unsigned)a.n ? now.cid[u] : -1);
+      }
+      if ((r0 + kListBatch) * 64 > end) {
+#pragma unroll
+        for (int u = 0; u < kListBatch; ++u) e[u] = (r0 + u) * 64 + lane < end ? e[u] : -1;
+      }
+      const int twice = r0 * 64 < lo ? -1 : 0;
+#pragma unroll
+      for (int u = 0; u < kListBatch; ++u) {
+        // Neighbours with the same id (a merged node's cells; their atomics would take their turns) are counted as one run:
+        // its first lane takes its number off, its last one adds its own and one. Whoever has nothing to add does so in a
+        // word of its own: a branch around the atomic costs more.
+        const unsigned long long heads = __ballot(e[u] != lane_before(e[u])) | 1ull, tails = heads >> 1 | 1ull << 63;
+        const unsigned long long act = __ballot(e[u] >= 0) & (heads | tails);
+        const unsigned add = (unsigned)((from_mask(tails, lane) ? lane + 1 : 0) - (from_mask(heads, lane) ? lane : 0));
+        const unsigned sum = WIDE ? (add << 16) + (add & (unsigned)twice) : add << (low(e[u]) ? 0 : 16);
+        atomicAdd(from_mask(act, lane) ? word(e[u]) : s_none + lane, sum);
+      }
+      if (lane == 0) {
+#pragma unroll
+        for (int u = 0; u < kListBatch; ++u) s_roots[r0 + u] = roots[u];
+      }
+    }
+    if (part) break;
+    // the own cells, a wavefront after the other
+#pragma unroll 1
+    for (int w = 0; w < kListSlice / 64; ++w) {
+      __syncthreads();
+      if (wave != w) continue;
+      if (id >= 0) place = (int)(low(id) ? *word(id) & 0xffffu : *word(id) >> 16) + __popcll(same & before);
+      wave_lds_fence();
+      if (id >= 0 && ((same >> lane) >> 1) == 0)  // the highest lane of an id's group counts them all
+        atomicAdd(word(id), (unsigned)__popcll(same) << (low(id) ? 0 : 16));
+    }
+    __syncthreads();  // (nobody counts the cells behind before the last of these has its place)
+  }
+  if (!WIDE) __syncthreads();
+  // the count of every id -> that of the ids before it in its run of 64, and the runs' totals (both halves side by side:
+  // all totals together fit 16 bits)
+#pragma unroll 1
+  for (int d0 = wave * 256; d0 < a.words; d0 += WAVES * 256 * kListPieces) {  // 16 lanes, four words each, to a run
+    uint4 c[kListPieces];
+#pragma unroll
+    for (int k = 0; k < kListPieces; ++k) {
+      const int d = d0 + k * WAVES * 256 + lane * 4;
+      c[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (d < a.words) c[k] = *reinterpret_cast<const uint4*>(count + d);
+    }
+#pragma unroll
+    for (int k = 0; k < kListPieces; ++k) {
+      const int d = d0 + k * WAVES * 256 + lane * 4;
+      if (WIDE) { c[k].x >>= 16; c[k].y >>= 16; c[k].z >>= 16; c[k].w >>= 16; }
+      c[k].y += c[k].x; c[k].z += c[k].y; c[k].w += c[k].z;
+      const unsigned upto = row16_inclusive(c[k].w, lane), ex = upto - c[k].w;
+      if (d < a.words) {
+        *reinterpret_cast<uint4*>(count + d) = make_uint4(ex, ex + c[k].x, ex + c[k].y, ex + c[k].z);
+        if ((lane & 15) == 15) {
+          s_first[d >> 6] = upto & 0xffffu;
+          if (!WIDE) s_first[per + (d >> 6)] = upto >> 16;
         }
       }
     }
   }
-  // ranks of the range's roots
-  const unsigned long long is_root = __ballot(tid < kListRange && own < hi && own_cid == own);
-  if (lane == 0) {
-    s_roots[wave] = roots;
-    s_below[wave] = below;
-    s_len[wave] = nlist;
-    if (wave < kListRange / 64) s_base[wave] = __popcll(is_root);  // (its place is not in use yet)
-  }
   __syncthreads();
-  int roots_before = 0, start = 0, in_range = 0, mine_before = 0;
-#pragma unroll
-  for (int w = 0; w < kListWaves; ++w) {
-    roots_before += s_roots[w];
-    start += s_below[w];
-    if (w < kListRange / 64) {
-      if (w < wave) mine_before += s_base[w];
-      in_range += s_base[w];
-    }
-  }
-  if (tid < kListRange) {
-    const int rk = roots_before + mine_before + __popcll(is_root & before);
-    s_rank[tid] = rk;
-    if (own < hi) {
-      a.rank[own] = rk;
-      if (own_cid == own && a.out_ids && rk < a.capacity) a.out_ids[rk] = own;
-      if (own % a.per_video == 0) a.offsets[own / a.per_video] = rk;
-    }
-  }
-  // The elements found are dealt out anew, the same number to every wavefront, in their order: those of a range of ids lie
-  // close together, often all in one or two wavefronts' cells.
-  int upto[kListWaves], all = 0;  // elements found up to and including each wavefront's
-#pragma unroll
-  for (int w = 0; w < kListWaves; ++w) {
-    all += s_len[w];
-    upto[w] = __builtin_amdgcn_readfirstlane(all);
-  }
-  const int q0 = (int)((unsigned)all * (unsigned)wave / kListWaves), q1 = (int)((unsigned)all * (unsigned)(wave + 1) / kListWaves);
-  auto element = [&](int q) {  // element q + lane, or -1
-    int finder = 0, first = 0;
-#pragma unroll
-    for (int w = 0; w < kListWaves - 1; ++w)
-      if (q + lane >= upto[w]) {
-        finder = w + 1;
-        first = upto[w];
-      }
-    return q + lane < q1 ? (int)list[finder * a.cap + (q + lane - first)] : -1;
+  const unsigned run = tid < runs ? s_first[tid] | (unsigned)__popcll(s_roots[tid]) << 16 : 0u;
+  const unsigned upto = wave_inclusive(run, lane);
+  if (lane == 63) s_wave[wave] = upto;
+  __syncthreads();
+  const int waves = (int)row16_inclusive(lane < WAVES ? s_wave[lane] : 0u, lane);
+  const unsigned all = (unsigned)lane_value(waves, WAVES - 1);
+  if (tid < runs) s_first[tid] = (wave ? (unsigned)lane_value(waves, wave - 1) : 0u) + upto - run;
+  __syncthreads();
+  auto rank_of = [&](int i) {
+    return (int)(s_first[i >> 6] >> 16) + __popcll(s_roots[i >> 6] & ((1ull << (i & 63)) - 1ull));
   };
-  int e0 = -1, key0 = 0;  // the first ones are kept
-#pragma unroll 1
-  for (int q = q0; q < q1; q += 64) {
-    const int e = element(q), key = e >= 0 ? a.cluster_ids[e] : 0, d = key - lo;
-    if (e >= 0) atomicAdd(&mycur[d >> 1], 1u << ((d & 1) * 16));
-    if (q == q0) {
-      e0 = e;
-      key0 = key;
+  if (mine) {
+    const int rk = rank_of(own);
+    a.rank[own] = rk;
+    if (own_cid == own && a.out_ids && rk < a.capacity) a.out_ids[rk] = own;
+    if (own % a.per_video == 0) a.offsets[own / a.per_video] = rk;
+    if (id >= 0) {
+      const unsigned ex = *word(id);
+      const int dst = (int)((s_first[id >> 6] & 0xffffu) + (low(id) ? ex & 0xffffu : ex >> 16)) + place;
+      a.order[dst] = own;
+      a.orow[dst] = rank_of(id);
+      if (id == own) a.seg[rk] = dst;
     }
-  }
-  __syncthreads();
-  // counts of the wavefronts -> where each one's elements of an id begin
-  int two[2] = {0, 0};
-  if (tid < kListRange / 2) {
-    unsigned run = 0;
-#pragma unroll
-    for (int w = 0; w < kListWaves; ++w) {
-      const unsigned c = cur[w * (kListRange / 2) + tid];
-      cur[w * (kListRange / 2) + tid] = run;
-      run += c;
-    }
-    two[0] = (int)(run & 0xffffu);
-    two[1] = (int)(run >> 16);
-  }
-  int sum;
-  const int ex = block_exclusive_scan<kListWaves>(two[0] + two[1], &sum);  // (its barriers: everybody is done with s_base)
-  if (tid < kListRange / 2) {
-    s_base[2 * tid] = start + ex;
-    s_base[2 * tid + 1] = start + ex + two[0];
   }
   if (tid == 0) {
     if (blockIdx.x == 0) a.kdev[2] = 0;  // the list of big clusters starts empty
     if (hi == a.n) {
-      const int k = roots_before + in_range;
+      const int k = (int)(all >> 16), live = (int)(all & 0xffffu);
       a.kdev[0] = k;
       if (a.host_k) *a.host_k = k;
-      a.kdev[1] = start + all;
+      a.kdev[1] = live;
       a.offsets[a.B] = k;
-      a.seg[k] = start + all;
+      a.seg[k] = live;
     }
-  }
-  __syncthreads();
-#pragma unroll 1
-  for (int q = q0; q < q1; q += 64) {
-    int e = e0, key = key0;
-    if (q != q0) {
-      e = element(q);
-      key = e >= 0 ? a.cluster_ids[e] : 0;
-    }
-    const int d = key - lo;
-    unsigned long long same = __ballot(e >= 0);
-#pragma unroll
-    for (int bit = 0; bit < kListBits; ++bit) {
-      const bool one = (d >> bit) & 1;
-      const unsigned long long m = __ballot(one);
-      same &= one ? m : ~m;
-    }
-    if (e >= 0) {
-      const int half = (d & 1) * 16, rk = s_rank[d];
-      const int dst = s_base[d] + (int)((mycur[d >> 1] >> half) & 0xffffu) + __popcll(same & before);
-      a.order[dst] = e;
-      a.orow[dst] = rk;
-      if (key == e) a.seg[rk] = dst;
-    }
-    wave_lds_fence();
-    if (e >= 0 && ((same >> lane) >> 1) == 0)  // highest lane of its id's group advances the cursor
-      atomicAdd(&mycur[d >> 1], (unsigned)__popcll(same) << ((d & 1) * 16));
-    wave_lds_fence();
   }
 }
 
@@ -1158,15 +1229,24 @@ void launch_reduce_prepare(const Geo& g, const int32_t* cluster_ids, const int32
   const int N = g.N;
   if (N <= kListMax) {
     ListArgs a;
-    a.n = N; a.W = g.W; a.HW = g.HW; a.both_halves = g.vec == 8;
-    a.cap = (N + kListThreads - 1) / kListThreads * kWave;
+    a.n = N; a.W = g.W; a.both_halves = g.vec == 8;
+    a.inv_w = (g.W & 7) == 1 && g.W > 1 ? 0xffffffffu / (unsigned)g.W + 1u : 0u;
+    a.words = list_words(N, N <= kListWide);
+    a.id_bits = 1;
+    while ((N - 1) >> a.id_bits) ++a.id_bits;
     a.cluster_ids = cluster_ids; a.node_map = node_map; a.node_level = node_level;
     a.rank = rb.rank; a.kdev = rb.kdev; a.host_k = rb.host_k;
     a.out_ids = zscan ? nullptr : out_ids; a.offsets = offsets; a.capacity = capacity;
     a.per_video = g.T * g.HW; a.B = g.B;
     a.order = rb.order; a.orow = rb.orow; a.seg = rb.seg;
-    hipLaunchKernelGGL(k_list_small, dim3((N + kListRange - 1) / kListRange), dim3(kListThreads),
-                       (size_t)kListWaves * a.cap * sizeof(uint16_t), s, a);
+    const dim3 slices((N + kListSlice - 1) / kListSlice);
+    const size_t lds = (size_t)a.words * sizeof(unsigned);
+    if (N <= kListTiny)
+      hipLaunchKernelGGL((k_list_small<kListThreadsTiny, true>), slices, dim3(kListThreadsTiny), lds, s, a);
+    else if (N <= kListWide)
+      hipLaunchKernelGGL((k_list_small<kListThreads, true>), slices, dim3(kListThreads), lds, s, a);
+    else
+      hipLaunchKernelGGL((k_list_small<kListThreads, false>), slices, dim3(kListThreads), lds, s, a);
     if (zscan)
       hipLaunchKernelGGL(k_zorder, dim3(g.F), dim3(256), 0, s, g, cluster_ids, rb.rank, capacity, rb.zpos, out_ids);
     return;

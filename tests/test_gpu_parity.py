@@ -957,16 +957,22 @@ def test_recorded_budget_searches_replay(lib, B, T, noise):
 @pytest.mark.parametrize("T,H,W,labels", [
     (1, 1, 1, "own"), (1, 7, 9, "random"), (1, 8, 8, "one"), (5, 13, 1, "random"),       # 1, 63, 64, 65 cells
     (1, 15, 17, "random"), (1, 16, 16, "own"), (257, 1, 1, "one"), (12, 32, 32, "random"),  # around 256 ids of a workgroup
-    (64, 32, 32, "one"), (257, 15, 17, "one"), (257, 15, 17, "random"), (64, 32, 32, "random"),  # 65535 cells, and 65536
+    (64, 32, 32, "one"), (257, 15, 17, "one"), (257, 15, 17, "random"), (64, 32, 32, "random"),
+    # up to 1024 cells by few threads, up to 12288 with a word of the count for every id, up to 49152 in one launch
+    (4, 16, 16, "random"), (41, 5, 5, "random"), (12, 32, 32, "random"), (12289, 1, 1, "random"), (48, 32, 32, "random"),
+    (199, 13, 19, "random"),
+    (2, 8, 8, "still"), (3, 9, 7, "still"), (300, 13, 13, "still"), (63, 32, 32, "still"), (300, 13, 13, "runs"),
 ])
 def test_member_lists_of_every_size(lib, T, H, W, labels):
-    """Up to 65535 cells the member lists are made by one launch, beyond that by sort passes: rows, counts, ids and the
-    clusters' means for labellings with no structure, every cell for itself, and all cells in one cluster. Whole numbers of
+    """Up to 49152 cells the member lists are made by one launch, beyond that by sort passes: rows, counts, ids and the
+    clusters' means for labellings with no structure, every cell for itself, all cells in one cluster, every cell with the
+    same cell of the first frame (a still scene), and runs of cells. Whole numbers of
     at most 255 in at most 2^16 cells: their fp32 sums stay below 2^24 and are exact in any order."""
     import torch
     N, D = T * H * W, 8
     rng = np.random.default_rng(N)
-    first = {"own": np.arange(N), "one": np.zeros(N, np.int64), "random": rng.integers(0, max(1, N // 3), N)}[labels]
+    first = {"own": np.arange(N), "one": np.zeros(N, np.int64), "random": rng.integers(0, max(1, N // 3), N),
+             "still": np.arange(N) % (H * W), "runs": np.arange(N) // 37}[labels]
     _, where, ids = np.unique(first, return_index=True, return_inverse=True)
     cluster = where[ids].astype(np.int32)                    # a cluster's id is its smallest member
     x = rng.integers(-255, 256, (N, D)).astype(np.float32)
