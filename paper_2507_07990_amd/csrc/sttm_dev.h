@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
+#include <stddef.h>
 #include <stdint.h>
 
 // Dynamic LDS of a kernel. (The second form serves the host-thread build used by the CPU tests.)
@@ -414,12 +415,16 @@ constexpr int kSelBins = 2048;
 // 1 + 2^-14 - v, 128 to the octave: 5e-7 wide at v = 1, where the similarities of still scenes crowd, 6e-5 at 0.99, 4e-3 at
 // a half, 8e-3 below zero.
 __device__ inline unsigned sel_bin(uint32_t key);
-// What the first pass over a large input found.
+// The bin again, in its upper bits, with the piece of the bin that the value is in (2048 to a bin) in the lower 11.
+__device__ inline unsigned sel_piece(uint32_t key);
+// What a pass over a large input found.
 struct SelFound {
   unsigned long long budget;  // target - base
-  unsigned long long acc;     // weight of the keys in the bins before the picked one
+  unsigned long long acc;     // weight of the keys in the bins (and pieces) before the picked one
   int rc;                     // 0 = searching, 1 = everything fits (tau = 1), 2 = the base alone exceeds the target
   int list;                   // which of the state's two lists holds the elements
+  unsigned bin;
+  int crowded;                // the picked bin holds too much to be listed: a second pass lists one of its pieces
 };
 // The list that such a pass makes of the picked bin; the elements themselves lie beside the state.
 struct SelList {
@@ -439,15 +444,27 @@ struct alignas(16) SelState {
   SelList list[2];
   unsigned begun;
   unsigned pad0;
-  SelFound found;
-  unsigned pad[20];
+  SelFound found[2];           // by the first pass, by the second one
+  unsigned pad[10];
+  unsigned pieces[2][kSelBins];  // weight per piece of the picked bin where that is crowded; taken in turn like the lists
 };
 static_assert(sizeof(SelState) % 128 == 0, "whole lines");
 
-// One workgroup zeroes a state.
-__device__ inline void sel_clear(SelState* st) {
+// Videos of more elements than this have a crowded bin searched piece by piece. Every workgroup of the kernel that uses the
+// threshold looks at all listed elements, so what that costs grows with the square of a video's size where similarities
+// crowd. 512 frames of 32x32, the searches and the kernels that use them, us, without and with the second pass: similarities
+// within 10^-4 of one 112 and 73, unrelated vectors 102 and 69, moving blocks 72 and 68; 128 frames of 32x32 (within 10^-4) 54
+// by one pass.
+#ifndef STTM_SEL_REFINE
+#define STTM_SEL_REFINE 131072
+#endif
+constexpr int kSelRefine = STTM_SEL_REFINE;
+
+// One workgroup zeroes a state (of a video of `elements` elements).
+__device__ inline void sel_clear(SelState* st, int elements) {
   unsigned* p = reinterpret_cast<unsigned*>(st);
-  for (int j = threadIdx.x; j < (int)(sizeof(SelState) / 4); j += blockDim.x) p[j] = 0;
+  const int words = (int)((elements > kSelRefine ? sizeof(SelState) : offsetof(SelState, pieces)) / 4);
+  for (int j = threadIdx.x; j < words; j += blockDim.x) p[j] = 0;
 }
 
 // Adds w to hist[digit] for the lanes with valid set; every lane of the wavefront must call it. The two
@@ -478,14 +495,15 @@ __device__ inline void sel_flush_bins(SelState* st, const unsigned* lds_hist) {
 
 constexpr int kSelThreads = 256;
 
-// Workgroup-wide (THREADS threads): the first bin of `hist` at which acc + running weight exceeds `budget`.
-// Returns false when the whole histogram fits. All threads get the same answer.
+// Workgroup-wide (THREADS threads): the first bin of `hist` at which acc + running weight exceeds `budget`, the weight
+// before it and (if asked for) its own. Returns false when the whole histogram fits. All threads get the same answer.
 // The histogram is the sum of COPIES arrays of kSelBins counters.
 template <int COPIES, int THREADS>
 __device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long long acc,
-                                unsigned long long budget, unsigned* digit, unsigned long long* acc_out) {
+                                unsigned long long budget, unsigned* digit, unsigned long long* acc_out,
+                                unsigned* weight = nullptr) {
   __shared__ unsigned long long wsum[THREADS / 64];
-  __shared__ unsigned s_digit;
+  __shared__ unsigned s_digit, s_weight;
   __shared__ unsigned long long s_acc;
   __shared__ int s_found;
   constexpr int PER = kSelBins / THREADS;
@@ -520,6 +538,7 @@ __device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long
     if (ex <= budget && ex + h[j] > budget) {
       s_found = 1;
       s_digit = (unsigned)(tid * PER + j);
+      s_weight = h[j];
       s_acc = ex;
     }
     ex += h[j];
@@ -528,6 +547,7 @@ __device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long
   const bool found = s_found != 0;
   *digit = s_digit;
   *acc_out = s_acc;
+  if (weight) *weight = s_weight;
   __syncthreads();
   return found;
 }
@@ -535,6 +555,10 @@ __device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long
 __device__ inline unsigned sel_bin(uint32_t key) {
   const float t = 1.00006103515625f - key_float(key);  // (at least 2^-14: similarities are at most 1)
   return 2047u - (unsigned)min(max((int)(__float_as_uint(t) - 0x38800000u) >> 16, 0), 2047);
+}
+__device__ inline unsigned sel_piece(uint32_t key) {
+  const float t = 1.00006103515625f - key_float(key);
+  return 0x3fffffu - (unsigned)min(max((int)(__float_as_uint(t) - 0x38800000u) >> 5, 0), 0x3fffff);
 }
 
 // A budget search that the kernel using its threshold carries out.
@@ -572,7 +596,8 @@ __device__ inline SelFound sel_begin(const Geo& g, int b, const int* target, int
   fd.budget = budget < 0 ? 0ull : (unsigned long long)budget;
   fd.acc = 0;
   fd.rc = budget < 0 ? 2 : 0;
-  fd.list = 0;
+  fd.list = fd.crowded = 0;
+  fd.bin = 0;
   return fd;
 }
 
@@ -602,7 +627,9 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
   if (q.whole) {
     fd = sel_begin(g, b, q.target, q.base_const, q.node_map);
   } else {
-    fd = q.states[b].found;
+    fd = q.states[b].found[0];
+    const unsigned long long acc = q.states[b].found[1].acc;  // (all loads at once)
+    if (fd.crowded) fd.acc = acc;
     const SelList first = q.states[b].list[0], second = q.states[b].list[1];
     count = min((int)(fd.list ? second.count : first.count), q.per_video);
     if (tid == 0) s_lo = fd.list ? second.lo : first.lo;

@@ -220,7 +220,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
   const int ty = y3 + (q2 >> 1) * 4, tx = x3 + (q2 & 1) * 4;
   const int th = max(0, min(4, H - ty)), tw = max(0, min(4, W - tx));  // valid rows / columns of the tile
   const bool has_next = CC && f % g.T != g.T - 1;
-  if (chunk == 0 && u == 0 && f % g.T == 0) sel_clear(sel + f / g.T);  // this video's budget search starts afresh
+  if (chunk == 0 && u == 0 && f % g.T == 0) sel_clear(sel + f / g.T, g.T * (g.NN - g.lvl_base[1]));  // this video's budget search starts afresh
   float S2[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) S2[v] = 0.f;
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_stats(Geo g, const void* __r
   const int ty = y3 + (q2 >> 1) * 4, tx = x3 + (q2 & 1) * 4;
   const int th = max(0, min(4, H - ty)), tw = max(0, min(4, W - tx));  // valid rows / columns of the tile
   if (chunk == 0 && u == 0)  // the budget searches of the videos that begin here start afresh
-    for (int b = (f0 + g.T - 1) / g.T; b * g.T < f1; ++b) sel_clear(sel + b);
+    for (int b = (f0 + g.T - 1) / g.T; b * g.T < f1; ++b) sel_clear(sel + b, g.T * (g.NN - g.lvl_base[1]));
   for (int i = tid; i < 3 * kUnitScalars; i += 256) (&st[0][0])[i] = 0.f;
   for (int i = tid; i < 2 * 4 * (VEC / 4) * 64; i += 256) (&tsum[0][0][0][0])[i] = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
@@ -969,10 +969,14 @@ void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float
 }
 
 // ------------------------------------------------------------------------------------------------
-// k_spatial_decide: coarse-to-fine search (Sec. 3.2). Grid (cells of a video / 256, videos); one thread per cell
+// k_spatial_decide: coarse-to-fine search (Sec. 3.2). Grid (cells of a video / threads, videos); one thread per cell
 // walks down from its root: the first node on the path whose smallest child similarity exceeds tau_S is kept.
+// Large videos take fewer and larger workgroups, since each carries the search out (512 frames of 13x13 random vectors 19.8 ->
+// 16.3 us, moving scenes of that size 10.9 and 11.1, of 46 frames of 27x27 9.9 and 10.4; 1024 threads 16.8, 12.3, 11.8).
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kSelThreads) void k_spatial_decide(Geo g, const float* __restrict__ m,
+constexpr int kDecideWide = 65536, kDecideThreads = 512;
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_spatial_decide(Geo g, const float* __restrict__ m,
                                                                 float* __restrict__ tau, TauArgs given,
                                                                 SelSearch pending,
                                                                 int32_t* __restrict__ node_map,
@@ -980,7 +984,7 @@ __global__ __launch_bounds__(kSelThreads) void k_spatial_decide(Geo g, const flo
   const int b = blockIdx.y, per_video = g.T * g.HW;
   float t;
   if (pending.states || given.n) {  // the budget search was left to this kernel, or the caller named the threshold
-    t = given.n ? given.v[b] : sel_threshold<kSelThreads>(g, pending, b);
+    t = given.n ? given.v[b] : sel_threshold<THREADS>(g, pending, b);
     if (blockIdx.x == 0 && threadIdx.x == 0) tau[b] = t;
   } else {
     t = tau[b];
@@ -1002,8 +1006,12 @@ __global__ __launch_bounds__(kSelThreads) void k_spatial_decide(Geo g, const flo
 void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauArgs& given, const SelSearch& pending,
                            int32_t* node_map, uint8_t* node_level, hipStream_t s) {
   const int per_video = g.T * g.HW;
-  hipLaunchKernelGGL(k_spatial_decide, dim3((per_video + kSelThreads - 1) / kSelThreads, g.B), dim3(kSelThreads), 0, s,
-                     g, m, tau, given, pending, node_map, node_level);
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3((per_video + threads - 1) / threads, g.B), dim3(threads), 0, s, g, m, tau, given, pending,
+                       node_map, node_level);
+  };
+  if (per_video > kDecideWide) launch(k_spatial_decide<kDecideThreads>, kDecideThreads);
+  else launch(k_spatial_decide<kSelThreads>, kSelThreads);
 }
 
 // Recovers node levels from a node map (callers may pass node_level == NULL to the temporal stage).
@@ -1056,65 +1064,57 @@ constexpr int kSelWhole = STTM_SEL_WHOLE;
 #define STTM_SEL_THREADS 512
 #endif
 constexpr int kPassThreads = STTM_SEL_THREADS, kSelPer = 4;
+// A bin of more weight than this is crowded.
+#ifndef STTM_SEL_CROWD
+#define STTM_SEL_CROWD 4096
+#endif
+constexpr unsigned kSelCrowd = STTM_SEL_CROWD;
 
-__global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint32_t* __restrict__ keys,
-                                                             const uint8_t* __restrict__ weights, int per_video,
-                                                             const int* __restrict__ target, int base_const,
-                                                             const int32_t* __restrict__ node_map,
-                                                             SelState* __restrict__ states,
-                                                             uint32_t* __restrict__ list_key,
-                                                             uint8_t* __restrict__ list_w) {
-  __shared__ unsigned s_lo, s_n, s_at, s_list;
-  const int b = blockIdx.y, tid = threadIdx.x;
-  if (tid == 0) s_lo = s_n = 0;
-  SelState* st = states + b;
-  // the slice's keys do not depend on the search: their loads fly while the bin is being found
-  const uint32_t* kv = keys + (size_t)b * per_video;
-  const int j0 = blockIdx.x * (kPassThreads * kSelPer);
+// A workgroup's slice of the elements, kSelPer to a thread.
+struct SelSlice {
   uint32_t key[kSelPer];
   unsigned w[kSelPer];
+};
+__device__ inline SelSlice sel_load(const uint32_t* keys, const uint8_t* weights, int per_video, int b) {
+  SelSlice q;
 #pragma unroll
   for (int u = 0; u < kSelPer; ++u) {
-    const int j = j0 + u * kPassThreads + tid;
-    key[u] = j < per_video ? kv[j] : 0u;
-    w[u] = weights && j < per_video ? weights[(size_t)b * per_video + j] : 1u;
+    const int j = (blockIdx.x * kSelPer + u) * kPassThreads + threadIdx.x;
+    const size_t at = (size_t)b * per_video + j;
+    q.key[u] = j < per_video ? keys[at] : 0u;
+    q.w[u] = weights && j < per_video ? weights[at] : 1u;
   }
-  unsigned turn = 0;
-  if (tid == 0) turn = atomicAdd(&st->begun, 1u);
-  SelFound fd = sel_begin(g, b, target, base_const, node_map);
-  unsigned bin = 0;
-  if (fd.rc == 0 && !sel_pick<kSelCopies, kPassThreads>(st->hist0[0], 0ull, fd.budget, &bin, &fd.acc)) fd.rc = 1;
-  if (tid == 0) {
-    fd.list = turn >= gridDim.x;
-    if (turn == 2 * gridDim.x - 1) atomicExch(&st->begun, 0u);  // (every workgroup of both searches has its number)
-    if (blockIdx.x == 0) {
-      st->found = fd;
-      st->list[1 - fd.list] = {0u, 0u};  // for the next search
-    }
-    s_list = fd.list;
-  }
-  if (fd.rc) return;  // uniform over the workgroup
+  return q;
+}
+
+// Appends the elements of the slice whose `where` (a bin, or a piece of one) is `picked` to the list, and notes the largest key
+// with a smaller one.
+template <class Where>
+__device__ inline void sel_append(SelSlice& q, Where where, unsigned picked, SelList* l, int per_video, int b,
+                                  uint32_t* __restrict__ list_key, uint8_t* __restrict__ list_w) {
+  __shared__ unsigned s_lo, s_n, s_at;
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (tid == 0) s_lo = s_n = 0;
   __syncthreads();
   unsigned lo = 0, place[kSelPer];  // key 0 is below every real value
 #pragma unroll
   for (int u = 0; u < kSelPer; ++u) {
-    const unsigned at = key[u] ? sel_bin(key[u]) : kSelBins;
-    if (at < bin) lo = max(lo, key[u]);
+    const unsigned at = q.key[u] ? where(q.key[u]) : 0xffffffffu;
+    if (at < picked) lo = max(lo, q.key[u]);
     place[u] = 0xffffffffu;
     // Equal keys of the wavefront's 64 become one element (for the two most frequent of them): still scenes are full of
     // them, and so are the scores of a node's descendants, which are the node's.
-    const int lane = tid & 63;
-    unsigned long long todo = __ballot(at == bin);
+    unsigned long long todo = __ballot(at == picked);
 #pragma unroll 1
     for (int it = 0; it < 2 && __popcll(todo) > 8; ++it) {
       const int leader = __ffsll((long long)todo) - 1;
-      const uint32_t leads = (uint32_t)__shfl((int)key[u], leader, 64);  // (by all lanes, whatever their own key)
-      const bool mine = at == bin && key[u] == leads;
+      const uint32_t leads = (uint32_t)__shfl((int)q.key[u], leader, 64);  // (by all lanes, whatever their own key)
+      const bool mine = at == picked && q.key[u] == leads;
       const unsigned long long m = __ballot(mine);
-      const unsigned sum = __popcll(__ballot(mine && (w[u] & 1))) + 2u * __popcll(__ballot(mine && (w[u] & 2)));
+      const unsigned sum = __popcll(__ballot(mine && (q.w[u] & 1))) + 2u * __popcll(__ballot(mine && (q.w[u] & 2)));
       if (lane == leader) {
         place[u] = atomicAdd(&s_n, 1u);
-        w[u] = sum;
+        q.w[u] = sum;
       }
       todo &= ~m;
     }
@@ -1122,10 +1122,9 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) lo = max(lo, (unsigned)__shfl_xor((int)lo, o, 64));
-  if ((tid & 63) == 0 && lo) atomicMax(&s_lo, lo);
+  if (lane == 0 && lo) atomicMax(&s_lo, lo);
   __syncthreads();
   if (tid == 0) {
-    SelList* l = &st->list[s_list];
     if (s_lo) atomicMax(&l->lo, s_lo);
     s_at = s_n ? atomicAdd(&l->count, s_n) : 0u;
   }
@@ -1134,9 +1133,78 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
   for (int u = 0; u < kSelPer; ++u) {
     if (place[u] == 0xffffffffu || s_at + place[u] >= (unsigned)per_video) continue;  // (never beyond the list's room)
     const size_t o = (size_t)b * per_video + s_at + place[u];
-    list_key[o] = key[u];
-    list_w[o] = (uint8_t)w[u];  // (at most 64 elements of weight 3)
+    list_key[o] = q.key[u];
+    list_w[o] = (uint8_t)q.w[u];  // (at most 64 elements of weight 3)
   }
+}
+
+// REFINE: a crowded bin is not listed, its pieces' weights are counted for k_select_piece.
+template <bool REFINE>
+__global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint32_t* __restrict__ keys,
+                                                             const uint8_t* __restrict__ weights, int per_video,
+                                                             const int* __restrict__ target, int base_const,
+                                                             const int32_t* __restrict__ node_map,
+                                                             SelState* __restrict__ states,
+                                                             uint32_t* __restrict__ list_key,
+                                                             uint8_t* __restrict__ list_w) {
+  __shared__ unsigned s_list;
+  const int b = blockIdx.y, tid = threadIdx.x;
+  SelState* st = states + b;
+  // the slice's keys do not depend on the search: their loads fly while the bin is being found
+  SelSlice q = sel_load(keys, weights, per_video, b);
+  unsigned turn = 0, weight = 0;
+  if (tid == 0) turn = atomicAdd(&st->begun, 1u);
+  SelFound fd = sel_begin(g, b, target, base_const, node_map);
+  if (fd.rc == 0 && !sel_pick<kSelCopies, kPassThreads>(st->hist0[0], 0ull, fd.budget, &fd.bin, &fd.acc, &weight)) fd.rc = 1;
+  fd.crowded = REFINE && fd.rc == 0 && weight > kSelCrowd;
+  if (tid == 0) {
+    fd.list = turn >= gridDim.x;
+    if (turn == 2 * gridDim.x - 1) atomicExch(&st->begun, 0u);  // (every workgroup of both searches has its number)
+    if (blockIdx.x == 0) {
+      st->found[0] = fd;
+      st->list[1 - fd.list] = {0u, 0u};  // for the next search
+    }
+    s_list = fd.list;
+  }
+  if (!REFINE && fd.rc) return;  // uniform over the workgroup
+  __syncthreads();
+  const unsigned list = s_list;
+  if constexpr (REFINE) {
+    if (blockIdx.x == 0)
+      for (int j = tid; j < kSelBins; j += kPassThreads) st->pieces[1 - list][j] = 0;
+    if (fd.rc) return;
+    if (fd.crowded) {
+      __shared__ unsigned h[kSelBins];
+      for (int j = tid; j < kSelBins; j += kPassThreads) h[j] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kSelPer; ++u)
+        wave_hist_add(h, q.key[u] && sel_bin(q.key[u]) == fd.bin, sel_piece(q.key[u]) & (kSelBins - 1), q.w[u]);
+      __syncthreads();
+      for (int j = tid; j < kSelBins; j += kPassThreads)
+        if (h[j]) atomicAdd(&st->pieces[list][j], h[j]);
+      return;
+    }
+  }
+  sel_append(q, [](uint32_t key) { return sel_bin(key); }, fd.bin, &st->list[list], per_video, b, list_key, list_w);
+}
+
+// The second pass over a video whose picked bin is crowded: lists one piece of it.
+__global__ __launch_bounds__(kPassThreads) void k_select_piece(Geo g, const uint32_t* __restrict__ keys,
+                                                              const uint8_t* __restrict__ weights, int per_video,
+                                                              SelState* __restrict__ states,
+                                                              uint32_t* __restrict__ list_key,
+                                                              uint8_t* __restrict__ list_w) {
+  const int b = blockIdx.y;
+  SelState* st = states + b;
+  SelFound fd = st->found[0];
+  if (!fd.crowded) return;  // uniform over the workgroup, as everywhere
+  SelSlice q = sel_load(keys, weights, per_video, b);
+  unsigned piece = 0;
+  if (!sel_pick<1, kPassThreads>(st->pieces[fd.list], fd.acc, fd.budget, &piece, &fd.acc)) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->found[1] = fd;
+  sel_append(q, [](uint32_t key) { return sel_piece(key); }, fd.bin * kSelBins + piece, &st->list[fd.list], per_video, b,
+             list_key, list_w);
 }
 
 // The whole search as a launch of its own (when the caller wants the threshold back).
@@ -1155,8 +1223,14 @@ static SelSearch launch_select(const Geo& g, const uint32_t* keys, const uint8_t
   SelSearch q = {st, keys, weights, per_video, true, target, base_const, node_map};
   if (per_video <= kSelWhole) return q;
   const dim3 grid((per_video + kPassThreads * kSelPer - 1) / (kPassThreads * kSelPer), g.B), block(kPassThreads);
-  hipLaunchKernelGGL(k_select_list, grid, block, 0, s, g, keys, weights, per_video, target, base_const, node_map, st,
-                     list_key, list_w);
+  if (per_video > kSelRefine) {
+    hipLaunchKernelGGL(k_select_list<true>, grid, block, 0, s, g, keys, weights, per_video, target, base_const, node_map, st,
+                       list_key, list_w);
+    hipLaunchKernelGGL(k_select_piece, grid, block, 0, s, g, keys, weights, per_video, st, list_key, list_w);
+  } else {
+    hipLaunchKernelGGL(k_select_list<false>, grid, block, 0, s, g, keys, weights, per_video, target, base_const, node_map, st,
+                       list_key, list_w);
+  }
   q.keys = list_key;
   q.weights = list_w;
   q.whole = false;

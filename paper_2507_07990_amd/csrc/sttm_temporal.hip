@@ -98,7 +98,7 @@ __global__ __launch_bounds__(256) void k_temporal_plan(Geo g, const uint8_t* __r
   const int f = blockIdx.x, t = f % g.T, b = f / g.T;
   const int H = g.H, W = g.W, HW = g.HW, tid = threadIdx.x;
   if (t == 0) {  // no pair ends here; the temporal budget search of this video starts afresh
-    sel_clear(sel + b);
+    sel_clear(sel + b, g.T * g.HW);
     return;
   }
   if (tid == 0) { nfast = nmid = nX = 0; }
@@ -720,6 +720,9 @@ void launch_temporal_parent(const Geo& g, int match, const int32_t* node_map, co
   const size_t lds = parent_lds(g, run, match);
   if (run > 1)
     hipLaunchKernelGGL(k_temporal_parent<kParThreads>, grid, dim3(kParThreads), lds, s, g, match, run, runs, node_map,
+                       node_level, sig, tau, given, pending, parent, ptr);
+  else if (g.HW > kSelThreads)  // (64 frames of 32x32: edges and roots 20.9 us by 256 threads a frame, 18.7 by 512)
+    hipLaunchKernelGGL(k_temporal_parent<2 * kSelThreads>, grid, dim3(2 * kSelThreads), lds, s, g, match, run, runs, node_map,
                        node_level, sig, tau, given, pending, parent, ptr);
   else
     hipLaunchKernelGGL(k_temporal_parent<kSelThreads>, grid, dim3(kSelThreads), lds, s, g, match, run, runs, node_map,

@@ -847,6 +847,10 @@ def _searched(values, weights, base, target):
     (32, 0.02, 512),    # all similarities within a few hundredths of one
     (200, 0.003, 512),  # and within 1e-4: more elements in the picked bin than a workgroup keeps
     (60, 0.0, 64),      # nothing but ties
+    (600, 0.5, 64),     # 153600 cells: a crowded bin is searched piece by piece, one that is not as ever
+    (1600, 0.003, 64),  # and so is one of the 136000 nodes above the cells
+    (600, 50.0, 256),   # unrelated vectors: similarities of either sign around zero
+    (600, 0.0, 64),     # ties
 ])
 def test_budget_searches_are_exact(lib, T, noise, D):
     """The thresholds found, against the rule applied to the similarity tables the library exports: the same fp32 values,
@@ -903,6 +907,7 @@ def test_budget_searches_are_exact(lib, T, noise, D):
 @pytest.mark.parametrize("B,T,noise", [
     (1, 40, 0.3),       # 10240 cells, 3400 nodes above them: the elements of the picked bin few
     (2, 150, 0.003),    # all similarities close to one: thousands of elements in the picked bin
+    (1, 600, 0.003),    # and searched piece by piece
 ])
 def test_recorded_budget_searches_replay(lib, B, T, noise):
     """A search and the call that uses its threshold, captured after statistics that were not: every replay gives the eager
