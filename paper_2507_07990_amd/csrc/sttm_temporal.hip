@@ -625,15 +625,22 @@ void launch_temporal_resolve(const Geo& g, int match, const int32_t* node_map,
 // the frame before the run that its chain leaves the run by.
 // (With one frame to a workgroup everywhere, and a launch more for the first 23 hops of every chain, these kernels took, us:
 // 64 frames of 13x13 15.3, now 12.8, 32 videos of 32 frames of 27x27 22.0 and 16.7, 96 frames of 11x19 12.6 and 9.7, six
-// clips of 25 frames 13.2 and 9.2. Runs of 23 frames for 512 frames: 25 against 18, too few workgroups.)
+// clips of 25 frames 13.2 and 9.2.)
 // ------------------------------------------------------------------------------------------------
 constexpr int kParThreads = 1024;  // of a workgroup with more than one frame
 constexpr int kParCells = 2048;  // cells of a run of more than one frame at most
 constexpr int kHops = 23;        // edges that one launch below follows
-// Frames of a run: as many as it takes for the runs of a video to be crossed by one launch, if that is few.
+// Frames of a run: as many as it takes for the runs of a video to be crossed by one launch, if these are no more cells than
+// one workgroup takes at a time and no longer than kRunFrames; else, while they are few cells all the same, a hundred or so
+// runs (a chain is followed frame by frame through a run, and few workgroups follow them) and a launch more. Edges and
+// roots, us, with as many as needed and by this rule: 1000 frames of 6x6 22.3 and 18.0, 2000 of 4x4 22.6 and 17.0, 512 of 8x8
+// 17.9 and 17.1; a pass over 8000 still frames of 2x2 171 and 134. Up to kRunFrames: 300 frames of 3x3 in runs of 14 14.1, of
+// 4 15.6; 200 of 9x9 in runs of 9 15.5, of 3 18.7, of one 20.6.
+constexpr int kRunFrames = 14, kRuns = 128, kRunLeast = 8;
 static int parent_run(const Geo& g) {
   const int needed = (g.T + kHops - 1) / kHops;
-  return needed * g.HW <= kParCells ? needed : 1;
+  if (needed * g.HW > kParCells) return 1;
+  return needed <= kRunFrames ? needed : max(kRunLeast, (g.T + kRuns - 1) / kRuns);
 }
 static size_t parent_lds(const Geo& g, int run, int match) {
   const size_t cells = (size_t)run * g.HW;

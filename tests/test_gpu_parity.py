@@ -789,15 +789,19 @@ def test_both_pyramid_kernels_give_the_same_bits(lib, H, W, D, dtype, R, tau_s, 
 
 
 @pytest.mark.parametrize("match", [0, 1, 2])
-@pytest.mark.parametrize("T", [23, 24, 69, 70, 600])   # runs of 1, 2, 3 and 4 frames, and one frame again (27 * 81 cells)
-def test_edges_and_roots_across_runs_of_frames(lib, T, match):
+@pytest.mark.parametrize("T,H", [
+    (23, 9), (24, 9), (69, 9), (70, 9), (600, 9),   # runs of 1, 2, 3 and 4 frames, and one frame again (27 * 81 cells)
+    (322, 9), (323, 9),                             # 14, and 8: runs that one launch does not cross
+    (1025, 4), (4000, 2),                           # 9 and 32
+])
+def test_edges_and_roots_across_runs_of_frames(lib, T, H, match):
     """The edges of a video's first frames do not depend on how many frames follow (and so on the frames a workgroup takes);
     every cell's cluster is where the edges lead from its node."""
     import torch
-    H = W = 9
+    W = H
     D = 16
     gen = torch.Generator(device="cuda:0").manual_seed(T + match)
-    blocks = torch.randn(2, 1, 3, 3, D, device="cuda:0", generator=gen).repeat_interleave(3, 2).repeat_interleave(3, 3)
+    blocks = torch.randn(2, 1, 3, 3, D, device="cuda:0", generator=gen).repeat_interleave(3, 2).repeat_interleave(3, 3)[:, :, :H, :W]
     x = (blocks + 0.35 * torch.randn(2, T, H, W, D, device="cuda:0", generator=gen)).contiguous()
 
     def edges(v):
@@ -815,7 +819,7 @@ def test_edges_and_roots_across_runs_of_frames(lib, T, match):
 
     nm, cl, pa = edges(x)
     root = np.where(pa >= 0, pa, np.arange(len(pa)))
-    for _ in range(10):                                      # 2^10 steps
+    for _ in range(12):                                      # 2^12 steps
         root = root[root]
     np.testing.assert_array_equal(cl, root[nm])
     assert 0 < (pa >= 0).sum() and len(np.unique(cl)) > 2
