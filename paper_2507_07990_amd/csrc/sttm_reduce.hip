@@ -711,7 +711,8 @@ __global__ __launch_bounds__(THREADS) void k_list_small(ListArgs a) {
   __syncthreads();
   const int waves = (int)row16_inclusive(lane < WAVES ? s_wave[lane] : 0u, lane);
   const unsigned all = (unsigned)lane_value(waves, WAVES - 1);
-  if (tid < runs) s_first[tid] = (wave ? (unsigned)lane_value(waves, wave - 1) : 0u) + upto - run;
+  const unsigned earlier = wave ? (unsigned)lane_value(waves, wave - 1) : 0u;  // (by all lanes of the wavefront)
+  if (tid < runs) s_first[tid] = earlier + upto - run;
   __syncthreads();
   auto rank_of = [&](int i) {
     return (int)(s_first[i >> 6] >> 16) + __popcll(s_roots[i >> 6] & ((1ull << (i & 63)) - 1ull));
