@@ -68,7 +68,7 @@ def test_emulated_destination_rules_orders_and_positions(emul, mode, order):
 
 
 def test_emulated_budget_threshold_left_to_the_consumer_kernels(emul):
-    """Without a host pointer for the threshold the last digit of the search is resolved by the kernels that use it:
+    """Without a host pointer for the threshold the value of the search is found by the kernels that use it:
     same partition, same clusters, same rows."""
     run_cpu, fake = emul
     feats = wl.generate(_variant(91, 2, 3, 5, 6, 24, "bf16"))
