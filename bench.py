@@ -130,11 +130,6 @@ def main() -> int:
     ap.add_argument("--positions", action="store_true", help="also emit the position indices of the rows each step")
     ap.add_argument("--no-cell-dots", action="store_true",
                     help="keep the spatial and temporal passes separate (sttm_set_cell_dots(0))")
-    ap.add_argument("--cell-dots-only", action="store_true",
-                    help="sttm_set_cell_dots(1) at every budget (default: 2 where 35 %% of the tokens or less are kept; "
-                         "both mean the same)")
-    ap.add_argument("--node-dots", action="store_true",
-                    help="sttm_set_cell_dots(2) at every budget")
     ap.add_argument("--no-node-sums", action="store_true",
                     help="reduce stage without the stage-1 partition: every cell is read again")
     ap.add_argument("--no-two-streams", action="store_true",
@@ -190,16 +185,8 @@ def main() -> int:
     s.sttm_set_match_mode({"first_passing": 0, "topleft_only": 1, "most_similar": 2}[args.match])
     s.sttm_set_output_order({"raster": 0, "zscan": 1}[args.order])
 
-    def dots_level(keep):
-        """Which frame-to-frame dot products the spatial pass leaves for the temporal stage (sttm_set_cell_dots): 0 none;
-        1 and 2 mean the same, those of cells and of 2x2 and 4x4 blocks."""
-        if args.no_cell_dots:
-            return 0
-        if args.node_dots:
-            return 2
-        if args.cell_dots_only or keep is None:
-            return 1
-        return 2 if keep <= 0.35 else 1
+    # whether the spatial pass leaves the frame-to-frame dot products of cells, 2x2 and 4x4 blocks for the temporal stage
+    level = 0 if args.no_cell_dots else 1
 
     s.ensure_workspace(B, T, H, W, D, dt, R)
     node_map = torch.empty(N, dtype=torch.int32, device=dev)
@@ -236,7 +223,6 @@ def main() -> int:
     def measure(keep):
         """W warm-up steps, then exactly K timed steps: the wall clock around all of them, and one HIP event
         between consecutive steps on the stream the library launches on, for the median step time."""
-        level = dots_level(keep)
         s.sttm_set_cell_dots(level)
         for _ in range(args.warmup):
             step(keep)
@@ -263,17 +249,15 @@ def main() -> int:
         # Algorithmic bytes per launch of each feature kernel: every input element it must see read once,
         # every output element written once (design notes: data layout / kernels). The temporal pass must see the
         # rows of the node pairs it computes: both nodes' cells when the coarser one is at most a 4x4 block, only the
-        # finer node's cells above that (the coarser node's sum is stored) -- and nothing for a pair of two single
-        # cells when the spatial pass left that dot product. A row needed by two frame pairs counts once.
+        # finer node's cells above that (the coarser node's sum is stored) -- and nothing for a pair of the same cell,
+        # 2x2 or 4x4 block when the spatial pass left that dot product. A row needed by two frame pairs counts once.
         lv = node_level.view(B, T, H * W)
         if T > 1:
             a, b = lv[:, 1:].int(), lv[:, :-1].int()
             J = torch.maximum(a, b)
             small = J <= 2
-            if level == 2:
+            if level:
                 small = small & (a != b)
-            elif level == 1:
-                small = small & (J > 0)
             need_t = small | ((J >= 3) & (a < b))   # rows of the later frame of a pair
             need_p = small | ((J >= 3) & (b < a))   # rows of the earlier frame
             need = torch.zeros(B, T, H * W, dtype=torch.bool, device=dev)
@@ -338,7 +322,7 @@ def main() -> int:
             c = lib.Sttm(0, stream_ptr=st.cuda_stream)
             c.sttm_set_match_mode({"first_passing": 0, "topleft_only": 1, "most_similar": 2}[args.match])
             c.sttm_set_output_order({"raster": 0, "zscan": 1}[args.order])
-            c.sttm_set_cell_dots(dots_level(keep))
+            c.sttm_set_cell_dots(level)
             c.ensure_workspace(B, T, H, W, D, dt, R)
             bufs = dict(node_map=torch.empty_like(node_map), node_level=torch.empty_like(node_level),
                         cluster=torch.empty_like(cluster), merged=torch.empty_like(merged),
