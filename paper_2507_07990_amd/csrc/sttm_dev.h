@@ -789,7 +789,7 @@ void launch_temporal_dots(const Geo& g, const void* feats, const uint8_t* node_l
                           hipStream_t s);
 size_t temporal_items_bytes(const Geo& g);
 size_t temporal_count_bytes();
-// The first pass works in 8x8-cell units (one wavefront per unit, chunk and frame) and leaves each unit's scalars
+// The first pass works in 8x8-cell units (one workgroup per unit and chunk) and leaves each unit's scalars
 // as one block of kUnitScalars floats: per 4x4 tile 16 squared norms, 16 cell and 4 level-1 dot products, then the
 // 4 level-2 dot products (padded to whole 128-byte lines), then per tile the 16 dot products of its cells with the
 // same cells of the next frame, then per tile the dot products of its four 2x2 blocks and of the tile itself with the

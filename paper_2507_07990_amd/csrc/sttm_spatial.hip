@@ -163,8 +163,9 @@ __device__ inline bool finite(float v) { return (__float_as_uint(v) & 0x7f800000
 // tile is asked for by two workgroups: its own frame's and the one of the frame before. Workgroups go to the eight dies
 // round-robin by their index; each die gets a contiguous range of frames and walks it in order, two frames at a time
 // with the same (unit, chunk) of both next to each other, so that the two requests come from the same die within a few
-// microseconds of each other and the second one is served by that die's L2. (180 frames of 18x24 tokens at D = 8192, 144
-// workgroups a frame, frame after frame: 2.44 GB fetched, 357 us; in pairs 331. Groups of 4 to 16 frames: 335-345.)
+// microseconds of each other and the second one is served by that die's L2. (The statistics call, frame after frame and in
+// pairs: 25 frames of 18x24 tokens at D = 8192, 144 workgroups a frame, 81.3 and 69.6 us; 64 of 13x13 at D = 3584 30.6 and
+// 29.7; 140 of those and 64 of 16x16 at D = 1152 the same; 150 of 15x20 at D = 1280 41.6 and 42.1.)
 constexpr int kPyrGroup = 2;
 __device__ __forceinline__ bool pyramid_place(const Geo& g, int NU, int& f, int& u, int& chunk) {
   const int per_die = (g.F + 7) / 8, die = blockIdx.x & 7;
@@ -403,16 +404,18 @@ __global__ __launch_bounds__(256, 3) void k_pyramid_tiles(Geo g, const void* __r
 //         nsum[f][node - first level-3 node][D] = the per-channel sums of the level-3 nodes (fp32), which
 //         the later stages read instead of re-adding up to 64 token rows.
 // What bounds it: memory. 512 frames of 13x13 at D = 3584 in bf16, 653 MB read and 44 MB written in 145 us: 138 without
-// the arithmetic, 124 without the stores, 111 without either. 180 frames of 18x24 at D = 8192: 1.31 GB and 79 MB in 255 us
-// (5.4 TB/s). (A wavefront that took a unit's tiles one after the other and asked for the next frame's rows as well, from
-// the cache its neighbour had just filled: 172 and 325 us.) The loads are marked
-// non-temporal: 158 and 286 us without. Eight places and two wavefronts per SIMD: 147 and 313. Two or three rounds of
-// workgroups with shorter runs read more rows twice: 154 and 161 us.
+// the arithmetic, 124 without the stores, 111 without either. 180 frames of 18x24 at D = 8192: 1.31 GB and 79 MB in 290 us
+// (4.8 TB/s). (A wavefront that took a unit's tiles one after the other and asked for the next frame's rows as well, from
+// the cache its neighbour had just filled: 172 and 328 us.) The loads are marked non-temporal: the 512 frames in 158 us
+// without. Eight places and two wavefronts per SIMD: 147. Two or three rounds of workgroups with shorter runs read more rows
+// of them twice: 154 and 161 us.
 // ------------------------------------------------------------------------------------------------
 constexpr int kWalkSlots = 6, kWalkPeriod = 3;  // places of a block's rows; frames after which their roles are the same again
 // Workgroups of one round: three wavefronts per SIMD. While a run stays this many frames long (3 % of the rows read twice)
-// there are more rounds, which even out what ragged units need: 1024 frames of 27x27 at D = 1152, 416 us in one round and
-// 400 in two. (The host-thread build of the tests asks for few, so that it has runs of more than one frame.)
+// there are more rounds, up to three, which even out what ragged units need. The statistics call (this kernel and the next)
+// with at most one, two and three rounds, us: 2000 frames of 13x13 at D = 3584 598, 595, 570; 600 of 18x24 at D = 8192 1052,
+// 1001, 977; 2048 of 27x27 at D = 1152 938, 925, 919; 1024 of those (long enough for two) 465, 463, 462.
+// (The host-thread build of the tests asks for few, so that it has runs of more than one frame.)
 #ifndef STTM_WALK_GROUPS
 #ifdef STTM_HOST_EMULATION
 #define STTM_WALK_GROUPS 2

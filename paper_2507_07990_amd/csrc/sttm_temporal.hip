@@ -75,10 +75,10 @@ constexpr int kFastRows = 16;
 constexpr int kBigNodes = 24;  // nodes at levels >= 3 of a 32x32 grid: 16 + 4 + 1
 constexpr int kTItemWords = 24, kTItemE = 6;  // 16-bit words of an item; the first of the e[]
 // Workgroups of the feature pass at most: what the chip holds at three wavefronts per SIMD, so that all start at once
-// and share the list evenly. (Two per SIMD, 1024 workgroups: 67 us for 512 frames of 13x13 at D = 3584, half the tokens
-// kept, 159 us for 1024 frames of 27x27 at D = 1152; three, 768: 55 and 130 us, 1536: 57 and 144; four per SIMD spill: 80
-// and 151. Three hold 168 registers, which the 16-bit instances use to the last one; none of them spills. With a fixed
-// share of the workgroups per queue, and the item read only when its turn came, 70 and 219.)
+// and share the list evenly. (The statistics call -- the planner, this pass and k_temporal_resolve -- with 512, 768 and 1536
+// workgroups, us: 512 frames of 13x13 at D = 3584, half the tokens kept, 29.8, 27.7, 29.9, a third kept 38.0, 36.8, 36.4;
+// 1024 frames of 27x27 at D = 1152 82.4, 72.6, 72.1. Three wavefronts per SIMD hold 168 registers, which the 16-bit instances
+// use to the last one; none of them spills, at four per SIMD they do.)
 constexpr int kTBlocks = 768;
 
 __host__ __device__ inline int temporal_queue_items(const Geo& g) {
