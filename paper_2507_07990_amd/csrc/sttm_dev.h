@@ -398,6 +398,46 @@ __device__ inline int lane_value(int v, int src) {
 #endif
 }
 
+// Running sum over the lanes of each row of sixteen, and over the wavefront; the largest value.
+#ifndef STTM_HOST_EMULATION
+__device__ inline unsigned row16_inclusive(unsigned v, int) {
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);  // row_shr:1 (zero from beyond the row)
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+  return v;
+}
+__device__ inline unsigned wave_inclusive(unsigned v, int lane) {
+  v = row16_inclusive(v, lane);
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15, to the second and fourth row
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31, to the third and fourth
+  return v;
+}
+__device__ inline unsigned wave_max(unsigned v) {
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false));
+  return (unsigned)lane_value((int)v, 63);
+}
+#else
+inline unsigned wave_max(unsigned v) {
+  for (int o = 32; o > 0; o >>= 1) v = max(v, (unsigned)__shfl_xor((int)v, o, 64));
+  return v;
+}
+inline unsigned lanes_inclusive(unsigned v, int lane, int width) {
+  for (int o = 1; o < width; o <<= 1) {
+    const unsigned t = __shfl_up(v, o, 64);
+    if ((lane & (width - 1)) >= o) v += t;
+  }
+  return v;
+}
+inline unsigned row16_inclusive(unsigned v, int lane) { return lanes_inclusive(v, lane, 16); }
+inline unsigned wave_inclusive(unsigned v, int lane) { return lanes_inclusive(v, lane, 64); }
+#endif
+
 // Orders LDS traffic between the lanes of one wavefront (no cross-wave synchronisation).
 __device__ inline void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -495,111 +535,102 @@ __device__ inline void sel_flush_bins(SelState* st, const unsigned* lds_hist) {
 
 constexpr int kSelThreads = 256;
 
-// Workgroup-wide (THREADS threads): the first bin of `hist` at which acc + running weight exceeds `budget`, the weight
-// before it and (if asked for) its own. Returns false when the whole histogram fits. All threads get the same answer.
-// The histogram is the sum of COPIES arrays of kSelBins counters.
+// Workgroup-wide (THREADS threads): the first bin of `hist` at which fd.acc + running weight exceeds the budget; fd.bin and
+// fd.acc become that bin and the weight before it, `weight` its own, fd.rc 1 where the whole histogram fits. All threads get
+// the same answer. The histogram is the sum of COPIES arrays of kSelBins counters. With `target` the budget is worked out
+// here as well: the target less the base, which is base_const or, with a node map, the kept nodes of the video's first frame
+// (fd.rc 2 where the base alone exceeds the target). Everything is requested at once: one trip to memory.
 template <int COPIES, int THREADS>
-__device__ inline bool sel_pick(const unsigned* __restrict__ hist, unsigned long long acc,
-                                unsigned long long budget, unsigned* digit, unsigned long long* acc_out,
-                                unsigned* weight = nullptr) {
-  __shared__ unsigned long long wsum[THREADS / 64];
-  __shared__ unsigned s_digit, s_weight;
-  __shared__ unsigned long long s_acc;
+__device__ inline void sel_pick(const Geo& g, int b, const unsigned* __restrict__ hist, const int* __restrict__ target,
+                                int base_const, const int32_t* __restrict__ node_map, SelFound& fd, unsigned& weight) {
+  constexpr int WAVES = THREADS / kWave;
+  static_assert(WAVES <= 16, "a row of lanes");
+  __shared__ unsigned wsum[WAVES], wbase[WAVES];
+  __shared__ unsigned s_digit, s_weight, s_acc;
   __shared__ int s_found;
-  constexpr int PER = kSelBins / THREADS;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int PER = kSelBins / THREADS < 4 ? 4 : kSelBins / THREADS;  // (of more threads than pieces some have none)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   static_assert(PER % 4 == 0, "whole 16-byte pieces");
-  unsigned h[PER];
-  unsigned long long tot = 0;
+  unsigned h[PER], base = 0, tot = 0;
 #pragma unroll
   for (int j = 0; j < PER; ++j) h[j] = 0;
+  if (tid * PER < kSelBins) {
 #pragma unroll
-  for (int c = 0; c < COPIES; ++c)  // all loads at once
+    for (int c = 0; c < COPIES; ++c)  // all loads at once
 #pragma unroll
-    for (int j = 0; j < PER; j += 4) {
-      const uint4 v = *reinterpret_cast<const uint4*>(hist + c * kSelBins + tid * PER + j);
-      h[j] += v.x; h[j + 1] += v.y; h[j + 2] += v.z; h[j + 3] += v.w;
+      for (int j = 0; j < PER; j += 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(hist + c * kSelBins + tid * PER + j);
+        h[j] += v.x; h[j + 1] += v.y; h[j + 2] += v.z; h[j + 3] += v.w;
+      }
+  }
+  if (node_map) {
+    for (int j = tid; j < g.HW; j += THREADS) {
+      const int i = b * g.T * g.HW + j;
+      base += (node_map[i] == i);
     }
+  }
+  const int want = target ? target[b] : 0;
 #pragma unroll
   for (int j = 0; j < PER; ++j) tot += h[j];
-  unsigned long long inc = tot;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const unsigned long long t = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += t;
-  }
+  const unsigned inc = wave_inclusive(tot, lane);
+  if (node_map) base = wave_inclusive(base, lane);
   if (tid == 0) s_found = 0;
-  if (lane == 63) wsum[wave] = inc;
+  if (lane == 63) {
+    wsum[wave] = inc;
+    wbase[wave] = base;
+  }
   __syncthreads();
-  unsigned long long ex = acc + inc - tot;
-  for (int w = 0; w < wave; ++w) ex += wsum[w];
+  const int sums = (int)row16_inclusive(lane < WAVES ? wsum[lane] : 0u, lane);
+  if (target) {
+    const int bases = (int)row16_inclusive(lane < WAVES ? wbase[lane] : 0u, lane);
+    const long long budget = (long long)want - (node_map ? lane_value(bases, WAVES - 1) : base_const);
+    fd.budget = budget < 0 ? 0ull : (unsigned long long)budget;
+    fd.rc = budget < 0 ? 2 : 0;
+  }
+  if (fd.rc) return;  // uniform over the workgroup
+  unsigned long long ex = fd.acc + (inc - tot) + (unsigned)(wave ? lane_value(sums, wave - 1) : 0);
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
-    if (ex <= budget && ex + h[j] > budget) {
+    if (ex <= fd.budget && ex + h[j] > fd.budget) {
       s_found = 1;
       s_digit = (unsigned)(tid * PER + j);
       s_weight = h[j];
-      s_acc = ex;
+      s_acc = (unsigned)ex;
     }
     ex += h[j];
   }
   __syncthreads();
-  const bool found = s_found != 0;
-  *digit = s_digit;
-  *acc_out = s_acc;
-  if (weight) *weight = s_weight;
-  __syncthreads();
-  return found;
+  fd.rc = s_found ? 0 : 1;
+  fd.bin = s_digit;
+  fd.acc = s_acc;
+  weight = s_weight;
 }
 
+// What the bins are made from: the bits of a positive float that falls as the value rises.
+__device__ inline unsigned sel_distance(uint32_t key) {
+  return __float_as_uint(1.00006103515625f - key_float(key));  // (at least 2^-14: similarities are at most 1; key 0: a NaN)
+}
 __device__ inline unsigned sel_bin(uint32_t key) {
-  const float t = 1.00006103515625f - key_float(key);  // (at least 2^-14: similarities are at most 1)
-  return 2047u - (unsigned)min(max((int)(__float_as_uint(t) - 0x38800000u) >> 16, 0), 2047);
+  return 2047u - (unsigned)min(max((int)(sel_distance(key) - 0x38800000u) >> 16, 0), 2047);
 }
 __device__ inline unsigned sel_piece(uint32_t key) {
-  const float t = 1.00006103515625f - key_float(key);
-  return 0x3fffffu - (unsigned)min(max((int)(__float_as_uint(t) - 0x38800000u) >> 5, 0), 0x3fffff);
+  return 0x3fffffu - (unsigned)min(max((int)(sel_distance(key) - 0x38800000u) >> 5, 0), 0x3fffff);
 }
+// The distances in a bin: from sel_first up to, not with, sel_past (where the bins before it begin).
+__device__ inline unsigned sel_first(unsigned bin) { return bin == 2047u ? 0u : 0x38800000u + ((2047u - bin) << 16); }
+__device__ inline unsigned sel_past(unsigned bin) { return bin == 0u ? 0x7f800001u : 0x38800000u + ((2048u - bin) << 16); }
 
 // A budget search that the kernel using its threshold carries out.
 struct SelSearch {
   const SelState* states;  // [videos]; NULL: no search is pending
-  const uint32_t* keys;    // [videos][per_video]: all elements' keys (0 = not an element) if `whole`, else those of the
-  const uint8_t* weights;  // picked bin; weights of the elements (NULL = 1 each)
+  const uint32_t* keys;    // [videos][per_video]: those of the picked bin's elements if they have been listed, else all
+  const uint8_t* weights;  // (0 = not an element); weights of the elements (NULL = 1 each)
   int per_video;
-  bool whole;              // a small input: nothing has been picked yet
+  bool listed;             // (a small input is left to the consumer as it is: nothing has been picked yet)
   const int* target;       // [videos]
   int base_const;          // base of the step function: spatial = roots of all frames
   const int32_t* node_map; // temporal: the kept nodes of the video's first frame are counted here
 };
-
-// Kept nodes of a video's first frame, by the whole workgroup.
-__device__ inline int sel_base(const Geo& g, int b, int base_const, const int32_t* node_map) {
-  if (!node_map) return base_const;
-  __shared__ int s_base;
-  if (threadIdx.x == 0) s_base = 0;
-  __syncthreads();
-  int c = 0;
-  for (int j = threadIdx.x; j < g.HW; j += blockDim.x) {
-    const int i = b * g.T * g.HW + j;
-    c += (node_map[i] == i);
-  }
-  if (c) atomicAdd(&s_base, c);
-  __syncthreads();
-  const int r = s_base;
-  __syncthreads();
-  return r;
-}
-__device__ inline SelFound sel_begin(const Geo& g, int b, const int* target, int base_const, const int32_t* node_map) {
-  const long long budget = (long long)target[b] - sel_base(g, b, base_const, node_map);
-  SelFound fd;
-  fd.budget = budget < 0 ? 0ull : (unsigned long long)budget;
-  fd.acc = 0;
-  fd.rc = budget < 0 ? 2 : 0;
-  fd.list = fd.crowded = 0;
-  fd.bin = 0;
-  return fd;
-}
 
 // Elements a search keeps in LDS; of more it reads the keys again in every round.
 #ifndef STTM_SEL_LIST
@@ -608,132 +639,231 @@ __device__ inline SelFound sel_begin(const Geo& g, int b, const int* target, int
 constexpr int kSelList = STTM_SEL_LIST;
 
 // tau of video b, by a workgroup of THREADS threads (256 or more): midpoint between the searched key and the largest key below it.
-// All threads get the value. The range of keys is cut into 256 pieces, of which one is picked, until it is one key: two
-// rounds for the elements of a bin, however many of them are equal.
+// All threads get the value. Of a small input the right bin is picked here and its elements are taken from among all keys; of
+// a large one they have been listed. Up to kSelFew of them are searched by one wavefront, each with each or bit by bit; else
+// the range of keys is cut into 256 pieces, of which one is picked, until it is one key (two rounds for the elements of a bin,
+// however many of them are equal).
+// What bounds it: one trip to memory (histogram, keys and base are requested together), then instructions that are fetched for
+// the first time, by time stamps of 64 frames of 13x13 in cycles: 1500 until the requests are out, 3000 until they are
+// answered, 2500 for the bin, 3000 for a look at 8192 keys, 600 to 5000 for the elements. So what is executed is kept short,
+// and what the caller reads for its own work is requested before.
+constexpr int kSelFew = kSelList < 256 ? kSelList : 256;
 template <int THREADS>
 __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
-  __shared__ uint32_t s_key[kSelList];
-  __shared__ uint8_t s_w[kSelList];
-  constexpr int kPieces = 256;
+  __shared__ uint32_t s_key[kSelList + kWave];  // (the last ones: where what is not in the bin goes)
+  __shared__ uint8_t s_w[kSelList + kWave];
+  constexpr int kPieces = 256, kBatch = 8;
   __shared__ unsigned hist[kPieces];
   __shared__ unsigned wsum[kPieces / 64];
-  __shared__ unsigned s_lo, s_not_min, s_max, s_total, s_piece, s_acc;  // (s_not_min: the complement of the smallest key)
-  const uint32_t* keys = q.keys + (size_t)b * q.per_video;
-  const uint8_t* weights = q.weights ? q.weights + (size_t)b * q.per_video : nullptr;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  SelFound fd;
-  int count = q.per_video;
-  if (tid == 0) s_lo = s_not_min = s_max = s_total = 0;
-  if (q.whole) {
-    fd = sel_begin(g, b, q.target, q.base_const, q.node_map);
-  } else {
-    fd = q.states[b].found[0];
-    const unsigned long long acc = q.states[b].found[1].acc;  // (all loads at once)
-    if (fd.crowded) fd.acc = acc;
-    const SelList first = q.states[b].list[0], second = q.states[b].list[1];
-    count = min((int)(fd.list ? second.count : first.count), q.per_video);
-    if (tid == 0) s_lo = fd.list ? second.lo : first.lo;
+  __shared__ unsigned s_lo, s_not_min, s_max, s_piece, s_acc;  // (s_not_min: the complement of the smallest key)
+  __shared__ int s_count;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const Window keys = make_window(q.keys + (size_t)b * q.per_video, (unsigned)q.per_video * 4u);
+  const Window weights = make_window(q.weights + (size_t)b * q.per_video, q.weights ? (unsigned)q.per_video : 0u);
+  const unsigned plain = q.weights ? 0u : 1u;
+  // keys j0 + tid, j0 + tid + THREADS, ... (0 behind the last one) with their weights
+  auto load = [&](uint32_t (&k)[kBatch], unsigned (&w)[kBatch], int j0) {
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      k[u] = (uint32_t)window_load_i32(keys, (unsigned)tid * 4u, (unsigned)(j0 + u * THREADS) * 4u);
+      w[u] = (unsigned)window_load_u8(weights, (unsigned)tid, (unsigned)(j0 + u * THREADS)) + plain;
+    }
+  };
+  if (tid == 0) {
+    s_lo = s_not_min = s_max = 0;
+    s_count = 0;
   }
-  if (fd.rc) return fd.rc == 1 ? 1.f : -2.f;  // uniform over the workgroup
-  __syncthreads();
-  unsigned kmin = 0xffffffffu, kmax = 0, total = 0;
-  // every key with its weight from memory, eight loads of either in flight
-  auto read = [&](auto use) {
-    constexpr int kBatch = 8;
+  SelFound fd;
+  int n = q.per_video;
+  unsigned first = 0, past = 0xffffffffu;  // the bin: what it makes of the values in it (see sel_first); of a list, all
+  if (q.listed) {
+    // (a list is short as a rule: the first keys are requested with its length)
+    uint32_t key = (uint32_t)window_load_i32(keys, (unsigned)tid * 4u, 0u);
+    unsigned weight = (unsigned)window_load_u8(weights, (unsigned)tid, 0u);
+    fd = q.states[b].found[0];
+    const unsigned long long acc = q.states[b].found[1].acc;
+    if (fd.crowded) fd.acc = acc;
+    const SelList l0 = q.states[b].list[0], l1 = q.states[b].list[1];
+    n = min((int)(fd.list ? l1.count : l0.count), q.per_video);
+    if (fd.rc) return fd.rc == 1 ? 1.f : -2.f;  // uniform over the workgroup
+    __syncthreads();
+    if (tid == 0) {
+      s_lo = fd.list ? l1.lo : l0.lo;
+      s_count = n;
+    }
 #pragma unroll 1
-    for (int j0 = tid; j0 < count; j0 += kBatch * THREADS) {
-      uint32_t k[kBatch];
-      unsigned w[kBatch];
+    for (int j = tid; j < min(n, kSelList); j += THREADS) {
+      if (j != tid) {
+        key = (uint32_t)window_load_i32(keys, (unsigned)j * 4u, 0u);
+        weight = (unsigned)window_load_u8(weights, (unsigned)j, 0u);
+      }
+      s_key[j] = key;
+      s_w[j] = (uint8_t)weight;
+    }
+  } else {
+    // the first keys do not depend on the search: they are on their way while the bin is being found
+    uint32_t k[kBatch];
+    unsigned w[kBatch];
+    load(k, w, 0);
+    unsigned weight;
+    fd.acc = 0;
+    sel_pick<kSelCopies, THREADS>(g, b, q.states[b].hist0[0], q.target, q.base_const, q.node_map, fd, weight);
+    if (fd.rc) return fd.rc == 1 ? 1.f : -2.f;
+    first = sel_first(fd.bin);
+    past = sel_past(fd.bin);
+    // the picked bin's elements into LDS (no branches: they cost more than what they save); the largest key below the bin
+    unsigned under = 0;
+#pragma unroll 1
+    for (int j0 = 0;;) {
+      bool in[kBatch];
+      int mine = 0;
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
-        const int j = min(j0 + u * THREADS, count - 1);
-        k[u] = keys[j];
-        w[u] = weights ? (unsigned)weights[j] : 1u;
+        const unsigned t = sel_distance(k[u]);
+        in[u] = (t - first < past - first) & (k[u] != 0);
+        mine += in[u];
+        under = max(under, t >= past ? k[u] : 0u);
       }
+      const int upto = (int)wave_inclusive((unsigned)mine, lane), all = lane_value(upto, 63);
+      int at = 0;
+      if (lane == 0 && all) at = atomicAdd(&s_count, all);
+      at = lane_value(at, 0) + upto - mine;
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u)
-        if (j0 + u * THREADS < count) use(j0 + u * THREADS, k[u], w[u]);
+      for (int u = 0; u < kBatch; ++u) {
+        const int to = (in[u] & (at < kSelList)) ? at : kSelList + lane;
+        s_key[to] = k[u];
+        s_w[to] = (uint8_t)w[u];
+        at += in[u];
+      }
+      j0 += kBatch * THREADS;
+      if (j0 >= n) break;
+      load(k, w, j0);
     }
-  };
-  read([&](int j, uint32_t k, unsigned w) {
-    if (j < kSelList) {
-      s_key[j] = k;
-      s_w[j] = (uint8_t)w;
-    }
-    if (k) {
-      kmin = min(kmin, k);
-      total += w;
-    }
-    kmax = max(kmax, k);
-  });
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    kmin = min(kmin, (unsigned)__shfl_xor((int)kmin, o, 64));
-    kmax = max(kmax, (unsigned)__shfl_xor((int)kmax, o, 64));
-    total += (unsigned)__shfl_xor((int)total, o, 64);
-  }
-  if (lane == 0) {
-    atomicMax(&s_not_min, ~kmin);
-    atomicMax(&s_max, kmax);
-    atomicAdd(&s_total, total);
+    under = wave_max(under);
+    if (lane == 0 && under) atomicMax(&s_lo, under);
   }
   __syncthreads();
-  if (fd.acc + s_total <= fd.budget) return 1.f;  // (a small input all of which fits)
-  const bool kept = count <= kSelList;
-  unsigned a = ~s_not_min, z = s_max, room = (unsigned)(fd.budget - fd.acc);  // weight that still fits before key a
+  const int count = s_count;
+  unsigned room = (unsigned)(fd.budget - fd.acc);  // weight that still fits before the searched key
+  unsigned a, under;                               // that key: the largest one with no more than that before it; the one below
+  if (count <= kSelFew) {
+    if (wave == 0) {
+      if (count <= kWave) {  // each with each
+        const unsigned own = lane < count ? s_key[lane] : 0u, weight = lane < count ? s_w[lane] : 0u;
+        unsigned before = 0, equal = 0, below = 0;
 #pragma unroll 1
-  while (a != z) {
-    const int shift = max(0, 24 - __builtin_clz(z - a));
-    if (tid < kPieces) hist[tid] = 0;
-    __syncthreads();
-    auto count_in = [&](int, uint32_t k, unsigned w) {
-      if (k >= a && k <= z) atomicAdd(&hist[(k - a) >> shift], w);
-    };
-    if (kept) {
-#pragma unroll 2
-      for (int j = tid; j < count; j += THREADS) count_in(j, s_key[j], s_w[j]);
-    } else {
-      read(count_in);
-    }
-    __syncthreads();
-    const unsigned h = tid < kPieces ? hist[tid] : 0u;
-    unsigned inc = h;
+        for (int j = 0; j < count; ++j) {
+          const unsigned kj = (unsigned)lane_value((int)own, j), wj = (unsigned)lane_value((int)weight, j);
+          before += kj < own ? wj : 0u;
+          equal += kj == own ? wj : 0u;
+          below = max(below, kj < own ? kj : 0u);
+        }
+        if (before <= room && before + equal > room) {  // (whoever holds this key has found the same)
+          s_piece = own;
+          s_max = below;
+        }
+      } else {  // the searched key's distance from the smallest one, bit by bit
+        constexpr int kPer = (kSelFew + kWave - 1) / kWave;
+        uint32_t k[kPer];
+        unsigned w[kPer], kmin = 0xffffffffu, kmax = 0, below = 0, d = 0;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned t = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += t;
+        for (int u = 0; u < kPer; ++u) {
+          const int j = u * kWave + lane;
+          k[u] = j < count ? s_key[j] : 0xffffffffu;
+          w[u] = j < count ? s_w[j] : 0u;
+          kmin = min(kmin, k[u]);
+          kmax = max(kmax, j < count ? k[u] : 0u);
+        }
+        kmin = ~wave_max(~kmin);
+        kmax = wave_max(kmax);
+#pragma unroll 1
+        for (int bit = kmax == kmin ? -1 : 31 - __builtin_clz(kmax - kmin); bit >= 0; --bit) {
+          const unsigned at = kmin + (d | 1u << bit);
+          unsigned before = 0;
+#pragma unroll
+          for (int u = 0; u < kPer; ++u) before += k[u] < at ? w[u] : 0u;
+          if ((unsigned)lane_value((int)wave_inclusive(before, lane), 63) <= room) d |= 1u << bit;
+        }
+        a = kmin + d;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) below = max(below, k[u] < a ? k[u] : 0u);
+        below = wave_max(below);
+        if (lane == 0) {
+          s_piece = a;
+          s_max = below;
+        }
+      }
     }
-    if (lane == 63 && tid < kPieces) wsum[wave] = inc;
     __syncthreads();
-    unsigned ex = inc - h;
-    for (int w = 0; w < min(wave, kPieces / 64); ++w) ex += wsum[w];
-    if (ex <= room && ex + h > room) {
-      s_piece = (unsigned)tid;
-      s_acc = ex;
-    }
-    __syncthreads();
-    a += s_piece << shift;
-    z = min(z, a + ((1u << shift) - 1u));
-    room -= s_acc;
-  }
-  // (an element may still lie below the searched key in its bin)
-  unsigned under = 0;
-  auto below = [&](int, uint32_t k, unsigned) {
-    if (k < a) under = max(under, k);
-  };
-  if (kept) {
-#pragma unroll 2
-    for (int j = tid; j < count; j += THREADS) below(j, s_key[j], 0u);
+    a = s_piece;
+    under = max(s_max, s_lo);
   } else {
-    read(below);
-  }
+    const bool kept = count <= kSelList;
+    auto read = [&](auto use) {  // (of all keys those of the bin)
+      if (kept) {
+#pragma unroll 1
+        for (int j = tid; j < count; j += THREADS) use(s_key[j], (unsigned)s_w[j]);
+      } else {
+#pragma unroll 1
+        for (int j0 = 0; j0 < n; j0 += kBatch * THREADS) {
+          uint32_t k[kBatch];
+          unsigned w[kBatch];
+          load(k, w, j0);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) under = max(under, (unsigned)__shfl_xor((int)under, o, 64));
-  if (lane == 0 && under) atomicMax(&s_lo, under);
-  __syncthreads();
-  const unsigned lo_key = s_lo;
+          for (int u = 0; u < kBatch; ++u)
+            if (j0 + u * THREADS + tid < n && k[u] && sel_distance(k[u]) - first < past - first) use(k[u], w[u]);
+        }
+      }
+    };
+    unsigned not_min = 0, kmax = 0;
+    read([&](uint32_t key, unsigned) {
+      not_min = max(not_min, ~key);
+      kmax = max(kmax, key);
+    });
+    not_min = wave_max(not_min);
+    kmax = wave_max(kmax);
+    if (lane == 0) {
+      atomicMax(&s_not_min, not_min);
+      atomicMax(&s_max, kmax);
+    }
+    __syncthreads();
+    a = ~s_not_min;
+    unsigned z = s_max;
+#pragma unroll 1
+    while (a != z) {
+      const int shift = max(0, 24 - __builtin_clz(z - a));
+      if (tid < kPieces) hist[tid] = 0;
+      __syncthreads();
+      read([&](uint32_t key, unsigned weight) {
+        if (key >= a && key <= z) atomicAdd(&hist[(key - a) >> shift], weight);
+      });
+      __syncthreads();
+      const unsigned h = tid < kPieces ? hist[tid] : 0u, inc = wave_inclusive(h, lane);
+      if (lane == 63 && tid < kPieces) wsum[wave] = inc;
+      __syncthreads();
+      unsigned ex = inc - h;
+      for (int v = 0; v < min(wave, kPieces / 64); ++v) ex += wsum[v];
+      if (ex <= room && ex + h > room) {
+        s_piece = (unsigned)tid;
+        s_acc = ex;
+      }
+      __syncthreads();
+      a += s_piece << shift;
+      z = min(z, a + ((1u << shift) - 1u));
+      room -= s_acc;
+    }
+    // (an element may still lie below the searched key in its bin)
+    under = 0;
+    read([&](uint32_t key, unsigned) {
+      if (key < a) under = max(under, key);
+    });
+    under = wave_max(under);
+    if (lane == 0 && under) atomicMax(&s_lo, under);
+    __syncthreads();
+    under = s_lo;
+  }
   const float hi = key_float(a);
-  const float lof = lo_key ? key_float(lo_key) : -2.f;
+  const float lof = under ? key_float(under) : -2.f;
   float t = 0.5f * (lof + hi);
   if (!(t < hi)) t = lof;
   return t;

@@ -479,33 +479,6 @@ inline int lane_before(int v) { const int r = __shfl_up(v, 1, 64); return (threa
 inline bool from_mask(unsigned long long m, int lane) { return (m >> lane) & 1ull; }
 #endif
 
-// Running sum over the lanes of each row of sixteen, and over the wavefront.
-#ifndef STTM_HOST_EMULATION
-__device__ inline unsigned row16_inclusive(unsigned v, int) {
-  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);  // row_shr:1 (zero from beyond the row)
-  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
-  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
-  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
-  return v;
-}
-__device__ inline unsigned wave_inclusive(unsigned v, int lane) {
-  v = row16_inclusive(v, lane);
-  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15, to the second and fourth row
-  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31, to the third and fourth
-  return v;
-}
-#else
-inline unsigned lanes_inclusive(unsigned v, int lane, int width) {
-  for (int o = 1; o < width; o <<= 1) {
-    const unsigned t = __shfl_up(v, o, 64);
-    if ((lane & (width - 1)) >= o) v += t;
-  }
-  return v;
-}
-inline unsigned row16_inclusive(unsigned v, int lane) { return lanes_inclusive(v, lane, 16); }
-inline unsigned wave_inclusive(unsigned v, int lane) { return lanes_inclusive(v, lane, 64); }
-#endif
-
 // ------------------------------------------------------------------------------------------------
 // k_list_small: all of the integer plumbing of a small input in one launch. A workgroup puts kListSlice consecutive cells
 // into the list. The place of an element is the number of elements with a smaller id plus that of earlier ones with the

@@ -974,10 +974,13 @@ void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float
 // ------------------------------------------------------------------------------------------------
 // k_spatial_decide: coarse-to-fine search (Sec. 3.2). Grid (cells of a video / threads, videos); one thread per cell
 // walks down from its root: the first node on the path whose smallest child similarity exceeds tau_S is kept.
-// Large videos take fewer and larger workgroups, since each carries the search out (512 frames of 13x13 random vectors 19.8 ->
-// 16.3 us, moving scenes of that size 10.9 and 11.1, of 46 frames of 27x27 9.9 and 10.4; 1024 threads 16.8, 12.3, 11.8).
+// Large videos, and searches through many keys, take fewer and larger workgroups, since each carries the search out (512 frames
+// of 13x13 random vectors 19.8 -> 16.3 us, moving scenes of that size 10.9 and 11.1, of 46 frames of 27x27 9.9 and 10.4; 1024
+// threads 16.8, 12.3, 11.8).
 // ------------------------------------------------------------------------------------------------
 constexpr int kDecideWide = 65536, kDecideThreads = 512;
+// A search that looks through more keys than this has larger workgroups as well.
+constexpr int kSelFewKeys = 2048;
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_spatial_decide(Geo g, const float* __restrict__ m,
                                                                 float* __restrict__ tau, TauArgs given,
@@ -985,6 +988,15 @@ __global__ __launch_bounds__(THREADS) void k_spatial_decide(Geo g, const float* 
                                                                 int32_t* __restrict__ node_map,
                                                                 uint8_t* __restrict__ node_level) {
   const int b = blockIdx.y, per_video = g.T * g.HW;
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  const int i = b * per_video + min(j, per_video - 1);
+  const int f = i / g.HW, c = i - f * g.HW;
+  const int y = c / g.W, x = c - y * g.W;
+  // the path's nodes do not depend on the threshold: they are on their way while it is being found
+  float path[kMaxLevels];
+#pragma unroll
+  for (int l = 1; l < kMaxLevels; ++l)  // (no branches: of a level above the roots the roots are read again)
+    path[l] = m[(size_t)f * g.NN + node_index(g, min(l, g.L), y >> min(l, g.L), x >> min(l, g.L))];
   float t;
   if (pending.states || given.n) {  // the budget search was left to this kernel, or the caller named the threshold
     t = given.n ? given.v[b] : sel_threshold<THREADS>(g, pending, b);
@@ -992,15 +1004,11 @@ __global__ __launch_bounds__(THREADS) void k_spatial_decide(Geo g, const float* 
   } else {
     t = tau[b];
   }
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= per_video) return;
-  const int i = b * per_video + j;
-  const int f = i / g.HW, c = i - f * g.HW;
-  const int y = c / g.W, x = c - y * g.W;
-  const float* mf = m + (size_t)f * g.NN;
-  int lvl = g.L;
-  for (; lvl >= 1; --lvl)
-    if (mf[node_index(g, lvl, y >> lvl, x >> lvl)] > t) break;
+  int lvl = 0;
+#pragma unroll
+  for (int l = 1; l < kMaxLevels; ++l)
+    if (l <= g.L && path[l] > t) lvl = l;  // (the last one that passes is the coarsest)
   const int y0 = (y >> lvl) << lvl, x0 = (x >> lvl) << lvl;
   node_map[i] = f * g.HW + y0 * g.W + x0;
   if (node_level) node_level[i] = (uint8_t)lvl;
@@ -1013,7 +1021,8 @@ void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauAr
     hipLaunchKernelGGL(kernel, dim3((per_video + threads - 1) / threads, g.B), dim3(threads), 0, s, g, m, tau, given, pending,
                        node_map, node_level);
   };
-  if (per_video > kDecideWide) launch(k_spatial_decide<kDecideThreads>, kDecideThreads);
+  const bool look = pending.states && !pending.listed && pending.per_video > kSelFewKeys;  // through all keys
+  if (per_video > kDecideWide || look) launch(k_spatial_decide<kDecideThreads>, kDecideThreads);
   else launch(k_spatial_decide<kSelThreads>, kSelThreads);
 }
 
@@ -1048,8 +1057,10 @@ void launch_node_levels(const Geo& g, const int32_t* node_map, uint8_t* node_lev
 // ------------------------------------------------------------------------------------------------
 // Budget-driven thresholds (see SelState). The statistics pass of the stage has filled the histogram of bins;
 // k_select_list, grid (slices, videos), picks the bin and lists its elements, and every workgroup of the kernel that uses
-// the threshold finds the value among those (sel_threshold). Where a video has no more elements than such a workgroup
-// keeps in LDS anyway, it is given all of them and no launch is made for the search.
+// the threshold finds the value among those (sel_threshold). Of a video of up to kSelWhole elements such a workgroup picks the
+// bin and looks through all keys by itself, and no launch is made for the search: passes of 64 frames of 13x13 (5440 and 10,816
+// elements) 116.8 us with the list and 112.6 without, of 16x16 (16,384) 105.7 and 101.4; 180 of 14x14 (14,400 and 35,280)
+// 227.4 with the list for both, 223.4 without the smaller one's, 225.4 without both; 512 of 13x13 (43,520) 402 and 409.
 // Input: keys[video][per_video] (0 = not an element), weights (NULL = 1 for every element).
 // What it costs is launches and dependent loads. Against a radix search of 11 + 11 + 10 bits, two launches and the last
 // digit in the kernel that uses the threshold (the first bits of a float tell similarities apart badly: four bins from a
@@ -1059,9 +1070,10 @@ void launch_node_levels(const Geo& g, const int32_t* node_map, uint8_t* node_lev
 // ------------------------------------------------------------------------------------------------
 // (The host-thread build of the tests that takes the large inputs' kernels lists the elements of every search.)
 #ifndef STTM_SEL_WHOLE
-#define STTM_SEL_WHOLE 2048
+#define STTM_SEL_WHOLE 20480
 #endif
 constexpr int kSelWhole = STTM_SEL_WHOLE;
+constexpr int kSelThreadsWhole = 1024;
 // Threads of the listing pass, and elements per thread. (Fewer in the host-thread build: a small input has several workgroups.)
 #ifndef STTM_SEL_THREADS
 #define STTM_SEL_THREADS 512
@@ -1157,8 +1169,8 @@ __global__ __launch_bounds__(kPassThreads) void k_select_list(Geo g, const uint3
   SelSlice q = sel_load(keys, weights, per_video, b);
   unsigned turn = 0, weight = 0;
   if (tid == 0) turn = atomicAdd(&st->begun, 1u);
-  SelFound fd = sel_begin(g, b, target, base_const, node_map);
-  if (fd.rc == 0 && !sel_pick<kSelCopies, kPassThreads>(st->hist0[0], 0ull, fd.budget, &fd.bin, &fd.acc, &weight)) fd.rc = 1;
+  SelFound fd = {};
+  sel_pick<kSelCopies, kPassThreads>(g, b, st->hist0[0], target, base_const, node_map, fd, weight);
   fd.crowded = REFINE && fd.rc == 0 && weight > kSelCrowd;
   if (tid == 0) {
     fd.list = turn >= gridDim.x;
@@ -1203,17 +1215,20 @@ __global__ __launch_bounds__(kPassThreads) void k_select_piece(Geo g, const uint
   SelFound fd = st->found[0];
   if (!fd.crowded) return;  // uniform over the workgroup, as everywhere
   SelSlice q = sel_load(keys, weights, per_video, b);
-  unsigned piece = 0;
-  if (!sel_pick<1, kPassThreads>(st->pieces[fd.list], fd.acc, fd.budget, &piece, &fd.acc)) return;
+  const unsigned bin = fd.bin;
+  unsigned weight;
+  sel_pick<1, kPassThreads>(g, b, st->pieces[fd.list], nullptr, 0, nullptr, fd, weight);
+  if (fd.rc) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) st->found[1] = fd;
-  sel_append(q, [](uint32_t key) { return sel_piece(key); }, fd.bin * kSelBins + piece, &st->list[fd.list], per_video, b,
+  sel_append(q, [](uint32_t key) { return sel_piece(key); }, bin * kSelBins + fd.bin, &st->list[fd.list], per_video, b,
              list_key, list_w);
 }
 
 // The whole search as a launch of its own (when the caller wants the threshold back).
-__global__ __launch_bounds__(kSelThreads) void k_select_tau(Geo g, SelSearch search, float* __restrict__ tau,
-                                                            float* __restrict__ host_tau) {
-  const float t = sel_threshold<kSelThreads>(g, search, blockIdx.x);
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_select_tau(Geo g, SelSearch search, float* __restrict__ tau,
+                                                        float* __restrict__ host_tau) {
+  const float t = sel_threshold<THREADS>(g, search, blockIdx.x);
   if (threadIdx.x == 0) {
     tau[blockIdx.x] = t;
     if (host_tau) host_tau[blockIdx.x] = t;
@@ -1223,7 +1238,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_tau(Geo g, SelSearch sea
 static SelSearch launch_select(const Geo& g, const uint32_t* keys, const uint8_t* weights, int per_video,
                                const int* target, int base_const, const int32_t* node_map, SelState* st,
                                uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
-  SelSearch q = {st, keys, weights, per_video, true, target, base_const, node_map};
+  SelSearch q = {st, keys, weights, per_video, false, target, base_const, node_map};
   if (per_video <= kSelWhole) return q;
   const dim3 grid((per_video + kPassThreads * kSelPer - 1) / (kPassThreads * kSelPer), g.B), block(kPassThreads);
   if (per_video > kSelRefine) {
@@ -1236,7 +1251,7 @@ static SelSearch launch_select(const Geo& g, const uint32_t* keys, const uint8_t
   }
   q.keys = list_key;
   q.weights = list_w;
-  q.whole = false;
+  q.listed = true;
   return q;
 }
 
@@ -1257,7 +1272,10 @@ SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const ui
 }
 
 void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s) {
-  hipLaunchKernelGGL(k_select_tau, dim3(g.B), dim3(kSelThreads), 0, s, g, search, tau, host_tau);
+  if (search.listed || search.per_video <= kSelFewKeys)
+    hipLaunchKernelGGL(k_select_tau<kSelThreads>, dim3(g.B), dim3(kSelThreads), 0, s, g, search, tau, host_tau);
+  else
+    hipLaunchKernelGGL(k_select_tau<kSelThreadsWhole>, dim3(g.B), dim3(kSelThreadsWhole), 0, s, g, search, tau, host_tau);
 }
 
 }  // namespace sttm

@@ -665,6 +665,17 @@ __global__ __launch_bounds__(THREADS) void k_temporal_parent(Geo g, int match, i
   unsigned long long* best = sm;
   int16_t* rep = reinterpret_cast<int16_t*>(reinterpret_cast<char*>(sm) + (size_t)run * HW * (match == 2 ? 8 : 4));
   uint8_t* lvl = reinterpret_cast<uint8_t*>(rep + (run + 1) * HW);
+  // What the frames hold does not depend on the threshold: it is on its way while that is being found.
+  constexpr int kPer = THREADS >= kParThreads ? kParCells / THREADS : (THREADS > kSelThreads ? 1024 : kSelThreads) / THREADS;
+  float val[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) val[u] = sig[i0 + min(tid + u * THREADS, cells - 1)];
+  for (int q = tid; q < cells + HW; q += THREADS) {  // (cell q of these tables is cell q - HW of the run)
+    if (t0 == 0 && q < HW) continue;
+    const int i = i0 - HW + q, f = i / HW;
+    rep[q] = (int16_t)(node_map[i] - f * HW);
+    lvl[q] = node_level[i];
+  }
   float th;
   if (pending.states || given.n) {  // the budget search was left to this kernel, or the caller named the threshold
     th = given.n ? given.v[b] : sel_threshold<THREADS>(g, pending, b);
@@ -672,23 +683,18 @@ __global__ __launch_bounds__(THREADS) void k_temporal_parent(Geo g, int match, i
   } else {
     th = tau[b];
   }
-  for (int q = tid; q < cells + HW; q += THREADS) {  // (cell q of these tables is cell q - HW of the run)
-    if (t0 == 0 && q < HW) continue;
-    const int i = i0 - HW + q, f = i / HW;
-    rep[q] = (int16_t)(node_map[i] - f * HW);
-    lvl[q] = node_level[i];
-  }
   for (int q = tid; q < cells; q += THREADS) {
     if (match == 2) best[q] = 0ull;
     else par[q] = 0x7fffffff;
   }
   __syncthreads();
-  for (int q = tid; q < cells; q += THREADS) {
-    const int r = q / HW, c = q - r * HW;
-    if (t0 + r == 0) continue;
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int q = tid + u * THREADS, r = q / HW, c = q - r * HW;
+    if (q >= cells || t0 + r == 0) continue;
     const int a = lvl[q + HW], bb = lvl[q], n = rep[q + HW], d = rep[q];
     if ((a <= bb ? n : d) != c) continue;  // not the top-left cell of the finer node
-    const float v = sig[i0 + q];
+    const float v = val[u];
     if (!(v > th)) continue;
     if (match == 2)
       atomicMax(&best[r * HW + n], ((unsigned long long)float_key(v) << 32) | (unsigned)(0x7fffffff - d));
