@@ -46,7 +46,6 @@ static_assert(kListMax == 0 || (kListRuns <= kListThreads && kListTiny / 128 * 2
 static_assert(kListSlice <= kListThreadsTiny, "a thread per cell");
 constexpr int kItem = 16;  // list positions per gather item
 constexpr int kBig = 64;   // clusters with more list slots than this are summed item by item, then combined
-constexpr int kTail = 8;
 constexpr int kMaxDigits = 1 << kMaxDigitBits;
 // How a scatter workgroup gets its start offsets from hist[tile][digit]: up to kDirectTiles tiles it adds up all
 // rows itself; up to kGroupTiles * kMaxGroups tiles a small kernel first adds the rows in groups of kGroupTiles
@@ -835,9 +834,6 @@ struct GatherArgs {
   const int32_t* zpos;  // output row of every cluster rank when the rows follow the Z-shaped scan, else NULL
 };
 
-// Wavefronts that share an item: one per chunk of the row, at most 16 (beyond that a wavefront takes several chunks).
-__host__ __device__ inline int gather_waves(const Geo& g) { return g.nC < 16 ? g.nC : 16; }
-
 template <int VEC>
 __device__ inline void store_partial(float* o, const float (&acc)[VEC]) {
 #pragma unroll
@@ -855,28 +851,25 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
   typedef typename R::Raw Raw;
   constexpr int VEC = R::VEC;
   // one-wavefront workgroups; consecutive ones take the chunks of one item
-  const int nw = gather_waves(g), wave = blockIdx.x % nw, item = blockIdx.x / nw, lane = threadIdx.x;
-  // Lane j < kItem describes list position p0 + j, the next kTail lanes the positions after the item (the start of
-  // a cluster that runs past it). The list entries are requested together with the list's length: entries at or
-  // beyond the end are stale and are not used.
+  const int chunk = blockIdx.x % g.nC, item = blockIdx.x / g.nC, lane = threadIdx.x;
+  // Lane j describes list position p0 + j: the item's first, those after it only where its last cluster runs past it. The
+  // list entries are requested together with the list's length: entries at or beyond the end are stale and are not used.
   const int p0 = item * kItem, pl = p0 + lane;
   int cell_l = 0, rank_l = 0;
-  if (lane < kItem + kTail && pl < g.N) {
+  if (pl < g.N) {
     cell_l = a.order[pl];
-    rank_l = a.orow[pl];  // clusters are listed in ascending id; the output row may differ
+    if (lane < kItem) rank_l = a.orow[pl];  // clusters are listed in ascending id; the output row may differ
   }
   const int M = a.kdev[1];
   const int p1 = min(p0 + kItem, M);
   if (p0 >= M) return;
   Slot sv = {0, 0, 0};
   int row_v = -1, beg_v = 0, end_v = 0;
-  if (lane < kItem + kTail && pl < M) {
+  if (lane < kItem && pl < M) {
     sv = describe<DT>(g, a.node_map, a.lvl, cell_l);
-    if (lane < kItem) {
-      beg_v = a.seg[rank_l];
-      end_v = a.seg[rank_l + 1];
-      row_v = a.zpos ? a.zpos[rank_l] : rank_l;
-    }
+    beg_v = a.seg[rank_l];
+    end_v = a.seg[rank_l + 1];
+    row_v = a.zpos ? a.zpos[rank_l] : rank_l;
   }
   const bool big = end_v - beg_v > kBig;
   const bool use = pl < p1 && (beg_v >= p0 || big);  // (else the tail of a cluster that an earlier item finishes)
@@ -897,7 +890,7 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
   unsigned add_m = (unsigned)__ballot(use && !one), mean_m = (unsigned)__ballot(closes && fits);
   unsigned share_m = (unsigned)__ballot(share), end_m = share_m | (unsigned)__ballot(closes);
   int inv_v = (int)__float_as_uint(1.f / (float)members);
-  if (wave == 0) {
+  if (chunk == 0) {
     if ((one || closes) && fits && a.counts) a.counts[row_v] = members;
     if (share) {
       const int slot = beg_v < p0 ? 0 : 1;
@@ -905,17 +898,34 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
       if (slot == 1) a.biglist[atomicAdd(a.bigcount, 1)] = make_int4(row_v, beg_v, end_v, 0);
     }
   }
-  // the cluster still open after the item's last position (the item is full then)
+  // The cluster still open after the item's last position (the item is full then) is followed to its end, kItem positions at
+  // a time. All of these are described at once: the lanes after the item's, and the first ones once more for what lies
+  // beyond the last lane.
   const int lastj = p1 - 1 - p0;
   const bool open = (add_m >> lastj & 1u) && !(end_m >> lastj & 1u);
+  static_assert(kBig + kItem <= 2 * kWave, "an open cluster's positions");
+  int open_row = 0, open_end = 0, open_inv = 0;
+  Slot beyond = {0, 0, 0};
+  if (open) {
+    open_row = lane_value(row_v, kItem - 1);
+    open_end = lane_value(end_v, kItem - 1);
+    if (lane >= kItem && pl < open_end) sv = describe<DT>(g, a.node_map, a.lvl, cell_l);
+    if (pl + kWave < open_end) beyond = describe<DT>(g, a.node_map, a.lvl, a.order[pl + kWave]);
+    const unsigned later = wave_inclusive((unsigned)((lane >= kItem ? sv.weight : 0) + beyond.weight), lane);
+    const int total = lane_value(members, kItem - 1) + lane_value((int)later, kWave - 1);
+    open_inv = (int)__float_as_uint(1.f / (float)total);
+    if (chunk == 0 && lane == 0 && open_row < a.capacity && a.counts) a.counts[open_row] = total;
+  }
+  const int ch0 = chunk * g.cch + lane * VEC;
+  const bool act = ch0 < g.D;
+  const int chl = act ? ch0 : 0;  // (a lane beyond the last channel reads the row's first channels and drops them)
+  float acc[VEC];
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
 #pragma unroll 1
-  for (int chunk = wave; chunk < g.nC; chunk += nw) {
-    const int ch0 = chunk * g.cch + lane * VEC;
-    const bool act = ch0 < g.D;
-    const int chl = act ? ch0 : 0;  // (a lane beyond the last channel reads the row's first channels and drops them)
+  for (int base = p0;;) {
     // (The slots' bits and numbers are taken from these registers where they are used: a copy the compiler cannot look
-    // through, or it takes all of them out of the loop -- which has one round unless a row has more than 16 chunks --
-    // and runs out of scalar registers.)
+    // through, or it takes all of them out of the loop and runs out of scalar registers.)
     STTM_OPAQUE_S(use_m); STTM_OPAQUE_S(one_m); STTM_OPAQUE_S(add_m);
     STTM_OPAQUE_S(mean_m); STTM_OPAQUE_S(share_m); STTM_OPAQUE_S(end_m);
     STTM_OPAQUE_V(sv.kind); STTM_OPAQUE_V(sv.idx); STTM_OPAQUE_V(row_v); STTM_OPAQUE_V(inv_v); STTM_OPAQUE_V(beg_v);
@@ -926,9 +936,12 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
       if (use_m >> j & 1u)
         raw[j] = load_slot<DT>(a.feats, a.nsum, g.D, chl, lane_value(sv.kind, j), lane_value(sv.idx, j));
     }
-    float acc[VEC];
+    // (all of them are waited for here: at each slot, behind a branch that may have stored a row, the compiler would wait
+    // for that store as well)
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
+    for (int j = 0; j < kItem; ++j) {
+      STTM_OPAQUE_V(raw[j].x); STTM_OPAQUE_V(raw[j].y); STTM_OPAQUE_V(raw[j].z); STTM_OPAQUE_V(raw[j].w);
+    }
 #pragma unroll
     for (int j = 0; j < kItem; ++j) {
       if (one_m >> j & 1u) {
@@ -949,37 +962,18 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
         for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
       }
     }
-    if (open) {
-      // the last cluster runs past the item: finish it from the list, kTail loads in flight (the first kTail positions
-      // after the item are already described, by lanes kItem ...)
-      const int open_row = lane_value(row_v, kItem - 1), open_end = lane_value(end_v, kItem - 1);
-      int total = lane_value(members, kItem - 1);
-      Slot ts = sv;
-      int first = kItem;  // lane of the batch's first position
-#pragma unroll 1
-      for (int q = p1; q < open_end; q += kTail) {
-        Raw tr[kTail];
-#pragma unroll
-        for (int u = 0; u < kTail; ++u) {
-          tr[u] = R::zero();
-          if (q + u < open_end)
-            tr[u] = load_slot<DT>(a.feats, a.nsum, g.D, chl, lane_value(ts.kind, first + u), lane_value(ts.idx, first + u));
-        }
-#pragma unroll
-        for (int u = 0; u < kTail; ++u)
-          if (q + u < open_end) {
-            acc_slot<DT>(tr[u], lane_value(ts.kind, first + u), acc);
-            total += lane_value(ts.weight, first + u);
-          }
-        first = 0;
-        if (lane < kTail && q + kTail + lane < open_end)
-          ts = describe<DT>(g, a.node_map, a.lvl, a.order[q + kTail + lane]);
-      }
-      if (open_row < a.capacity) {
-        if (act) store_mean<DT, ODT>(a.merged, (size_t)open_row * g.D + ch0, acc, 1.f / (float)total);
-        if (chunk == 0 && lane == 0 && a.counts) a.counts[open_row] = total;
-      }
-    }
+    base += kItem;
+    if (!open || base >= open_end) break;
+    const int left = open_end - base;
+    use_m = add_m = left < kItem ? (1u << left) - 1u : (1u << kItem) - 1u;
+    end_m = left <= kItem ? 1u << (left - 1) : 0u;
+    mean_m = open_row < a.capacity ? end_m : 0u;
+    one_m = share_m = 0u;
+    row_v = open_row;
+    inv_v = open_inv;
+    const bool past = base - p0 == kWave;  // (at most once: kBig + kItem positions)
+    sv.kind = past ? beyond.kind : __shfl_down(sv.kind, kItem, 64);
+    sv.idx = past ? beyond.idx : __shfl_down(sv.idx, kItem, 64);
   }
 }
 
@@ -1298,7 +1292,7 @@ void launch_reduce_gather(const Geo& g, const void* feats, const float* nsum, co
                           const uint8_t* node_level, int out_dtype, int64_t capacity, void* merged, int32_t* counts,
                           const ReduceBuffers& rb, bool zscan, hipStream_t s) {
   const int nitems = (g.N + kItem - 1) / kItem;
-  dim3 grid((unsigned)(nitems * gather_waves(g))), block(64);  // <= N + 15 workgroups
+  const dim3 grid((unsigned)nitems * (unsigned)g.nC), block(64);  // (16 KB of features each: fewer than 2^32 threads)
   const GatherArgs a = gather_args(feats, nsum, node_map, node_level, capacity, merged, counts, rb, zscan);
   STTM_DISPATCH_IO(k_reduce, g.dtype, out_dtype, grid, block, s, g, a);
 }
