@@ -507,6 +507,15 @@ __device__ inline void sel_clear(SelState* st, int elements) {
   for (int j = threadIdx.x; j < words; j += blockDim.x) p[j] = 0;
 }
 
+// The whole grid zeroes the states of `videos` videos.
+__device__ inline void sel_clear_all(SelState* st, int videos, int elements) {
+  constexpr int kWords = (int)(sizeof(SelState) / 4);
+  const int words = elements > kSelRefine ? kWords : (int)(offsetof(SelState, pieces) / 4);
+  const long long all = (long long)videos * words, step = (long long)gridDim.x * blockDim.x;
+  for (long long j = (long long)blockIdx.x * blockDim.x + threadIdx.x; j < all; j += step)
+    reinterpret_cast<unsigned*>(st + j / words)[j % words] = 0;
+}
+
 // Adds w to hist[digit] for the lanes with valid set; every lane of the wavefront must call it. The two
 // most frequent digits of the wavefront are combined before the atomic (real similarities sit in
 // tight clusters, which would otherwise serialise on one LDS word); whatever is left goes through plain

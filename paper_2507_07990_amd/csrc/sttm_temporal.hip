@@ -30,7 +30,7 @@ __device__ inline void block_sum16(const typename Row<DT>::Elem* fb, int D, int 
 }
 
 // ------------------------------------------------------------------------------------------------
-// The feature pass of the temporal stage, in two kernels.
+// The feature pass of the temporal stage, in two kernels, or for small inputs in one (k_temporal_tiles).
 // The two frames' partitions are both quadtree cuts, so any two overlapping nodes are nested; a pair is named by
 // the top-left cell q of its finer node, and its "join" block is the coarser node.
 //
@@ -222,21 +222,241 @@ __device__ inline float rows16_sum(const float* tb, int lane) {
   return acc;
 }
 
+// One item for one chunk of the channels, by a wavefront: `words` holds the item's 16-bit words, one per lane; `tb` is a staging
+// area of kFastRows rows of 68 floats in LDS.
+template <int DT>
+__device__ __forceinline__ void temporal_item(const Geo& g, const void* __restrict__ feats_v, const float* __restrict__ nsum,
+                                              float* __restrict__ pd_part, int words, int chunk, float* tb, int lane) {
+  typedef Row<DT> R;
+  typedef typename R::Raw Raw;
+  constexpr int VEC = R::VEC;
+  const int H = g.H, W = g.W, HW = g.HW, NB = g.NN - g.lvl_base[3];
+  auto e = [&](int j) { return lane_value(words, kTItemE + j); };
+  const int f = (lane_value(words, 0) & 0xffff) | (lane_value(words, 1) << 16), type = lane_value(words, 2);
+  const int it_n = lane_value(words, 3), it_a = lane_value(words, 4);
+  const bool coarse_is_t = lane_value(words, 5) != 0;
+  const int ch0 = chunk * g.cch + lane * VEC;
+  const bool act = ch0 < g.D;
+  const int chl = act ? ch0 : 0;  // (a lane beyond the last channel reads the first ones; its share is dropped below)
+  const typename R::Elem* ft = reinterpret_cast<const typename R::Elem*>(feats_v) + (size_t)f * HW * g.D;
+  const typename R::Elem* fp = ft - (size_t)HW * g.D;
+  auto row = [&](const typename R::Elem* frame, int cell) {
+    return *reinterpret_cast<const Raw*>(frame + (size_t)cell * g.D + chl);
+  };
+  float* out = pd_part + (size_t)(f * g.nC + chunk) * HW;
+  if (type == 0) {
+    // ---- up to four 2x2 regions, two at a time (16 rows in flight)
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {
+      if (half * 2 >= it_n) break;
+      Raw rt[2][4], rp[2][4];
+#pragma unroll
+      for (int rr = 0; rr < 2; ++rr) {
+        const int ri = half * 2 + rr;
+        const int c0 = ri < it_n ? (e(ri) & 1023) : HW;  // (HW: no such row)
+        const int y0 = c0 / W, x0 = c0 - y0 * W;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int y = y0 + (k >> 1), x = x0 + (k & 1);
+          rt[rr][k] = R::zero();
+          rp[rr][k] = R::zero();
+          if (y < H && x < W) {
+            rt[rr][k] = row(ft, y * W + x);
+            rp[rr][k] = row(fp, y * W + x);
+          }
+        }
+      }
+#pragma unroll
+      for (int rr = 0; rr < 2; ++rr) {
+        const int ri = half * 2 + rr;
+        const int ee = ri < it_n ? e(ri) : 0;
+        const bool t_block = (ee >> 10) & 1, p_block = (ee >> 11) & 1;  // wave-uniform
+        if (!t_block && !p_block) {  // four cells against four cells: no sums needed
+#pragma unroll
+          for (int k = 0; k < 4; ++k) tb[(ri * 4 + k) * 68 + lane] = act ? R::dot(rt[rr][k], rp[rr][k]) : 0.f;
+          continue;
+        }
+        // a frame that holds the 2x2 block takes part with the sum of its four cells
+        float st[VEC], sp[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) st[v] = sp[v] = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          float xv[VEC];
+          if (t_block) {
+            R::unpack(rt[rr][k], xv);
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) st[v] += xv[v];
+          }
+          if (p_block) {
+            R::unpack(rp[rr][k], xv);
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) sp[v] += xv[v];
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          float xa[VEC], xb[VEC];
+          if (t_block) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) xa[v] = st[v];
+          } else {
+            R::unpack(rt[rr][k], xa);
+          }
+          if (p_block) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) xb[v] = sp[v];
+          } else {
+            R::unpack(rp[rr][k], xb);
+          }
+          float d = 0.f;
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) d = fmaf(xa[v], xb[v], d);
+          tb[(ri * 4 + k) * 68 + lane] = act ? d : 0.f;
+        }
+      }
+    }
+    wave_lds_fence();
+    const float acc = rows16_sum(tb, lane);
+    int row_l = lane;  // (what is derived from it is worked out here: kept through the loop it does not fit the registers)
+    STTM_OPAQUE_V(row_l);
+    const int ri = (row_l >> 2) & 3, k = row_l & 3, ee = __shfl(words, kTItemE + ri, 64);
+    if (row_l < kFastRows && ri < it_n) {
+      const int c0 = ee & 1023, y = c0 / W + (k >> 1), x = c0 % W + (k & 1);
+      const bool both_block = ((ee >> 10) & 3) == 3;
+      if (y < H && x < W && (k == 0 || !both_block)) out[y * W + x] = acc;
+    }
+    wave_lds_fence();
+  } else if (type == 1) {
+    // ---- a 4x4 join block: its sum in the frame where it is one node, then every cell of the other frame dotted
+    //      with it; the dot product of a finer node is the sum over its cells
+    const int y0 = it_a / W, x0 = it_a - y0 * W;
+    const typename R::Elem* coarse = coarse_is_t ? ft : fp;
+    const typename R::Elem* fine = coarse_is_t ? fp : ft;
+    float SA[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) SA[v] = 0.f;
+    {
+      Raw rc[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int y = y0 + (j >> 2), x = x0 + (j & 3);
+        rc[j] = R::zero();
+        if (y < H && x < W) rc[j] = row(coarse, y * W + x);
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        float tv[VEC];
+        R::unpack(rc[j], tv);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) SA[v] += tv[v];
+      }
+    }
+    // (the compiler asks for these sixteen rows before it adds up the first sixteen: all 32 are in flight, and fit)
+    {
+      Raw rf[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int y = y0 + (j >> 2), x = x0 + (j & 3);
+        rf[j] = R::zero();
+        if (y < H && x < W) rf[j] = row(fine, y * W + x);
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        float tv[VEC];
+        R::unpack(rf[j], tv);
+        float d = 0.f;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) d = fmaf(tv[v], SA[v], d);
+        tb[j * 68 + lane] = act ? d : 0.f;
+      }
+    }
+    wave_lds_fence();
+    const float cd = rows16_sum(tb, lane);  // lane i < 16: cell (i / 4, i % 4) of the block against the coarse sum
+    wave_lds_fence();
+    const float s4 = (cd + __shfl_down(cd, 1, 64)) + (__shfl_down(cd, 4, 64) + __shfl_down(cd, 5, 64));  // 2x2 at lane
+    float s16 = s4;  // lanes 0, 2, 8, 10 hold the four 2x2 sums
+    s16 = (s16 + __shfl_down(s16, 2, 64)) + (__shfl_down(s16, 8, 64) + __shfl_down(s16, 10, 64));
+    const int lf = __shfl_down(words, kTItemE, 64);  // level of the other frame's node at the lane's cell
+    int cell_l = lane;  // (as above)
+    STTM_OPAQUE_V(cell_l);
+    if (cell_l < 16) {
+      const int dy = cell_l >> 2, dx = cell_l & 3, y = y0 + dy, x = x0 + dx;
+      if (y < H && x < W) {
+        const int cb = y * W + x;
+        if (lf == 0) out[cb] = cd;
+        else if (lf == 1 && !(dy & 1) && !(dx & 1)) out[cb] = s4;
+        else if (lf == 2 && lane == 0) out[cb] = s16;
+      }
+    }
+  } else {
+    // ---- under a join block at a level >= 3: its stored sum against single cells (sixteen at a time) or against
+    //      one finer node
+    const int fc = coarse_is_t ? f : f - 1;  // frame in which the join block is one node
+    const typename R::Elem* fine = coarse_is_t ? fp : ft;
+    const float* srow = nsum + ((size_t)fc * NB + it_a) * g.D + chl;
+    float S[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; v += 4) {
+      const float4 q = *reinterpret_cast<const float4*>(srow + v);
+      S[v] = q.x; S[v + 1] = q.y; S[v + 2] = q.z; S[v + 3] = q.w;
+    }
+    if (type == 2) {
+      Raw r[16];
+#pragma unroll
+      for (int jj = 0; jj < 16; ++jj) {
+        r[jj] = R::zero();
+        if (jj < it_n) r[jj] = row(fine, e(jj));
+      }
+#pragma unroll
+      for (int jj = 0; jj < 16; ++jj) {
+        float xv[VEC];
+        R::unpack(r[jj], xv);
+        float d = 0.f;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) d = fmaf(xv[v], S[v], d);
+        tb[jj * 68 + lane] = act ? d : 0.f;
+      }
+      wave_lds_fence();
+      const float acc = rows16_sum(tb, lane);
+      const int cell = __shfl_down(words, kTItemE, 64);
+      if (lane < it_n) out[cell] = acc;
+      wave_lds_fence();
+    } else {
+      const int q = e(0), lf = e(1);
+      const int y = q / W, x = q - y * W;
+      float SB[VEC];
+      if (lf >= 3) {
+        const int ff = coarse_is_t ? f - 1 : f;
+        const float* brow = nsum + ((size_t)ff * NB + node_index(g, lf, y >> lf, x >> lf) - g.lvl_base[3]) * g.D + chl;
+#pragma unroll
+        for (int v = 0; v < VEC; v += 4) {
+          const float4 t = *reinterpret_cast<const float4*>(brow + v);
+          SB[v] = t.x; SB[v + 1] = t.y; SB[v + 2] = t.z; SB[v + 3] = t.w;
+        }
+      } else {
+        const int s = 1 << lf;
+        block_sum16<DT>(fine + chl, g.D, W, y, x, min(s, H - y), min(s, W - x), SB);
+      }
+      float d = 0.f;
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) d = fmaf(SB[v], S[v], d);
+      if (!act) d = 0.f;
+      d = wave_sum(d);
+      if (lane == 0) out[q] = d;
+    }
+  }
+}
+
 template <int DT>
 __global__ __launch_bounds__(256, 3) void k_temporal_dots(Geo g, const void* __restrict__ feats_v,
                                                        const float* __restrict__ nsum,
                                                        const TItem* __restrict__ items,
                                                        const int* __restrict__ count, float* __restrict__ pd_part) {
-  typedef Row<DT> R;
-  typedef typename R::Raw Raw;
-  constexpr int VEC = R::VEC;
   __shared__ float tbuf[4][kFastRows * 68];
   // (the wavefront's number is the same in all its lanes: said explicitly, so that everything derived from it --
   // the task, the item and the row addresses -- is kept in scalar registers)
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int H = g.H, W = g.W, HW = g.HW;
-  const int NB = g.NN - g.lvl_base[3];
-  float* tb = tbuf[wave];
   // where each queue's items lie in the list: lane q holds the number of items up to and including queue q's
   static_assert(kTQueues == kWave, "a lane per queue");
   const int mine = count[lane * kTCountStride];
@@ -267,223 +487,96 @@ __global__ __launch_bounds__(256, 3) void k_temporal_dots(Geo g, const void* __r
   for (; task < ntasks; task += stride) {
     const int words = next_words, chunk = task % g.nC;
     if (task + stride < ntasks) next_words = fetch(task + stride);
-    auto e = [&](int j) { return lane_value(words, kTItemE + j); };
-    const int f = (lane_value(words, 0) & 0xffff) | (lane_value(words, 1) << 16), type = lane_value(words, 2);
-    const int it_n = lane_value(words, 3), it_a = lane_value(words, 4);
-    const bool coarse_is_t = lane_value(words, 5) != 0;
-    const int ch0 = chunk * g.cch + lane * VEC;
-    const bool act = ch0 < g.D;
-    const int chl = act ? ch0 : 0;  // (a lane beyond the last channel reads the first ones; its share is dropped below)
-    const typename R::Elem* ft = reinterpret_cast<const typename R::Elem*>(feats_v) + (size_t)f * HW * g.D;
-    const typename R::Elem* fp = ft - (size_t)HW * g.D;
-    auto row = [&](const typename R::Elem* frame, int cell) {
-      return *reinterpret_cast<const Raw*>(frame + (size_t)cell * g.D + chl);
-    };
-    float* out = pd_part + (size_t)(f * g.nC + chunk) * HW;
-    if (type == 0) {
-      // ---- up to four 2x2 regions, two at a time (16 rows in flight)
-#pragma unroll 1
-      for (int half = 0; half < 2; ++half) {
-        if (half * 2 >= it_n) break;
-        Raw rt[2][4], rp[2][4];
-#pragma unroll
-        for (int rr = 0; rr < 2; ++rr) {
-          const int ri = half * 2 + rr;
-          const int c0 = ri < it_n ? (e(ri) & 1023) : HW;  // (HW: no such row)
-          const int y0 = c0 / W, x0 = c0 - y0 * W;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int y = y0 + (k >> 1), x = x0 + (k & 1);
-            rt[rr][k] = R::zero();
-            rp[rr][k] = R::zero();
-            if (y < H && x < W) {
-              rt[rr][k] = row(ft, y * W + x);
-              rp[rr][k] = row(fp, y * W + x);
-            }
-          }
-        }
-#pragma unroll
-        for (int rr = 0; rr < 2; ++rr) {
-          const int ri = half * 2 + rr;
-          const int ee = ri < it_n ? e(ri) : 0;
-          const bool t_block = (ee >> 10) & 1, p_block = (ee >> 11) & 1;  // wave-uniform
-          if (!t_block && !p_block) {  // four cells against four cells: no sums needed
-#pragma unroll
-            for (int k = 0; k < 4; ++k) tb[(ri * 4 + k) * 68 + lane] = act ? R::dot(rt[rr][k], rp[rr][k]) : 0.f;
-            continue;
-          }
-          // a frame that holds the 2x2 block takes part with the sum of its four cells
-          float st[VEC], sp[VEC];
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) st[v] = sp[v] = 0.f;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            float xv[VEC];
-            if (t_block) {
-              R::unpack(rt[rr][k], xv);
-#pragma unroll
-              for (int v = 0; v < VEC; ++v) st[v] += xv[v];
-            }
-            if (p_block) {
-              R::unpack(rp[rr][k], xv);
-#pragma unroll
-              for (int v = 0; v < VEC; ++v) sp[v] += xv[v];
-            }
-          }
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            float xa[VEC], xb[VEC];
-            if (t_block) {
-#pragma unroll
-              for (int v = 0; v < VEC; ++v) xa[v] = st[v];
-            } else {
-              R::unpack(rt[rr][k], xa);
-            }
-            if (p_block) {
-#pragma unroll
-              for (int v = 0; v < VEC; ++v) xb[v] = sp[v];
-            } else {
-              R::unpack(rp[rr][k], xb);
-            }
-            float d = 0.f;
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) d = fmaf(xa[v], xb[v], d);
-            tb[(ri * 4 + k) * 68 + lane] = act ? d : 0.f;
-          }
-        }
-      }
-      wave_lds_fence();
-      const float acc = rows16_sum(tb, lane);
-      int row_l = lane;  // (what is derived from it is worked out here: kept through the loop it does not fit the registers)
-      STTM_OPAQUE_V(row_l);
-      const int ri = (row_l >> 2) & 3, k = row_l & 3, ee = __shfl(words, kTItemE + ri, 64);
-      if (row_l < kFastRows && ri < it_n) {
-        const int c0 = ee & 1023, y = c0 / W + (k >> 1), x = c0 % W + (k & 1);
-        const bool both_block = ((ee >> 10) & 3) == 3;
-        if (y < H && x < W && (k == 0 || !both_block)) out[y * W + x] = acc;
-      }
-      wave_lds_fence();
-    } else if (type == 1) {
-      // ---- a 4x4 join block: its sum in the frame where it is one node, then every cell of the other frame dotted
-      //      with it; the dot product of a finer node is the sum over its cells
-      const int y0 = it_a / W, x0 = it_a - y0 * W;
-      const typename R::Elem* coarse = coarse_is_t ? ft : fp;
-      const typename R::Elem* fine = coarse_is_t ? fp : ft;
-      float SA[VEC];
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) SA[v] = 0.f;
-      {
-        Raw rc[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int y = y0 + (j >> 2), x = x0 + (j & 3);
-          rc[j] = R::zero();
-          if (y < H && x < W) rc[j] = row(coarse, y * W + x);
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          float tv[VEC];
-          R::unpack(rc[j], tv);
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) SA[v] += tv[v];
-        }
-      }
-      // (the compiler asks for these sixteen rows before it adds up the first sixteen: all 32 are in flight, and fit)
-      {
-        Raw rf[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int y = y0 + (j >> 2), x = x0 + (j & 3);
-          rf[j] = R::zero();
-          if (y < H && x < W) rf[j] = row(fine, y * W + x);
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          float tv[VEC];
-          R::unpack(rf[j], tv);
-          float d = 0.f;
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) d = fmaf(tv[v], SA[v], d);
-          tb[j * 68 + lane] = act ? d : 0.f;
-        }
-      }
-      wave_lds_fence();
-      const float cd = rows16_sum(tb, lane);  // lane i < 16: cell (i / 4, i % 4) of the block against the coarse sum
-      wave_lds_fence();
-      const float s4 = (cd + __shfl_down(cd, 1, 64)) + (__shfl_down(cd, 4, 64) + __shfl_down(cd, 5, 64));  // 2x2 at lane
-      float s16 = s4;  // lanes 0, 2, 8, 10 hold the four 2x2 sums
-      s16 = (s16 + __shfl_down(s16, 2, 64)) + (__shfl_down(s16, 8, 64) + __shfl_down(s16, 10, 64));
-      const int lf = __shfl_down(words, kTItemE, 64);  // level of the other frame's node at the lane's cell
-      int cell_l = lane;  // (as above)
-      STTM_OPAQUE_V(cell_l);
-      if (cell_l < 16) {
-        const int dy = cell_l >> 2, dx = cell_l & 3, y = y0 + dy, x = x0 + dx;
-        if (y < H && x < W) {
-          const int cb = y * W + x;
-          if (lf == 0) out[cb] = cd;
-          else if (lf == 1 && !(dy & 1) && !(dx & 1)) out[cb] = s4;
-          else if (lf == 2 && lane == 0) out[cb] = s16;
-        }
-      }
-    } else {
-      // ---- under a join block at a level >= 3: its stored sum against single cells (sixteen at a time) or against
-      //      one finer node
-      const int fc = coarse_is_t ? f : f - 1;  // frame in which the join block is one node
-      const typename R::Elem* fine = coarse_is_t ? fp : ft;
-      const float* srow = nsum + ((size_t)fc * NB + it_a) * g.D + chl;
-      float S[VEC];
-#pragma unroll
-      for (int v = 0; v < VEC; v += 4) {
-        const float4 q = *reinterpret_cast<const float4*>(srow + v);
-        S[v] = q.x; S[v + 1] = q.y; S[v + 2] = q.z; S[v + 3] = q.w;
-      }
-      if (type == 2) {
-        Raw r[16];
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-          r[jj] = R::zero();
-          if (jj < it_n) r[jj] = row(fine, e(jj));
-        }
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-          float xv[VEC];
-          R::unpack(r[jj], xv);
-          float d = 0.f;
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) d = fmaf(xv[v], S[v], d);
-          tb[jj * 68 + lane] = act ? d : 0.f;
-        }
-        wave_lds_fence();
-        const float acc = rows16_sum(tb, lane);
-        const int cell = __shfl_down(words, kTItemE, 64);
-        if (lane < it_n) out[cell] = acc;
-        wave_lds_fence();
-      } else {
-        const int q = e(0), lf = e(1);
-        const int y = q / W, x = q - y * W;
-        float SB[VEC];
-        if (lf >= 3) {
-          const int ff = coarse_is_t ? f - 1 : f;
-          const float* brow = nsum + ((size_t)ff * NB + node_index(g, lf, y >> lf, x >> lf) - g.lvl_base[3]) * g.D + chl;
-#pragma unroll
-          for (int v = 0; v < VEC; v += 4) {
-            const float4 t = *reinterpret_cast<const float4*>(brow + v);
-            SB[v] = t.x; SB[v + 1] = t.y; SB[v + 2] = t.z; SB[v + 3] = t.w;
-          }
-        } else {
-          const int s = 1 << lf;
-          block_sum16<DT>(fine + chl, g.D, W, y, x, min(s, H - y), min(s, W - x), SB);
-        }
-        float d = 0.f;
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) d = fmaf(SB[v], S[v], d);
-        if (!act) d = 0.f;
-        d = wave_sum(d);
-        if (lane == 0) out[q] = d;
-      }
-    }
+    temporal_item<DT>(g, feats_v, nsum, pd_part, words, chunk, tbuf[wave], lane);
   }
 }
+
+// ------------------------------------------------------------------------------------------------
+// k_temporal_tiles: the same for small inputs, without a plan: a wavefront takes a 4x4 tile of a frame pair for one chunk of
+// the channels, finds out from the two frames' levels there what it has to do, and does it item by item, the same arithmetic
+// on the same rows (`share` wavefronts take turns at the items of one). What a plan costs is a launch, two trips to memory for
+// making its items and one for reading them; what it gives is an even share of the work for every wavefront, which matters
+// once there are many more tiles than wavefronts. Both are bound by the latency of the rows a single item waits for.
+// ------------------------------------------------------------------------------------------------
+template <int DT>
+__global__ __launch_bounds__(256, 3) void k_temporal_tiles(Geo g, const void* __restrict__ feats_v,
+                                                        const float* __restrict__ nsum,
+                                                        const uint8_t* __restrict__ node_level, bool skip_same,
+                                                        float* __restrict__ pd_part, SelState* __restrict__ sel, int share) {
+  __shared__ float tbuf[4][kFastRows * 68];
+  __shared__ int item[4][kTItemWords];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  const int H = g.H, W = g.W, TX = (W + 3) >> 2, tiles = TX * ((H + 3) >> 2);
+  sel_clear_all(sel, g.B, g.T * g.HW);  // the temporal budget searches start afresh
+  // Workgroups go to the eight dies round-robin by their index; each die has an eighth of the frames, so that both pairs
+  // that need a frame's rows mostly meet in its L2.
+  const long long tasks = (long long)g.F * tiles * g.nC;
+  const int die = blockIdx.x & 7, first = (int)(tasks * die / 8), last = (int)(tasks * (die + 1) / 8);
+  const int slot = (int)(blockIdx.x >> 3) * 4 + wave, task = first + slot / share, turn = slot % share;
+  if (task >= last) return;  // (the wavefronts of a workgroup share nothing from here on)
+  const int chunk = task % g.nC, tile = task / g.nC % tiles, f = task / g.nC / tiles;
+  if (f % g.T == 0) return;
+  const int y0 = tile / TX * 4, x0 = (tile - tile / TX * TX) * 4, head = y0 * W + x0;
+  // lane i < 16: cell (i / 4, i % 4) of the tile, if there is one
+  const int dy = lane >> 2 & 3, dx = lane & 3, cell = head + dy * W + dx;
+  const bool in = lane < 16 && y0 + dy < H && x0 + dx < W;
+  const size_t at = (size_t)f * g.HW + (in ? cell : head);
+  const int a = node_level[at], b = node_level[at - g.HW];
+  // a node above level 1 covers the tile: the first cell speaks for it
+  const int a0 = lane_value(a, 0), b0 = lane_value(b, 0), J = max(a0, b0), lf = min(a0, b0);
+  const bool coarse_is_t = a0 >= b0, corner = !(dy & 1) && !(dx & 1);
+  // What there is to do: one item of the lanes in `heads`, then an item for each lane in `blocks` (2x2 blocks under a node
+  // of level 3 or more).
+  int type, aa = 0;
+  unsigned heads, blocks = 0;
+  if (J <= 1) {
+    type = 0;
+    heads = (unsigned)__ballot(in && corner && !(skip_same && a == b));
+  } else if (J == 2) {
+    type = 1;
+    heads = skip_same && a0 == b0 ? 0u : 0xffffu;
+    aa = head;
+  } else {
+    aa = node_index(g, J, y0 >> J, x0 >> J) - g.lvl_base[3];
+    type = lf >= 2 ? 3 : 2;
+    heads = lf >= 2 ? ((y0 | x0) & ((1 << lf) - 1) ? 0u : 1u) : (unsigned)__ballot(in && min(a, b) == 0);
+    if (lf < 2) blocks = (unsigned)__ballot(in && corner && min(a, b) == 1);
+  }
+  int* w = item[wave];
+#pragma unroll 1
+  for (int left = (heads != 0) + (int)__popcll((unsigned long long)blocks); left > 0; --left) {
+    const bool whole = heads != 0;
+    if (!whole) type = 3;
+    const unsigned mine = whole ? heads : blocks & (0u - blocks);
+    if (whole) heads = 0;
+    else blocks &= blocks - 1u;
+    if (left % share != turn) continue;
+    if (mine >> (lane & 31) & (unsigned)(lane < 16)) {
+      const int to = kTItemE + (int)__popcll((unsigned long long)(mine & ((1u << (lane & 15)) - 1u)));
+      w[to] = type == 0 ? cell | (a == 1 ? 1 << 10 : 0) | (b == 1 ? 1 << 11 : 0) : type == 1 ? (in ? min(coarse_is_t ? b : a, 2) : 0) : cell;
+      if (type == 3) w[to + 1] = min(a, b);
+    }
+    if (lane < kTItemE)
+      w[lane] = lane == 0 ? f & 0xffff : lane == 1 ? f >> 16 : lane == 2 ? type : lane == 3 ? (int)__popcll((unsigned long long)mine) : lane == 4 ? aa : (int)coarse_is_t;
+    wave_lds_fence();
+    const int words = w[min(lane, kTItemWords - 1)];
+    temporal_item<DT>(g, feats_v, nsum, pd_part, words, chunk, tbuf[wave], lane);
+    wave_lds_fence();
+  }
+}
+
+// Up to this many (frame, tile, chunk) triples take the kernel without a plan. A pass with the plan and without, us: 7168
+// triples (64 frames of 13x13 at D = 3584) 108.5 and 105.4, 5760 (96 of 11x19, fp32, D = 1000) 160.3 and 154.9, 9000 (150 of
+// 15x20 at D = 1280) 157.8 and 156.9, 20,160 (180 of 14x14 at D = 3584) 220.6 and 223.7, 57,344 401 and 420.
+// (The host-thread build of the tests that takes the large inputs' kernels takes the plan.)
+#ifndef STTM_TEMPORAL_TILES_MAX
+#define STTM_TEMPORAL_TILES_MAX 12288
+#endif
+constexpr long long kTilesMax = STTM_TEMPORAL_TILES_MAX;
+// Of few triples the items of one are shared out among four or two wavefronts (8 frames of 8x8: 49.4 and 45.9 us a pass; 37 of
+// 16x5 108.1 and 106.4; four wavefronts for 7168 triples: 106.4 and 109.8).
+constexpr long long kTilesFour = 1024, kTilesTwo = 3072;
+static long long temporal_tasks(const Geo& g) { return (long long)g.F * ((g.H + 3) / 4) * ((g.W + 3) / 4) * g.nC; }
 
 size_t temporal_items_bytes(const Geo& g) { return (size_t)kTQueues * temporal_queue_items(g) * sizeof(TItem); }
 size_t temporal_count_bytes() { return (size_t)kTQueues * kTCountStride * sizeof(int); }
@@ -491,9 +584,20 @@ size_t temporal_count_bytes() { return (size_t)kTQueues * kTCountStride * sizeof
 void launch_temporal_dots(const Geo& g, const void* feats, const uint8_t* node_level, const float* nsum,
                           bool skip_same, float* pd_part, SelState* sel, void* items, int* item_count,
                           hipStream_t s) {
+  if (g.T == 1) return;  // no pairs
+  if (const long long tasks = temporal_tasks(g); tasks <= kTilesMax) {
+    const int share = tasks <= kTilesFour ? 4 : tasks <= kTilesTwo ? 2 : 1;
+    const dim3 grid(8u * (unsigned)(((tasks / 8 + 1) * share + 3) / 4)), block(256);  // a die has at most tasks / 8 + 1 of them
+    if (g.dtype == 1)
+      hipLaunchKernelGGL(k_temporal_tiles<1>, grid, block, 0, s, g, feats, nsum, node_level, skip_same, pd_part, sel, share);
+    else if (g.dtype == 2)
+      hipLaunchKernelGGL(k_temporal_tiles<2>, grid, block, 0, s, g, feats, nsum, node_level, skip_same, pd_part, sel, share);
+    else
+      hipLaunchKernelGGL(k_temporal_tiles<0>, grid, block, 0, s, g, feats, nsum, node_level, skip_same, pd_part, sel, share);
+    return;
+  }
   TItem* q = reinterpret_cast<TItem*>(items);
   hipLaunchKernelGGL(k_temporal_plan, dim3(g.F), dim3(256), 0, s, g, node_level, skip_same, q, item_count, sel);
-  if (g.T == 1) return;  // no pairs (an empty pass over them takes 2.2 us of the 98 of one image of 24x24)
   // enough wavefronts for about four tasks each if every pair came with all the items it can have; whole rounds of dies
   const long long worst = (long long)g.F * temporal_items_per_pair(g) * g.nC;
   long long blocks = (worst + 15) / 16;
@@ -552,6 +656,7 @@ __global__ __launch_bounds__(256) void k_temporal_resolve(Geo g, int match,
   const int f = blockIdx.x, HW = g.HW, W = g.W;
   if (f == 0) temporal_clear(item_count, threadIdx.x);  // the feature pass is over: its queues are empty for the next one
   if (f % g.T == 0) {
+    if (g.T == 1) sel_clear(sel + f, HW);  // (the feature pass over frame pairs, which does so, is left out)
     for (int c = threadIdx.x; c < HW; c += blockDim.x) sel_key[(size_t)f * HW + c] = 0;
     return;
   }

@@ -11,7 +11,7 @@ LIB = os.path.join(HERE, "libsttm_cpu.so")
 LIB_LARGE = os.path.join(HERE, "libsttm_cpu_large.so")  # every input takes the kernels of the large ones
 # ... and a small one has several workgroups that list the elements of a search, more elements than a search keeps, and
 # crowded bins
-LARGE = ["-DSTTM_PYR_TILES_MAX=0", "-DSTTM_SEL_WHOLE=0", "-DSTTM_SEL_THREADS=64", "-DSTTM_SEL_LIST=32",
+LARGE = ["-DSTTM_PYR_TILES_MAX=0", "-DSTTM_TEMPORAL_TILES_MAX=0", "-DSTTM_SEL_WHOLE=0", "-DSTTM_SEL_THREADS=64", "-DSTTM_SEL_LIST=32",
          "-DSTTM_SEL_REFINE=0", "-DSTTM_SEL_CROWD=40"]
 SOURCES = ["sttm_api.hip", "sttm_spatial.hip", "sttm_temporal.hip", "sttm_reduce.hip"]
 SANITIZE_EXE = os.path.join(HERE, "sanitize_run")

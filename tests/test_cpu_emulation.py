@@ -325,3 +325,24 @@ def test_emulated_pass_issues_no_memset(emul):
     before = lib.hip_emul_memsets()
     run_cpu.run_cpu(wl.generate(_variant(86, 1, 2, 3, 3, 8, "f32")), tau_s=0.5, tau_t=0.5, lib=lib)
     assert lib.hip_emul_memsets() == before
+
+
+@pytest.mark.parametrize("H,W,dtype,cell_dots,levels", [
+    (32, 32, "f32", 1, [5, 0, 3, 1, 2, 0, 1]),       # every kind of item, as many of each as there can be
+    (13, 11, "bf16", 0, [2, 1, 0, 2, 4, 3, 1, 1]),   # tiles beyond the edge; equal levels count as well
+    (9, 18, "f16", 1, [1, 5, 4, 3, 3, 0, 0, 2]),
+])
+def test_emulated_temporal_pass_with_and_without_a_plan(emul, large, H, W, dtype, cell_dots, levels):
+    """The kernel that finds its work by itself against the one that is given a plan: all tables and outputs the same bit for
+    bit, on partitions of uniform levels and on one that mixes them."""
+    run_cpu, _ = emul
+    T = len(levels)
+    feats = wl.generate(_variant(106, 1, T, H, W, 8, dtype))
+    for nm, nl in (_uniform_partition(T, H, W, levels), (None, None)):
+        kw = dict(tau_s=0.7, tau_t=0.3, cell_dots=cell_dots)
+        if nm is not None:
+            kw["node_map_override"] = (nm, nl)
+        a, b = (run_cpu.run_cpu(feats, lib=lib, **kw) for lib in (large, run_cpu.load()))
+        for name, x in vars(a).items():
+            if isinstance(x, np.ndarray):
+                np.testing.assert_array_equal(x, getattr(b, name), err_msg=name)

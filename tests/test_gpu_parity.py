@@ -1157,3 +1157,46 @@ def test_whole_pass_replayed_from_a_graph(lib):
         assert all(torch.equal(a, b) for a, b in zip(want, got))
     K = int(want[6][-1])
     assert 1 < K < len(want[2]) and bool((want[1] > 0).any())
+
+
+@pytest.mark.parametrize("T,noise,D", [
+    (80, 0.3, 64),      # 20480 cells, the most that every user of a threshold looks through by itself; few in the picked bin
+    (81, 0.3, 64),      # one frame more: their elements are listed
+    (79, 50.0, 256),    # unrelated vectors: thousands in the picked bin, more than a workgroup keeps
+    (40, 0.003, 512),   # all similarities within 1e-4
+    (30, 0.0, 64),      # nothing but ties
+    (3, 1.0, 64),
+])
+def test_budget_searches_are_exact_where_the_consumer_looks_through_all_keys(lib, T, noise, D):
+    test_budget_searches_are_exact(lib, T, noise, D)
+
+
+@pytest.mark.parametrize("short,T,H,W,D", [
+    (5, 900, 13, 13, 64),     # four wavefronts to a tile, and a plan
+    (100, 900, 13, 13, 64),   # two
+    (760, 900, 13, 13, 64),   # one
+    (3, 100, 32, 29, 264),    # two chunks, the second of two lanes
+])
+def test_pair_similarities_with_and_without_a_plan(lib, short, T, H, W, D):
+    """The first frames of a video by themselves, too few for a plan, against the whole video: the same similarities bit for
+    bit wherever one is defined."""
+    import torch
+    cfg = wl.Workload("v", T + short, 1, T, H, W, D, "f32", wl.pow2_ceil(max(H, W)).bit_length() - 1, 0.1, 0.7)
+    x = torch.from_numpy(wl.generate(cfg)).to("cuda:0")
+    s = lib.Sttm(0)
+    s.ensure_workspace(1, T, H, W, D, lib.STTM_F32, 1)
+
+    def similarities(t):
+        n = t * H * W
+        nm, sig = torch.empty(n, dtype=torch.int32, device="cuda:0"), torch.empty(n, device="cuda:0")
+        nl = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        s.sttm_spatial_quadtree(x, lib.STTM_F32, 1, t, H, W, D, 1, [0.8], nm, nl)
+        s.sttm_temporal_stats(x, nm, nl)
+        s.sttm_export(lib.STTM_TBL_PAIR_SIM, sig)
+        rep, lv = (nm.view(t, -1) % (H * W)).long(), nl.view(t, -1)
+        finer = torch.where(lv[1:] <= lv[:-1], rep[1:], rep[:-1])
+        return sig.view(t, -1)[1:], finer == torch.arange(H * W, device="cuda:0"), lv
+
+    a, defined, lv = similarities(short)
+    b, _, _ = similarities(T)
+    assert torch.equal(a[defined], b[:short - 1][defined]) and len(torch.unique(lv)) > 2
