@@ -350,7 +350,7 @@ struct Timed {
 
 int after_launch(sttm_ctx* c) { return hip_check(c, hipGetLastError(), "kernel launch"); }
 
-int run_spatial_stats(sttm_ctx* c, const void* feats) {
+int run_spatial_stats(sttm_ctx* c, const void* feats, const DecideArgs& decide) {
   {
     Timed t(c, STTM_KERNEL_PYRAMID_STATS);
     launch_pyramid_stats(c->g, feats, c->g.T > 1 && c->cell_dots, at<float>(c, c->lay.part),
@@ -360,7 +360,7 @@ int run_spatial_stats(sttm_ctx* c, const void* feats) {
                           at<float>(c, c->lay.nrm2),
                           at<float>(c, c->lay.sim),
                           at<float>(c, c->lay.m), at<uint32_t>(c, c->lay.sel_key_s), at<uint8_t>(c, c->lay.sel_w_s),
-                          at<SelState>(c, c->lay.sel_s), at<int>(c, c->lay.tcount), c->stream);
+                          at<SelState>(c, c->lay.sel_s), at<int>(c, c->lay.tcount), decide, c->stream);
   int rc = after_launch(c);
   if (rc == STTM_OK) {
     c->have_spatial = true;
@@ -516,7 +516,7 @@ int sttm_spatial_stats(sttm_ctx* ctx, const void* feats_dev, int dtype, int B, i
   STTM_HIP(ctx, hipSetDevice(ctx->device));
   rc = bind_shape(ctx, dtype, B, T, H, W, D, root_grid);
   if (rc) return rc;
-  return run_spatial_stats(ctx, feats_dev);
+  return run_spatial_stats(ctx, feats_dev, DecideArgs{});
 }
 
 int sttm_spatial_quadtree(sttm_ctx* ctx, const void* feats_dev, int dtype, int B, int T, int H, int W, int D,
@@ -526,27 +526,28 @@ int sttm_spatial_quadtree(sttm_ctx* ctx, const void* feats_dev, int dtype, int B
   if (!node_map_dev) return fail(ctx, STTM_ERR_NULL, "node_map is NULL");
   STTM_HIP(ctx, hipSetDevice(ctx->device));
   int rc;
-  TauArgs given = {};
   if (tau_s_host) {
+    DecideArgs decide = {};
     rc = check_feats(ctx, feats_dev);
     if (rc) return rc;
     rc = bind_shape(ctx, dtype, B, T, H, W, D, root_grid);
     if (rc) return rc;
-    rc = take_tau(ctx, tau_s_host, at<float>(ctx, ctx->lay.tau_s), &ctx->h_tau_s, &given);
+    decide.tau = at<float>(ctx, ctx->lay.tau_s);
+    rc = take_tau(ctx, tau_s_host, decide.tau, &ctx->h_tau_s, &decide.given);
     if (rc) return rc;
     ctx->have_tau_s = true;
     ctx->tau_s_pending = false;
-    rc = run_spatial_stats(ctx, feats_dev);
-    if (rc) return rc;
-  } else {
-    if (!ctx->bound || !ctx->have_spatial)
-      return fail(ctx, STTM_ERR_STATE, "no spatial statistics in the workspace (call sttm_spatial_stats first)");
-    if (!same_shape(ctx->g, dtype, B, T, H, W, D, root_grid))
-      return fail(ctx, STTM_ERR_SHAPE, "shape differs from the one the statistics were computed for");
-    if (!ctx->have_tau_s)
-      return fail(ctx, STTM_ERR_STATE, "no spatial threshold chosen (call sttm_budget_threshold first)");
+    decide.node_map = node_map_dev;
+    decide.node_level = node_level_dev;
+    return run_spatial_stats(ctx, feats_dev, decide);
   }
-  launch_spatial_decide(ctx->g, at<float>(ctx, ctx->lay.m), at<float>(ctx, ctx->lay.tau_s), given,
+  if (!ctx->bound || !ctx->have_spatial)
+    return fail(ctx, STTM_ERR_STATE, "no spatial statistics in the workspace (call sttm_spatial_stats first)");
+  if (!same_shape(ctx->g, dtype, B, T, H, W, D, root_grid))
+    return fail(ctx, STTM_ERR_SHAPE, "shape differs from the one the statistics were computed for");
+  if (!ctx->have_tau_s)
+    return fail(ctx, STTM_ERR_STATE, "no spatial threshold chosen (call sttm_budget_threshold first)");
+  launch_spatial_decide(ctx->g, at<float>(ctx, ctx->lay.m), at<float>(ctx, ctx->lay.tau_s),
                         ctx->tau_s_pending ? ctx->search_s : SelSearch{}, node_map_dev, node_level_dev,
                         ctx->stream);
   ctx->tau_s_pending = false;  // the kernel has left the threshold in the workspace

@@ -892,9 +892,6 @@ constexpr int kTCountStride = 32;  // ints between two queues' counters: a 128-b
 __device__ inline void temporal_clear(int* item_count, int tid) {
   if (tid < kTQueues) item_count[tid * kTCountStride] = 0;
 }
-// Also works out the levels above an 8x8 unit from the stored unit sums (extends `nsum`).
-void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float* nrm2, float* sim, float* m,
-                             uint32_t* sel_key, uint8_t* sel_w, SelState* sel, int* item_count, hipStream_t s);
 // Thresholds a caller has named, handed to the kernels that use them as a launch argument (n = 0: none). A copy from the
 // caller's memory to the device is a stream operation of its own: 2.5-5 us there and about as much on the host.
 constexpr int kTauArgs = 32;
@@ -902,11 +899,22 @@ struct TauArgs {
   int n;
   float v[kTauArgs];
 };
-// `given`: if it holds thresholds the kernel takes them from there (and leaves them in `tau` for later readers).
+// The decision about the partition, where it is made with the statistics: from the thresholds in `given` (which are left in `tau`
+// for later readers) or, if there are none, from those in `tau`. node_map NULL: not made.
+struct DecideArgs {
+  TauArgs given;
+  float* tau;
+  int32_t* node_map;
+  uint8_t* node_level;
+};
+// Also works out the levels above an 8x8 unit from the stored unit sums (extends `nsum`).
+void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float* nrm2, float* sim, float* m,
+                             uint32_t* sel_key, uint8_t* sel_w, SelState* sel, int* item_count, const DecideArgs& decide,
+                             hipStream_t s);
 // `pending`: a budget search that has not been carried out yet (or states == NULL); the kernel then works the threshold out
 // itself (and leaves it in `tau` for later readers) instead of reading `tau`.
-void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauArgs& given, const SelSearch& pending,
-                           int32_t* node_map, uint8_t* node_level, hipStream_t s);
+void launch_spatial_decide(const Geo& g, const float* m, float* tau, const SelSearch& pending, int32_t* node_map,
+                           uint8_t* node_level, hipStream_t s);
 // Begins a budget search and says how it goes on. A small input is left to whoever uses the threshold; of a large one the
 // elements of the right bin are listed (`list_key`, `list_w`: [videos][select_elements()]).
 SelSearch launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
@@ -954,6 +962,8 @@ inline size_t nsum_nodes(const Geo& g) { return g.L >= 3 ? (size_t)(g.NN - g.lvl
 void launch_temporal_resolve(const Geo& g, int match, const int32_t* node_map, const uint8_t* node_level,
                              const float* pd_part, const float* cell_part, const float* nrm2, float* sig, float* e,
                              uint32_t* sel_key, SelState* sel, int* item_count, hipStream_t s);
+// `given`: if it holds thresholds the kernel takes them from there (and leaves them in `tau` for later readers); `pending` as
+// above.
 void launch_temporal_parent(const Geo& g, int match, const int32_t* node_map, const uint8_t* node_level,
                             const float* sig, float* tau, const TauArgs& given, const SelSearch& pending, int32_t* parent,
                             int32_t* ptr, hipStream_t s);

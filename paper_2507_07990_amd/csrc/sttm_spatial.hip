@@ -825,7 +825,8 @@ __global__ __launch_bounds__(UP == 2 ? kFinThreadsWide : kFinThreads) void k_spa
                                                                   float* __restrict__ sim, float* __restrict__ m,
                                                                   uint32_t* __restrict__ sel_key,
                                                                   uint8_t* __restrict__ sel_w,
-                                                                  SelState* __restrict__ sel, int* __restrict__ item_count) {
+                                                                  SelState* __restrict__ sel, int* __restrict__ item_count,
+                                                                  DecideArgs decide) {
   STTM_DYNAMIC_LDS(float, sm);
   __shared__ unsigned h0[kSelBins];
   __shared__ __attribute__((aligned(16))) float red[UP ? kUpRows * kFinWaves : 1];
@@ -930,6 +931,18 @@ __global__ __launch_bounds__(UP == 2 ? kFinThreadsWide : kFinThreads) void k_spa
     m[fo + idx] = mv;
   }
   __syncthreads();
+  if (decide.node_map) {  // the caller has named the threshold: the frame's partition (see k_spatial_decide)
+    const int b = f / g.T;
+    const float t = decide.given.n ? decide.given.v[b] : decide.tau[b];
+    if (decide.given.n && f % g.T == 0 && tid == 0) decide.tau[b] = t;
+    for (int c = tid; c < g.HW; c += nthr) {
+      const int y = c / g.W, x = c - y * g.W;
+      int l = g.L;
+      while (l >= 1 && !(s_sim[node_index(g, l, y >> l, x >> l)] > t)) --l;
+      decide.node_map[f * g.HW + c] = f * g.HW + (y >> l << l) * g.W + (x >> l << l);
+      if (decide.node_level) decide.node_level[f * g.HW + c] = (uint8_t)l;
+    }
+  }
 #pragma unroll 1
   for (int i0 = g.lvl_base[1]; i0 < g.NN; i0 += nthr) {  // uniform trip count: the histogram update is wave-wide
     const int idx = i0 + tid;
@@ -959,21 +972,24 @@ __global__ __launch_bounds__(UP == 2 ? kFinThreadsWide : kFinThreads) void k_spa
 }
 
 void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float* nrm2, float* sim, float* m,
-                             uint32_t* sel_key, uint8_t* sel_w, SelState* sel, int* item_count, hipStream_t s) {
+                             uint32_t* sel_key, uint8_t* sel_w, SelState* sel, int* item_count, const DecideArgs& decide,
+                             hipStream_t s) {
   const int up = g.L < 4 ? 0 : (g.P == 16 ? 1 : 2);
   const int threads = up == 2 && g.F <= kFinWideFrames ? kFinThreadsWide : (g.NN <= 256 && !up ? 256 : kFinThreads);  // one node per thread where it fits
   const size_t lds = ((size_t)unit_cols(g) * unit_rows(g) * kUnitStats + 4 * (size_t)g.NN) * sizeof(float);
   if (up == 0)
-    hipLaunchKernelGGL(k_spatial_finalize<0>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel, item_count);
+    hipLaunchKernelGGL(k_spatial_finalize<0>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel, item_count, decide);
   else if (up == 1)
-    hipLaunchKernelGGL(k_spatial_finalize<1>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel, item_count);
+    hipLaunchKernelGGL(k_spatial_finalize<1>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel, item_count, decide);
   else
-    hipLaunchKernelGGL(k_spatial_finalize<2>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel, item_count);
+    hipLaunchKernelGGL(k_spatial_finalize<2>, dim3(g.F), dim3(threads), lds, s, g, part, nsum, nrm2, sim, m, sel_key, sel_w, sel, item_count, decide);
 }
 
 // ------------------------------------------------------------------------------------------------
 // k_spatial_decide: coarse-to-fine search (Sec. 3.2). Grid (cells of a video / threads, videos); one thread per cell
-// walks down from its root: the first node on the path whose smallest child similarity exceeds tau_S is kept.
+// walks down from its root: the first node on the path whose smallest child similarity exceeds tau_S is kept. (Where the caller
+// has named the threshold k_spatial_finalize does so itself: 8 frames of 8x8 45.0 -> 43.9 us a pass, six clips of 25 frames of
+// 15x20 156.3 -> 155.2, 85 frames of 31x31 379.7 -> 377.8.)
 // Large videos, and searches through many keys, take fewer and larger workgroups, since each carries the search out (512 frames
 // of 13x13 random vectors 19.8 -> 16.3 us, moving scenes of that size 10.9 and 11.1, of 46 frames of 27x27 9.9 and 10.4; 1024
 // threads 16.8, 12.3, 11.8).
@@ -983,8 +999,7 @@ constexpr int kDecideWide = 65536, kDecideThreads = 512;
 constexpr int kSelFewKeys = 2048;
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_spatial_decide(Geo g, const float* __restrict__ m,
-                                                                float* __restrict__ tau, TauArgs given,
-                                                                SelSearch pending,
+                                                                float* __restrict__ tau, SelSearch pending,
                                                                 int32_t* __restrict__ node_map,
                                                                 uint8_t* __restrict__ node_level) {
   const int b = blockIdx.y, per_video = g.T * g.HW;
@@ -998,8 +1013,8 @@ __global__ __launch_bounds__(THREADS) void k_spatial_decide(Geo g, const float* 
   for (int l = 1; l < kMaxLevels; ++l)  // (no branches: of a level above the roots the roots are read again)
     path[l] = m[(size_t)f * g.NN + node_index(g, min(l, g.L), y >> min(l, g.L), x >> min(l, g.L))];
   float t;
-  if (pending.states || given.n) {  // the budget search was left to this kernel, or the caller named the threshold
-    t = given.n ? given.v[b] : sel_threshold<THREADS>(g, pending, b);
+  if (pending.states) {  // the budget search was left to this kernel
+    t = sel_threshold<THREADS>(g, pending, b);
     if (blockIdx.x == 0 && threadIdx.x == 0) tau[b] = t;
   } else {
     t = tau[b];
@@ -1014,11 +1029,10 @@ __global__ __launch_bounds__(THREADS) void k_spatial_decide(Geo g, const float* 
   if (node_level) node_level[i] = (uint8_t)lvl;
 }
 
-void launch_spatial_decide(const Geo& g, const float* m, float* tau, const TauArgs& given, const SelSearch& pending,
-                           int32_t* node_map, uint8_t* node_level, hipStream_t s) {
+void launch_spatial_decide(const Geo& g, const float* m, float* tau, const SelSearch& pending, int32_t* node_map, uint8_t* node_level, hipStream_t s) {
   const int per_video = g.T * g.HW;
   auto launch = [&](auto kernel, int threads) {
-    hipLaunchKernelGGL(kernel, dim3((per_video + threads - 1) / threads, g.B), dim3(threads), 0, s, g, m, tau, given, pending,
+    hipLaunchKernelGGL(kernel, dim3((per_video + threads - 1) / threads, g.B), dim3(threads), 0, s, g, m, tau, pending,
                        node_map, node_level);
   };
   const bool look = pending.states && !pending.listed && pending.per_video > kSelFewKeys;  // through all keys
