@@ -759,59 +759,67 @@ __device__ inline Slot describe(const Geo& g, const int32_t* __restrict__ node_m
   return e;
 }
 
-// A lane's 16 bytes of a slot (kind and idx are the same in all lanes, chl is the lane's first channel): one request
-// whichever table the slot lives in. This is the last use of a feature row, and node sums are read once as well.
+// Where a slot's row, or its half of the channels of a node's sum, begins.
 template <int DT>
-__device__ inline typename Row<DT>::Raw load_slot(const void* feats, const float* nsum, int D, int chl, int kind,
-                                                  int idx) {
-  typedef Row<DT> R;
-  const size_t first = (size_t)idx * D;
-  const char* row = kind == 0 ? static_cast<const char*>(feats) + first * sizeof(typename R::Elem)
-                              : reinterpret_cast<const char*>(nsum) + (first + (kind - 1) * 4) * sizeof(float);
-  const unsigned off = (unsigned)chl * (kind == 0 ? (unsigned)sizeof(typename R::Elem) : (unsigned)sizeof(float));
-  return load_once(reinterpret_cast<const typename R::Raw*>(row + off));
+__device__ inline uint64_t slot_address(const void* feats, const float* nsum, int D, const Slot& e) {
+  const size_t first = (size_t)e.idx * D;
+  return e.kind == 0 ? reinterpret_cast<uint64_t>(static_cast<const typename Row<DT>::Elem*>(feats) + first)
+                     : reinterpret_cast<uint64_t>(nsum + first + (e.kind - 1) * 4);
 }
+// The address that lane `src` holds in two halves, in scalar registers; said to be one of global memory (a load from an
+// address of any kind counts as one from LDS too, and is waited for as such).
+#ifndef STTM_HOST_EMULATION
+#define STTM_GLOBAL __attribute__((address_space(1)))
+#else
+#define STTM_GLOBAL
+#endif
+__device__ inline char* lane_address(uint2 v, int src) {
+  const uint64_t a = (uint64_t)(unsigned)lane_value((int)v.y, src) << 32 | (unsigned)lane_value((int)v.x, src);
+  return (char*)(STTM_GLOBAL char*)a;
+}
+__device__ inline uint2 halves(uint64_t a) { return make_uint2((unsigned)a, (unsigned)(a >> 32)); }
 
+// (fp32 rows and node sums share a layout)
 template <int DT>
-__device__ inline void acc_slot(const float4& r, int, float (&acc)[4]) {  // fp32 rows and node sums share a layout
+__device__ inline void acc_slot(const float4& r, unsigned, unsigned, float (&acc)[4]) {
   acc[0] += r.x; acc[1] += r.y; acc[2] += r.z; acc[3] += r.w;
 }
 // (Three steps, each skipped or not: as one choice of three the sums came out of it in three sets of registers and were
 // moved back into one, eight moves a slot. The node sum's two halves add to different channels, so their order is free.)
 template <int DT>
-__device__ inline void acc_slot(const uint4& r, int kind, float (&acc)[8]) {
-  if (kind == 0) Row<DT>::add_row(r, acc);
+__device__ inline void acc_slot(const uint4& r, unsigned half1, unsigned half2, float (&acc)[8]) {
+  if (!(half1 | half2)) Row<DT>::add_row(r, acc);
   const float f0 = __uint_as_float(r.x), f1 = __uint_as_float(r.y);
   const float f2 = __uint_as_float(r.z), f3 = __uint_as_float(r.w);
-  if (kind == 1) {
-    STTM_OPAQUE_S(kind);  // (keeps this a branch; the additions are not made by every slot and dropped)
+  if (half1) {
+    STTM_OPAQUE_S(half1);  // (keeps this a branch; the additions are not made by every slot and dropped)
     acc[0] += f0; acc[1] += f1; acc[2] += f2; acc[3] += f3;
   }
-  if (kind == 2) {
-    STTM_OPAQUE_S(kind);
+  if (half2) {
+    STTM_OPAQUE_S(half2);
     acc[4] += f0; acc[5] += f1; acc[6] += f2; acc[7] += f3;
   }
 }
 
+// A lane's channels of a row's mean, written at `to`.
 template <int DT, int ODT>
-__device__ inline void store_mean(void* merged_v, size_t elem_off, const float (&acc)[Row<DT>::VEC], float inv) {
+__device__ inline void store_mean(void* to, const float (&acc)[Row<DT>::VEC], float inv) {
   constexpr int VEC = Row<DT>::VEC;
   if (ODT == 0) {
-    float* o = reinterpret_cast<float*>(merged_v) + elem_off;
+    float* o = static_cast<float*>(to);
 #pragma unroll
     for (int v = 0; v < VEC; v += 4)
       store_once(reinterpret_cast<float4*>(o + v),
                  make_float4(acc[v] * inv, acc[v + 1] * inv, acc[v + 2] * inv, acc[v + 3] * inv));
   } else {
-    uint16_t* o = reinterpret_cast<uint16_t*>(merged_v) + elem_off;
     uint32_t w[VEC / 2];
 #pragma unroll
     for (int v = 0; v < VEC; v += 2)
       w[v / 2] = ODT == 1 ? pack2_bf16(acc[v] * inv, acc[v + 1] * inv) : pack2_f16(acc[v] * inv, acc[v + 1] * inv);
     if (VEC == 8)
-      store_once(reinterpret_cast<uint4*>(o), make_uint4(w[0], w[1], w[2 % (VEC / 2)], w[3 % (VEC / 2)]));
+      store_once(static_cast<uint4*>(to), make_uint4(w[0], w[1], w[2 % (VEC / 2)], w[3 % (VEC / 2)]));
     else
-      *reinterpret_cast<uint2*>(o) = make_uint2(w[0], w[1]);
+      *static_cast<uint2*>(to) = make_uint2(w[0], w[1]);
   }
 }
 
@@ -890,17 +898,19 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
   unsigned add_m = (unsigned)__ballot(use && !one), mean_m = (unsigned)__ballot(closes && fits);
   unsigned share_m = (unsigned)__ballot(share), end_m = share_m | (unsigned)__ballot(closes);
   int inv_v = (int)__float_as_uint(1.f / (float)members);
+  const int part_slot = beg_v < p0 ? 0 : 1;  // of a big cluster's share: which of the item's two
   if (chunk == 0) {
     if ((one || closes) && fits && a.counts) a.counts[row_v] = members;
     if (share) {
-      const int slot = beg_v < p0 ? 0 : 1;
-      a.bigw[item * 2 + slot] = members;
-      if (slot == 1) a.biglist[atomicAdd(a.bigcount, 1)] = make_int4(row_v, beg_v, end_v, 0);
+      a.bigw[item * 2 + part_slot] = members;
+      if (part_slot == 1) a.biglist[atomicAdd(a.bigcount, 1)] = make_int4(row_v, beg_v, end_v, 0);
     }
   }
   // The cluster still open after the item's last position (the item is full then) is followed to its end, kItem positions at
   // a time. All of these are described at once: the lanes after the item's, and the first ones once more for what lies
   // beyond the last lane.
+  constexpr size_t kOutBytes = ODT == 0 ? 4 : 2;
+  char* const merged = static_cast<char*>(a.merged);
   const int lastj = p1 - 1 - p0;
   const bool open = (add_m >> lastj & 1u) && !(end_m >> lastj & 1u);
   static_assert(kBig + kItem <= 2 * kWave, "an open cluster's positions");
@@ -916,9 +926,14 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
     open_inv = (int)__float_as_uint(1.f / (float)total);
     if (chunk == 0 && lane == 0 && open_row < a.capacity && a.counts) a.counts[open_row] = total;
   }
+  // Where each slot's data is and where its result goes, a lane each: per slot two scalar reads are left of either.
+  uint2 src = halves(slot_address<DT>(a.feats, a.nsum, g.D, sv));
+  uint2 dst = halves(share ? reinterpret_cast<uint64_t>(a.bigpart + ((size_t)item * 2 + part_slot) * g.D)
+                           : reinterpret_cast<uint64_t>(merged + (size_t)row_v * g.D * kOutBytes));
+  unsigned long long half1_m = __ballot(sv.kind == 1), half2_m = __ballot(sv.kind == 2);
   const int ch0 = chunk * g.cch + lane * VEC;
   const bool act = ch0 < g.D;
-  const int chl = act ? ch0 : 0;  // (a lane beyond the last channel reads the row's first channels and drops them)
+  const unsigned chl = act ? (unsigned)ch0 : 0u;  // (a lane beyond the last channel reads the row's first channels and drops them)
   float acc[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
@@ -928,13 +943,17 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
     // through, or it takes all of them out of the loop and runs out of scalar registers.)
     STTM_OPAQUE_S(use_m); STTM_OPAQUE_S(one_m); STTM_OPAQUE_S(add_m);
     STTM_OPAQUE_S(mean_m); STTM_OPAQUE_S(share_m); STTM_OPAQUE_S(end_m);
-    STTM_OPAQUE_V(sv.kind); STTM_OPAQUE_V(sv.idx); STTM_OPAQUE_V(row_v); STTM_OPAQUE_V(inv_v); STTM_OPAQUE_V(beg_v);
+    STTM_OPAQUE_V(src.x); STTM_OPAQUE_V(src.y); STTM_OPAQUE_V(dst.x); STTM_OPAQUE_V(dst.y); STTM_OPAQUE_V(inv_v);
+    unsigned half1 = (unsigned)half1_m, half2 = (unsigned)half2_m;
+    STTM_OPAQUE_S(half1); STTM_OPAQUE_S(half2);
+    const unsigned wide = half1 | half2;
     Raw raw[kItem];
 #pragma unroll
     for (int j = 0; j < kItem; ++j) {
       raw[j] = R::zero();
+      // (this is the last use of a feature row, and node sums are read once as well)
       if (use_m >> j & 1u)
-        raw[j] = load_slot<DT>(a.feats, a.nsum, g.D, chl, lane_value(sv.kind, j), lane_value(sv.idx, j));
+        raw[j] = load_once(reinterpret_cast<const Raw*>(lane_address(src, j) + (DT == 0 ? chl * 4u : chl * 2u << (wide >> j & 1u))));
     }
     // (all of them are waited for here: at each slot, behind a branch that may have stored a row, the compiler would wait
     // for that store as well)
@@ -945,18 +964,15 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
 #pragma unroll
     for (int j = 0; j < kItem; ++j) {
       if (one_m >> j & 1u) {
-        Raw* o = reinterpret_cast<Raw*>(reinterpret_cast<typename R::Elem*>(a.merged) + (size_t)lane_value(row_v, j) * g.D + chl);
-        if (act) store_once(o, raw[j]);
+        if (act) store_once(reinterpret_cast<Raw*>(lane_address(dst, j) + chl * (unsigned)kOutBytes), raw[j]);
       }
-      if (add_m >> j & 1u) acc_slot<DT>(raw[j], lane_value(sv.kind, j), acc);
+      if (add_m >> j & 1u) acc_slot<DT>(raw[j], half1 >> j & 1u, half2 >> j & 1u, acc);
       if (end_m >> j & 1u) {
         if (mean_m >> j & 1u) {
-          const size_t off = (size_t)lane_value(row_v, j) * g.D + ch0;
           const float inv = __uint_as_float((unsigned)lane_value(inv_v, j));
-          if (act) store_mean<DT, ODT>(a.merged, off, acc, inv);
+          if (act) store_mean<DT, ODT>(lane_address(dst, j) + chl * (unsigned)kOutBytes, acc, inv);
         } else if (share_m >> j & 1u) {
-          const int slot = lane_value(beg_v, j) < p0 ? 0 : 1;
-          if (act) store_partial<VEC>(a.bigpart + ((size_t)item * 2 + slot) * g.D + ch0, acc);
+          if (act) store_partial<VEC>(reinterpret_cast<float*>(lane_address(dst, j)) + chl, acc);
         }
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
@@ -969,11 +985,17 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
     end_m = left <= kItem ? 1u << (left - 1) : 0u;
     mean_m = open_row < a.capacity ? end_m : 0u;
     one_m = share_m = 0u;
-    row_v = open_row;
+    dst = halves(reinterpret_cast<uint64_t>(merged + (size_t)open_row * g.D * kOutBytes));
     inv_v = open_inv;
-    const bool past = base - p0 == kWave;  // (at most once: kBig + kItem positions)
-    sv.kind = past ? beyond.kind : __shfl_down(sv.kind, kItem, 64);
-    sv.idx = past ? beyond.idx : __shfl_down(sv.idx, kItem, 64);
+    if (base - p0 == kWave) {  // (at most once: kBig + kItem positions)
+      src = halves(slot_address<DT>(a.feats, a.nsum, g.D, beyond));
+      half1_m = __ballot(beyond.kind == 1);
+      half2_m = __ballot(beyond.kind == 2);
+    } else {
+      src = make_uint2((unsigned)__shfl_down((int)src.x, kItem, 64), (unsigned)__shfl_down((int)src.y, kItem, 64));
+      half1_m >>= kItem;
+      half2_m >>= kItem;
+    }
   }
 }
 
@@ -1042,7 +1064,7 @@ __global__ __launch_bounds__(64 * kBigSeg) void k_reduce_big_combine(Geo g, Gath
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] += segsum[u - 1][lane][v];
       if (chunk == 0 && lane == 0 && a.counts) a.counts[k] = total;
-      if (act) store_mean<DT, ODT>(a.merged, (size_t)k * g.D + ch0, acc, 1.f / (float)total);
+      if (act) store_mean<DT, ODT>(static_cast<char*>(a.merged) + ((size_t)k * g.D + ch0) * (ODT == 0 ? 4 : 2), acc, 1.f / (float)total);
     }
     __syncthreads();
   }
