@@ -1002,8 +1002,10 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
 // A fixed number of workgroups per chunk walks the list of big clusters. A cluster's partial sums are added up
 // in item order (the starting item's own, then the left-hand shares of the items after it): the run of items is
 // cut into kBigSeg contiguous segments, one wavefront each, eight loads in flight, and the segment sums are
-// added in segment order through LDS -- an order that depends on the list alone.
-constexpr int kBigGrid = 256;
+// added in segment order through LDS -- an order that depends on the list alone. (64 workgroups of a chunk instead of 256, of
+// which most found nothing to do: six clips with large clusters and fp32 rows 154.4 -> 149.4 us a pass, still ones without
+// the partition 144.6 -> 134.9, others the same; 32: 32 videos of 27x27 903 -> 913.)
+constexpr int kBigGrid = 64;
 constexpr int kBigBatch = 8;
 constexpr int kBigSeg = 8;
 
@@ -1015,9 +1017,11 @@ __global__ __launch_bounds__(64 * kBigSeg) void k_reduce_big_combine(Geo g, Gath
   const int seg = threadIdx.x >> 6, lane = threadIdx.x & 63, chunk = blockIdx.y;
   const int ch0 = chunk * g.cch + lane * VEC;
   const bool act = ch0 < g.D;
+  // (the first entry is requested with the list's length: behind the list's end it is stale and not used)
+  int4 en = a.biglist[blockIdx.x];
   const int nbig = *a.bigcount;
   for (int e = blockIdx.x; e < nbig; e += gridDim.x) {  // uniform over the workgroup
-    const int4 en = a.biglist[e];
+    if (e != (int)blockIdx.x) en = a.biglist[e];
     const int k = en.x, it0 = en.y / kItem, it1 = (en.z - 1) / kItem;
     // the partial sums of the cluster: number 0 is the starting item's (slot 1), number j > 0 item it0 + j's (slot 0)
     const int np = it1 - it0 + 1, per = (np + kBigSeg - 1) / kBigSeg;
