@@ -21,7 +21,7 @@ inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
   size_t part, nsum, nrm2, sim, m, sel_key_s, sel_w_s, sel_key_t, tau_s, tau_t, target_s, target_t, sel_s, sel_t, list_key_s, list_w_s, list_key_t, list_w_t, lvl,
       titems, tcount, pd_part, sig, e, parent, ptr_a, ptr_b;
-  size_t rank, key_a, val_a, key_b, val_b, order, orow, hist, tot, gsum, tile_roots, seg, kdev,
+  size_t rank, key, pair_a, pair_b, list, hist, tot, gsum, tile_roots, seg, kdev,
       bigpart, bigw, biglist, zpos, possum, poscnt;
   size_t total;
 };
@@ -60,12 +60,10 @@ size_t layout_reduce(const Geo& g, size_t off, Layout* lp) {
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
   const size_t N = g.N;
   l.rank = take(N * sizeof(int32_t));
-  l.key_a = take(N * sizeof(int32_t));
-  l.val_a = take(N * sizeof(int32_t));
-  l.key_b = take(N * sizeof(int32_t));
-  l.val_b = take(N * sizeof(int32_t));
-  l.order = take(N * sizeof(int32_t));
-  l.orow = take(N * sizeof(int32_t));
+  l.pair_a = take(N * sizeof(uint2));
+  l.key = l.pair_a;  // (read by the first pass, long before these pairs are written)
+  l.pair_b = take(N * sizeof(uint2));
+  l.list = take(N * sizeof(uint2));
   l.hist = take(reduce_hist_entries(g.N) * sizeof(int32_t));
   l.tot = take(2048 * sizeof(int32_t));
   l.gsum = take(reduce_gsum_entries() * sizeof(int32_t));
@@ -251,12 +249,10 @@ ReduceBuffers reduce_buffers(char* base, const Layout& l) {
   ReduceBuffers rb;
   auto i32 = [&](size_t off) { return reinterpret_cast<int32_t*>(base + off); };
   rb.rank = i32(l.rank);
-  rb.key_a = i32(l.key_a);
-  rb.val_a = i32(l.val_a);
-  rb.key_b = i32(l.key_b);
-  rb.val_b = i32(l.val_b);
-  rb.order = i32(l.order);
-  rb.orow = i32(l.orow);
+  rb.key = i32(l.key);
+  rb.pair_a = reinterpret_cast<uint2*>(base + l.pair_a);
+  rb.pair_b = reinterpret_cast<uint2*>(base + l.pair_b);
+  rb.list = reinterpret_cast<uint2*>(base + l.list);
   rb.hist = i32(l.hist);
   rb.tot = i32(l.tot);
   rb.gsum = i32(l.gsum);
@@ -821,7 +817,7 @@ int sttm_positions(sttm_ctx* ctx, const int32_t* cluster_ids_dev, const int32_t*
   ReduceBuffers rb;
   std::memset(&rb, 0, sizeof rb);
   rb.rank = at<int32_t>(ctx, ctx->lay.rank);
-  rb.order = at<int32_t>(ctx, ctx->lay.order);
+  rb.list = at<uint2>(ctx, ctx->lay.list);
   rb.seg = at<int32_t>(ctx, ctx->lay.seg);
   rb.kdev = at<int32_t>(ctx, ctx->lay.kdev);
   rb.zpos = at<int32_t>(ctx, ctx->lay.zpos);

@@ -983,12 +983,10 @@ void launch_node_levels(const Geo& g, const int32_t* node_map, uint8_t* node_lev
 
 struct ReduceBuffers {
   int32_t* rank;        // [N]   exclusive count of roots before every cell
-  int32_t* key_a;       // [N] sort ping
-  int32_t* val_a;       // [N]
-  int32_t* key_b;       // [N] sort pong
-  int32_t* val_b;       // [N]
-  int32_t* order;       // [N] sorted element list (live part first)
-  int32_t* orow;        // [N] output row of every list position
+  int32_t* key;         // [N] keys of the cells, for the first pass
+  uint2* pair_a;        // [N] (key, cell): sort ping; `key` is its first half
+  uint2* pair_b;        // [N] sort pong
+  uint2* list;          // [N] the sorted elements: (cell, output row)
   int32_t* hist;        // [tiles][digits] radix histogram of the running pass
   int32_t* tot;         // [digits] column totals (very large inputs)
   int32_t* gsum;        // [groups of tiles][digits] partial column sums (medium inputs)

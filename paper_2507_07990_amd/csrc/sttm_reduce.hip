@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_reduce_prep(Geo g, const int32
 
 // Digit histogram per tile of the (compacted) keys of a later pass; tiles beyond the list write zeros.
 __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const int32_t* __restrict__ kdev, int shift, int dbits,
-                                                            const int32_t* __restrict__ keys,
+                                                            const uint2* __restrict__ pairs,
                                                             int32_t* __restrict__ hist) {
   __shared__ int cnt[kMaxDigits];
   const int DIG = 1 << dbits, b = blockIdx.x, tid = threadIdx.x, n = kdev[1];
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_hist(const int32_t* __res
 #pragma unroll
   for (int j = 0; j < kSortPer; ++j) {
     const int i = b * kSortTile + j * kSortThreads + tid;
-    if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & (DIG - 1)], 1);
+    if (i < n) atomicAdd(&cnt[((int)pairs[i].x >> shift) & (DIG - 1)], 1);
   }
   __syncthreads();
   for (int d = tid; d < DIG; d += kSortThreads) hist[(size_t)b * DIG + d] = cnt[d];
@@ -270,10 +270,9 @@ __device__ inline void sort_add_rows(const int32_t* __restrict__ table, int r0, 
 struct SortArgs {
   int n, shift, dbits, nb, mode;  // mode: how the start offsets are found (see kDirectTiles)
   const int32_t* gsum;
-  const int32_t* keys;
-  const int32_t* vals;
-  int32_t* keys_out;
-  int32_t* vals_out;  // LAST: the sorted element list
+  const int32_t* keys;  // FIRST
+  const uint2* in;      // else: (key, cell)
+  uint2* out;           // LAST: the sorted element list, (cell, output row)
   const int32_t* hist;
   const int32_t* tot;
   // FIRST
@@ -287,7 +286,6 @@ struct SortArgs {
   int64_t capacity;
   int per_video, B;
   // LAST
-  int32_t* orow;
   int32_t* seg;
 };
 
@@ -308,8 +306,14 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(SortArgs a) {
 #pragma unroll
   for (int r = 0; r < kSortPer; ++r) {
     const int i = e0 + r * 64 + lane, j = min(i, a.n - 1);
-    key[r] = a.keys[j];
-    val[r] = FIRST ? i : a.vals[j];
+    if (FIRST) {
+      key[r] = a.keys[j];
+      val[r] = i;
+    } else {
+      const uint2 e = a.in[j];
+      key[r] = (int)e.x;
+      val[r] = (int)e.y;
+    }
     rk0[r] = FIRST ? a.rank[j] : 0;
     cid[r] = FIRST ? a.cluster_ids[j] : 0;
   }
@@ -454,13 +458,9 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(SortArgs a) {
     const int digit = (key[r] >> a.shift) & (DIG - 1), half = (digit & 1) * 16;
     if (key[r] >= 0) {
       const int dst = s_base[digit] + (int)((mycur[digit >> 1] >> half) & 0xffffu) + __popcll(same[r] & below);
-      a.vals_out[dst] = val[r];
-      if (LAST) {
-        a.orow[dst] = aux[r];
-        if (key[r] == val[r]) a.seg[aux[r]] = dst;
-      } else {
-        a.keys_out[dst] = key[r];
-      }
+      // (in one piece: what bounds this pass on a large input is lines that are written eight bytes at a time)
+      a.out[dst] = LAST ? make_uint2((unsigned)val[r], (unsigned)aux[r]) : make_uint2((unsigned)key[r], (unsigned)val[r]);
+      if (LAST && key[r] == val[r]) a.seg[aux[r]] = dst;
     }
     wave_lds_fence();
     if (r + 1 < kSortPer && key[r] >= 0 && ((same[r] >> lane) >> 1) == 0)  // highest lane of its digit group advances the cursor
@@ -512,8 +512,7 @@ struct ListArgs {
   int64_t* offsets;
   int64_t capacity;
   int per_video, B;
-  int32_t* order;
-  int32_t* orow;
+  uint2* list;
   int32_t* seg;
 };
 
@@ -697,8 +696,7 @@ __global__ __launch_bounds__(THREADS) void k_list_small(ListArgs a) {
     if (id >= 0) {
       const unsigned ex = *word(id);
       const int dst = (int)((s_first[id >> 6] & 0xffffu) + (low(id) ? ex & 0xffffu : ex >> 16)) + place;
-      a.order[dst] = own;
-      a.orow[dst] = rank_of(id);
+      a.list[dst] = make_uint2((unsigned)own, (unsigned)rank_of(id));
       if (id == own) a.seg[rk] = dst;
     }
   }
@@ -828,8 +826,7 @@ struct GatherArgs {
   const float* nsum;
   const int32_t* node_map;  // the stage-1 partition, or both NULL when every slot is a cell
   const uint8_t* lvl;
-  const int32_t* order;
-  const int32_t* orow;
+  const uint2* list;
   const int32_t* seg;
   const int32_t* kdev;
   int64_t capacity;
@@ -865,8 +862,9 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
   const int p0 = item * kItem, pl = p0 + lane;
   int cell_l = 0, rank_l = 0;
   if (pl < g.N) {
-    cell_l = a.order[pl];
-    if (lane < kItem) rank_l = a.orow[pl];  // clusters are listed in ascending id; the output row may differ
+    const uint2 e = a.list[pl];
+    cell_l = (int)e.x;
+    rank_l = (int)e.y;  // clusters are listed in ascending id; the output row may differ
   }
   const int M = a.kdev[1];
   const int p1 = min(p0 + kItem, M);
@@ -920,7 +918,7 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
     open_row = lane_value(row_v, kItem - 1);
     open_end = lane_value(end_v, kItem - 1);
     if (lane >= kItem && pl < open_end) sv = describe<DT>(g, a.node_map, a.lvl, cell_l);
-    if (pl + kWave < open_end) beyond = describe<DT>(g, a.node_map, a.lvl, a.order[pl + kWave]);
+    if (pl + kWave < open_end) beyond = describe<DT>(g, a.node_map, a.lvl, (int)a.list[pl + kWave].x);
     const unsigned later = wave_inclusive((unsigned)((lane >= kItem ? sv.weight : 0) + beyond.weight), lane);
     const int total = lane_value(members, kItem - 1) + lane_value((int)later, kWave - 1);
     open_inv = (int)__float_as_uint(1.f / (float)total);
@@ -1172,7 +1170,7 @@ __global__ __launch_bounds__(256) void k_positions_cells(Geo g, const int32_t* _
 }
 
 __global__ __launch_bounds__(256) void k_positions_rows(Geo g, const int32_t* __restrict__ kdev,
-                                                        const int32_t* __restrict__ order,
+                                                        const uint2* __restrict__ list,
                                                         const int32_t* __restrict__ seg,
                                                         const int32_t* __restrict__ zpos,
                                                         const uint8_t* __restrict__ node_level,
@@ -1185,7 +1183,7 @@ __global__ __launch_bounds__(256) void k_positions_rows(Geo g, const int32_t* __
                                                         int32_t* __restrict__ root_tyxl) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;  // cluster rank (ascending id)
   if (r >= kdev[0]) return;
-  const int root = order[seg[r]];  // the root is the first element of its cluster's list
+  const int root = (int)list[seg[r]].x;  // the root is the first element of its cluster's list
   const int row = zpos ? zpos[r] : r;
   if (row >= capacity) return;
   const int per_video = g.T * g.HW, b = root / per_video, loc = root - b * per_video;
@@ -1212,7 +1210,7 @@ void launch_positions(const Geo& g, const int32_t* cluster_ids, const int32_t* n
     hipLaunchKernelGGL(k_positions_cells, grid, block, 0, s, g, cluster_ids, node_level ? node_map : nullptr,
                        node_level, rb.rank, possum, poscnt);
   }
-  hipLaunchKernelGGL(k_positions_rows, grid, block, 0, s, g, rb.kdev, rb.order, rb.seg, zscan ? rb.zpos : nullptr,
+  hipLaunchKernelGGL(k_positions_rows, grid, block, 0, s, g, rb.kdev, rb.list, rb.seg, zscan ? rb.zpos : nullptr,
                      node_level, offsets, possum, poscnt, capacity, survived, reassigned, merged_pos, root_tyxl);
 }
 
@@ -1232,7 +1230,7 @@ void launch_reduce_prepare(const Geo& g, const int32_t* cluster_ids, const int32
     a.rank = rb.rank; a.kdev = rb.kdev; a.host_k = rb.host_k;
     a.out_ids = zscan ? nullptr : out_ids; a.offsets = offsets; a.capacity = capacity;
     a.per_video = g.T * g.HW; a.B = g.B;
-    a.order = rb.order; a.orow = rb.orow; a.seg = rb.seg;
+    a.list = rb.list; a.seg = rb.seg;
     const dim3 slices((N + kListSlice - 1) / kListSlice);
     const size_t lds = (size_t)a.words * sizeof(unsigned);
     if (N <= kListTiny)
@@ -1249,15 +1247,13 @@ void launch_reduce_prepare(const Geo& g, const int32_t* cluster_ids, const int32
   const int DIG = 1 << pl.dbits;
   const dim3 grid(pl.nb), block(kSortThreads);
   hipLaunchKernelGGL(k_reduce_prep, grid, dim3(kPrepThreads), 0, s, g, cluster_ids, node_map, node_level, pl.dbits,
-                     rb.key_a, rb.rank, rb.tile_roots, rb.hist, rb.kdev + 2);
-  const int32_t* kin = rb.key_a;
-  const int32_t* vin = nullptr;
-  int32_t* kout = rb.key_b;
-  int32_t* vout = rb.val_b;
+                     rb.key, rb.rank, rb.tile_roots, rb.hist, rb.kdev + 2);
+  const uint2* in = nullptr;
+  uint2* out = rb.pair_b;
   for (int pass = 0; pass < pl.passes; ++pass) {
     const bool first = pass == 0, last = pass == pl.passes - 1;
     if (!first)
-      hipLaunchKernelGGL(k_sort_hist, grid, block, 0, s, rb.kdev, pass * pl.dbits, pl.dbits, kin, rb.hist);
+      hipLaunchKernelGGL(k_sort_hist, grid, block, 0, s, rb.kdev, pass * pl.dbits, pl.dbits, in, rb.hist);
     if (pl.mode == 2)
       hipLaunchKernelGGL(k_sort_colscan, dim3((DIG + 255) / 256), dim3(256), 0, s, pl.nb, DIG, rb.hist, rb.tot);
     else if (pl.mode == 1)
@@ -1265,18 +1261,17 @@ void launch_reduce_prepare(const Geo& g, const int32_t* cluster_ids, const int32
                          s, pl.nb, DIG, rb.hist, rb.gsum);
     SortArgs a;
     a.n = N; a.shift = pass * pl.dbits; a.dbits = pl.dbits; a.nb = pl.nb; a.mode = pl.mode; a.gsum = rb.gsum;
-    a.keys = kin; a.vals = vin; a.keys_out = kout; a.vals_out = last ? rb.order : vout;
+    a.keys = rb.key; a.in = in; a.out = last ? rb.list : out;
     a.hist = rb.hist; a.tot = rb.tot;
     a.cluster_ids = cluster_ids; a.rank = rb.rank; a.tile_roots = rb.tile_roots;
     a.kdev = rb.kdev; a.host_k = rb.host_k; a.out_ids = zscan ? nullptr : out_ids; a.offsets = offsets; a.capacity = capacity;
     a.per_video = g.T * g.HW; a.B = g.B;
-    a.orow = rb.orow; a.seg = rb.seg;
+    a.seg = rb.seg;
     if (first) hipLaunchKernelGGL((k_sort_pass<true, false>), grid, block, 0, s, a);
     else if (last) hipLaunchKernelGGL((k_sort_pass<false, true>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_sort_pass<false, false>), grid, block, 0, s, a);
-    kin = kout;
-    vin = vout;
-    if (kout == rb.key_b) { kout = rb.key_a; vout = rb.val_a; } else { kout = rb.key_b; vout = rb.val_b; }
+    in = out;
+    out = out == rb.pair_b ? rb.pair_a : rb.pair_b;
   }
   if (zscan)
     hipLaunchKernelGGL(k_zorder, dim3(g.F), dim3(256), 0, s, g, cluster_ids, rb.rank, capacity, rb.zpos, out_ids);
@@ -1286,7 +1281,7 @@ static GatherArgs gather_args(const void* feats, const float* nsum, const int32_
                               const uint8_t* node_level, int64_t capacity, void* merged, int32_t* counts,
                               const ReduceBuffers& rb, bool zscan) {
   GatherArgs a;
-  a.feats = feats; a.nsum = nsum; a.node_map = node_map; a.lvl = node_level; a.order = rb.order; a.orow = rb.orow;
+  a.feats = feats; a.nsum = nsum; a.node_map = node_map; a.lvl = node_level; a.list = rb.list;
   a.seg = rb.seg; a.kdev = rb.kdev; a.capacity = capacity; a.merged = merged; a.counts = counts;
   a.bigpart = rb.bigpart; a.bigw = rb.bigw;
   a.biglist = reinterpret_cast<int4*>(rb.biglist); a.bigcount = rb.kdev + 2;
