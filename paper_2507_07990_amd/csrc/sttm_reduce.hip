@@ -961,16 +961,19 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
     }
 #pragma unroll
     for (int j = 0; j < kItem; ++j) {
+      // (every lane takes part where another lane's address is read, also those beyond the last channel)
       if (one_m >> j & 1u) {
-        if (act) store_once(reinterpret_cast<Raw*>(lane_address(dst, j) + chl * (unsigned)kOutBytes), raw[j]);
+        char* const to = lane_address(dst, j);
+        if (act) store_once(reinterpret_cast<Raw*>(to + chl * (unsigned)kOutBytes), raw[j]);
       }
       if (add_m >> j & 1u) acc_slot<DT>(raw[j], half1 >> j & 1u, half2 >> j & 1u, acc);
       if (end_m >> j & 1u) {
+        char* const to = lane_address(dst, j);
         if (mean_m >> j & 1u) {
           const float inv = __uint_as_float((unsigned)lane_value(inv_v, j));
-          if (act) store_mean<DT, ODT>(lane_address(dst, j) + chl * (unsigned)kOutBytes, acc, inv);
+          if (act) store_mean<DT, ODT>(to + chl * (unsigned)kOutBytes, acc, inv);
         } else if (share_m >> j & 1u) {
-          if (act) store_partial<VEC>(reinterpret_cast<float*>(lane_address(dst, j)) + chl, acc);
+          if (act) store_partial<VEC>(reinterpret_cast<float*>(to) + chl, acc);
         }
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
