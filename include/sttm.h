@@ -93,7 +93,7 @@ typedef enum {
 
 /* Creates a context on HIP device `device`. `hip_stream` is a hipStream_t owned by the caller (NULL = the
  * default stream); every kernel and copy of this context is enqueued on it. Host memory only is allocated: besides the
- * context itself a pinned block of 8 KB that kernels write thresholds and row counts for the caller into. A destroyed
+ * context itself a pinned block of 4 KB that kernels write thresholds and row counts for the caller into. A destroyed
  * context's block is kept for the next one (up to 64 per device): sttm_destroy waits for nothing, and neither call ends
  * a stream capture that runs meanwhile. */
 int sttm_create(sttm_ctx** out, int device, void* hip_stream);

@@ -2,7 +2,6 @@
 #include "sttm_dev.h"
 #include "../../include/sttm.h"
 
-#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -149,15 +148,14 @@ void* static_scratch_on(int device, hipError_t* err) {
 constexpr int kHostTaus = 1024;
 struct HostOut {
   int32_t k;
-  uint32_t calls;             // searches whose values were handed back through this block
-  uint64_t tau[kHostTaus];    // a threshold's bits, and above them the number of the search that found it
+  float tau[kHostTaus];
   HostOut* next;  // in the list of idle blocks
 };
 
 namespace {
 // The blocks of contexts that are gone, kept for later contexts of the same device: a free would end a stream capture
 // that runs meanwhile and waits for the work of every other context, and a context may go at any time (a garbage
-// collection). At most kIdleBlocks (512 KB) are kept per device; more are freed.
+// collection). At most kIdleBlocks (256 KB) are kept per device; more are freed.
 constexpr int kIdleBlocks = 64;
 std::mutex g_idle_mutex;
 HostOut* g_idle[kMaxDevices] = {};
@@ -186,10 +184,7 @@ HostOut* take_host_out(int device) {
   }
   RelaxedCapture relaxed;
   void* p = nullptr;
-  if (relaxed.ok && hipHostMalloc(&p, sizeof(HostOut), hipHostMallocDefault) == hipSuccess) {
-    std::memset(p, 0, sizeof(HostOut));
-    return static_cast<HostOut*>(p);
-  }
+  if (relaxed.ok && hipHostMalloc(&p, sizeof(HostOut), hipHostMallocDefault) == hipSuccess) return static_cast<HostOut*>(p);
   (void)hipGetLastError();
   return nullptr;
 }
@@ -393,19 +388,6 @@ int run_temporal_stats(sttm_ctx* c, const void* feats, const int32_t* node_map, 
     c->node_map_temporal = node_map;
   }
   return rc;
-}
-
-// Waits until the search's kernel, the last one on the stream, has written all of its values, whose number they carry; what
-// was enqueued before it is complete then. 5 us less than a synchronisation of the stream, which sends a packet of its own and
-// waits for that: a pass with both values handed back 154.8 -> 145.0 us (96 frames of 11x19, fp32), 91.7 -> 89.6 (one image).
-// False after kArrivalWait (a long queue, a capture in progress, a fault): the caller synchronises the stream then.
-constexpr std::chrono::microseconds kArrivalWait{200};
-bool arrived(const uint64_t* values, int n, uint32_t call) {
-  const auto until = std::chrono::steady_clock::now() + kArrivalWait;
-  for (int i = 0; i < n; ++i)
-    while ((uint32_t)(__atomic_load_n(values + i, __ATOMIC_ACQUIRE) >> 32) != call)
-      if (std::chrono::steady_clock::now() > until) return false;
-  return true;
 }
 
 int check_feats(sttm_ctx* c, const void* feats) {
@@ -659,11 +641,8 @@ int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_ho
   float* tau_dev = at<float>(ctx, spatial ? ctx->lay.tau_s : ctx->lay.tau_t);
   // When the caller does not ask for the value, the search is carried out (or, of a large input, finished) by the kernel
   // that uses the threshold; otherwise by a launch of its own.
-  uint64_t* host_tau = tau_out_host && ctx->host_out && g.B <= kHostTaus ? ctx->host_out->tau : nullptr;
-  if (host_tau) {
-    ctx->host_out_busy = true;
-    ++ctx->host_out->calls;
-  }
+  float* host_tau = tau_out_host && ctx->host_out && g.B <= kHostTaus ? ctx->host_out->tau : nullptr;
+  if (host_tau) ctx->host_out_busy = true;
   SelSearch search;
   if (spatial) {
     search = launch_select_spatial(g, at<uint32_t>(ctx, ctx->lay.sel_key_s), at<uint8_t>(ctx, ctx->lay.sel_w_s), target_dev,
@@ -678,19 +657,16 @@ int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_ho
     ctx->search_t = search;
     ctx->tau_t_pending = tau_out_host == nullptr;
   }
-  if (tau_out_host) launch_select_tau(g, search, tau_dev, host_tau, host_tau ? ctx->host_out->calls : 0u, ctx->stream);
+  if (tau_out_host) launch_select_tau(g, search, tau_dev, host_tau, ctx->stream);
   rc = after_launch(ctx);
   if (rc) return rc;
   if (stage == STTM_STAGE_SPATIAL) ctx->have_tau_s = true; else ctx->have_tau_t = true;
   if (tau_out_host) {
     if (!host_tau)
       STTM_HIP(ctx, hipMemcpyAsync(tau_out_host, tau_dev, g.B * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
-    if (!host_tau || !arrived(host_tau, g.B, ctx->host_out->calls)) STTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    STTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
     ctx->host_out_busy = false;
-    for (int b = 0; host_tau && b < g.B; ++b) {
-      const uint32_t bits = (uint32_t)host_tau[b];
-      std::memcpy(tau_out_host + b, &bits, sizeof bits);
-    }
+    if (host_tau) std::memcpy(tau_out_host, host_tau, g.B * sizeof(float));
   }
   return STTM_OK;
 }

@@ -285,15 +285,6 @@ template <class T> inline T load_once(const T* p) { return *p; }
 template <class T> inline void store_once(T* p, const T& v) { *p = v; }
 #endif
 
-// Eight bytes in one piece to memory that the host reads while the kernel may still run.
-__device__ inline void store_for_host(uint64_t* p, uint64_t v) {
-#ifndef STTM_HOST_EMULATION
-  __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-#else
-  *p = v;
-#endif
-}
-
 // A stretch of global memory with its length: a load beyond it gives zeros and fetches nothing, a store beyond it is
 // dropped, by the hardware's own check of every access against the length. Address = base + uniform + lane.
 #ifndef STTM_HOST_EMULATION
@@ -931,9 +922,8 @@ SelSearch launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_
 SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
                                  SelState* state, uint32_t* list_key, uint8_t* list_w, hipStream_t s);
 // Carries a search out now, for a caller who wants the thresholds back.
-// `host_tau` (may be NULL): host memory the device can write, which receives the thresholds as well, each in one piece with
-// the call's number above it.
-void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, uint64_t* host_tau, unsigned call, hipStream_t s);
+// `host_tau` (may be NULL): host memory the device can write, which receives the thresholds as well.
+void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s);
 // Elements per video of a spatial / temporal search: what its list has room for.
 int select_elements(const Geo& g, bool spatial);
 inline size_t select_state_bytes(int B) { return (size_t)B * sizeof(SelState); }

@@ -1238,14 +1238,14 @@ __global__ __launch_bounds__(kPassThreads) void k_select_piece(Geo g, const uint
              list_key, list_w);
 }
 
-// The whole search as a launch of its own (when the caller wants the threshold back). `call`: its number, see the header.
+// The whole search as a launch of its own (when the caller wants the threshold back).
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_select_tau(Geo g, SelSearch search, float* __restrict__ tau,
-                                                        uint64_t* __restrict__ host_tau, unsigned call) {
+                                                        float* __restrict__ host_tau) {
   const float t = sel_threshold<THREADS>(g, search, blockIdx.x);
   if (threadIdx.x == 0) {
     tau[blockIdx.x] = t;
-    if (host_tau) store_for_host(host_tau + blockIdx.x, (uint64_t)call << 32 | __float_as_uint(t));
+    if (host_tau) host_tau[blockIdx.x] = t;
   }
 }
 
@@ -1285,11 +1285,11 @@ SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const ui
   return launch_select(g, keys, nullptr, select_elements(g, false), target, 0, node_map, state, list_key, list_w, s);
 }
 
-void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, uint64_t* host_tau, unsigned call, hipStream_t s) {
+void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s) {
   if (search.listed || search.per_video <= kSelFewKeys)
-    hipLaunchKernelGGL(k_select_tau<kSelThreads>, dim3(g.B), dim3(kSelThreads), 0, s, g, search, tau, host_tau, call);
+    hipLaunchKernelGGL(k_select_tau<kSelThreads>, dim3(g.B), dim3(kSelThreads), 0, s, g, search, tau, host_tau);
   else
-    hipLaunchKernelGGL(k_select_tau<kSelThreadsWhole>, dim3(g.B), dim3(kSelThreadsWhole), 0, s, g, search, tau, host_tau, call);
+    hipLaunchKernelGGL(k_select_tau<kSelThreadsWhole>, dim3(g.B), dim3(kSelThreadsWhole), 0, s, g, search, tau, host_tau);
 }
 
 }  // namespace sttm
