@@ -21,7 +21,7 @@
  *     never allocates or frees device memory: all intermediate tables live in a caller-provided workspace.
  *   - "host" pointers are ordinary host memory, read or written before the call returns.
  *   - all work is enqueued on the context's stream; calls return before the GPU finishes unless they
- *     hand a value back through a host pointer (documented per call), in which case they wait for it.
+ *     hand a value back through a host pointer (documented per call), in which case they synchronise the stream.
  *   - in a stream capture, explicit thresholds of up to 32 videos are recorded by value. With more videos, and for the
  *     targets of a budget search, the recorded copy reads a buffer of the context again at every replay: such a graph
  *     is replayed only while the context lives and has not been given other thresholds (targets) since.
@@ -175,8 +175,7 @@ int sttm_temporal_merge(sttm_ctx* ctx, const void* feats_dev, const int32_t* nod
  * chosen is the midpoint of the last interval between consecutive distinct v on which K <= target (1 if K never
  * exceeds it, -2 if even merging everything exceeds it). Requires the stage's statistics in the workspace; stores
  * the thresholds on the device for the following sttm_spatial_quadtree / sttm_temporal_merge call with NULL
- * thresholds. tau_out: host array [B] or NULL; when non-NULL the call waits until the values, and with them everything
- * enqueued on the stream before, are there (by their own arrival, or by synchronising the stream), and copies them out
+ * thresholds. tau_out: host array [B] or NULL; when non-NULL the stream is synchronised and the values copied out
  * (with NULL the rest of the search, for a video of few elements all of it, is left to that following call, which saves a
  * launch). */
 int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_host, float* tau_out_host);
