@@ -313,6 +313,7 @@ __device__ __forceinline__ void window_store(Window w, unsigned lane_off, unsign
 #else
 struct Window { char* base; unsigned bytes; };
 inline Window make_window(const void* base, unsigned bytes) {
+  if (base && reinterpret_cast<uintptr_t>(base) < 65536) hip_emul::g_off_null = true;  // (no memory there: NULL and an offset)
   return {static_cast<char*>(const_cast<void*>(base)), bytes};
 }
 template <class Raw>
@@ -668,7 +669,8 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
   __shared__ int s_count;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const Window keys = make_window(q.keys + (size_t)b * q.per_video, (unsigned)q.per_video * 4u);
-  const Window weights = make_window(q.weights + (size_t)b * q.per_video, q.weights ? (unsigned)q.per_video : 0u);
+  const Window weights = make_window(q.weights ? q.weights + (size_t)b * q.per_video : nullptr,
+                                     q.weights ? (unsigned)q.per_video : 0u);
   const unsigned plain = q.weights ? 0u : 1u;
   // keys j0 + tid, j0 + tid + THREADS, ... (0 behind the last one) with their weights
   auto load = [&](uint32_t (&k)[kBatch], unsigned (&w)[kBatch], int j0) {

@@ -11,6 +11,7 @@ alignas(16) float g_dynamic_lds[40960];  // 160 KB, the LDS of one CU
 Pinned g_pinned;
 int g_memsets = 0;
 bool g_recording = false;
+bool g_off_null = false;
 std::vector<std::function<void()>> g_recorded;
 thread_local hipStreamCaptureMode t_capture_mode = hipStreamCaptureModeGlobal;
 
@@ -85,3 +86,4 @@ extern "C" int hip_emul_replay() {
 }
 
 extern "C" int hip_emul_memsets() { return hip_emul::g_memsets; }  // hipMemsetAsync calls so far
+extern "C" int hip_emul_off_null() { return hip_emul::g_off_null; }      // a window of memory has begun at NULL plus an offset

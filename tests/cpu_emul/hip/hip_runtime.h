@@ -67,6 +67,7 @@ void note_launch(const char* kernel, dim3 grid);  // what hip_emul_last_grid (em
 // hip_emul_replay in emul.cpp).
 extern bool g_recording;
 extern std::vector<std::function<void()>> g_recorded;
+extern bool g_off_null;  // a kernel has worked out an address from NULL
 }  // namespace hip_emul
 
 #define threadIdx (hip_emul::t_threadIdx)

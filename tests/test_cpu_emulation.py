@@ -79,6 +79,15 @@ def test_emulated_budget_threshold_left_to_the_consumer_kernels(emul):
     np.testing.assert_array_equal(a.merged, b.merged)
 
 
+def test_emulated_searches_without_weights_work_out_no_address_of_them(emul):
+    """The elements of a temporal search have no weights: there is no table, and nothing is added to its absent address for
+    the videos after the first."""
+    run_cpu, _ = emul
+    lib = run_cpu.load()
+    run_cpu.run_cpu(wl.generate(_variant(91, 3, 3, 5, 6, 24, "bf16")), keep=0.5, lib=lib)
+    assert not lib.hip_emul_off_null()
+
+
 @pytest.mark.parametrize("kw", [dict(keep=0.5), dict(tau_s=0.95, tau_t=0.6)])
 def test_emulated_temporal_pass_without_the_cell_dot_products(emul, kw):
     """With the option off the temporal pass computes every pair itself: same partition and clusters as with the
