@@ -4,6 +4,7 @@
 #include <hip/hip_fp16.h>
 #include <stddef.h>
 #include <stdint.h>
+#include <type_traits>
 
 // Dynamic LDS of a kernel. (The second form serves the host-thread build used by the CPU tests.)
 #ifndef STTM_HOST_EMULATION
@@ -642,6 +643,21 @@ struct SelSearch {
   const int32_t* node_map; // temporal: the kept nodes of the video's first frame are counted here
 };
 
+// How a kernel comes by its threshold, which the host knows when it launches it: named by the caller or found by an earlier
+// launch, by a search among listed elements, or by one that looks through all keys. Each is an instance of its own: with
+// all three in one, k_temporal_parent of a frame of 169 cells was 12.8 KB of code and 90 registers, also where nothing was
+// searched; now 1.9 KB and 13 registers, 7.1 and 27, 12.2 and 88.
+enum { kTauKnown, kTauListed, kTauLook };
+inline int tau_kind(const SelSearch& pending) { return !pending.states ? kTauKnown : pending.listed ? kTauListed : kTauLook; }
+// f(kind), with the kind as a constant
+template <class F>
+inline void with_tau_kind(const SelSearch& pending, F f) {
+  const int kind = tau_kind(pending);
+  if (kind == kTauKnown) f(std::integral_constant<int, kTauKnown>());
+  else if (kind == kTauListed) f(std::integral_constant<int, kTauListed>());
+  else f(std::integral_constant<int, kTauLook>());
+}
+
 // Elements a search keeps in LDS; of more it reads the keys again in every round.
 #ifndef STTM_SEL_LIST
 #define STTM_SEL_LIST 4096
@@ -658,8 +674,9 @@ constexpr int kSelList = STTM_SEL_LIST;
 // answered, 2500 for the bin, 3000 for a look at 8192 keys, 600 to 5000 for the elements. So what is executed is kept short,
 // and what the caller reads for its own work is requested before.
 constexpr int kSelFew = kSelList < 256 ? kSelList : 256;
-template <int THREADS>
+template <int THREADS, int KIND>
 __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
+  static_assert(KIND != kTauKnown, "a search");
   __shared__ uint32_t s_key[kSelList + kWave];  // (the last ones: where what is not in the bin goes)
   __shared__ uint8_t s_w[kSelList + kWave];
   constexpr int kPieces = 256, kBatch = 8;
@@ -686,8 +703,8 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
   }
   SelFound fd;
   int n = q.per_video;
-  unsigned first = 0, past = 0xffffffffu;  // the bin: what it makes of the values in it (see sel_first); of a list, all
-  if (q.listed) {
+  unsigned first = 0, past = 0;  // of all keys, the bin: what it makes of the values in it (see sel_first)
+  if constexpr (KIND == kTauListed) {
     // (a list is short as a rule: the first keys are requested with its length)
     uint32_t key = (uint32_t)window_load_i32(keys, (unsigned)tid * 4u, 0u);
     unsigned weight = (unsigned)window_load_u8(weights, (unsigned)tid, 0u);
@@ -822,7 +839,8 @@ __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {
           load(k, w, j0);
 #pragma unroll
           for (int u = 0; u < kBatch; ++u)
-            if (j0 + u * THREADS + tid < n && k[u] && sel_distance(k[u]) - first < past - first) use(k[u], w[u]);
+            if (j0 + u * THREADS + tid < n && (KIND == kTauListed || (k[u] && sel_distance(k[u]) - first < past - first)))
+              use(k[u], w[u]);
         }
       }
     };

@@ -1,7 +1,6 @@
 // Spatial stage (Sec. 3.2): pyramid sums, squared norms, parent-child cosine similarities, the
 // coarse-to-fine decision, and the budget-driven threshold for it.
 #include "sttm_dev.h"
-#include <type_traits>
 
 namespace sttm {
 
@@ -997,7 +996,7 @@ void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float
 constexpr int kDecideWide = 65536, kDecideThreads = 512;
 // A search that looks through more keys than this has larger workgroups as well.
 constexpr int kSelFewKeys = 2048;
-template <int THREADS>
+template <int THREADS, int KIND>
 __global__ __launch_bounds__(THREADS) void k_spatial_decide(Geo g, const float* __restrict__ m,
                                                                 float* __restrict__ tau, SelSearch pending,
                                                                 int32_t* __restrict__ node_map,
@@ -1013,8 +1012,8 @@ __global__ __launch_bounds__(THREADS) void k_spatial_decide(Geo g, const float* 
   for (int l = 1; l < kMaxLevels; ++l)  // (no branches: of a level above the roots the roots are read again)
     path[l] = m[(size_t)f * g.NN + node_index(g, min(l, g.L), y >> min(l, g.L), x >> min(l, g.L))];
   float t;
-  if (pending.states) {  // the budget search was left to this kernel
-    t = sel_threshold<THREADS>(g, pending, b);
+  if constexpr (KIND != kTauKnown) {  // the budget search was left to this kernel
+    t = sel_threshold<THREADS, KIND>(g, pending, b);
     if (blockIdx.x == 0 && threadIdx.x == 0) tau[b] = t;
   } else {
     t = tau[b];
@@ -1031,13 +1030,15 @@ __global__ __launch_bounds__(THREADS) void k_spatial_decide(Geo g, const float* 
 
 void launch_spatial_decide(const Geo& g, const float* m, float* tau, const SelSearch& pending, int32_t* node_map, uint8_t* node_level, hipStream_t s) {
   const int per_video = g.T * g.HW;
-  auto launch = [&](auto kernel, int threads) {
+  const bool look = tau_kind(pending) == kTauLook && pending.per_video > kSelFewKeys;  // through all keys
+  const bool wide = per_video > kDecideWide || look;
+  with_tau_kind(pending, [&](auto kind) {
+    constexpr int KIND = decltype(kind)::value;
+    const int threads = wide ? kDecideThreads : kSelThreads;
+    const auto kernel = wide ? k_spatial_decide<kDecideThreads, KIND> : k_spatial_decide<kSelThreads, KIND>;
     hipLaunchKernelGGL(kernel, dim3((per_video + threads - 1) / threads, g.B), dim3(threads), 0, s, g, m, tau, pending,
                        node_map, node_level);
-  };
-  const bool look = pending.states && !pending.listed && pending.per_video > kSelFewKeys;  // through all keys
-  if (per_video > kDecideWide || look) launch(k_spatial_decide<kDecideThreads>, kDecideThreads);
-  else launch(k_spatial_decide<kSelThreads>, kSelThreads);
+  });
 }
 
 // Recovers node levels from a node map (callers may pass node_level == NULL to the temporal stage).
@@ -1239,10 +1240,10 @@ __global__ __launch_bounds__(kPassThreads) void k_select_piece(Geo g, const uint
 }
 
 // The whole search as a launch of its own (when the caller wants the threshold back).
-template <int THREADS>
+template <int THREADS, int KIND>
 __global__ __launch_bounds__(THREADS) void k_select_tau(Geo g, SelSearch search, float* __restrict__ tau,
                                                         float* __restrict__ host_tau) {
-  const float t = sel_threshold<THREADS>(g, search, blockIdx.x);
+  const float t = sel_threshold<THREADS, KIND>(g, search, blockIdx.x);
   if (threadIdx.x == 0) {
     tau[blockIdx.x] = t;
     if (host_tau) host_tau[blockIdx.x] = t;
@@ -1286,10 +1287,12 @@ SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const ui
 }
 
 void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s) {
-  if (search.listed || search.per_video <= kSelFewKeys)
-    hipLaunchKernelGGL(k_select_tau<kSelThreads>, dim3(g.B), dim3(kSelThreads), 0, s, g, search, tau, host_tau);
-  else
-    hipLaunchKernelGGL(k_select_tau<kSelThreadsWhole>, dim3(g.B), dim3(kSelThreadsWhole), 0, s, g, search, tau, host_tau);
+  const bool whole = !search.listed && search.per_video > kSelFewKeys;
+  const int threads = whole ? kSelThreadsWhole : kSelThreads;
+  const auto kernel = search.listed ? k_select_tau<kSelThreads, kTauListed>
+                      : whole       ? k_select_tau<kSelThreadsWhole, kTauLook>
+                                    : k_select_tau<kSelThreads, kTauLook>;
+  hipLaunchKernelGGL(kernel, dim3(g.B), dim3(threads), 0, s, g, search, tau, host_tau);
 }
 
 }  // namespace sttm

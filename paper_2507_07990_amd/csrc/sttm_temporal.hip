@@ -752,7 +752,7 @@ static size_t parent_lds(const Geo& g, int run, int match) {
   return cells * (match == 2 ? 8 : 4) + (cells + g.HW) * 3 + 16;
 }
 
-template <int THREADS>
+template <int THREADS, int KIND>
 __global__ __launch_bounds__(THREADS) void k_temporal_parent(Geo g, int match, int run, int runs,
                                                                  const int32_t* __restrict__ node_map,
                                                                  const uint8_t* __restrict__ node_level,
@@ -782,8 +782,9 @@ __global__ __launch_bounds__(THREADS) void k_temporal_parent(Geo g, int match, i
     lvl[q] = node_level[i];
   }
   float th;
-  if (pending.states || given.n) {  // the budget search was left to this kernel, or the caller named the threshold
-    th = given.n ? given.v[b] : sel_threshold<THREADS>(g, pending, b);
+  if (KIND != kTauKnown || given.n) {  // the budget search was left to this kernel, or the caller named the threshold
+    if constexpr (KIND == kTauKnown) th = given.v[b];
+    else th = sel_threshold<THREADS, KIND>(g, pending, b);
     if (t0 == 0 && tid == 0) tau[b] = th;
   } else {
     th = tau[b];
@@ -836,15 +837,16 @@ void launch_temporal_parent(const Geo& g, int match, const int32_t* node_map, co
   const int run = parent_run(g), runs = (g.T + run - 1) / run;
   const dim3 grid(g.B * runs);
   const size_t lds = parent_lds(g, run, match);
-  if (run > 1)
-    hipLaunchKernelGGL(k_temporal_parent<kParThreads>, grid, dim3(kParThreads), lds, s, g, match, run, runs, node_map,
-                       node_level, sig, tau, given, pending, parent, ptr);
-  else if (g.HW > kSelThreads)  // (64 frames of 32x32: edges and roots 20.9 us by 256 threads a frame, 18.7 by 512)
-    hipLaunchKernelGGL(k_temporal_parent<2 * kSelThreads>, grid, dim3(2 * kSelThreads), lds, s, g, match, run, runs, node_map,
-                       node_level, sig, tau, given, pending, parent, ptr);
-  else
-    hipLaunchKernelGGL(k_temporal_parent<kSelThreads>, grid, dim3(kSelThreads), lds, s, g, match, run, runs, node_map,
-                       node_level, sig, tau, given, pending, parent, ptr);
+  // (64 frames of 32x32: edges and roots 20.9 us by 256 threads a frame, 18.7 by 512)
+  const int threads = run > 1 ? kParThreads : g.HW > kSelThreads ? 2 * kSelThreads : kSelThreads;
+  with_tau_kind(pending, [&](auto kind) {
+    constexpr int KIND = decltype(kind)::value;
+    const auto kernel = run > 1              ? k_temporal_parent<kParThreads, KIND>
+                        : g.HW > kSelThreads ? k_temporal_parent<2 * kSelThreads, KIND>
+                                             : k_temporal_parent<kSelThreads, KIND>;
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, s, g, match, run, runs, node_map, node_level, sig, tau, given,
+                       pending, parent, ptr);
+  });
 }
 
 // ------------------------------------------------------------------------------------------------

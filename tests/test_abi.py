@@ -76,3 +76,20 @@ def test_no_kernel_uses_scratch_memory():
     assert len(kernels) > 50
     assert {k[".name"]: k[".private_segment_fixed_size"] for k in kernels
             if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]} == {}
+
+
+def test_kernels_that_use_a_threshold_carry_the_search_they_make_and_no_other():
+    """They are built in three kinds, the last template argument: 0 the threshold is known, 1 it is searched among listed
+    elements, 2 among all keys. The first has no search's tables in LDS, the second not the third's batch of keys in
+    registers (48 is what these kernels took when a search among listed elements was all there was)."""
+    from paper_2507_07990_amd import binding
+    kernels = _kernel_metadata(binding.LIB_PATH)
+    for name, kinds in (("k_temporal_parent", 3), ("k_spatial_decide", 3), ("k_select_tau", 2)):
+        kind = {}
+        for k in kernels:
+            m = re.search(name + r"ILi\d+ELi(\d)EE", k[".name"])
+            if m:
+                kind.setdefault(int(m[1]), []).append(k)
+        assert len(kind) == kinds, name
+        assert all(k[".group_segment_fixed_size"] == 0 for k in kind.get(0, [])), name
+        assert all(k[".vgpr_count"] <= 48 for k in kind[1]), name
