@@ -13,6 +13,8 @@ LIB_LARGE = os.path.join(HERE, "libsttm_cpu_large.so")  # every input takes the 
 # crowded bins
 LARGE = ["-DSTTM_PYR_TILES_MAX=0", "-DSTTM_TEMPORAL_TILES_MAX=0", "-DSTTM_SEL_WHOLE=0", "-DSTTM_SEL_THREADS=64", "-DSTTM_SEL_LIST=32",
          "-DSTTM_SEL_REFINE=0", "-DSTTM_SEL_CROWD=40"]
+# Every search has its elements listed, and keeps as many as on the device: lists that take several trips to be read.
+LIB_LISTED, LISTED = os.path.join(HERE, "libsttm_cpu_listed.so"), ["-DSTTM_SEL_WHOLE=0"]
 SOURCES = ["sttm_api.hip", "sttm_spatial.hip", "sttm_temporal.hip", "sttm_reduce.hip"]
 SANITIZE_EXE = os.path.join(HERE, "sanitize_run")
 SANITIZE_EXE_LARGE = os.path.join(HERE, "sanitize_run_large")
@@ -42,6 +44,10 @@ def build(verbose: bool = False, large: bool = False) -> str:
     # (two of these live in one process: -fno-gnu-unique keeps the statics of their template functions apart)
     return _compile(["-fPIC", "-shared", "-fno-gnu-unique"] + (LARGE if large else []), [], LIB_LARGE if large else LIB,
                     verbose)
+
+
+def build_listed(verbose: bool = False) -> str:
+    return _compile(["-fPIC", "-shared", "-fno-gnu-unique"] + LISTED, [], LIB_LISTED, verbose)
 
 
 if __name__ == "__main__":

@@ -355,3 +355,21 @@ def test_emulated_temporal_pass_with_and_without_a_plan(emul, large, H, W, dtype
         for name, x in vars(a).items():
             if isinstance(x, np.ndarray):
                 np.testing.assert_array_equal(x, getattr(b, name), err_msg=name)
+
+
+@pytest.mark.parametrize("T,H,W", [
+    (3, 16, 16),    # temporal pairs 512: the elements after the first 256 are a batch that is not full
+    (10, 16, 16),   # 2304: those that were requested with the length, and one whole batch
+    (11, 7, 31),    # 2170: a batch less a few
+    (4, 32, 32),    # 3072, by 1024 threads
+])
+def test_emulated_search_among_a_long_list(emul, T, H, W):
+    """All similarities in one bin and listed: the thresholds are those of the search through all keys."""
+    from tests.cpu_emul import build_cpu
+    run_cpu, _ = emul
+    rng = np.random.default_rng(T)
+    feats = np.repeat(rng.standard_normal((1, 1, H, W, 8)), T, axis=1) + 0.0
+    feats = (100 * rng.standard_normal(8) + feats + 1e-3 * rng.standard_normal(feats.shape)).astype(np.float32)
+    a, b = (run_cpu.run_cpu(feats, lib=lib, keep=0.4) for lib in (run_cpu.load(build_cpu.build_listed()), run_cpu.load()))
+    for name in ("tau_s", "tau_t", "node_map", "cluster_ids"):
+        np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
