@@ -1000,13 +1000,15 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
   }
 }
 
-// A fixed number of workgroups per chunk walks the list of big clusters. A cluster's partial sums are added up
+// A number of workgroups per chunk that follows from the sizes walks the list of big clusters. A cluster's partial sums are added up
 // in item order (the starting item's own, then the left-hand shares of the items after it): the run of items is
 // cut into kBigSeg contiguous segments, one wavefront each, eight loads in flight, and the segment sums are
-// added in segment order through LDS -- an order that depends on the list alone. (64 workgroups of a chunk instead of 256, of
-// which most found nothing to do: six clips with large clusters and fp32 rows 154.4 -> 149.4 us a pass, still ones without
-// the partition 144.6 -> 134.9, others the same; 32: 32 videos of 27x27 903 -> 913.)
-constexpr int kBigGrid = 64;
+// added in segment order through LDS -- an order that depends on the list alone. The workgroups of a chunk: one for every
+// kBigPer clusters that the list has room for, from kBigGrid to kBigMost. By 64, by 256 and by this rule, us: six clips of 25
+// frames of 15x20 with fp32 rows (most workgroups find nothing to do) 7.8, 12.4 and 8.0; 32 videos of 27x27 11.3, 8.1 and
+// 8.1; 1152 clusters of 100 cells and one chunk 36.8, 12.7 and 12.9; 2048 of 70 and two chunks 61.3, 21.9 and 22.0 (by one
+// for every 16 places 35.2).
+constexpr int kBigGrid = 64, kBigMost = 256, kBigPer = 8;
 constexpr int kBigBatch = 8;
 constexpr int kBigSeg = 8;
 
@@ -1326,7 +1328,7 @@ void launch_reduce_big(const Geo& g, const void* feats, const float* nsum, const
                        const uint8_t* node_level, int out_dtype, int64_t capacity, void* merged, int32_t* counts,
                        const ReduceBuffers& rb, bool zscan, hipStream_t s) {
   const int nmax = (int)reduce_biglist_entries(g);
-  dim3 grid(nmax < kBigGrid ? nmax : kBigGrid, g.nC), block(64 * kBigSeg);
+  dim3 grid(min(nmax, min(kBigMost, max(kBigGrid, nmax / kBigPer))), g.nC), block(64 * kBigSeg);
   const GatherArgs a = gather_args(feats, nsum, node_map, node_level, capacity, merged, counts, rb, zscan);
   STTM_DISPATCH_IO(k_reduce_big_combine, g.dtype, out_dtype, grid, block, s, g, a);
 }

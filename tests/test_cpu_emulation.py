@@ -373,3 +373,29 @@ def test_emulated_search_among_a_long_list(emul, T, H, W):
     a, b = (run_cpu.run_cpu(feats, lib=lib, keep=0.4) for lib in (run_cpu.load(build_cpu.build_listed()), run_cpu.load()))
     for name in ("tau_s", "tau_t", "node_map", "cluster_ids"):
         np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
+
+
+@pytest.mark.parametrize("B,T,H,W,D,least,most", [
+    (1, 10, 8, 8, 8, 10, 10),          # as many as there can be large clusters
+    (6, 25, 15, 20, 8, 64, 128),       # of the few hundred there could be, few are there as a rule
+    (32, 100, 6, 6, 256, 200, 256),    # a still scene: 1152 of them, one chunk
+    (32, 27, 27, 27, 8, 256, 256),
+])
+def test_emulated_combination_of_large_clusters_has_workgroups_for_them(emul, B, T, H, W, D, least, most):
+    """Launched, not carried out: the workgroups of a chunk that walk the list of large clusters."""
+    run_cpu, _ = emul
+    lib, ptr, h = run_cpu.load(), run_cpu._p, ctypes.c_void_p()
+    N = B * T * H * W
+    x, merged = run_cpu._aligned(N * D * 2, 16), run_cpu._aligned(N * D * 2, 16)
+    cluster, counts = np.zeros(N, np.int32), np.zeros(N, np.int32)
+    offsets, grid = np.zeros(B + 1, np.int64), (ctypes.c_uint * 3)()
+    assert lib.sttm_create(ctypes.byref(h), 0, None) == 0
+    lib.hip_emul_last_grid(None, None)
+    lib.hip_emul_record(1)
+    try:
+        assert lib.sttm_reduce_noalloc(h, ptr(x), 2, B, T, H, W, D, ptr(cluster), 2, ctypes.c_int64(N), ptr(merged), ptr(counts),
+                                       None, ptr(offsets)) == 0, lib.sttm_last_error(h)
+    finally:
+        lib.hip_emul_record(0)
+    assert lib.hip_emul_last_grid(b"k_reduce_big", grid) and least <= grid[0] <= most and grid[1] == 1
+    lib.sttm_destroy(h)
