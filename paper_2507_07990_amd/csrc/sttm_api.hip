@@ -647,13 +647,15 @@ int sttm_budget_threshold(sttm_ctx* ctx, int stage, const double* target_keep_ho
   if (spatial) {
     search = launch_select_spatial(g, at<uint32_t>(ctx, ctx->lay.sel_key_s), at<uint8_t>(ctx, ctx->lay.sel_w_s), target_dev,
                                    at<SelState>(ctx, ctx->lay.sel_s),
-                                   at<uint32_t>(ctx, ctx->lay.list_key_s), at<uint8_t>(ctx, ctx->lay.list_w_s), ctx->stream);
+                                   at<uint32_t>(ctx, ctx->lay.list_key_s), at<uint8_t>(ctx, ctx->lay.list_w_s),
+                                   tau_out_host != nullptr, ctx->stream);
     ctx->search_s = search;
     ctx->tau_s_pending = tau_out_host == nullptr;
   } else {
     search = launch_select_temporal(g, ctx->node_map_temporal, at<uint32_t>(ctx, ctx->lay.sel_key_t), target_dev,
                                     at<SelState>(ctx, ctx->lay.sel_t),
-                                    at<uint32_t>(ctx, ctx->lay.list_key_t), at<uint8_t>(ctx, ctx->lay.list_w_t), ctx->stream);
+                                    at<uint32_t>(ctx, ctx->lay.list_key_t), at<uint8_t>(ctx, ctx->lay.list_w_t),
+                                    tau_out_host != nullptr, ctx->stream);
     ctx->search_t = search;
     ctx->tau_t_pending = tau_out_host == nullptr;
   }

@@ -948,11 +948,13 @@ void launch_spatial_finalize(const Geo& g, const float* part, float* nsum, float
 void launch_spatial_decide(const Geo& g, const float* m, float* tau, const SelSearch& pending, int32_t* node_map,
                            uint8_t* node_level, hipStream_t s);
 // Begins a budget search and says how it goes on. A small input is left to whoever uses the threshold; of a large one the
-// elements of the right bin are listed (`list_key`, `list_w`: [videos][select_elements()]).
+// elements of the right bin are listed (`list_key`, `list_w`: [videos][select_elements()]). `handed_back`: launch_select_tau
+// will carry it out.
 SelSearch launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
-                                SelState* state, uint32_t* list_key, uint8_t* list_w, hipStream_t s);
+                                SelState* state, uint32_t* list_key, uint8_t* list_w, bool handed_back, hipStream_t s);
 SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
-                                 SelState* state, uint32_t* list_key, uint8_t* list_w, hipStream_t s);
+                                 SelState* state, uint32_t* list_key, uint8_t* list_w, bool handed_back,
+                                 hipStream_t s);
 // Carries a search out now, for a caller who wants the thresholds back.
 // `host_tau` (may be NULL): host memory the device can write, which receives the thresholds as well.
 void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s);

@@ -1076,6 +1076,12 @@ void launch_node_levels(const Geo& g, const int32_t* node_map, uint8_t* node_lev
 // bin and looks through all keys by itself, and no launch is made for the search: passes of 64 frames of 13x13 (5440 and 10,816
 // elements) 116.8 us with the list and 112.6 without, of 16x16 (16,384) 105.7 and 101.4; 180 of 14x14 (14,400 and 35,280)
 // 227.4 with the list for both, 223.4 without the smaller one's, 225.4 without both; 512 of 13x13 (43,520) 402 and 409.
+// Every workgroup of every video looks through its video's keys, so in a batch the elements of all videos count as well, up to
+// kSelWholeAll of them. Passes over B videos of 13x13 at D = 512 with the list and without (temporal elements in all): 32 of
+// 16 frames (86,528) 140.8 and 139.8 us, 8 of 64 (86,528) 139.6 and 135.7, 12 of 64 (129,792) 172.0 and 173.0, 8 of 100
+// (135,200) 180.2 and 179.7, 16 of 64 (173,056) 198.5 and 201.9, 16 of 100 (270,400) 267.8 and 274.7; 8 of 64 frames of 16x16
+// (131,072) 157.6 and 154.5, 64 of 40 of 8x8 (163,840) 199.4 and 211.3. Where the thresholds are handed back one workgroup a
+// video looks, whatever B is: 16 of 64 frames of 13x13 247 and 242, 16 of 100 317 and 314.
 // Input: keys[video][per_video] (0 = not an element), weights (NULL = 1 for every element).
 // What it costs is launches and dependent loads. Against a radix search of 11 + 11 + 10 bits, two launches and the last
 // digit in the kernel that uses the threshold (the first bits of a float tell similarities apart badly: four bins from a
@@ -1087,7 +1093,7 @@ void launch_node_levels(const Geo& g, const int32_t* node_map, uint8_t* node_lev
 #ifndef STTM_SEL_WHOLE
 #define STTM_SEL_WHOLE 20480
 #endif
-constexpr int kSelWhole = STTM_SEL_WHOLE;
+constexpr int kSelWhole = STTM_SEL_WHOLE, kSelWholeAll = 131072;
 constexpr int kSelThreadsWhole = 1024;
 // Threads of the listing pass, and elements per thread. (Fewer in the host-thread build: a small input has several workgroups.)
 #ifndef STTM_SEL_THREADS
@@ -1252,9 +1258,10 @@ __global__ __launch_bounds__(THREADS) void k_select_tau(Geo g, SelSearch search,
 
 static SelSearch launch_select(const Geo& g, const uint32_t* keys, const uint8_t* weights, int per_video,
                                const int* target, int base_const, const int32_t* node_map, SelState* st,
-                               uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
+                               uint32_t* list_key, uint8_t* list_w, bool handed_back, hipStream_t s) {
   SelSearch q = {st, keys, weights, per_video, false, target, base_const, node_map};
-  if (per_video <= kSelWhole) return q;
+  const bool few = handed_back || per_video <= kSelFewKeys || (long long)g.B * per_video <= kSelWholeAll;
+  if (per_video <= kSelWhole && few) return q;
   const dim3 grid((per_video + kPassThreads * kSelPer - 1) / (kPassThreads * kSelPer), g.B), block(kPassThreads);
   if (per_video > kSelRefine) {
     hipLaunchKernelGGL(k_select_list<true>, grid, block, 0, s, g, keys, weights, per_video, target, base_const, node_map, st,
@@ -1273,17 +1280,20 @@ static SelSearch launch_select(const Geo& g, const uint32_t* keys, const uint8_t
 int select_elements(const Geo& g, bool spatial) { return g.T * (spatial ? g.NN - g.lvl_base[1] : g.HW); }
 
 SelSearch launch_select_spatial(const Geo& g, const uint32_t* keys, const uint8_t* weights, const int* target,
-                                SelState* state, uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
+                                SelState* state, uint32_t* list_key, uint8_t* list_w, bool handed_back,
+                                hipStream_t s) {
   int roots = 0;
   for (int ry = 0; ry < g.R; ++ry)
     for (int rx = 0; rx < g.R; ++rx) roots += node_exists(g, g.L, ry, rx);
   return launch_select(g, keys, weights, select_elements(g, true), target, roots * g.T, nullptr, state, list_key, list_w,
-                       s);
+                       handed_back, s);
 }
 
 SelSearch launch_select_temporal(const Geo& g, const int32_t* node_map, const uint32_t* keys, const int* target,
-                                 SelState* state, uint32_t* list_key, uint8_t* list_w, hipStream_t s) {
-  return launch_select(g, keys, nullptr, select_elements(g, false), target, 0, node_map, state, list_key, list_w, s);
+                                 SelState* state, uint32_t* list_key, uint8_t* list_w, bool handed_back,
+                                 hipStream_t s) {
+  return launch_select(g, keys, nullptr, select_elements(g, false), target, 0, node_map, state, list_key, list_w, handed_back,
+                       s);
 }
 
 void launch_select_tau(const Geo& g, const SelSearch& search, float* tau, float* host_tau, hipStream_t s) {

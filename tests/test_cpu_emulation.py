@@ -399,3 +399,44 @@ def test_emulated_combination_of_large_clusters_has_workgroups_for_them(emul, B,
         lib.hip_emul_record(0)
     assert lib.hip_emul_last_grid(b"k_reduce_big", grid) and least <= grid[0] <= most and grid[1] == 1
     lib.sttm_destroy(h)
+
+
+@pytest.mark.parametrize("B,T,spatial,temporal", [
+    (4, 64, False, False),
+    (16, 64, False, True),     # 87,040 and 173,056 elements of all videos
+    (16, 121, True, True),     # 10,285 and 20,449 a video
+    (128, 16, False, True),    # 1360 a video: too few to be listed; 2704
+    (1, 122, False, True),     # 20,618 of one video
+])
+def test_emulated_searches_of_a_batch_are_listed_where_all_its_elements_are_many(emul, B, T, spatial, temporal):
+    """Launched, not carried out: whether a search has the elements of the picked bin listed depends on the elements of a
+    video and, where every workgroup of the kernel that uses the threshold searches, on those of all videos."""
+    run_cpu, _ = emul
+    lib, ptr, h, H, D = run_cpu.load(), run_cpu._p, ctypes.c_void_p(), 13, 8
+    N, need = B * T * H * H, lib.sttm_workspace_bytes(B, T, H, H, D, 0, 1)
+    ws, x = run_cpu._aligned(need), run_cpu._aligned(N * D * 4, 16)
+    nm, nl, grid = np.zeros(N, np.int32), np.zeros(N, np.uint8), (ctypes.c_uint * 3)()
+    keep = (ctypes.c_double * B)(*[0.5] * B)
+
+    def chk(rc):
+        assert rc == 0, lib.sttm_last_error(h)
+
+    def listed(stage, back=None):
+        lib.hip_emul_last_grid(None, None)
+        chk(lib.sttm_budget_threshold(h, stage, keep, back))
+        return bool(lib.hip_emul_last_grid(b"k_select_list", grid))
+
+    chk(lib.sttm_create(ctypes.byref(h), 0, None))
+    chk(lib.sttm_set_workspace(h, ptr(ws), ctypes.c_size_t(need)))
+    lib.hip_emul_record(1)
+    try:
+        chk(lib.sttm_spatial_stats(h, ptr(x), 0, B, T, H, H, D, 1))
+        assert listed(0) == spatial
+        chk(lib.sttm_spatial_quadtree(h, ptr(x), 0, B, T, H, H, D, 1, None, ptr(nm), ptr(nl)))
+        chk(lib.sttm_temporal_stats(h, ptr(x), ptr(nm), ptr(nl)))
+        assert listed(1) == temporal
+        # one workgroup a video makes a search whose threshold is handed back
+        assert listed(1, (ctypes.c_float * B)()) == (T * H * H > 20480)
+    finally:
+        lib.hip_emul_record(0)
+    lib.sttm_destroy(h)

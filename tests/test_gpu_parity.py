@@ -1200,3 +1200,27 @@ def test_pair_similarities_with_and_without_a_plan(lib, short, T, H, W, D):
     a, defined, lv = similarities(short)
     b, _, _ = similarities(T)
     assert torch.equal(a[defined], b[:short - 1][defined]) and len(torch.unique(lv)) > 2
+
+
+@pytest.mark.parametrize("B,T", [(16, 64), (9, 64), (128, 16), (2, 122)])
+def test_budget_searches_of_a_batch_by_either_route(lib, B, T):
+    """Thresholds handed back are searched for among all keys of a video of up to 20,480 elements, those left to the kernels
+    that use them among listed elements where a batch has more than 131,072: the same partition and clusters."""
+    import torch
+    H, D = 13, 64
+    x = torch.from_numpy(wl.generate(wl.Workload("v", T + B, B, T, H, H, D, "f32", 4, 0.2, 0.7))).to("cuda:0")
+    s, sh, N = lib.Sttm(0), (lib.STTM_F32, B, T, H, H, D, 1), B * T * H * H
+    s.ensure_workspace(B, T, H, H, D, lib.STTM_F32, 1)
+    nm, cl = (torch.empty((2, N), dtype=torch.int32, device="cuda:0") for _ in range(2))
+    nl = torch.empty(N, dtype=torch.uint8, device="cuda:0")
+    keep = [0.2 + 0.6 * b / B for b in range(B)]
+    s.sttm_spatial_stats(x, *sh)
+    for i, back in enumerate((True, False)):
+        s.sttm_budget_threshold(lib.STTM_STAGE_SPATIAL, keep, want_tau=back)
+        s.sttm_spatial_quadtree(x, *sh, None, nm[i], nl)
+    assert torch.equal(nm[0], nm[1])
+    s.sttm_temporal_stats(x, nm[1], nl)
+    for i, back in enumerate((True, False)):
+        s.sttm_budget_threshold(lib.STTM_STAGE_TEMPORAL, keep, want_tau=back)
+        s.sttm_temporal_merge(x, nm[1], nl, None, cl[i])
+    assert torch.equal(cl[0], cl[1]) and len(torch.unique(cl[0])) < len(torch.unique(nm[0])) < N
