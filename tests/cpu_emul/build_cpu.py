@@ -15,6 +15,8 @@ LARGE = ["-DSTTM_PYR_TILES_MAX=0", "-DSTTM_TEMPORAL_TILES_MAX=0", "-DSTTM_SEL_WH
          "-DSTTM_SEL_REFINE=0", "-DSTTM_SEL_CROWD=40"]
 # Every search has its elements listed, and keeps as many as on the device: lists that take several trips to be read.
 LIB_LISTED, LISTED = os.path.join(HERE, "libsttm_cpu_listed.so"), ["-DSTTM_SEL_WHOLE=0"]
+# Every search looks through all keys, and its bins hold more elements than it keeps.
+LIB_CROWDED, CROWDED = os.path.join(HERE, "libsttm_cpu_crowded.so"), ["-DSTTM_SEL_LIST=32"]
 SOURCES = ["sttm_api.hip", "sttm_spatial.hip", "sttm_temporal.hip", "sttm_reduce.hip"]
 SANITIZE_EXE = os.path.join(HERE, "sanitize_run")
 SANITIZE_EXE_LARGE = os.path.join(HERE, "sanitize_run_large")
@@ -32,12 +34,12 @@ def _compile(flags, extra_sources, out, verbose):
     return out
 
 
-def build_sanitized(verbose: bool = False, large: bool = False) -> str:
+def build_sanitized(verbose: bool = False, large: bool = False, crowded: bool = False) -> str:
     """tests/cpu_emul/sanitize_main.cpp and the library's sources in one executable, under AddressSanitizer and
     UndefinedBehaviorSanitizer (any report ends the run with a non-zero status)."""
     flags = ["-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer"]
-    return _compile(flags + (LARGE if large else []), ["sanitize_main.cpp"],
-                    SANITIZE_EXE_LARGE if large else SANITIZE_EXE, verbose)
+    return _compile(flags + (LARGE if large else CROWDED if crowded else []), ["sanitize_main.cpp"],
+                    SANITIZE_EXE_LARGE if large else SANITIZE_EXE + "_crowded" if crowded else SANITIZE_EXE, verbose)
 
 
 def build(verbose: bool = False, large: bool = False) -> str:
@@ -48,6 +50,10 @@ def build(verbose: bool = False, large: bool = False) -> str:
 
 def build_listed(verbose: bool = False) -> str:
     return _compile(["-fPIC", "-shared", "-fno-gnu-unique"] + LISTED, [], LIB_LISTED, verbose)
+
+
+def build_crowded(verbose: bool = False) -> str:
+    return _compile(["-fPIC", "-shared", "-fno-gnu-unique"] + CROWDED, [], LIB_CROWDED, verbose)
 
 
 if __name__ == "__main__":

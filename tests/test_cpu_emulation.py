@@ -440,3 +440,27 @@ def test_emulated_searches_of_a_batch_are_listed_where_all_its_elements_are_many
     finally:
         lib.hip_emul_record(0)
     lib.sttm_destroy(h)
+
+
+@pytest.mark.parametrize("noise", [0.0, 0.003])
+def test_emulated_search_through_all_keys_of_a_bin_that_is_not_kept(emul, noise):
+    """More elements in the picked bin than a search keeps, which are then read again from among all keys of their video: the
+    thresholds of the search that keeps them."""
+    from tests.cpu_emul import build_cpu
+    run_cpu, _ = emul
+    rng = np.random.default_rng(12)
+    feats = (rng.standard_normal(16) + noise * rng.standard_normal((3, 4, 9, 7, 16)).round(1)).astype(np.float32)
+    feats[:, 2] = feats[:, 1]                              # a frame that repeats: its pairs are all alike
+    crowded = run_cpu.load(build_cpu.build_crowded())
+    for kw in (dict(keep=0.4), dict(keep=0.7, defer_tau=True)):
+        a, b = (run_cpu.run_cpu(feats, lib=lib, **kw) for lib in (crowded, run_cpu.load()))
+        for name in ("tau_s", "tau_t", "node_map", "cluster_ids"):
+            np.testing.assert_array_equal(getattr(a, name), getattr(b, name), err_msg=name)
+
+
+def test_emulated_search_through_all_keys_of_a_bin_that_is_not_kept_runs_clean_under_sanitizers():
+    import subprocess
+    from tests.cpu_emul import build_cpu
+    r = subprocess.run([build_cpu.build_sanitized(crowded=True), "still"], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-4000:])
+    assert r.stdout.count("case ") == 1 and "runtime error" not in r.stderr and "AddressSanitizer" not in r.stderr

@@ -1224,3 +1224,86 @@ def test_budget_searches_of_a_batch_by_either_route(lib, B, T):
         s.sttm_budget_threshold(lib.STTM_STAGE_TEMPORAL, keep, want_tau=back)
         s.sttm_temporal_merge(x, nm[1], nl, None, cl[i])
     assert torch.equal(cl[0], cl[1]) and len(torch.unique(cl[0])) < len(torch.unique(nm[0])) < N
+
+
+@pytest.mark.parametrize("dtype,T", [("f16", 33), ("bf16", 33), ("bf16", 31), ("f16", 26), ("f32", 65), ("f32", 58)])
+def test_clusters_that_run_past_their_item(lib, dtype, T):
+    """Videos whose first frame is single cells and whose others hold one still node of 8x8: a cluster of 50 to 64 slots
+    (halves of node sums in 16 bits), which begins in every position of an item of sixteen, so that its last slots lie beyond
+    the sixty-fourth position from there; rows of two chunks, the second partly filled. With the partition, and without, where
+    the same cluster has thousands of slots. Whole numbers up to 8 in at most 4096 cells: all sums are exact."""
+    import torch
+    B, H, D = 16, 9, 584
+    F, N = B * T, B * T * H * H
+    tt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    dt = {"f32": lib.STTM_F32, "bf16": lib.STTM_BF16, "f16": lib.STTM_F16}[dtype]
+    x = torch.randint(-8, 9, (N, D), device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(T))
+    cell = torch.arange(N, device="cuda:0").view(B, T, H, H)
+    nm, nl, cl = cell.clone(), torch.zeros((B, T, H, H), dtype=torch.uint8, device="cuda:0"), cell.clone()
+    nm[:, 1:, :8, :8] = cell[:, 1:, :1, :1]
+    nl[:, 1:, :8, :8] = 3
+    cl[:, 1:, :8, :8] = cell[:, 1:2, :1, :1]
+    nm, cl, nl, xt = nm.flatten().int(), cl.flatten().int(), nl.flatten(), x.to(tt)
+    s = lib.Sttm(0)
+    s.ensure_workspace(B, T, H, H, D, dt, 1)
+    s.sttm_spatial_quadtree(xt, dt, B, T, H, H, D, 1, [0.5] * B, torch.empty_like(nm), torch.empty_like(nl))
+    roots, rank, size = torch.unique(cl, return_inverse=True, return_counts=True)
+    K = len(roots)
+    sums = torch.zeros((K, D), dtype=torch.int64, device="cuda:0").index_add_(0, rank, x)
+    want = (sums.float() * (1.0 / size.float())[:, None]).to(tt)
+    begins = set()
+    if dtype != "f32":
+        slots = 81 + 19 * (T - 1)                               # of a video; the cluster's are 2 (T - 1)
+        begins = {(b * slots + 81) % 16 for b in range(B)}
+    for a, b in ((nm, nl), (None, None)):
+        merged = torch.full((N, D), 7.0, dtype=tt, device="cuda:0")
+        counts, ids = (torch.full((N,), -1, dtype=torch.int32, device="cuda:0") for _ in range(2))
+        offsets = torch.zeros(B + 1, dtype=torch.int64, device="cuda:0")
+        assert s.sttm_reduce(xt, cl, a, b, dt, N, merged, counts, ids, offsets) == K
+        assert torch.equal(ids[:K], roots) and torch.equal(counts[:K].long(), size)
+        assert torch.equal(merged[:K], want) and bool((merged[K:] == 7.0).all())
+    assert dtype == "f32" or T not in (33, 31) or len(begins) == 16
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("cell_dots", [0, 1])
+@pytest.mark.parametrize("short,T,H,W,D", [
+    (3, 72, 27, 29, 1544),    # few tiles, shared out among four wavefronts; four chunks, the last of one lane
+    (14, 72, 27, 29, 1544),   # one wavefront each
+    (100, 800, 8, 8, 1544),   # two
+])
+def test_pair_similarities_of_16_bits_with_and_without_a_plan(lib, dtype, cell_dots, short, T, H, W, D):
+    """As for fp32, in rows of four chunks, with the same-node products of the spatial pass and without them."""
+    import torch
+    tt, dt = (torch.bfloat16, lib.STTM_BF16) if dtype == "bf16" else (torch.float16, lib.STTM_F16)
+    gen = torch.Generator("cuda:0").manual_seed(T + short)
+    def spread(a, side):                                         # one value a block of cells
+        return a.repeat_interleave(side, 1).repeat_interleave(side, 2)[:, :H, :W]
+
+    # blocks of 8x8 of their own noise, with one vector for all cells or one for each block of 4x4: levels 0, 2 and 3
+    place = torch.randint(0, 4, (T, (H + 7) // 8, (W + 7) // 8), device="cuda:0", generator=gen)
+    noise = spread(torch.tensor([0.05, 0.05, 0.1, 3.0], device="cuda:0")[place], 8)[..., None]
+    fine = torch.arange(1, 65, device="cuda:0").view(1, 8, 8).expand(T, 8, 8)
+    which = torch.where(spread(place, 8) == 1, spread(fine, 4), 65 + spread(fine[:, ::2, ::2], 8))
+    bases = torch.randn((130, D), device="cuda:0", generator=gen)
+    x = torch.empty((T, H, W, D), dtype=tt, device="cuda:0")
+    for t in range(T):
+        x[t] = (bases[which[t]] + noise[t] * torch.randn((H, W, D), device="cuda:0", generator=gen)).to(tt)
+    s = lib.Sttm(0)
+    s.sttm_set_cell_dots(cell_dots)
+    s.ensure_workspace(1, T, H, W, D, dt, 1)
+
+    def similarities(t):
+        n = t * H * W
+        nm, sig = torch.empty(n, dtype=torch.int32, device="cuda:0"), torch.empty(n, device="cuda:0")
+        nl = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        s.sttm_spatial_quadtree(x, dt, 1, t, H, W, D, 1, [0.95], nm, nl)
+        s.sttm_temporal_stats(x, nm, nl)
+        s.sttm_export(lib.STTM_TBL_PAIR_SIM, sig)
+        rep, lv = (nm.view(t, -1) % (H * W)).long(), nl.view(t, -1)
+        finer = torch.where(lv[1:] <= lv[:-1], rep[1:], rep[:-1])
+        return sig.view(t, -1)[1:], finer == torch.arange(H * W, device="cuda:0"), lv
+
+    a, defined, lv = similarities(short)
+    b, _, _ = similarities(T)
+    assert torch.equal(a[defined], b[:short - 1][defined]) and len(torch.unique(lv)) > 2
