@@ -550,7 +550,9 @@ constexpr int kSelThreads = 256;
 // fd.acc become that bin and the weight before it, `weight` its own, fd.rc 1 where the whole histogram fits. All threads get
 // the same answer. The histogram is the sum of COPIES arrays of kSelBins counters. With `target` the budget is worked out
 // here as well: the target less the base, which is base_const or, with a node map, the kept nodes of the video's first frame
-// (fd.rc 2 where the base alone exceeds the target). Everything is requested at once: one trip to memory.
+// (fd.rc 2 where the base alone exceeds the target). The copies are requested at once, with whatever the caller has requested
+// before. The base's cells are counted after that, a trip to memory for every THREADS of them, and the target is another: two
+// trips for a spatial search, three or more for a temporal one.
 template <int COPIES, int THREADS>
 __device__ inline void sel_pick(const Geo& g, int b, const unsigned* __restrict__ hist, const int* __restrict__ target,
                                 int base_const, const int32_t* __restrict__ node_map, SelFound& fd, unsigned& weight) {
@@ -646,7 +648,7 @@ struct SelSearch {
 // How a kernel comes by its threshold, which the host knows when it launches it: named by the caller or found by an earlier
 // launch, by a search among listed elements, or by one that looks through all keys. Each is an instance of its own: with
 // all three in one, k_temporal_parent of a frame of 169 cells was 12.8 KB of code and 90 registers, also where nothing was
-// searched; now 1.9 KB and 13 registers, 7.1 and 27, 12.2 and 88.
+// searched; now 1.9 KB and 13 registers, 7.9 and 27, 12.2 and 88.
 enum { kTauKnown, kTauListed, kTauLook };
 inline int tau_kind(const SelSearch& pending) { return !pending.states ? kTauKnown : pending.listed ? kTauListed : kTauLook; }
 // f(kind), with the kind as a constant
@@ -669,10 +671,10 @@ constexpr int kSelList = STTM_SEL_LIST;
 // a large one they have been listed. Up to kSelFew of them are searched by one wavefront, each with each or bit by bit; else
 // the range of keys is cut into 256 pieces, of which one is picked, until it is one key (two rounds for the elements of a bin,
 // however many of them are equal).
-// What bounds it: one trip to memory (histogram, keys and base are requested together), then instructions that are fetched for
-// the first time, by time stamps of 64 frames of 13x13 in cycles: 1500 until the requests are out, 3000 until they are
-// answered, 2500 for the bin, 3000 for a look at 8192 keys, 600 to 5000 for the elements. So what is executed is kept short,
-// and what the caller reads for its own work is requested before.
+// What bounds it: trips to memory (histogram and first keys are one, then the base's and the target's, see sel_pick), and
+// instructions that are fetched for the first time, by time stamps of 64 frames of 13x13 in cycles: 1500 until the first
+// requests are out, 3000 until they are answered, 2500 for the bin, 3000 for a look at 8192 keys, 600 to 5000 for the
+// elements. So what is executed is kept short, and what the caller reads for its own work is requested before.
 constexpr int kSelFew = kSelList < 256 ? kSelList : 256;
 template <int THREADS, int KIND>
 __device__ inline float sel_threshold(const Geo& g, const SelSearch& q, int b) {

@@ -848,7 +848,7 @@ __device__ inline void store_partial(float* o, const float (&acc)[VEC]) {
 // What a slot asks for is decided for all slots at once, a lane each, and kept as bit masks in scalar registers: per
 // slot only its loads, additions and row stores are left, on scalar branches and addresses. The counts, and which
 // items hold shares of a big cluster, are written by the lanes together. (Read from lane to lane per slot, by masked
-// branches, the kernel was 31 KB of code, now 17: 8 frames of 8x8 tokens 13.1 -> 8.8 us, 96 of 11x19 in fp32 33 -> 26; and it
+// branches, the kernel was 31 KB of code, now 13: 8 frames of 8x8 tokens 13.1 -> 8.8 us, 96 of 11x19 in fp32 33 -> 26; and it
 // issues less: 1024 frames of 27x27 at D = 1152 306 -> 266 us (1.72 GB, 6.5 TB/s), 512 of 13x13 at D = 3584 140 -> 134.)
 template <int DT, int ODT>
 __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
