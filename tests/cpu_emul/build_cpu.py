@@ -15,14 +15,26 @@ LARGE = ["-DSTTM_PYR_TILES_MAX=0", "-DSTTM_TEMPORAL_TILES_MAX=0", "-DSTTM_SEL_WH
          "-DSTTM_SEL_REFINE=0", "-DSTTM_SEL_CROWD=40"]
 # Every search has its elements listed, and keeps as many as on the device: lists that take several trips to be read.
 LIB_LISTED, LISTED = os.path.join(HERE, "libsttm_cpu_listed.so"), ["-DSTTM_SEL_WHOLE=0"]
-# Every search looks through all keys, and its bins hold more elements than it keeps.
+# Every search looks through all keys, and its bins hold more elements than it keeps (the sanitized build of the kernels of
+# small inputs as well).
 LIB_CROWDED, CROWDED = os.path.join(HERE, "libsttm_cpu_crowded.so"), ["-DSTTM_SEL_LIST=32"]
 SOURCES = ["sttm_api.hip", "sttm_spatial.hip", "sttm_temporal.hip", "sttm_reduce.hip"]
 SANITIZE_EXE = os.path.join(HERE, "sanitize_run")
 SANITIZE_EXE_LARGE = os.path.join(HERE, "sanitize_run_large")
 
 
+def _up_to_date(out):
+    """Built after the last change of any file that goes into it."""
+    if not os.path.exists(out):
+        return False
+    folders = [CSRC, os.path.join(ROOT, "include"), HERE, os.path.join(HERE, "hip")]
+    files = [os.path.join(d, f) for d in folders for f in os.listdir(d) if f.endswith((".h", ".hip", ".cpp", "build_cpu.py"))]
+    return os.path.getmtime(out) > max(map(os.path.getmtime, files))
+
+
 def _compile(flags, extra_sources, out, verbose):
+    if _up_to_date(out):
+        return out
     cmd = ["g++", "-std=c++17", "-O1", "-g", "-pthread", "-I", HERE, "-I", CSRC, "-Wno-unknown-pragmas",
            "-Wno-attributes"] + flags
     for s in [os.path.join(CSRC, s) for s in SOURCES] + [os.path.join(HERE, s) for s in ["emul.cpp"] + extra_sources]:
@@ -34,12 +46,12 @@ def _compile(flags, extra_sources, out, verbose):
     return out
 
 
-def build_sanitized(verbose: bool = False, large: bool = False, crowded: bool = False) -> str:
+def build_sanitized(verbose: bool = False, large: bool = False) -> str:
     """tests/cpu_emul/sanitize_main.cpp and the library's sources in one executable, under AddressSanitizer and
     UndefinedBehaviorSanitizer (any report ends the run with a non-zero status)."""
     flags = ["-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer"]
-    return _compile(flags + (LARGE if large else CROWDED if crowded else []), ["sanitize_main.cpp"],
-                    SANITIZE_EXE_LARGE if large else SANITIZE_EXE + "_crowded" if crowded else SANITIZE_EXE, verbose)
+    return _compile(flags + (LARGE if large else CROWDED), ["sanitize_main.cpp"], SANITIZE_EXE_LARGE if large else SANITIZE_EXE,
+                    verbose)
 
 
 def build(verbose: bool = False, large: bool = False) -> str:
