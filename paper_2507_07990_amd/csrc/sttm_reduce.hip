@@ -1004,11 +1004,17 @@ __global__ __launch_bounds__(64) void k_reduce(Geo g, GatherArgs a) {
 // in item order (the starting item's own, then the left-hand shares of the items after it): the run of items is
 // cut into kBigSeg contiguous segments, one wavefront each, eight loads in flight, and the segment sums are
 // added in segment order through LDS -- an order that depends on the list alone. The workgroups of a chunk: one for every
-// kBigPer clusters that the list has room for, from kBigGrid to kBigMost. By 64, by 256 and by this rule, us: six clips of 25
-// frames of 15x20 with fp32 rows (most workgroups find nothing to do) 7.8, 12.4 and 8.0; 32 videos of 27x27 11.3, 8.1 and
-// 8.1; 1152 clusters of 100 cells and one chunk 36.8, 12.7 and 12.9; 2048 of 70 and two chunks 61.3, 21.9 and 22.0 (by one
-// for every 16 places 35.2).
-constexpr int kBigGrid = 64, kBigMost = 256, kBigPer = 8;
+// kBigPer clusters that the list has room for, but kBigMost at most and at least as many as it takes for two to a compute unit
+// in all; and an odd number of them: workgroups go to the eight dies in turn, and by an even number the chunks of a cluster,
+// which lie side by side in memory, mostly meet on one. us by 64, by 256, and by this rule:
+//   six clips of 25 frames of 15x20, fp32 rows (three chunks; room for 693, few are there)         7.7   12.9    8.1
+//   five videos of 115 frames of 17x17, two chunks                                               11.1   13.8    9.9
+//   64 frames of 14x16, fp32 rows, seven chunks (room for 221; 73 and 221 alike)                  19.9   12.2   12.0
+//   1152 clusters of 100 cells, one chunk                                                        36.5   12.8   12.9
+//   2048 clusters of 70 cells, two chunks (nothing but still scenes: an odd number costs here)    60.8   22.1   23.4
+//   576 of 90, four chunks                                                                       20.1   15.4   17.3
+//   32 videos of 32 frames of 27x27, three chunks                                                11.3    8.5    8.2
+constexpr int kBigGrid = 65, kBigMost = 255, kBigPer = 4;
 constexpr int kBigBatch = 8;
 constexpr int kBigSeg = 8;
 
@@ -1328,7 +1334,9 @@ void launch_reduce_big(const Geo& g, const void* feats, const float* nsum, const
                        const uint8_t* node_level, int out_dtype, int64_t capacity, void* merged, int32_t* counts,
                        const ReduceBuffers& rb, bool zscan, hipStream_t s) {
   const int nmax = (int)reduce_biglist_entries(g);
-  dim3 grid(min(nmax, min(kBigMost, max(kBigGrid, nmax / kBigPer))), g.nC), block(64 * kBigSeg);
+  int n = min(nmax, min(kBigMost, max(max(kBigGrid, 2 * kBigMost / g.nC), nmax / kBigPer)));
+  n -= n > 1 && n % 2 == 0;
+  const dim3 grid(n, g.nC), block(64 * kBigSeg);
   const GatherArgs a = gather_args(feats, nsum, node_map, node_level, capacity, merged, counts, rb, zscan);
   STTM_DISPATCH_IO(k_reduce_big_combine, g.dtype, out_dtype, grid, block, s, g, a);
 }

@@ -374,10 +374,12 @@ def test_emulated_search_among_a_long_list(emul, T, H, W):
 
 
 @pytest.mark.parametrize("B,T,H,W,D,least,most", [
-    (1, 10, 8, 8, 8, 10, 10),          # as many as there can be large clusters
-    (6, 25, 15, 20, 8, 64, 128),       # of the few hundred there could be, few are there as a rule
+    (1, 10, 8, 8, 8, 9, 10),           # about as many as there can be large clusters
+    (1, 1, 8, 8, 8, 1, 1),
+    (6, 25, 15, 20, 1280, 64, 192),    # of the few hundred there could be, few are there as a rule
     (32, 100, 6, 6, 256, 200, 256),    # a still scene: 1152 of them, one chunk
-    (32, 27, 27, 27, 8, 256, 256),
+    (32, 27, 27, 27, 8, 250, 256),
+    (1, 64, 14, 16, 8, 64, 221),
 ])
 def test_emulated_combination_of_large_clusters_has_workgroups_for_them(emul, B, T, H, W, D, least, most):
     """Launched, not carried out: the workgroups of a chunk that walk the list of large clusters."""
@@ -395,7 +397,8 @@ def test_emulated_combination_of_large_clusters_has_workgroups_for_them(emul, B,
                                        None, ptr(offsets)) == 0, lib.sttm_last_error(h)
     finally:
         lib.hip_emul_record(0)
-    assert lib.hip_emul_last_grid(b"k_reduce_big", grid) and least <= grid[0] <= most and grid[1] == 1
+    assert lib.hip_emul_last_grid(b"k_reduce_big", grid) and least <= grid[0] <= most and grid[1] == (D + 511) // 512
+    assert grid[0] % 2 == 1                                 # a cluster's chunks go to different dies
     lib.sttm_destroy(h)
 
 
