@@ -39,10 +39,11 @@ def _compile(flags, extra_sources, out, verbose):
            "-Wno-attributes"] + flags
     for s in [os.path.join(CSRC, s) for s in SOURCES] + [os.path.join(HERE, s) for s in ["emul.cpp"] + extra_sources]:
         cmd += ["-x", "c++", s]
-    cmd += ["-o", out]
+    cmd += ["-o", out + ".part"]  # (in place only when it is whole)
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True)
+    os.replace(out + ".part", out)
     return out
 
 
